@@ -346,15 +346,17 @@ kv_status kv_decode_bytes(const kv_cache *cache, int32_t layer, size_t *bytes);
  * -- and up to 8 query heads per kv head (with KV_MEAN_CROSS_HEAD:
  * at most 64 query heads); with path 2 a decode of any other layer returns KV_E_UNSUPPORTED.  The
  * vector-ALU kernels serve every format (about twenty times slower: use kv_decode_path_used to see
- * which family a layer gets).  Returns KV_E_BAD_CONFIG for other values.  Affects later calls on
+ * which family a layer gets).  16-bit layers count as family 1; under the automatic choice a kernel
+ * of their own serves them (softmax attention over raw rows on the matrix cores, at the rate of
+ * the others), with path 1 the vector-ALU kernel does.  Returns KV_E_BAD_CONFIG for other values.  Affects later calls on
  * this cache only. */
 kv_status kv_set_decode_path(kv_cache *cache, int32_t path);
 
 /* Which kernel family a decode call of `layer` would run on in the cache's present state:
  * *path = 1 (vector-ALU kernels) or 2 (matrix-core kernels).  A layer whose format the matrix-core
  * kernels do not take (different widths for keys and values with other groups than 32 / 32 or with a
- * block table, group_tokens != group_channels with KV_MEAN_CROSS_HEAD, a 16-bit layer) is served by the vector-ALU kernels under the automatic choice, at a small fraction
- * of the rate: this call makes that visible.  Errors as kv_decode_splits. */
+ * block table, group_tokens != group_channels with KV_MEAN_CROSS_HEAD) is served by the vector-ALU kernels under the automatic choice, at a small fraction
+ * of the rate: this call makes that visible.  (A 16-bit layer reports 1 as well, see kv_set_decode_path.)  Errors as kv_decode_splits. */
 kv_status kv_decode_path_used(const kv_cache *cache, int32_t layer, int32_t *path);
 
 /* Force the number of sequence splits of later decode calls on this cache (clamped to the number

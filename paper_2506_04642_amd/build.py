@@ -22,6 +22,7 @@ UNITS = [
     # are issued by hand and name M0 as clobbered, which the compiler remarks on at every use
     # (the assembly text is kept next to the object and read by verify_hand_loads after the compile)
     ("decode_mfma.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm", "-save-temps=obj"]),
+    ("decode_raw.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
     ("xhead_dense.hip", []),
     ("stream_probe.hip", []),
 ]

@@ -202,6 +202,9 @@ kv_status layer_ok(const kv_cache *k, int layer)
     return KV_OK;
 }
 
+// A 16-bit layer under the automatic choice: the kernel for raw rows (path 1 keeps the vector-ALU kernel).
+bool use_raw(const kv_cache *k, const DecodeArgs &a) { return k->decode_path == 0 && decode_raw_supported(a); }
+
 kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a)
 {
     const kv_config &c = k->cfg;
@@ -246,6 +249,10 @@ kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a)
         a->n_splits = decode_mfma_splits(*a);
         const int cap = mfma_split_bound(c);
         if (a->n_splits > cap) a->n_splits = cap;
+    } else if (use_raw(k, *a)) {
+        // (never more splits than the vector-ALU kernel would use: the workspace a call needs, and what
+        // fits the static one, stay what they are)
+        a->n_splits = decode_raw_splits(*a, a->n_splits);
     }
     if (k->forced_splits > 0) {
         const int work = a->n_blocks + (a->r > 0 ? 1 : 0);
@@ -811,7 +818,8 @@ kv_status kv_decode_attn_split(const kv_cache *cache, int32_t layer, const void 
     a.out = nullptr;
     hipStream_t s = (hipStream_t)stream;
     if (cache->decode_path == 2 && !decode_mfma_supported(a)) return KV_E_UNSUPPORTED;
-    hipError_t e = use_mfma(cache, a) ? launch_decode_split_mfma(a, s) : launch_decode_split_valu(a, s);
+    hipError_t e = use_mfma(cache, a) ? launch_decode_split_mfma(a, s)
+                                      : use_raw(cache, a) ? launch_decode_split_raw(a, s) : launch_decode_split_valu(a, s);
     return e == hipSuccess ? KV_OK : KV_E_HIP;
 }
 

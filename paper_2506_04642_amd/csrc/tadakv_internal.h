@@ -185,6 +185,10 @@ bool compressv_supported(const LayerGeom &g); // formats the fused value project
 hipError_t launch_compressv(const ProjectArgs &p, hipStream_t s);
 hipError_t launch_decode_split_valu(const DecodeArgs &a, hipStream_t s);
 hipError_t launch_decode_split_mfma(const DecodeArgs &a, hipStream_t s);
+// layers stored in 16 bits
+bool decode_raw_supported(const DecodeArgs &a);
+int decode_raw_splits(const DecodeArgs &a, int cap); // preferred split count, at most cap
+hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s);
 // the calling thread's next matrix-core split launch records its begin and end into these (one-shot; null cancels)
 void set_split_timing_events(hipEvent_t begin, hipEvent_t end);
 bool decode_mfma_supported(const DecodeArgs &a);
