@@ -314,6 +314,9 @@ kv_status kv_decode_attn_merge16(const kv_cache *cache, int32_t layer, void *out
  * KV_E_EMPTY if the layer holds no token.  Sequences that are not active (kv_cache_set_active) are
  * skipped. */
 kv_status kv_dequant(const kv_cache *cache, int32_t layer, float *k_out, float *v_out, int32_t t_cap, void *stream);
+/* As kv_dequant, and every other row of the outputs (past a sequence's length, and of sequences that are
+ * not active) is written with zeros: the outputs need no clearing before the call. */
+kv_status kv_dequant_padded(const kv_cache *cache, int32_t layer, float *k_out, float *v_out, int32_t t_cap, void *stream);
 
 /* One step of the decode loop in a single call (Algorithm 1 steps 8-9, KVCache.update followed by
  * TaDAFlashAttn): append ONE new token per sequence, then attend over the whole cache including it.

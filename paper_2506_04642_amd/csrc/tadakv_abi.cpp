@@ -857,7 +857,7 @@ kv_status kv_decode_attn_merge16(const kv_cache *cache, int32_t layer, void *out
     return merge_impl(cache, layer, nullptr, (uint16_t *)out16, workspace, workspace_bytes, stream);
 }
 
-kv_status kv_dequant(const kv_cache *cache, int32_t layer, float *k_out, float *v_out, int32_t t_cap, void *stream)
+static kv_status dequant_impl(const kv_cache *cache, int32_t layer, float *k_out, float *v_out, int32_t t_cap, int pad, void *stream)
 {
     kv_status st = layer_ok(cache, layer);
     if (st != KV_OK) return st;
@@ -872,7 +872,18 @@ kv_status kv_dequant(const kv_cache *cache, int32_t layer, float *k_out, float *
     q.k_out = k_out;
     q.v_out = v_out;
     q.t_cap = t_cap;
+    q.pad = pad;
     return launch_dequant(q, (hipStream_t)stream) == hipSuccess ? KV_OK : KV_E_HIP;
+}
+
+kv_status kv_dequant(const kv_cache *cache, int32_t layer, float *k_out, float *v_out, int32_t t_cap, void *stream)
+{
+    return dequant_impl(cache, layer, k_out, v_out, t_cap, 0, stream);
+}
+
+kv_status kv_dequant_padded(const kv_cache *cache, int32_t layer, float *k_out, float *v_out, int32_t t_cap, void *stream)
+{
+    return dequant_impl(cache, layer, k_out, v_out, t_cap, 1, stream);
 }
 
 kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,

@@ -173,6 +173,7 @@ struct DequantArgs {
     DecodeArgs d;
     float *k_out, *v_out; // [batch][t_cap][n_kv_heads][128] binary32, either may be null
     int t_cap;
+    int pad; // not 0: zeros go to the rows past a sequence's length
 };
 
 // records the outcome of a launch for kv_last_hip_error and passes it through

@@ -50,6 +50,36 @@ def test_reconstruction_is_bit_exact(kv, oracle, bits, G, Gc, mode):
             assert not got[b, n:].any()
 
 
+@pytest.mark.parametrize("kb,vb,G,R,extra", [(4, 2, 32, 64, 0), (2, 8, 32, 64, 1), (8, 8, 128, 256, 0), (16, 16, 64, 128, 3), (4, 4, 32, 32, 40)])
+def test_rows_past_the_length(kv, oracle, kb, vb, G, R, extra):
+    """Raw tails longer than a block, outputs that end with the longest sequence or well behind it: kv_dequant
+    leaves every row past a sequence's length alone, kv_dequant_padded writes zeros there (also for a
+    sequence that is switched off)."""
+    import torch
+
+    print("case padding kb=%d vb=%d G=%d R=%d extra=%d" % (kb, vb, G, R, extra), flush=True)
+    B, Hkv = 3, 3
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv, Hkv=Hkv, T_max=4 * R, G=G, Gc=G, R=R, dtype=BF16, mode=CHAN, k_bits=(kb,), v_bits=(vb,))
+    lengths = [2 * R + R - 1, R + 1, 5]
+    for b, n in enumerate(lengths):
+        k, v = synth.make_kv(1700 + b, 1, n, Hkv, 128, BF16)
+        gpu.append_seq(0, b, to_dev(k[0], BF16), to_dev(v[0], BF16))
+        orc.append_seq(0, b, k[0], v[0])
+    kv.kv_cache_set_active(gpu.handle, [1, 1, 0])
+    t_cap = lengths[0] + extra
+    for call, fill in ((kv.kv_dequant, -7.0), (kv.kv_dequant_padded, 0.0)):
+        out = torch.full((2, B, t_cap, Hkv, 128), -7.0, dtype=torch.float32, device="cuda:0")
+        call(gpu.handle, 0, out[0].data_ptr(), out[1].data_ptr(), t_cap)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        for which in (0, 1):
+            for b, n in enumerate(lengths[:2]):
+                want = np.transpose(orc.reconstruct(0, b, which), (1, 0, 2))
+                assert np.array_equal(got[which, b, :n].view(np.uint32), want.view(np.uint32)), (which, b)
+                assert (got[which, b, n:] == fill).all()
+            assert (got[which, 2] == fill).all()
+
+
 def test_reconstruction_argument_errors(kv, oracle):
     import torch
 
