@@ -65,15 +65,6 @@ __device__ __forceinline__ void lds_reads_done(u32x4 (&a)[4], u32x4 (&b)[8])
                    "+v"(b[4]), "+v"(b[5]), "+v"(b[6]), "+v"(b[7]));
 }
 
-// two binary32 values rounded (nearest even) to the 16-bit type, packed low | high << 16
-template <int DT> __device__ __forceinline__ uint32_t narrow2(float lo, float hi)
-{
-    if (DT == 1) {
-        const __bf16 a = (__bf16)lo, b = (__bf16)hi;
-        return (uint32_t) * (const uint16_t *)&a | ((uint32_t) * (const uint16_t *)&b << 16);
-    }
-    return (uint32_t)f16_rne(lo) | ((uint32_t)f16_rne(hi) << 16);
-}
 // the 16-bit pattern of a binary32 value that is exactly representable in the type
 template <int DT> __device__ __forceinline__ uint32_t bits16_exact(float f)
 {

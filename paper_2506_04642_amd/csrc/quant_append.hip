@@ -443,23 +443,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
             for (int j = 0; j < 8; j++) pre[j] = *(const uint4 *)(src_row(a, which, b, h, fb * G + 8 * tg + j) + c8 * 8);
         }
 
-        // ---- per-channel block mean, the sum: over the tokens in order
+        // ---- rotation of new key rows, and the sum of the per-channel block mean, over the tokens in order
         uint32_t mean_pair = 0u; // binary16 means of channels 2 lane and 2 lane + 1
-        if (gm.mean_mode == 0 && !ROPE) {
+        const bool turn = ROPE && which == 0;
+        if (gm.mean_mode == 0 || turn) {
             // The raw rows go through LDS ([token][sixteen 16-byte pieces], the pieces of a row
             // rotated by four per eight tokens so that the four lanes of a quad, whose rows lie
             // 2 KiB apart, write to different banks) and come back with a channel pair's 32 tokens
             // in one lane (lane l: channels 2 l and 2 l + 1; one whole row per read instruction):
             // every lane adds, instead of a quarter of them at a time.  The wave's LDS operations
             // complete in the order issued.
-            const int piece_w = (c8 + 4 * tg) & 15;
-#pragma unroll
-            for (int j = 0; j < 8; j++) *(uint4 *)(img + (8 * tg + j) * 256 + piece_w * 16) = pre[j];
             float s0 = 0.0f, s1 = 0.0f;
+            if (turn) {
+                rope_rows(pre, img, a, fb * G - a.r_old, lane, s0, s1);
+            } else {
+                const int piece_w = (c8 + 4 * tg) & 15;
+#pragma unroll
+                for (int j = 0; j < 8; j++) *(uint4 *)(img + (8 * tg + j) * 256 + piece_w * 16) = pre[j];
+            }
             const unsigned char *rd = img + (lane & 3) * 4;
             // (eight rows at a time: all 32 reads at once would hold 32 more registers)
 #pragma unroll 1
-            for (int tq = 0; tq < G / 8; tq++) {
+            for (int tq = turn ? G / 8 : 0; tq < G / 8; tq++) {
                 const unsigned char *rq = rd + tq * 2048 + ((((lane >> 2) + 4 * tq) & 15) << 4);
                 uint32_t w[8];
 #pragma unroll
@@ -484,60 +489,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
         float x[8][8]; // [token j][channel e]
         widen_pieces(pre, gm.dtype, x);
 
-        if (ROPE && which == 0) {
-            const int tn0 = fb * G + 8 * tg - a.r_old; // index of this lane's first token in the call's input
-            if (gm.dtype == 1) rope_in_lanes<1>(x, a, tn0, lane);
-            else rope_in_lanes<0>(x, a, tn0, lane);
-        }
-
         // ---- mean-centring
         if (gm.mean_mode == 0) {
             // per channel over the block: the sum runs over the tokens in order
             float m[8];
             const int mean_off = (which == 0 ? gm.k_mean : gm.v_mean) - base_off;
-            if (ROPE) {
-                // (the instance that rotates the keys, which then exist in registers only) the four
-                // lanes of a quad add their eight tokens one after the other and hand the running sum on
-                float acc[8];
-#pragma unroll
-                for (int e = 0; e < 8; e++) acc[e] = 0.0f;
-#pragma unroll
-                for (int p = 0; p < 4; p++) {
-                    float cin[8];
-#pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        cin[e] = p == 0 ? 0.0f : (p == 1 ? quad_bcast_f<0>(acc[e]) : (p == 2 ? quad_bcast_f<1>(acc[e]) : quad_bcast_f<2>(acc[e])));
-                    if (tg == p) {
-#pragma unroll
-                        for (int e = 0; e < 8; e++) {
-                            float sacc = cin[e];
-#pragma unroll
-                            for (int j = 0; j < 8; j++) sacc = sacc + x[j][e];
-                            acc[e] = sacc;
-                        }
-                    }
-                }
-                uint32_t mpk[4];
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const uint32_t m16 = quad_bcast_u<3>((uint32_t)f16_rne(acc[e] / (float)G));
-                    m[e] = f16_val((uint16_t)m16);
-                    if (e & 1) mpk[e >> 1] |= m16 << 16;
-                    else mpk[e >> 1] = m16;
-                }
-                if (tg == 0) *(uint4 *)(img + mean_off + c8 * 16) = uint4{mpk[0], mpk[1], mpk[2], mpk[3]};
-            } else {
-                // (summed above, while only the raw rows were held) the record's mean row is the lanes'
-                // words in order
-                const uint32_t mp = mean_pair;
-                *(uint32_t *)(img + mean_off + lane * 4) = mp;
-                // channels 8 c8 + 2 k and + 2 k + 1 are quad lane k's
-                const uint32_t q0 = quad_bcast_u<0>(mp), q1 = quad_bcast_u<1>(mp), q2 = quad_bcast_u<2>(mp), q3 = quad_bcast_u<3>(mp);
-                m[0] = f16_val((uint16_t)(q0 & 0xFFFFu)); m[1] = f16_val((uint16_t)(q0 >> 16));
-                m[2] = f16_val((uint16_t)(q1 & 0xFFFFu)); m[3] = f16_val((uint16_t)(q1 >> 16));
-                m[4] = f16_val((uint16_t)(q2 & 0xFFFFu)); m[5] = f16_val((uint16_t)(q2 >> 16));
-                m[6] = f16_val((uint16_t)(q3 & 0xFFFFu)); m[7] = f16_val((uint16_t)(q3 >> 16));
-            }
+            // (summed above, while only the raw rows were held) the record's mean row is the lanes'
+            // words in order
+            const uint32_t mp = mean_pair;
+            *(uint32_t *)(img + mean_off + lane * 4) = mp;
+            // channels 8 c8 + 2 k and + 2 k + 1 are quad lane k's
+            const uint32_t q0 = quad_bcast_u<0>(mp), q1 = quad_bcast_u<1>(mp), q2 = quad_bcast_u<2>(mp), q3 = quad_bcast_u<3>(mp);
+            m[0] = f16_val((uint16_t)(q0 & 0xFFFFu)); m[1] = f16_val((uint16_t)(q0 >> 16));
+            m[2] = f16_val((uint16_t)(q1 & 0xFFFFu)); m[3] = f16_val((uint16_t)(q1 >> 16));
+            m[4] = f16_val((uint16_t)(q2 & 0xFFFFu)); m[5] = f16_val((uint16_t)(q2 >> 16));
+            m[6] = f16_val((uint16_t)(q3 & 0xFFFFu)); m[7] = f16_val((uint16_t)(q3 >> 16));
 #pragma unroll
             for (int j = 0; j < 8; j++)
 #pragma unroll
@@ -720,13 +686,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
 // forms the deviations and emits metadata, codes and words part by part.  With a per-channel
 // mean m the extrema of the deviations are those of the raw values moved by m: rounding is
 // monotone, so min_t fl(x_t - m) = fl(min_t x_t - m).
-template <int G, int GC, int BITS, bool ROPE> struct WaveImage {
+template <int G, int GC, int BITS> struct WaveImage {
     static constexpr int NGV = kHeadDim / GC;
     static constexpr int META_BYTES = G * NGV * 4 + 256 > 768 ? G * NGV * 4 + 256 : 768;
     static constexpr int BYTES = G * kHeadDim * BITS / 8 + META_BYTES; // the larger of a record's key and value part
 };
-template <int G, int GC, int BITS, bool ROPE>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ROPE ? 2 : 3, 8))) void flush_wave_parts_kernel(AppendArgs a, int n_items)
+template <int G, int GC, int BITS>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))) void flush_wave_parts_kernel(AppendArgs a, int n_items)
 {
     constexpr int NP = G / 32; // parts of 32 tokens
     constexpr int NGV = kHeadDim / GC;
@@ -737,7 +703,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ROPE ?
     const int tg = lane & 3, c8 = lane >> 2;
     const int U = a.batch * a.n_kv_heads;
     const int workers = (int)gridDim.x * (kThreads / 64);
-    constexpr int IMG_BYTES = WaveImage<G, GC, BITS, ROPE>::BYTES;
+    constexpr int IMG_BYTES = WaveImage<G, GC, BITS>::BYTES;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_img[]; // [waves][IMG_BYTES], sized at launch
     unsigned char *img = lds_img + wave * IMG_BYTES;
 
@@ -768,12 +734,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ROPE ?
 #pragma unroll
             for (int j = 0; j < 8; j++) pre[j] = *(const uint4 *)(src_row(a, which, b, h, fb * G + 32 * half + 8 * tg + j) + c8 * 8);
             widen_pieces(pre, gm.dtype, x);
-            if (ROPE && which == 0) {
-                // both passes turn the rows the same way, so they see the same values
-                const int tn0 = fb * G + 32 * half + 8 * tg - a.r_old; // this lane's first token in the call's input
-                if (gm.dtype == 1) rope_in_lanes<1>(x, a, tn0, lane);
-                else rope_in_lanes<0>(x, a, tn0, lane);
-            }
             if (mode == 1) {
 #pragma unroll
                 for (int j = 0; j < 8; j++) {
@@ -900,15 +860,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(ROPE ?
 // workgroups that share the compute unit fill the gaps).  The keys' extrema are those of the parts'.
 // Codes, metadata and mean go into one image of the record's key or value part in LDS (it takes the
 // place of the raw rows, which nobody needs once the sums are formed), which the waves then write out
-// together as one linear run.  For the plain bulk append (no rotation, no device-resident lengths);
-// the other calls use flush_wave_parts_kernel, which reads the block twice.
+// together as one linear run.  For the bulk append; a step on
+// device-resident lengths uses flush_wave_parts_kernel, which reads the block twice.  With the rotation three
+// waves per SIMD and 8 to 14 spilled registers beat two without spills at G = 64 and 4 or 8 bits (137 -> 129,
+// 147 -> 138 us per 65536 tokens of 8 kv heads) and lose or draw elsewhere.
 template <int G, int GC, int BITS, bool ROPE>
-__global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(ROPE ? 2 : 3, 8))) void flush_coop_kernel(AppendArgs a, int n_items)
+__global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(ROPE && !(G == 64 && BITS > 2) ? 2 : 3, 8))) void flush_coop_kernel(AppendArgs a, int n_items)
 {
     constexpr int NP = G / 32; // parts of 32 tokens = waves of the workgroup
     constexpr int NGV = kHeadDim / GC;
     constexpr int qmax = (1 << BITS) - 1;
-    constexpr int IMG_BYTES = WaveImage<G, GC, BITS, false>::BYTES;
+    constexpr int IMG_BYTES = WaveImage<G, GC, BITS>::BYTES;
     constexpr int UNI_BYTES = IMG_BYTES > NP * 8192 ? IMG_BYTES : NP * 8192;
     __shared__ __attribute__((aligned(16))) unsigned char lds_uni[UNI_BYTES]; // raw rows [part][8 KiB], then the image
     __shared__ __attribute__((aligned(16))) float lds_sum[kHeadDim];         // running sums, by channel
@@ -923,6 +885,7 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
     unsigned char *img = lds_uni;
     unsigned char *raw = lds_uni + part * 8192;
 
+
     // (the grid is even: a workgroup alternates between keys and values, which cost differently, and
     // items 2 j and 2 j + 1 are the two sides of one block)
     for (int it = (int)blockIdx.x; it < n_items; it += (int)gridDim.x) {
@@ -936,35 +899,22 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
 #pragma unroll
         for (int j = 0; j < 8; j++) pre[j] = *(const uint4 *)(src_row(a, which, b, h, fb * G + 32 * part + 8 * tg + j) + c8 * 8);
 
+        // the rows in the layout of the sum ([token][sixteen 16-byte pieces], the pieces of a row
+        // rotated by four per eight tokens: see flush_wave_kernel); new key rows are turned there
         if (ROPE && which == 0) {
-            // the key rows of the call are turned here, once (rows from the raw buffer were turned when
-            // they were stored), and go back into their 16-bit form, which holds them exactly: what
-            // follows takes them as it takes rows that need no turning, and no register keeps the
-            // widened values through the sums
-            float xr[8][8];
-            widen_pieces(pre, gm.dtype, xr);
-            const int tn0 = fb * G + 32 * part + 8 * tg - a.r_old; // this lane's first token in the call's input
-            if (gm.dtype == 1) rope_in_lanes<1>(xr, a, tn0, lane);
-            else rope_in_lanes<0>(xr, a, tn0, lane);
+            float s0 = 0.0f, s1 = 0.0f; // (the part's own sums: not those the mean is formed from)
+            rope_rows(pre, raw, a, fb * G + 32 * part - a.r_old, lane, s0, s1);
+        } else if (mode == 0) {
+            const int piece_w = (c8 + 4 * tg) & 15;
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
-                uint32_t w[4];
-#pragma unroll
-                for (int q = 0; q < 4; q++)
-                    w[q] = gm.dtype == 1 ? pack16_exact<1>(xr[j][2 * q], xr[j][2 * q + 1]) : pack16_exact<0>(xr[j][2 * q], xr[j][2 * q + 1]);
-                pre[j] = uint4{w[0], w[1], w[2], w[3]};
-            }
+            for (int j = 0; j < 8; j++) *(uint4 *)(raw + (8 * tg + j) * 256 + piece_w * 16) = pre[j];
         }
 
         float m[8];
 #pragma unroll
         for (int e = 0; e < 8; e++) m[e] = 0.0f;
         if (mode == 0) {
-            // the rows in the layout of the sum ([token][sixteen 16-byte pieces], the pieces of a row
-            // rotated by four per eight tokens: see flush_wave_kernel), widened
-            const int piece_w = (c8 + 4 * tg) & 15;
-#pragma unroll
-            for (int j = 0; j < 8; j++) *(uint4 *)(raw + (8 * tg + j) * 256 + piece_w * 16) = pre[j];
+            // a channel pair's tokens, widened
             float xs0[32], xs1[32];
             const unsigned char *rd = raw + (lane & 3) * 4;
 #pragma unroll
@@ -1245,19 +1195,19 @@ template <int GC, int BITS, bool ROPE> hipError_t launch_flush_wave(const Append
     return note_launch(hipGetLastError());
 }
 
-template <int G, int GC, int BITS, bool ROPE> hipError_t launch_flush_wave_parts(const AppendArgs &a, hipStream_t s)
+template <int G, int GC, int BITS> hipError_t launch_flush_wave_parts(const AppendArgs &a, hipStream_t s)
 {
     const int U = a.batch * a.n_kv_heads;
     const long long items = (long long)a.n_flush_blocks * U * 2;
     if (items > 0x7FFFFFFF) return hipErrorInvalidValue;
-    constexpr size_t lds = (size_t)(kThreads / 64) * WaveImage<G, GC, BITS, ROPE>::BYTES;
+    constexpr size_t lds = (size_t)(kThreads / 64) * WaveImage<G, GC, BITS>::BYTES;
     static const int slots = [] {
         int per_cu = 0, dev = 0, cus = 0;
         if (lds > 64 * 1024 &&
-            hipFuncSetAttribute((const void *)flush_wave_parts_kernel<G, GC, BITS, ROPE>,
+            hipFuncSetAttribute((const void *)flush_wave_parts_kernel<G, GC, BITS>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_wave_parts_kernel<G, GC, BITS, ROPE>, kThreads, lds) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_wave_parts_kernel<G, GC, BITS>, kThreads, lds) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -1266,7 +1216,7 @@ template <int G, int GC, int BITS, bool ROPE> hipError_t launch_flush_wave_parts
     if (slots < 1) return hipErrorInvalidValue;
     const long long want = (items + kThreads / 64 - 1) / (kThreads / 64);
     const int grid = want < slots ? (int)want : slots;
-    hipLaunchKernelGGL((flush_wave_parts_kernel<G, GC, BITS, ROPE>), dim3(grid), dim3(kThreads), lds, s, a, (int)items);
+    hipLaunchKernelGGL((flush_wave_parts_kernel<G, GC, BITS>), dim3(grid), dim3(kThreads), lds, s, a, (int)items);
     return note_launch(hipGetLastError());
 }
 
@@ -1350,17 +1300,17 @@ hipError_t launch_flush(const AppendArgs &a, hipStream_t s)
     }
 #undef TADAKV_COOP
     if (a.geom.G == 64 && kb == a.geom.v_bits && kb != 16) {
-        // blocks of 64 tokens: the same arithmetic in two passes over two parts of 32 tokens
+        // a step on device-resident lengths (which rotates nothing), blocks of 64 tokens: the same arithmetic
+        // in two passes over two parts of 32 tokens
         const int gc = a.geom.Gc;
-#define TADAKV_PARTS(GV, GCV, R)                                                \
-    (kb == 2 ? launch_flush_wave_parts<GV, GCV, 2, R>(a, s)                     \
-             : kb == 4 ? launch_flush_wave_parts<GV, GCV, 4, R>(a, s) : launch_flush_wave_parts<GV, GCV, 8, R>(a, s))
-        if (a.rope != 0) return gc == 32 ? TADAKV_PARTS(64, 32, true) : gc == 64 ? TADAKV_PARTS(64, 64, true) : TADAKV_PARTS(64, 128, true);
-        return gc == 32 ? TADAKV_PARTS(64, 32, false) : gc == 64 ? TADAKV_PARTS(64, 64, false) : TADAKV_PARTS(64, 128, false);
+#define TADAKV_PARTS(GV, GCV)                                                \
+    (kb == 2 ? launch_flush_wave_parts<GV, GCV, 2>(a, s)                     \
+             : kb == 4 ? launch_flush_wave_parts<GV, GCV, 4>(a, s) : launch_flush_wave_parts<GV, GCV, 8>(a, s))
+        return gc == 32 ? TADAKV_PARTS(64, 32) : gc == 64 ? TADAKV_PARTS(64, 64) : TADAKV_PARTS(64, 128);
     }
     if (a.geom.G == 128 && a.geom.Gc == 128 && kb == a.geom.v_bits && kb != 16) {
         // blocks of 128 tokens with one value group per token: four parts
-        return a.rope != 0 ? TADAKV_PARTS(128, 128, true) : TADAKV_PARTS(128, 128, false);
+        return TADAKV_PARTS(128, 128);
 #undef TADAKV_PARTS
     }
     if (a.geom.G == 32) return launch_flush_gc<32>(a, s);

@@ -40,15 +40,6 @@ template <int DT> __device__ __forceinline__ float round16(float f)
     return __half2float(__float2half_rn(f));
 }
 
-// Two values that the 16-bit type holds exactly (DT: 0 binary16, 1 bfloat16), as the type's bit patterns
-// in one word, a in the low half: one instruction.
-template <int DT> __device__ __forceinline__ uint32_t pack16_exact(float a, float b)
-{
-    if (DT == 1) return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
-    typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, (h2_t)__builtin_amdgcn_cvt_pkrtz(a, b)); // (exact values: no rounding takes place)
-}
-
 // One rotated pair: (a, b) -> (a cos - b sin, b cos + a sin), rounded to the 16-bit type and widened again.
 template <int DT>
 __device__ __forceinline__ void rope_pair_t(float xa, float xb, float c, float s, float &ya, float &yb)
@@ -178,66 +169,131 @@ __device__ __forceinline__ MetaOut meta_of(float mn, float mx, int qmax)
     return o;
 }
 
-// Rotation of this lane's 8 x 8 key values, token pair by token pair (Alg. 1 step 5).  With the
-// (i, i + 64) pairing the partner channel lives in lane l ^ 32 (same tokens); with (2i, 2i + 1)
-// it is the neighbouring register.  Rows that come from the residual buffer (tn < 0) were
-// rotated when they were stored.
-template <int DT>
-__device__ __forceinline__ void rope_in_lanes(float (&x)[8][8], const AppendArgs &a, int tn0, int lane)
+// Two binary32 values rounded (nearest even) to the 16-bit type, packed low | high << 16.
+template <int DT> __device__ __forceinline__ uint32_t narrow2(float lo, float hi)
 {
-    const int c8 = lane >> 2;
-    const bool half_mode = a.rope == 1;
-    // first of this lane's pair indices: 8 pairs (half) or 4 pairs (interleaved)
-    const int i0 = half_mode ? 8 * (c8 & 7) : 4 * c8;
+    if (DT == 1) {
+        const __bf16 a = (__bf16)lo, b = (__bf16)hi; // the conversion instruction of this chip
+        return (uint32_t) * (const uint16_t *)&a | ((uint32_t) * (const uint16_t *)&b << 16);
+    }
+    return (uint32_t)f16_rne(lo) | ((uint32_t)f16_rne(hi) << 16);
+}
+template <int DT> __device__ __forceinline__ float low16(uint32_t w) { return DT == 1 ? __uint_as_float(w << 16) : f16_val((uint16_t)(w & 0xFFFFu)); }
+template <int DT> __device__ __forceinline__ float high16(uint32_t w) { return DT == 1 ? __uint_as_float(w & 0xFFFF0000u) : f16_val((uint16_t)(w >> 16)); }
+
+// ---- rotation of 32 key rows that lie in LDS (Alg. 1 step 5), by one wave.
+// The rows are [token][sixteen 16-byte pieces], the pieces of a row rotated by four per eight tokens;
+// lane l reads the word of channels 2 l and 2 l + 1 of a row (a whole row per instruction) and leaves the
+// turned word in its place, so that what follows finds rows that need no turning, and can add up a
+// channel's tokens on the way.  With the (i, i + 64) pairing the partner word is in lane l ^ 32: the two
+// halves of two rows change places (one instruction for both words), after which lane l holds both words
+// of pairs 2 (l & 31) and + 1 of row 2 k + l / 32, turns them, and the halves change back.  The angles
+// are then eight bytes of each table per lane and two rows, 512 contiguous bytes per instruction: each is
+// read once per item.  With (2 i, 2 i + 1) a word is a pair.
+// Against the rotation in the quantiser's own lane layout (a lane exchange per element, every angle read
+// twice, the mean's sum by a quarter of the lanes at a time, 76 to 96 bytes of registers spilled):
+// 131 to 143 us per call of 65536 tokens of 8 kv heads at G = 32 with (i, i + 64), 116 to 127 us with (2 i, 2 i + 1),
+// bf16 -- now 103 to 113 and 98 to 112 (the plain append: 80 to 91).
+struct Angles { // of eight rows: (i, i + 64): pairs 2 (l & 31), + 1 of row 2 k + l / 32; (2 i, 2 i + 1): pair l of rows 2 k, 2 k + 1
+    float2 c[4], s[4];
+};
+// The angles of eight rows, t0: index in the call's input of the first of them (OLD: rows before the input
+// are not turned and get the first token's angles).
+template <bool HALF, bool OLD> __device__ __forceinline__ void rope_angles(Angles &g, const AppendArgs &a, int t0, int lane)
+{
+    const float *pc = a.rope_cos + (HALF ? 2 * (lane & 31) : lane), *ps = a.rope_sin + (HALF ? 2 * (lane & 31) : lane);
+    if (!OLD) {
+        const long long o = ((long long)t0 + (HALF ? lane >> 5 : 0)) * 64;
+        pc += o;
+        ps += o;
+    }
 #pragma unroll
-    for (int jb = 0; jb < 8; jb += 2) {
-        float4 cs[2][2], sn[2][2];
-#pragma unroll
-        for (int d = 0; d < 2; d++) {
-            int tn = tn0 + jb + d;
-            tn = tn < 0 ? 0 : tn;
-            const float *pc = a.rope_cos + (long long)tn * 64 + i0, *ps = a.rope_sin + (long long)tn * 64 + i0;
-            cs[d][0] = *(const float4 *)pc;
-            sn[d][0] = *(const float4 *)ps;
-            if (half_mode) {
-                cs[d][1] = *(const float4 *)(pc + 4);
-                sn[d][1] = *(const float4 *)(ps + 4);
-            } else {
-                cs[d][1] = float4{0.0f, 0.0f, 0.0f, 0.0f};
-                sn[d][1] = float4{0.0f, 0.0f, 0.0f, 0.0f};
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < 2; d++) {
-            const int j = jb + d;
-            const bool turn = tn0 + j >= 0;
-            const float cv[8] = {cs[d][0].x, cs[d][0].y, cs[d][0].z, cs[d][0].w, cs[d][1].x, cs[d][1].y, cs[d][1].z, cs[d][1].w};
-            const float sv[8] = {sn[d][0].x, sn[d][0].y, sn[d][0].z, sn[d][0].w, sn[d][1].x, sn[d][1].y, sn[d][1].z, sn[d][1].w};
-            if (half_mode) {
-                // lower channel of the pair: x cos - partner sin; upper: x cos + partner sin.  The sign
-                // goes into the sine once per token (a product with the negated sine is the negated
-                // product, and adding that is the subtraction, bit for bit).
-                const bool lower = c8 < 8;
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const float sg = lower ? -sv[e] : sv[e];
-                    const float xp = from_lane_f(x[j][e], lane ^ 32);
-                    const float p1 = x[j][e] * cv[e], p2 = xp * sg;
-                    const float y = round16<DT>(p1 + p2);
-                    x[j][e] = turn ? y : x[j][e];
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const float xa = x[j][2 * k], xb = x[j][2 * k + 1];
-                    float ya, yb;
-                    rope_pair_t<DT>(xa, xb, cv[k], sv[k], ya, yb);
-                    x[j][2 * k] = turn ? ya : xa;
-                    x[j][2 * k + 1] = turn ? yb : xb;
-                }
-            }
+    for (int k = 0; k < 4; k++) {
+        if (HALF) {
+            const int o = OLD ? max(t0 + 2 * k + (lane >> 5), 0) * 64 : 128 * k;
+            g.c[k] = *(const float2 *)(pc + o);
+            g.s[k] = *(const float2 *)(ps + o);
+        } else {
+            const int o = OLD ? max(t0 + 2 * k, 0) * 64 : 128 * k, o1 = OLD ? max(t0 + 2 * k + 1, 0) * 64 : 128 * k + 64;
+            g.c[k] = float2{pc[o], pc[o1]};
+            g.s[k] = float2{ps[o], ps[o1]};
         }
     }
+}
+// Eight rows (p: this lane's word of the first of them), turned in place; s0, s1: the running sums.
+template <int DT, bool HALF, bool OLD>
+__device__ __forceinline__ void rope_eight(unsigned char *p, const Angles &g, int t0, float &s0, float &s1)
+{
+    uint32_t w[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) w[k] = *(const uint32_t *)(p + k * 256);
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const uint32_t w0 = w[2 * k], w1 = w[2 * k + 1];
+        uint32_t y0, y1;
+        if (HALF) {
+            const auto ab = __builtin_amdgcn_permlane32_swap(w0, w1, false, false);
+            const float a0 = low16<DT>(ab[0]), a1 = high16<DT>(ab[0]), b0 = low16<DT>(ab[1]), b1 = high16<DT>(ab[1]);
+            const float pa0 = a0 * g.c[k].x, pb0 = b0 * g.s[k].x, qb0 = b0 * g.c[k].x, qa0 = a0 * g.s[k].x;
+            const float pa1 = a1 * g.c[k].y, pb1 = b1 * g.s[k].y, qb1 = b1 * g.c[k].y, qa1 = a1 * g.s[k].y;
+            const auto yy = __builtin_amdgcn_permlane32_swap(narrow2<DT>(pa0 - pb0, pa1 - pb1), narrow2<DT>(qb0 + qa0, qb1 + qa1), false, false);
+            y0 = yy[0];
+            y1 = yy[1];
+        } else {
+            const float a0 = low16<DT>(w0), b0 = high16<DT>(w0), a1 = low16<DT>(w1), b1 = high16<DT>(w1);
+            const float pa0 = a0 * g.c[k].x, pb0 = b0 * g.s[k].x, qb0 = b0 * g.c[k].x, qa0 = a0 * g.s[k].x;
+            const float pa1 = a1 * g.c[k].y, pb1 = b1 * g.s[k].y, qb1 = b1 * g.c[k].y, qa1 = a1 * g.s[k].y;
+            y0 = narrow2<DT>(pa0 - pb0, qb0 + qa0);
+            y1 = narrow2<DT>(pa1 - pb1, qb1 + qa1);
+        }
+        if (OLD) { // rows that waited in the residual buffer were turned when they were stored
+            y0 = t0 + 2 * k >= 0 ? y0 : w0;
+            y1 = t0 + 2 * k + 1 >= 0 ? y1 : w1;
+        }
+        *(uint32_t *)(p + 2 * k * 256) = y0;
+        *(uint32_t *)(p + (2 * k + 1) * 256) = y1;
+        s0 = s0 + low16<DT>(y0);
+        s1 = s1 + high16<DT>(y0);
+        s0 = s0 + low16<DT>(y1);
+        s1 = s1 + high16<DT>(y1);
+    }
+}
+// The 32 rows that the wave has loaded (pre[j]: token 8 tg + j, channels 8 c8 .. + 7) through LDS: in as they
+// came, out turned; s0, s1: sums of channels 2 lane and 2 lane + 1 over the turned rows, in token order.
+// tn0: index in the call's input of the first row.
+template <int DT, bool HALF, bool OLD>
+__device__ __forceinline__ void rope_rows_t(uint4 (&pre)[8], unsigned char *rows, const AppendArgs &a, int tn0, int lane, float &s0, float &s1)
+{
+    const int tg = lane & 3, c8 = lane >> 2, piece_w = (c8 + 4 * tg) & 15;
+    Angles g[2]; // (sixteen rows ahead)
+    rope_angles<HALF, OLD>(g[0], a, tn0, lane);
+    rope_angles<HALF, OLD>(g[1], a, tn0 + 8, lane);
+#pragma unroll
+    for (int j = 0; j < 8; j++) *(uint4 *)(rows + (8 * tg + j) * 256 + piece_w * 16) = pre[j];
+#pragma unroll
+    for (int tq = 0; tq < 4; tq++) {
+        unsigned char *p = rows + tq * 2048 + ((((lane >> 2) + 4 * tq) & 15) << 4) + (lane & 3) * 4;
+        rope_eight<DT, HALF, OLD>(p, g[tq & 1], tn0 + 8 * tq, s0, s1);
+        if (tq < 2) rope_angles<HALF, OLD>(g[tq & 1], a, tn0 + 8 * (tq + 2), lane);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; j++) pre[j] = *(const uint4 *)(rows + (8 * tg + j) * 256 + piece_w * 16);
+}
+__device__ __forceinline__ void rope_rows(uint4 (&pre)[8], unsigned char *rows, const AppendArgs &a, int tn0, int lane, float &s0, float &s1)
+{
+#define TADAKV_ROPE(DT, HALF)                                                      \
+    do {                                                                           \
+        if (tn0 < 0) rope_rows_t<DT, HALF, true>(pre, rows, a, tn0, lane, s0, s1); \
+        else rope_rows_t<DT, HALF, false>(pre, rows, a, tn0, lane, s0, s1);        \
+    } while (0)
+    if (a.geom.dtype == 1) {
+        if (a.rope == 1) TADAKV_ROPE(1, true);
+        else TADAKV_ROPE(1, false);
+    } else {
+        if (a.rope == 1) TADAKV_ROPE(0, true);
+        else TADAKV_ROPE(0, false);
+    }
+#undef TADAKV_ROPE
 }
 
 // Minimum / maximum as the bare instructions.  fminf / fmaxf make the compiler put a quieting

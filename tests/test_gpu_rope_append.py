@@ -114,6 +114,21 @@ def test_rope_append_blocks_of_128(kv, oracle, bits, mode, pairing):
     check_attention(gpu, orc, 0, synth.make_q(340 + bits, 2, 8, 128, BF16), BF16)
 
 
+@pytest.mark.parametrize("pairing", [HALF, INTER])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("G,mode", [(32, CHAN), (32, NONE), (64, NONE), (128, CHAN)])
+def test_rope_append_block_begun_with_an_odd_row(kv, oracle, G, mode, dtype, pairing):
+    """The rows of a block that come from the raw buffer end inside a pair of rows, inside a group of eight and
+    inside a part of 32: those before pass as they are, those after are turned."""
+    print("case rope_odd_start G=%d mode=%d dtype=%d pairing=%d" % (G, mode, dtype, pairing), flush=True)
+    B, Hkv, T = 2, 3, 3 * G + 11
+    k, v = synth.make_kv(350 + G, B, T, Hkv, 128, dtype)
+    for first in (1, G // 2 + 3, G - 1):
+        gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv, Hkv=Hkv, T_max=4 * G, G=G, Gc=32, R=G, dtype=dtype, mode=mode, k_bits=(8,))
+        rope_append_both(gpu, orc, 0, k, v, dtype, pairing, [first, T - first], pos0=91)
+        check_bytes(gpu, orc, 0)
+
+
 def test_rope_append_equals_rotating_first(kv, oracle):
     """The fused call stores what a separate rotation (here: the oracle's) followed by the plain
     append stores; strided input views are accepted."""
