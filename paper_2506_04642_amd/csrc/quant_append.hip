@@ -70,6 +70,43 @@ __device__ __forceinline__ void step_store_unit(const AppendArgs &a, int u)
         after[1] = ok ? (full ? 0 : r + 1) : r;
     }
 }
+// Row i of the raw tail of unit u (of the launch): input token copy_src + i -> residual row copy_dst + i, keys
+// and values, by 32 threads.
+template <bool ROPE> __device__ __forceinline__ void tail_row(const AppendArgs &a, int u, int i)
+{
+    const int b = u / a.n_kv_heads, h = u % a.n_kv_heads;
+    const int lane = threadIdx.x & 31, which = lane >> 4, ch = lane & 15;
+    if (a.sides && which != a.sides - 1) return;
+    const uint16_t *base = which == 0 ? a.k_new : a.v_new;
+    const uint16_t *src = base + (long long)b * a.stride_b + (long long)(a.copy_src + i) * a.stride_t +
+                          (long long)h * a.stride_h + ch * 8;
+    const long long off = (which == 0 ? a.geom.k_resid_off : a.geom.v_resid_off) +
+                          ((long long)(a.b0 * a.n_kv_heads + u) * a.geom.R + a.copy_dst + i) * (kHeadDim * 2) + ch * 16;
+    if (ROPE && a.rope != 0 && which == 0) {
+        const uint16_t *row = src - ch * 8;
+        const int tn = a.copy_src + i;
+        const float *cs = a.rope_cos + (long long)tn * 64, *sn = a.rope_sin + (long long)tn * 64;
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            w[e] = (uint32_t)narrow16(rope_elem(row, ch * 8 + 2 * e, cs, sn, a.rope, a.geom.dtype), a.geom.dtype) |
+                   ((uint32_t)narrow16(rope_elem(row, ch * 8 + 2 * e + 1, cs, sn, a.rope, a.geom.dtype), a.geom.dtype) << 16);
+        *(uint4 *)(a.layer + off) = uint4{w[0], w[1], w[2], w[3]};
+        return;
+    }
+    *(uint4 *)(a.layer + off) = *(const uint4 *)src;
+}
+// The raw tail inside a quantiser's launch, after the workgroup's items: a launch of its own takes 5 us of a
+// call, as much as 4000 tokens' compression.  Allowed where nothing that the launch reads lies in the rows
+// it writes (AppendArgs::tail_too).
+template <int THREADS, bool ROPE> __device__ __forceinline__ void tail_rows(const AppendArgs &a)
+{
+    if (!a.tail_too) return;
+    constexpr int per = THREADS / 32;
+    const int rows = a.copy_n * a.batch * a.n_kv_heads;
+#pragma unroll 1
+    for (int i = (int)blockIdx.x * per + ((int)threadIdx.x >> 5); i < rows; i += (int)gridDim.x * per) tail_row<ROPE>(a, i / a.copy_n, i % a.copy_n);
+}
 // (token, channel) of the first code of packed word w and whether the word runs along
 // channels (keys) or tokens (values); a word holds 32/bits codes.
 __device__ __forceinline__ void word_origin(int which, int bits, int G, int w, int &t0, int &c0)
@@ -375,6 +412,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((G == 
         }
         __syncthreads(); // the next item reuses the LDS buffers
     }
+    tail_rows<kThreads, ROPE>(a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -676,6 +714,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
         for (int off = lane * 16; off < part_bytes; off += 64 * 16) *(uint4 *)(rec + base_off + off) = *(const uint4 *)(img + off);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the image is in registers before the next item overwrites it
     }
+    tail_rows<kThreads, ROPE>(a);
 }
 
 
@@ -885,6 +924,7 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
     unsigned char *img = lds_uni;
     unsigned char *raw = lds_uni + part * 8192;
 
+    tail_rows<64 * NP, ROPE>(a); // (ahead of the items here: behind them it cost the 2-bit instances 3 to 6 more spilled registers)
 
     // (the grid is even: a workgroup alternates between keys and values, which cost differently, and
     // items 2 j and 2 j + 1 are the two sides of one block)
@@ -1106,33 +1146,12 @@ __global__ __launch_bounds__(kThreads) void xhead_mean_kernel(AppendArgs a)
     }
 }
 
-// Raw tail: input tokens [copy_src, copy_src + copy_n) -> residual rows [copy_dst, ...).
+// The raw tail as a launch of its own: calls that compress nothing, and calls whose compression reads
+// the rows of the residual buffer that the tail replaces (see append_impl).
 __global__ __launch_bounds__(kThreads) void resid_copy_kernel(AppendArgs a)
 {
-    const int u = blockIdx.y;
-    const int b = u / a.n_kv_heads, h = u % a.n_kv_heads;
     const int i = blockIdx.x * 8 + (threadIdx.x >> 5);
-    if (i >= a.copy_n) return;
-    const int lane = threadIdx.x & 31, which = lane >> 4, ch = lane & 15;
-    if (a.sides && which != a.sides - 1) return;
-    const uint16_t *base = which == 0 ? a.k_new : a.v_new;
-    const uint16_t *src = base + (long long)b * a.stride_b + (long long)(a.copy_src + i) * a.stride_t +
-                          (long long)h * a.stride_h + ch * 8;
-    const long long off = (which == 0 ? a.geom.k_resid_off : a.geom.v_resid_off) +
-                          ((long long)(a.b0 * a.n_kv_heads + u) * a.geom.R + a.copy_dst + i) * (kHeadDim * 2) + ch * 16;
-    if (a.rope != 0 && which == 0) {
-        const uint16_t *row = src - ch * 8;
-        const int tn = a.copy_src + i;
-        const float *cs = a.rope_cos + (long long)tn * 64, *sn = a.rope_sin + (long long)tn * 64;
-        uint32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-            w[e] = (uint32_t)narrow16(rope_elem(row, ch * 8 + 2 * e, cs, sn, a.rope, a.geom.dtype), a.geom.dtype) |
-                   ((uint32_t)narrow16(rope_elem(row, ch * 8 + 2 * e + 1, cs, sn, a.rope, a.geom.dtype), a.geom.dtype) << 16);
-        *(uint4 *)(a.layer + off) = uint4{w[0], w[1], w[2], w[3]};
-        return;
-    }
-    *(uint4 *)(a.layer + off) = *(const uint4 *)src;
+    if (i < a.copy_n) tail_row<true>(a, blockIdx.y, i);
 }
 
 } // namespace

@@ -560,8 +560,11 @@ static kv_status append_impl(kv_cache *cache, int32_t layer, int seq0, int n_seq
             a.copy_dst = r_old;
             a.copy_n = n_new;
         }
+        // (a call that starts on an empty residual buffer stores its raw tail in the same launch; otherwise the
+        // compression reads the buffer's rows, and the tail follows it)
+        a.tail_too = a.n_flush_blocks > 0 && r_old == 0 && a.copy_n > 0;
         if (a.n_flush_blocks > 0 && launch_flush(a, s) != hipSuccess) return KV_E_HIP;
-        if (a.copy_n > 0 && launch_resid_copy(a, s) != hipSuccess) return KV_E_HIP;
+        if (a.copy_n > 0 && !a.tail_too && launch_resid_copy(a, s) != hipSuccess) return KV_E_HIP;
         for (int b = b0; b < b1; b++) {
             cache->P(layer, b) += (int)n_flush_tok;
             cache->R(layer, b) = (int)(total - n_flush_tok);
@@ -667,8 +670,11 @@ kv_status kv_compressv_append(kv_cache *cache, int32_t layer, const void *k_new,
             a.copy_dst = r_old;
             a.copy_n = n_new;
         }
+        // (a call that starts on an empty residual buffer stores its raw tail in the same launch; otherwise the
+        // compression reads the buffer's rows, and the tail follows it)
+        a.tail_too = a.n_flush_blocks > 0 && r_old == 0 && a.copy_n > 0;
         if (a.n_flush_blocks > 0 && launch_flush(a, s) != hipSuccess) return KV_E_HIP;
-        if (a.copy_n > 0 && launch_resid_copy(a, s) != hipSuccess) return KV_E_HIP;
+        if (a.copy_n > 0 && !a.tail_too && launch_resid_copy(a, s) != hipSuccess) return KV_E_HIP;
         // ---- values: projected by the kernels that also compress them (whole blocks of this call's
         // tokens) or store them as raw rows (tokens that complete a block begun earlier, and the tail)
         ProjectArgs p{};
@@ -702,7 +708,7 @@ kv_status kv_compressv_append(kv_cache *cache, int32_t layer, const void *k_new,
             if (n_pre > 0 && !raw_rows(0, n_pre, r_old)) return KV_E_HIP;
             const int n_old_blocks = (r_old + n_pre) / G; // blocks whose rows all wait in the residual buffer now
             if (n_old_blocks > 0) {
-                AppendArgs av = a;
+                AppendArgs av = a; // (only reached with rows in the buffer: the tail is not in its launch)
                 av.sides = 2;
                 av.rope = 0;
                 av.r_old = r_old + n_pre;
