@@ -334,7 +334,8 @@ kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void
                                       int64_t stride_b, int64_t stride_h, const void *q,
                                       void *workspace, size_t workspace_bytes, void *stream);
 
-/* Number of sequence splits kv_decode_attn uses for `layer` at its current length. */
+/* Number of sequence splits kv_decode_attn uses for `layer` at its current length (where the sequences
+ * differ in length, of the sequence with the most). */
 kv_status kv_decode_splits(const kv_cache *cache, int32_t layer, int32_t *n_splits);
 
 /* Bytes kv_decode_attn must read and write for `layer` at its current length: packed codes,

@@ -416,7 +416,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     // workgroups (parts) share a (sequence, split) and read the same mean rows -- they sit 8 apart in
     // the launch order when the split count allows (same XCD and so the same L2, resident together)
     const int parts = XF ? a.n_kv_heads / NW : 1;
-    int sp = blockIdx.x, half = 0; // half: which part
+    int sp = blockIdx.x, half = 0, u_ = blockIdx.y, ns_ = a.n_splits, row0 = 0; // half: which part
+    if (XH == 0) unit_and_split(a, u_, sp, ns_, row0);
     if (XF && parts > 1) {
         if (a.n_splits % 8 == 0) {
             half = (sp >> 3) % parts;
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
             sp /= parts;
         }
     }
-    const int u = XF ? (int)blockIdx.y * a.n_kv_heads + half * NW + wave : (int)blockIdx.y;
+    const int u = XF ? (int)blockIdx.y * a.n_kv_heads + half * NW + wave : u_;
     const int b = u / a.n_kv_heads, h = u % a.n_kv_heads;
     const int g = a.g;
     const int cw0 = XF ? 0 : wave; // this wave's first local chunk
@@ -439,7 +440,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     // front to back as one moving window instead of as n_splits far-apart streams
     const int b_end = seq_blocks(a, b) * HB, r_seq = seq_resid(a, b); // this sequence's packed blocks and raw tokens
     const int chunks_total = (b_end + NBC - 1) / NBC;
-    const int ns = a.n_splits;
+    const int nr = XH == 0 ? a.resid_splits : 0, ns = ns_ - nr; // splits for raw tokens only, splits with chunks
+    const int b_mine = sp < ns ? chunks_total : 0;               // (none for the former)
     // local chunk j of this split is the unit's chunk sp + ns * j
     const int w0 = sp * NBC;          // first block of local chunk 0
     const int cstride = ns * NBC;     // blocks between consecutive local chunks
@@ -447,9 +449,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     // halves of its k-th block; n_chunks is then the wave's own bound (cw0 + CW * its chunks; the
     // CW waves that share a unit's chunks: all of the workgroup's, or, in the fused cross-head form,
     // this one alone)
-    const int blocks_sp = sp * HB < chunks_total ? (chunks_total / HB - sp + ns - 1) / ns : 0; // H2 only
+    const int blocks_sp = sp * HB < b_mine ? (chunks_total / HB - sp + ns - 1) / ns : 0; // H2 only
     const int n_chunks = H2 ? cw0 + CW * 2 * ((blocks_sp - cw0 + CW - 1) / CW)
-                            : (sp < chunks_total ? (chunks_total - sp + ns - 1) / ns : 0);
+                            : (sp < b_mine ? (chunks_total - sp + ns - 1) / ns : 0);
     // first block (as the arithmetic counts them) of this wave's local chunk ci = cw0 + CW * k
     auto blk_of = [&](int ci) {
         if (!H2) return w0 + ci * cstride;
@@ -1142,7 +1144,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     // ---- raw residual tokens (Sec. 3.3) in tiles of 32, dealt to the splits in turn after the
     // unit's last chunk; wave w of the split takes tokens 8 w .. 8 w + 7 of a tile into its own
     // online-softmax state, with its own LDS region as scratch (no workgroup barrier)
-    const int rt_first = (sp - chunks_total % ns + ns) % ns; // this split's first tile
+    // (or to the splits that take nothing else: see plan_resid in tadakv_abi.cpp)
+    const int rt_step = nr ? nr : ns;
+    const int rt_first = nr ? (sp < ns ? r_seq : sp - ns) : (sp - chunks_total % ns + ns) % ns; // this split's first tile
     if (rt_first * 32 + 8 * cw0 < r_seq) {
         unsigned char *L = (unsigned char *)lds;
         constexpr int RS = 264;  // bytes per staged row (33 * 8): rows start in different banks
@@ -1172,8 +1176,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
         const int t_fresh = a.k_fresh ? r_seq - 1 : -1;
         // (fused cross-head form: the wave has the unit to itself and takes all four groups of a tile)
         for (int tg8 = XF ? 0 : wave;; tg8 += XF ? 1 : 4) {
-            const int t0 = (rt_first + ns * (tg8 >> 2)) * 32 + 8 * (tg8 & 3);
-            if ((rt_first + ns * (tg8 >> 2)) * 32 >= r_seq) break;
+            const int t0 = (rt_first + rt_step * (tg8 >> 2)) * 32 + 8 * (tg8 & 3);
+            if ((rt_first + rt_step * (tg8 >> 2)) * 32 >= r_seq) break;
             if (t0 >= r_seq) continue;
             const int nt = r_seq - t0 < 8 ? r_seq - t0 : 8;
             wave_lds_fence();
@@ -1299,7 +1303,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 #pragma unroll
                 for (int ct = 0; ct < 8; ct++) o[ct] += all[w * WAVE_DW + (hg * 10 + 2 + ct) * 64 + lane] * wt;
             }
-            float *dst = a.ws + (((long long)u * g + head) * a.n_splits + sp) * kPartialStride;
+            const long long at = XH == 0 ? (long long)row0 + head * ns_ + sp : ((long long)u * g + head) * ns_ + sp;
+            float *dst = a.ws + at * kPartialStride;
 #pragma unroll
             for (int ct = 0; ct < 8; ct++) dst[16 * ct + n] = o[ct];
             if (n == 0) {
@@ -1333,7 +1338,10 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hip
 {
     if (!RecLayout<B, G, GC, MEAN>::matches(a.geom)) return hipErrorInvalidValue;
     if (XH == 2 && (a.n_kv_heads < NW || a.n_kv_heads % NW != 0)) return hipErrorInvalidValue;
+    if (a.uneven && XH != 0) return hipErrorInvalidValue;
+    static_assert(XH != 0 || NW == kSplitWaves, "the planner of uneven splits counts on it");
     dim3 grid(XH == 2 ? a.n_splits * (a.n_kv_heads / NW) : a.n_splits, XH == 2 ? a.batch : a.batch * a.n_kv_heads);
+    if (a.uneven) grid = dim3(a.uneven_total, a.n_kv_heads);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
     if (t_ev_begin && t_ev_end) {
         // the dispatch itself stamps the events: the kernel's execution, without the gaps before and after it
@@ -1375,6 +1383,10 @@ struct DoLaunch {
 struct DoPlan {
     int result = 1;
     template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &a) { result = plan_inst<B, G, GC, MEAN, NW, NHG, XH, PG>(a); }
+};
+struct DoSlots {
+    int result = 0;
+    template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &) { result = resident_blocks<B, G, GC, MEAN, NW, NHG, XH, PG>(); }
 };
 struct DoMatch {
     bool result = false;
@@ -1508,6 +1520,14 @@ int decode_mfma_splits(const DecodeArgs &a)
 {
     if (!decode_mfma_supported(a)) return 1;
     DoPlan p;
+    pick(a, p);
+    return p.result;
+}
+
+int decode_mfma_slots(const DecodeArgs &a)
+{
+    if (!decode_mfma_supported(a)) return 0;
+    DoSlots p;
     pick(a, p);
     return p.result;
 }

@@ -33,7 +33,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
-constexpr int kRawWaves = 4;
+constexpr int kRawWaves = kSplitWaves;
 constexpr int kChunk = 32;       // tokens a wave takes at a time
 constexpr int kRowBytes = 256;   // one token's row
 constexpr float kScoreScale = 0.08838834764831845f * 1.4426950408889634f; // log2(e) / sqrt(128)
@@ -62,7 +62,9 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
     const LayerGeom &gm = a.geom;
     const int lane = threadIdx.x & 63, row = lane >> 4, n = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int sp = blockIdx.x, u = blockIdx.y, ns = a.n_splits, g = a.g;
+    int sp, u, ns, row0;
+    unit_and_split(a, u, sp, ns, row0);
+    const int g = a.g;
     const int b = u / a.n_kv_heads, h = u % a.n_kv_heads;
     const int sh = gm.G >> 6; // log2 of the chunks per block of the cache (32, 64, 128 tokens: 1, 2, 4)
     const int nb = seq_blocks(a, b), r = seq_resid(a, b);
@@ -230,7 +232,7 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
             num += state[w][at] * wt;
             den += state[w][33 * ST + head] * wt;
         }
-        float *dst = a.ws + (((long long)u * g + head) * ns + sp) * kPartialStride;
+        float *dst = a.ws + ((long long)row0 + head * ns + sp) * kPartialStride;
         dst[c] = num;
         if (c == 0) {
             dst[kHeadDim] = Mx;
@@ -260,13 +262,18 @@ bool decode_raw_supported(const DecodeArgs &a)
     return g.k_bits == 16 && g.v_bits == 16 && a.g <= kMaxGroupQ && a.batch * a.n_kv_heads <= 65535;
 }
 
+int decode_raw_slots(const DecodeArgs &a)
+{
+    const bool pg = a.geom.table != nullptr;
+    return a.geom.dtype == 1 ? (pg ? resident_blocks<1, true>() : resident_blocks<1, false>())
+                             : (pg ? resident_blocks<0, true>() : resident_blocks<0, false>());
+}
+
 // One resident round of workgroups, at least four chunks per wave unless the device cannot be filled even
 // so (a launch that small is bound by latency: one chunk per wave); never more splits than `cap`.
 int decode_raw_splits(const DecodeArgs &a, int cap)
 {
-    const bool pg = a.geom.table != nullptr;
-    const int slots = a.geom.dtype == 1 ? (pg ? resident_blocks<1, true>() : resident_blocks<1, false>())
-                                        : (pg ? resident_blocks<0, true>() : resident_blocks<0, false>());
+    const int slots = decode_raw_slots(a);
     const int U = a.batch * a.n_kv_heads;
     const int chunks = a.n_blocks * (a.geom.G / kChunk) + (a.r + kChunk - 1) / kChunk;
     int ns = slots / U;
@@ -280,7 +287,7 @@ int decode_raw_splits(const DecodeArgs &a, int cap)
 hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s)
 {
     if (!decode_raw_supported(a)) return hipErrorInvalidValue;
-    const dim3 grid(a.n_splits, a.batch * a.n_kv_heads), block(64 * kRawWaves);
+    const dim3 grid = a.uneven ? dim3(a.uneven_total, a.n_kv_heads) : dim3(a.n_splits, a.batch * a.n_kv_heads), block(64 * kRawWaves);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
     const bool pg = a.geom.table != nullptr;
     if (a.geom.dtype == 1) {

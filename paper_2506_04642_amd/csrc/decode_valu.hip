@@ -363,8 +363,8 @@ __global__ __launch_bounds__(256) void merge_kernel(DecodeArgs a)
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int uq = blockIdx.x; // (unit, head-in-group)
     const int u = uq / a.g, i = uq % a.g;
-    const int ns = a.n_splits;
-    const float *base = a.ws + (long long)uq * ns * kPartialStride;
+    int ns;
+    const float *base = a.ws + partial_row(a, u, i, ns) * kPartialStride;
     float M = -INFINITY;
     for (int j = threadIdx.x; j < ns; j += 256) M = fmaxf(M, base[j * kPartialStride + kHeadDim]);
     M = wave_max(M);
@@ -555,6 +555,7 @@ template <int KB, int VB> hipError_t launch_one(const DecodeArgs &a, hipStream_t
 
 hipError_t launch_decode_split_valu(const DecodeArgs &a, hipStream_t s)
 {
+    if (a.uneven) return hipErrorInvalidValue; // (this kernel takes one split count for all)
     if (a.batch * a.n_kv_heads > 65535) return hipErrorInvalidValue;
     const int kb = a.geom.k_bits, vb = a.geom.v_bits;
     if ((kb == 16) != (vb == 16)) return hipErrorInvalidValue; // mixed raw / packed sides: not built

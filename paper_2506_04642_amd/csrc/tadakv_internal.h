@@ -114,13 +114,22 @@ struct DecodeArgs {
     LayerGeom geom;
     const unsigned char *layer;
     const uint16_t *q;   // [batch][Hq][128]
-    float *ws;           // partials [U][g][n_splits][kPartialStride]
+    float *ws;           // partials [U][g][n_splits][kPartialStride] (uneven: see partial_row)
     float *out;          // [batch][Hq][128]
     uint16_t *out16;     // the same in the cache's 16-bit type, if not null (then `out` is not written)
     int n_kv_heads, n_q_heads, batch, g;
     int n_blocks;        // packed blocks in the layer
     int r;               // residual tokens
     int n_splits;
+    // not 0: a split count per sequence in place of n_splits, for the kernels without a mean over the heads and
+    // the kernel of the 16-bit layers: as many as its chunks need for `uneven` rounds of a workgroup's waves
+    // (uneven_count); grid (uneven_total, n_kv_heads), a sequence's splits behind those of the one before
+    int uneven;
+    int uneven_chunk;  // tokens of such a chunk (32, 64 or 128), uneven_tails: the raw tokens are chunks, too
+    int uneven_tails, uneven_total;
+    // of a unit's splits the last resid_splits take its raw tokens (tiles of 32 in turn) and no chunks; 0: the raw
+    // tokens are dealt to all splits behind their chunks (matrix-core kernel without a mean over the heads)
+    int resid_splits;
     int blocks_per_split;
     // matrix-core kernel only: the newest residual token (index r - 1) is not in the cache yet;
     // the kernel takes it from these rows and stores it (null: every token is in the cache)
@@ -170,6 +179,73 @@ __host__ __device__ inline int seq_resid(const DecodeArgs &a, int b)
     return a.ragged ? a.r_seq[b] : a.r;
 }
 
+constexpr int kSplitWaves = 4; // wavefronts of a workgroup that share a unit's chunks (kernels that take uneven splits)
+// splits of a sequence that holds nb packed blocks and r raw tokens
+__host__ __device__ inline int uneven_count(const DecodeArgs &a, int nb, int r)
+{
+    const int chunks = (nb * a.geom.G + a.uneven_chunk - 1) / a.uneven_chunk + (a.uneven_tails ? (r + a.uneven_chunk - 1) / a.uneven_chunk : 0);
+    const int per = kSplitWaves * a.uneven, n = (chunks + per - 1) / per;
+    return n > 0 ? n + a.resid_splits : (r > 0 ? 1 + a.resid_splits : 0);
+}
+// Where sequence b's splits begin, and how many there are: every lane counts those of up to four sequences and
+// the lanes add up (a table of the offsets in the arguments is one more dependent load from
+// memory and made every launch 0.3 us longer, also those that do not use it).  b < 0: the sequence that split x
+// belongs to.
+__device__ __forceinline__ void uneven_find(const DecodeArgs &a, int x, int &b, int &first, int &ns)
+{
+    const int lane = threadIdx.x & 63;
+    int before = 0;
+    for (int b0 = 0;; b0 += 64) {
+        const int i = b0 + lane;
+        const int n = i < a.batch ? uneven_count(a, a.nb_seq[i], a.r_seq[i]) : 0;
+        int end = n;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(end, o);
+            end += lane >= o ? t : 0;
+        }
+        end += before;
+        // (split x: behind the sequences that end at or before it)
+        const int at = b >= 0 ? b : b0 + (int)__popcll(__builtin_amdgcn_ballot_w64(i < a.batch && end <= x));
+        if (at < b0 + 64 || b0 + 64 >= a.batch) {
+            b = at < a.batch ? at : a.batch - 1;
+            ns = __builtin_amdgcn_readlane(n, b - b0);
+            first = __builtin_amdgcn_readlane(end, b - b0) - ns;
+            return;
+        }
+        before = __builtin_amdgcn_readlane(end, 63);
+    }
+}
+// first partial result of (unit u, query head i of its group) and the number of its splits
+__device__ __forceinline__ long long partial_row(const DecodeArgs &a, int u, int i, int &ns)
+{
+    if (!a.uneven) {
+        ns = a.n_splits;
+        return ((long long)u * a.g + i) * ns;
+    }
+    int b = u / a.n_kv_heads, first;
+    uneven_find(a, 0, b, first, ns);
+    return ((long long)first * a.n_kv_heads + (long long)(u % a.n_kv_heads) * ns) * a.g + (long long)i * ns;
+}
+// unit and split of this workgroup, the number of the unit's splits and its first partial result (query head 0;
+// head i: i * ns further).  Grid: see DecodeArgs::uneven; otherwise (n_splits, units).
+__device__ __forceinline__ void unit_and_split(const DecodeArgs &a, int &u, int &sp, int &ns, int &row)
+{
+    if (!a.uneven) {
+        sp = blockIdx.x;
+        u = blockIdx.y;
+        ns = a.n_splits;
+        row = u * a.g * ns;
+        return;
+    }
+    int b = -1, first;
+    uneven_find(a, blockIdx.x, b, first, ns);
+    b = __builtin_amdgcn_readfirstlane(b);
+    sp = (int)blockIdx.x - first;
+    u = b * a.n_kv_heads + (int)blockIdx.y;
+    row = (first * a.n_kv_heads + (int)blockIdx.y * ns) * a.g;
+}
+
 // reconstruction of a layer's contents: lengths and geometry as for a decode launch
 struct DequantArgs {
     DecodeArgs d;
@@ -191,12 +267,14 @@ hipError_t launch_decode_split_mfma(const DecodeArgs &a, hipStream_t s);
 // layers stored in 16 bits
 bool decode_raw_supported(const DecodeArgs &a);
 int decode_raw_splits(const DecodeArgs &a, int cap); // preferred split count, at most cap
+int decode_raw_slots(const DecodeArgs &a);           // workgroups the device holds at once
 hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s);
 // the calling thread's next matrix-core split launch records its begin and end into these (one-shot; null cancels)
 void set_split_timing_events(hipEvent_t begin, hipEvent_t end);
 bool decode_mfma_supported(const DecodeArgs &a);
 bool xhead_fused(const DecodeArgs &a); // cross-head mean: both mean terms inside the matrix-core split kernel
 int decode_mfma_splits(const DecodeArgs &a); // preferred split count of the matrix-core kernel
+int decode_mfma_slots(const DecodeArgs &a);  // workgroups of it the device holds at once
 hipError_t launch_decode_merge(const DecodeArgs &a, hipStream_t s);
 hipError_t launch_dequant(const DequantArgs &q, hipStream_t s);
 // cross-head mean, matrix-core path: scores of the queries against the key mean plane (before the

@@ -1,0 +1,131 @@
+"""Decode launches whose splits are not one count for all: sequences of very different lengths get splits by
+their length, and the raw tokens get splits of their own where the device holds them.  Attention against the
+oracle (binary64) on both kinds of launch, over the edges of the plan: sequences without tokens, with raw tokens
+only, batches beyond one wavefront's count of sequences, group sizes, head counts, 16-bit layers, paged blocks."""
+import numpy as np
+import pytest
+
+from paper_2506_04642_amd import synth
+from parity_util import make_pair, to_dev
+
+pytestmark = pytest.mark.gpu
+
+F16, BF16 = 0, 1
+CHAN, NONE = 0, 2
+TOL = 2e-3 / 40  # unit-scale values: the oracle tests' measured errors are below 1e-5
+
+
+@pytest.fixture(scope="module")
+def kv():
+    import torch
+
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    from paper_2506_04642_amd import binding
+
+    return binding
+
+
+def fill(gpu, orc, lengths, Hkv, dtype, seed):
+    for b, n in enumerate(lengths):
+        if n:
+            k, v = synth.make_kv(seed + b, 1, n, Hkv, 128, dtype)
+            gpu.append_seq(0, b, to_dev(k[0], dtype), to_dev(v[0], dtype))
+            orc.append_seq(0, b, k[0], v[0])
+
+
+def check(kv, gpu, orc, B, Hq, dtype, seed):
+    import torch
+
+    q = synth.make_q(seed, B, Hq, 128, dtype)
+    got = gpu.attend(0, to_dev(q, dtype))
+    torch.cuda.synchronize()
+    got = got.cpu().numpy().astype(np.float64)
+    assert np.all(np.isfinite(got))
+    assert float(np.max(np.abs(got - orc.attend(0, q)))) <= TOL
+    return q, got
+
+
+@pytest.mark.parametrize("bits,G,Gc,R,Hkv,g,mode", [(4, 32, 32, 32, 2, 4, CHAN), (2, 64, 64, 64, 1, 8, CHAN), (8, 128, 128, 128, 2, 1, NONE),
+                                                    (4, 64, 32, 128, 3, 3, CHAN), (16, 32, 32, 64, 2, 5, CHAN)])
+@pytest.mark.parametrize("lengths", [[2900, 1, 0, 130, 64, 33], [7, 0, 0, 0, 1500, 640, 31, 3], [900] * 5 + [2000]])
+def test_splits_by_length(kv, oracle, bits, G, Gc, R, Hkv, g, mode, lengths):
+    print("case uneven bits=%d G=%d Gc=%d R=%d heads=%d x %d %s" % (bits, G, Gc, R, Hkv, g, lengths), flush=True)
+    B = len(lengths)
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=3072, G=G, Gc=Gc, R=R, dtype=BF16, mode=mode, k_bits=(bits,))
+    fill(gpu, orc, lengths, Hkv, BF16, 1900 + bits)
+    q, got = check(kv, gpu, orc, B, Hkv * g, BF16, 1900)
+    for b, n in enumerate(lengths):
+        if n == 0:
+            assert not got[b].any()
+    assert kv.kv_decode_workspace_need(gpu.handle, 0) <= gpu.ws_bytes
+
+
+@pytest.mark.parametrize("B", [63, 64, 65, 131])
+def test_splits_by_length_over_many_sequences(kv, oracle, B):
+    """More sequences than a wavefront has lanes: the launch finds a split's sequence in several steps.  One long
+    sequence at either end and in the middle, empty ones between."""
+    print("case uneven batch=%d" % B, flush=True)
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=2, Hkv=1, T_max=4096, G=32, R=32, dtype=F16, k_bits=(4,))
+    lengths = [(5 * b + 1) % 47 if b % 7 else 0 for b in range(B)]
+    lengths[0], lengths[B // 2], lengths[B - 1] = 3000, 2500, 3500
+    fill(gpu, orc, lengths, 1, F16, 2000)
+    check(kv, gpu, orc, B, 2, F16, 2000)
+    # the launch is uneven: the longest sequence has more splits than one count for all would give it
+    plain, _ = make_pair(kv, oracle, B=B, Hq=2, Hkv=1, T_max=4096, G=32, R=32, dtype=F16, k_bits=(4,))
+    k, v = synth.make_kv(1, B, 3500, 1, 128, F16)
+    plain.append(0, to_dev(k, F16), to_dev(v, F16))
+    assert kv.kv_decode_splits(gpu.handle, 0) > kv.kv_decode_splits(plain.handle, 0)
+
+
+def test_workspace_that_fits_one_count_only(kv, oracle):
+    """A workspace too small for splits by length, but large enough for one count for all, is still accepted."""
+    import torch
+
+    print("case uneven_workspace", flush=True)
+    lengths = [6000, 40, 40, 40]
+    gpu, orc = make_pair(kv, oracle, B=4, Hq=8, Hkv=2, T_max=6144, dtype=BF16, k_bits=(2,))
+    fill(gpu, orc, lengths, 2, BF16, 2100)
+    q, got = check(kv, gpu, orc, 4, 8, BF16, 2100)
+    need = kv.kv_decode_workspace_need(gpu.handle, 0)
+    kv.kv_set_decode_splits(gpu.handle, 1)
+    one = kv.kv_decode_workspace_need(gpu.handle, 0)
+    kv.kv_set_decode_splits(gpu.handle, 0)
+    out = torch.empty((4, 8, 128), dtype=torch.float32, device="cuda:0")
+    qd = to_dev(q, BF16)
+    accepted = 0
+    for size in (need, need - 1, need // 2, one, one - 1):
+        try:
+            kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), out.data_ptr(), gpu.workspace.data_ptr(), size)
+        except kv.KVError as e:
+            assert e.status == kv.KV_E_WORKSPACE and size < need
+            continue
+        torch.cuda.synchronize()
+        accepted += 1
+        assert float(np.max(np.abs(out.cpu().numpy() - got))) <= TOL
+    assert accepted >= 1
+
+
+@pytest.mark.parametrize("bits,G,R,raw", [(4, 32, 32, 31), (2, 32, 128, 127), (8, 64, 256, 255), (4, 128, 128, 1), (2, 64, 128, 97)])
+@pytest.mark.parametrize("g", [1, 8])
+def test_splits_for_the_raw_tokens(kv, oracle, bits, G, R, raw, g):
+    """Few chunks and up to eight tiles of raw tokens: the tiles go to splits of their own, also when the step that
+    attends appends the newest token itself."""
+    import torch
+
+    print("case resid_splits bits=%d G=%d R=%d raw=%d g=%d" % (bits, G, R, raw, g), flush=True)
+    B, Hkv, T = 2, 2, 4 * R + raw - 1
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=5 * R, G=G, Gc=G, R=R, dtype=BF16, k_bits=(bits,))
+    k, v = synth.make_kv(2200 + raw, B, T + 1, Hkv, 128, BF16)
+    kd, vd = to_dev(k, BF16), to_dev(v, BF16)
+    if T:
+        gpu.append(0, kd[:, :T], vd[:, :T])
+    q = synth.make_q(2200, B, Hkv * g, 128, BF16)
+    got = gpu.append_attend(0, kd[:, T], vd[:, T], to_dev(q, BF16))
+    torch.cuda.synchronize()
+    orc.append(0, k, v)
+    assert float(np.max(np.abs(got.cpu().numpy().astype(np.float64) - orc.attend(0, q)))) <= TOL
+    again = gpu.attend(0, to_dev(q, BF16))
+    torch.cuda.synchronize()
+    assert torch.equal(got, again)
+    img = orc.layer_image(0)
+    assert np.array_equal(gpu.layers[0].cpu().numpy()[img["valid"]], img["bytes"][img["valid"]])
