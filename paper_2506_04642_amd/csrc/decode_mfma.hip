@@ -404,6 +404,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     __shared__ __attribute__((aligned(16))) uint32_t lds_xs[XF ? XS_DW : 1], lds_pb[XF ? PB_DW : 1], lds_al[XF ? AL_DW : 1],
         lds_ev[XF ? 16 : 1];
 
+    decode_args_here(a);
     const LayerGeom &gm = a.geom;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform: lets addresses live in scalars
@@ -431,9 +432,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     const int b = u / a.n_kv_heads, h = u % a.n_kv_heads;
     const int g = a.g;
     const int cw0 = XF ? 0 : wave; // this wave's first local chunk
-
-    // rows 4i+3 of the operands (the unused fourth limb) must read as zero
-    for (int i = lane; i < OPER_DW; i += 64) ak[i] = 0u;
 
     // ---- chunks of this split: the splits of a unit interleave chunk by chunk (split sp, wave w
     // takes chunks sp + n_splits * (w + NW * k)), so that together they sweep the unit's records
@@ -513,6 +511,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
         for (int ph = 0; ph < 2; ph++) qraw[hg][ph] = *(const uint2 *)(qp + 32 * vq + 16 * ph + 4 * qa);
     }
     if (cw0 < n_chunks) issue(cw0);
+    // rows 4i+3 of the operands (the unused fourth limb) must read as zero
+    for (int i = lane; i < OPER_DW; i += 64) ak[i] = 0u;
     // fused cross-head form: row r (token of the chunk that starts with block blk0) of the key (which
     // = 0) or value (1) mean plane.  The second block of a chunk that does not exist is read as the first.
     // (it: the number of that chunk among this wave's, for the slots under paged placement)

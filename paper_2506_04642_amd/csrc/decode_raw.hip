@@ -59,6 +59,7 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
     constexpr int NW = kRawWaves;
     constexpr int ST = 33; // floats per row of the state exchange (32 lanes of live columns, padded)
     __shared__ float state[NW][34 * ST];
+    decode_args_here(a);
     const LayerGeom &gm = a.geom;
     const int lane = threadIdx.x & 63, row = lane >> 4, n = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));

@@ -360,6 +360,8 @@ __global__ __launch_bounds__(256) void merge_kernel(DecodeArgs a)
 {
     __shared__ float red[4][3][64];
     __shared__ float mx[4];
+    asm volatile("" : : "s"(a.g), "s"(a.n_kv_heads), "s"(a.n_q_heads), "s"(a.n_splits), "s"(a.uneven), "s"(a.ws), "s"(a.out), "s"(a.out16),
+                 "s"(a.len_dev), "s"(a.xo), "s"(a.n_blocks), "s"(a.n_xr)); // (see decode_args_here)
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int uq = blockIdx.x; // (unit, head-in-group)
     const int u = uq / a.g, i = uq % a.g;
