@@ -606,6 +606,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
         }
     };
     if (XF) {
+        // the key-mean rows of the first two chunks (of the first one again if there is no second) are on their
+        // way while the queries are fetched and narrowed; their scores follow below
+        u32x4 kb[2][NHG][4];
+#pragma unroll
+        for (int e = 0; e < NHG; e++) km_row[e] = 16 * ((wave * NHG + e) & 3) + n;
+        if (n_chunks > 0) {
+            kmean_fetch(kb[0], blk_of(0), 0);
+            kmean_fetch(kb[1], blk_of(n_chunks > 1 ? 1 : 0), n_chunks > 1 ? 1 : 0);
+        }
 #pragma unroll
         for (int e = 0; e < NHG; e++) {
             const int pj = wave * NHG + e, rb = pj >> 2, tt = pj & 3; // head block, token tile
@@ -624,7 +633,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
                 }
                 qA[e][ks] = u32x4{o[0], o[1], o[2], o[3]};
             }
-            km_row[e] = 16 * tt + n;
             // result register j: head 16 rb + 4 row + j, token 16 tt + n; the 16-token groups of head
             // hp's row are rotated by (hp % 4 + hp / 4) % 4
             xs_w[e] = (16 * rb + 4 * row) * 64 + n;
@@ -640,18 +648,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 #pragma unroll
             for (int c = 0; c < NCT; c++) accv[rb][c] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         // the scores of the first two chunks
+        if (n_chunks > 0) {
+            glb_wait_but<0>();
 #pragma unroll
-        for (int c0 = 0; c0 < 2; c0++)
-            if (c0 < n_chunks) {
-                u32x4 kb[NHG][4];
-                kmean_fetch(kb, blk_of(c0), c0);
-                glb_wait_but<0>();
+            for (int c0 = 0; c0 < 2; c0++)
 #pragma unroll
                 for (int e = 0; e < NHG; e++)
 #pragma unroll
-                    for (int ks = 0; ks < 4; ks++) glb_got(kb[e][ks]);
-                kmean_scores(kb, c0);
-            }
+                    for (int ks = 0; ks < 4; ks++) glb_got(kb[c0][e][ks]);
+            kmean_scores(kb[0], 0);
+            kmean_scores(kb[1], 1);
+        }
         if (lane < 16) lds_ev[lane] = 0u;
         wave_lds_fence();
         __builtin_amdgcn_s_barrier();
@@ -1142,12 +1149,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     }
 
     // ---- raw residual tokens (Sec. 3.3) in tiles of 32, dealt to the splits in turn after the
-    // unit's last chunk; wave w of the split takes tokens 8 w .. 8 w + 7 of a tile into its own
-    // online-softmax state, with its own LDS region as scratch (no workgroup barrier)
-    // (or to the splits that take nothing else: see plan_resid in tadakv_abi.cpp)
+    // unit's last chunk (or to the splits that take nothing else: see plan_resid in tadakv_abi.cpp); wave w of
+    // the split takes tokens 8 w .. 8 w + 7 of a tile into its own online-softmax state, with its own LDS
+    // region as scratch (no workgroup barrier).  In the fused cross-head form a wave has its unit to itself
+    // and would take the four groups of eight of a tile one after the other, 1.2 us each behind its last chunk:
+    // there the groups are what is dealt to the splits.
     const int rt_step = nr ? nr : ns;
     const int rt_first = nr ? (sp < ns ? r_seq : sp - ns) : (sp - chunks_total % ns + ns) % ns; // this split's first tile
-    if (rt_first * 32 + 8 * cw0 < r_seq) {
+    constexpr int RT = XF ? 8 : 32;
+    if (rt_first * RT + 8 * cw0 < r_seq) {
         unsigned char *L = (unsigned char *)lds;
         constexpr int RS = 264;  // bytes per staged row (33 * 8): rows start in different banks
         constexpr int NH = 4 * NHG;
@@ -1174,10 +1184,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
         // a token appended by this very call: read from the caller's rows and stored in the cache here
         const long long fresh_off = (long long)b * a.fresh_stride_b + (long long)h * a.fresh_stride_h;
         const int t_fresh = a.k_fresh ? r_seq - 1 : -1;
-        // (fused cross-head form: the wave has the unit to itself and takes all four groups of a tile)
-        for (int tg8 = XF ? 0 : wave;; tg8 += XF ? 1 : 4) {
-            const int t0 = (rt_first + rt_step * (tg8 >> 2)) * 32 + 8 * (tg8 & 3);
-            if ((rt_first + rt_step * (tg8 >> 2)) * 32 >= r_seq) break;
+        for (int rt = rt_first; rt * RT < r_seq; rt += rt_step) {
+            const int t0 = rt * RT + 8 * cw0;
             if (t0 >= r_seq) continue;
             const int nt = r_seq - t0 < 8 ? r_seq - t0 : 8;
             wave_lds_fence();
@@ -1280,8 +1288,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     PHASE(13)
     PHASE_DONE
     __syncthreads();
-    if (XF || wave == 0) {
-        constexpr int MW = XF ? 1 : NW; // waves whose states make up the partial result
+    {
+        // (a wave works out 8 / NW channel tiles of the workgroup's partial result, or, in the fused
+        // cross-head form, all of its own head's)
+        constexpr int MW = XF ? 1 : NW;                // waves whose states make up a partial result
+        constexpr int MCT = XF ? 8 : 8 / NW;
+        const int ct0 = XF ? 0 : wave * MCT;
         const float *all = (const float *)lds_all + (XF ? wave * WAVE_DW : 0);
 #pragma unroll
         for (int hg = 0; hg < NHG; hg++) {
@@ -1293,21 +1305,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
                 Mw[w] = all[w * WAVE_DW + (hg * 10 + 0) * 64 + lane];
                 M = fmaxf(M, Mw[w]);
             }
-            float lsum = 0.0f, o[8];
+            float lsum = 0.0f, o[MCT];
 #pragma unroll
-            for (int ct = 0; ct < 8; ct++) o[ct] = 0.0f;
+            for (int ct = 0; ct < MCT; ct++) o[ct] = 0.0f;
 #pragma unroll
             for (int w = 0; w < MW; w++) {
                 const float wt = Mw[w] == -INFINITY ? 0.0f : exp2f(Mw[w] - M); // a wave that saw no token
                 lsum += all[w * WAVE_DW + (hg * 10 + 1) * 64 + lane] * wt;
 #pragma unroll
-                for (int ct = 0; ct < 8; ct++) o[ct] += all[w * WAVE_DW + (hg * 10 + 2 + ct) * 64 + lane] * wt;
+                for (int ct = 0; ct < MCT; ct++) o[ct] += all[w * WAVE_DW + (hg * 10 + 2 + ct0 + ct) * 64 + lane] * wt;
             }
             const long long at = XH == 0 ? (long long)row0 + head * ns_ + sp : ((long long)u * g + head) * ns_ + sp;
             float *dst = a.ws + at * kPartialStride;
 #pragma unroll
-            for (int ct = 0; ct < 8; ct++) dst[16 * ct + n] = o[ct];
-            if (n == 0) {
+            for (int ct = 0; ct < MCT; ct++) dst[16 * (ct0 + ct) + n] = o[ct];
+            if (ct0 == 0 && n == 0) {
                 dst[kHeadDim] = M;
                 dst[kHeadDim + 1] = lsum;
             }
