@@ -899,25 +899,44 @@ kv_status kv_set_decode_splits(kv_cache *cache, int32_t n_splits)
     return KV_OK;
 }
 
-kv_status kv_decode_attn_split(const kv_cache *cache, int32_t layer, const void *q,
-                               void *workspace, size_t workspace_bytes, void *stream)
+// The split launch; *a keeps the plan, for the merge of the same call.
+static kv_status split_impl(const kv_cache *cache, int32_t layer, const void *q, void *workspace, size_t workspace_bytes,
+                            void *stream, DecodeArgs *a)
 {
     kv_status st = layer_ok(cache, layer);
     if (st != KV_OK) return st;
     if (!q) return KV_E_NULL;
     if ((uintptr_t)q % 16) return KV_E_ALIGN;
-    DecodeArgs a{};
-    st = fill_decode(cache, layer, &a);
+    st = fill_decode(cache, layer, a);
     if (st != KV_OK) return st;
-    st = bind_workspace(cache, &a, workspace, workspace_bytes);
+    st = bind_workspace(cache, a, workspace, workspace_bytes);
     if (st != KV_OK) return st;
-    a.q = (const uint16_t *)q;
-    a.out = nullptr;
+    a->q = (const uint16_t *)q;
+    a->out = nullptr;
     hipStream_t s = (hipStream_t)stream;
-    if (cache->decode_path == 2 && !decode_mfma_supported(a)) return KV_E_UNSUPPORTED;
-    hipError_t e = use_mfma(cache, a) ? launch_decode_split_mfma(a, s)
-                                      : use_raw(cache, a) ? launch_decode_split_raw(a, s) : launch_decode_split_valu(a, s);
+    const bool mfma = use_mfma(cache, *a);
+    if (cache->decode_path == 2 && !mfma) return KV_E_UNSUPPORTED;
+    hipError_t e = mfma ? launch_decode_split_mfma(*a, s) : use_raw(cache, *a) ? launch_decode_split_raw(*a, s) : launch_decode_split_valu(*a, s);
     return e == hipSuccess ? KV_OK : KV_E_HIP;
+}
+
+kv_status kv_decode_attn_split(const kv_cache *cache, int32_t layer, const void *q,
+                               void *workspace, size_t workspace_bytes, void *stream)
+{
+    DecodeArgs a{};
+    return split_impl(cache, layer, q, workspace, workspace_bytes, stream, &a);
+}
+
+// The merge of a planned launch (the plan is a function of the cache's state and the workspace).
+static kv_status merge_planned(DecodeArgs *a, float *out, uint16_t *out16, void *stream)
+{
+    a->q = nullptr;
+    a->k_fresh = a->v_fresh = nullptr;
+    a->out = out;
+    a->out16 = out16;
+    // cross-head mean on the matrix-core path: the value mean plane's share joins the partials first
+    if (a->xs && launch_xhead_values(*a, (hipStream_t)stream) != hipSuccess) return KV_E_HIP;
+    return launch_decode_merge(*a, (hipStream_t)stream) == hipSuccess ? KV_OK : KV_E_HIP;
 }
 
 static kv_status merge_impl(const kv_cache *cache, int32_t layer, float *out, uint16_t *out16,
@@ -932,12 +951,7 @@ static kv_status merge_impl(const kv_cache *cache, int32_t layer, float *out, ui
     if (st != KV_OK) return st;
     st = bind_workspace(cache, &a, const_cast<void *>(workspace), workspace_bytes);
     if (st != KV_OK) return st;
-    a.q = nullptr;
-    a.out = out;
-    a.out16 = out16;
-    // cross-head mean on the matrix-core path: the value mean plane's share joins the partials first
-    if (a.xs && launch_xhead_values(a, (hipStream_t)stream) != hipSuccess) return KV_E_HIP;
-    return launch_decode_merge(a, (hipStream_t)stream) == hipSuccess ? KV_OK : KV_E_HIP;
+    return merge_planned(&a, out, out16, stream);
 }
 
 kv_status kv_decode_attn_merge(const kv_cache *cache, int32_t layer, float *out,
@@ -983,9 +997,9 @@ kv_status kv_dequant_padded(const kv_cache *cache, int32_t layer, float *k_out, 
     return dequant_impl(cache, layer, k_out, v_out, t_cap, 1, stream);
 }
 
-kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
-                                      int64_t stride_b, int64_t stride_h, const void *q,
-                                      void *workspace, size_t workspace_bytes, void *stream)
+static kv_status append_split_impl(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
+                                   int64_t stride_b, int64_t stride_h, const void *q,
+                                   void *workspace, size_t workspace_bytes, void *stream, DecodeArgs *plan)
 {
     kv_status st = layer_ok(cache, layer);
     if (st != KV_OK) return st;
@@ -1002,33 +1016,38 @@ kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void
     }
 
     // the decode launch as it will look once the token is in, checked before anything is enqueued
-    const std::vector<int> p_old(cache->packed.begin() + (size_t)layer * c.batch, cache->packed.begin() + (size_t)(layer + 1) * c.batch);
-    const std::vector<int> r_old(cache->resid.begin() + (size_t)layer * c.batch, cache->resid.begin() + (size_t)(layer + 1) * c.batch);
-    auto restore = [&] {
+    // (the lengths with the token in; taken back by undoing the step)
+    auto step = [&](bool back) {
         for (int b = 0; b < c.batch; b++) {
-            cache->P(layer, b) = p_old[b];
-            cache->R(layer, b) = r_old[b];
+            if (!cache->on(b)) continue;
+            int &p = cache->P(layer, b), &r = cache->R(layer, b);
+            if (back) {
+                if (r == 0) { // the step filled the buffer
+                    p -= c.resid_cap;
+                    r = c.resid_cap;
+                }
+                r--;
+            } else if (++r == c.resid_cap) {
+                p += c.resid_cap;
+                r = 0;
+            }
         }
     };
-    for (int b = 0; b < c.batch; b++) {
-        if (!cache->on(b)) continue;
-        const bool fl = r_old[b] + 1 == c.resid_cap;
-        cache->P(layer, b) = fl ? p_old[b] + c.resid_cap : p_old[b];
-        cache->R(layer, b) = fl ? 0 : r_old[b] + 1;
-    }
-    DecodeArgs a{};
+    step(false);
+    DecodeArgs &a = *plan;
     st = fill_decode(cache, layer, &a);
     const bool mfma = st == KV_OK && use_mfma(cache, a);
     if (st == KV_OK) st = bind_workspace(cache, &a, workspace, workspace_bytes);
     if (st == KV_OK && cache->decode_path == 2 && !mfma) st = KV_E_UNSUPPORTED;
     if (st != KV_OK || flush || !mfma) {
-        restore();
+        step(true);
         if (st != KV_OK) return st;
         // a block is due for compression, or the layer is served by the vector-ALU kernels:
         // the two steps run as launches of their own
         st = kv_quant_append(cache, layer, k_new, v_new, 1, stride_b, 0, stride_h, stream);
         if (st != KV_OK) return st;
-        return kv_decode_attn_split(cache, layer, q, workspace, workspace_bytes, stream);
+        a = DecodeArgs{};
+        return split_impl(cache, layer, q, workspace, workspace_bytes, stream, &a);
     }
     a.q = (const uint16_t *)q;
     a.out = nullptr;
@@ -1037,10 +1056,18 @@ kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void
     a.fresh_stride_b = stride_b;
     a.fresh_stride_h = stride_h;
     if (launch_decode_split_mfma(a, (hipStream_t)stream) != hipSuccess) {
-        restore();
+        step(true);
         return KV_E_HIP;
     }
     return KV_OK;
+}
+
+kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
+                                      int64_t stride_b, int64_t stride_h, const void *q,
+                                      void *workspace, size_t workspace_bytes, void *stream)
+{
+    DecodeArgs a{};
+    return append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, workspace, workspace_bytes, stream, &a);
 }
 
 kv_status kv_append_decode_attn(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
@@ -1049,10 +1076,10 @@ kv_status kv_append_decode_attn(kv_cache *cache, int32_t layer, const void *k_ne
 {
     if (!out) return KV_E_NULL;
     if ((uintptr_t)out % 16) return KV_E_ALIGN;
-    kv_status st = kv_append_decode_attn_split(cache, layer, k_new, v_new, stride_b, stride_h, q, workspace,
-                                               workspace_bytes, stream);
+    DecodeArgs a{};
+    kv_status st = append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, workspace, workspace_bytes, stream, &a);
     if (st != KV_OK) return st;
-    return kv_decode_attn_merge(cache, layer, out, workspace, workspace_bytes, stream);
+    return merge_planned(&a, out, nullptr, stream);
 }
 
 kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, float *out,
@@ -1060,9 +1087,10 @@ kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, fl
 {
     if (!out) return KV_E_NULL;
     if ((uintptr_t)out % 16) return KV_E_ALIGN;
-    kv_status st = kv_decode_attn_split(cache, layer, q, workspace, workspace_bytes, stream);
+    DecodeArgs a{};
+    kv_status st = split_impl(cache, layer, q, workspace, workspace_bytes, stream, &a);
     if (st != KV_OK) return st;
-    return kv_decode_attn_merge(cache, layer, out, workspace, workspace_bytes, stream);
+    return merge_planned(&a, out, nullptr, stream);
 }
 
 kv_status kv_dev_lengths_bytes(const kv_config *cfg, size_t *bytes)
