@@ -352,55 +352,91 @@ template <int KB, int VB> __global__ __launch_bounds__(kThreads) void decode_spl
 
 // Cross-split merge (flash decoding, App. A):
 //   out[b, head] = sum_j o_j 2^(m_j - M) / sum_j l_j 2^(m_j - M),  M = max_j m_j.
-// One workgroup per query head, a lane owns two channels; wave w adds up the
-// splits w, w + 4, ... in rising order and the four sums are added in wave order, so the result
-// does not depend on timing.  A long-context launch has a hundred splits per head and few heads:
-// the loads of a wave are independent and issued several splits at a time.
-__global__ __launch_bounds__(256) void merge_kernel(DecodeArgs a)
+// One workgroup of NW waves per query head, a lane owns two channels; wave w takes the splits w, w + NW, ... in
+// rising order, NB at a time, with a running maximum of its own, and the waves' states are joined in wave order,
+// so the result does not depend on timing.  Bound by latency: what the split kernel has just written comes from
+// memory, and with NW x NB at least the number of splits all of it is requested at once (launch_decode_merge).
+// Against two passes over the splits, the maxima first, with four waves (us a call): 16-bit layer of 4 x 8213
+// tokens, 24 splits, 37.4 -> 36.1; one sequence of 8205, 33 splits, 10.34 -> 10.10; 4 x 16461 with the mean over the
+// heads, 64 splits, two layers, 65.2 -> 64.4; the kernel itself with 7 splits 3.6 -> 2.9.  More splits a wave (16) or
+// one count for all were slower: a wave's loads are then issued in two groups, or the unused ones cost.
+template <int NB, int NW> __global__ __launch_bounds__(64 * NW) void merge_kernel(DecodeArgs a)
 {
-    __shared__ float red[4][3][64];
-    __shared__ float mx[4];
+    __shared__ float red[NW][3][64];
+    __shared__ float mx[NW];
     asm volatile("" : : "s"(a.g), "s"(a.n_kv_heads), "s"(a.n_q_heads), "s"(a.n_splits), "s"(a.uneven), "s"(a.ws), "s"(a.out), "s"(a.out16),
                  "s"(a.len_dev), "s"(a.xo), "s"(a.n_blocks), "s"(a.n_xr)); // (see decode_args_here)
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int uq = blockIdx.x; // (unit, head-in-group)
     const int u = uq / a.g, i = uq % a.g;
     int ns;
     const float *base = a.ws + partial_row(a, u, i, ns) * kPartialStride;
-    float M = -INFINITY;
-    for (int j = threadIdx.x; j < ns; j += 256) M = fmaxf(M, base[j * kPartialStride + kHeadDim]);
-    M = wave_max(M);
-    if (lane == 0) mx[wave] = M;
-    __syncthreads();
-    M = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
-    float n0 = 0.0f, n1 = 0.0f, den = 0.0f;
-#pragma unroll 8
-    for (int j = wave; j < ns; j += 4) {
-        const float *pj = base + j * kPartialStride;
-        const float w = pj[kHeadDim] == -INFINITY ? 0.0f : exp2f(pj[kHeadDim] - M);
-        const float2 o = *(const float2 *)(pj + 2 * lane);
-        n0 += o.x * w;
-        n1 += o.y * w;
-        den += pj[kHeadDim + 1] * w;
-    }
-    // cross-head mean: the value mean plane's share, already relative to M (one term per range)
-    if (a.xo && a.n_blocks > 0) {
-        const float *xb = a.xo + (long long)uq * a.n_xr * kHeadDim;
-#pragma unroll 8
-        for (int r = wave; r < a.n_xr; r += 4) {
-            const float2 o = *(const float2 *)(xb + r * kHeadDim + 2 * lane);
-            n0 += o.x;
-            n1 += o.y;
+    float M = -INFINITY, n0 = 0.0f, n1 = 0.0f, den = 0.0f;
+    for (int j0 = wave; j0 < ns; j0 += NW * NB) {
+        float2 ml[NB], o[NB];
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            const float *pj = base + (j0 + NW * k < ns ? j0 + NW * k : j0) * kPartialStride;
+            ml[k] = *(const float2 *)(pj + kHeadDim);
+            o[k] = *(const float2 *)(pj + 2 * lane);
         }
+        float m_new = M;
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            ml[k].x = j0 + NW * k < ns ? ml[k].x : -INFINITY;
+            m_new = fmaxf(m_new, ml[k].x);
+        }
+        const float alpha = M == -INFINITY ? 0.0f : exp2f(M - m_new);
+        n0 *= alpha;
+        n1 *= alpha;
+        den *= alpha;
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            const float w = ml[k].x == -INFINITY ? 0.0f : exp2f(ml[k].x - m_new);
+            n0 += o[k].x * w;
+            n1 += o[k].y * w;
+            den += ml[k].y * w;
+        }
+        M = m_new;
     }
     red[wave][0][lane] = n0;
     red[wave][1][lane] = n1;
     red[wave][2][lane] = den;
+    if (lane == 0) mx[wave] = M;
     __syncthreads();
+    M = mx[0];
+#pragma unroll
+    for (int w = 1; w < NW; w++) M = fmaxf(M, mx[w]);
+    n0 = n1 = den = 0.0f;
+    if (a.xo && a.n_blocks > 0) {
+        // cross-head mean in kernels of its own: the value mean plane's share, already relative to the largest
+        // split maximum (one term per range)
+        const float *xb = a.xo + (long long)uq * a.n_xr * kHeadDim;
+#pragma unroll 8
+        for (int r = wave; r < a.n_xr; r += NW) {
+            const float2 o = *(const float2 *)(xb + r * kHeadDim + 2 * lane);
+            n0 += o.x;
+            n1 += o.y;
+        }
+        __shared__ float xr[NW][2][64];
+        xr[wave][0][lane] = n0;
+        xr[wave][1][lane] = n1;
+        __syncthreads();
+        n0 = n1 = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            n0 += xr[w][0][lane];
+            n1 += xr[w][1][lane];
+        }
+    }
     if (wave != 0) return;
-    n0 = ((red[0][0][lane] + red[1][0][lane]) + red[2][0][lane]) + red[3][0][lane];
-    n1 = ((red[0][1][lane] + red[1][1][lane]) + red[2][1][lane]) + red[3][1][lane];
-    den = ((red[0][2][lane] + red[1][2][lane]) + red[2][2][lane]) + red[3][2][lane];
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+        const float s = mx[w] == -INFINITY ? 0.0f : exp2f(mx[w] - M);
+        n0 += red[w][0][lane] * s;
+        n1 += red[w][1][lane] * s;
+        den += red[w][2][lane] * s;
+    }
     const int b = u / a.n_kv_heads, h = u % a.n_kv_heads;
     float2 r;
     // a sequence that holds no token (every split empty, M == -inf) gives zeros
@@ -588,7 +624,13 @@ hipError_t launch_decode_merge(const DecodeArgs &a, hipStream_t s)
 {
     dim3 grid(a.batch * a.n_q_heads);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
-    hipLaunchKernelGGL(merge_kernel, grid, dim3(256), 0, s, a);
+    // everything requested at once: 2, 8 or 9 splits a wave, 4 to 16 waves (up to 8, 36, 72, 128 splits: 32 or 64 for
+    // the chunks and up to four for the raw tokens)
+    const int ns = a.uneven ? a.uneven_most : a.n_splits;
+    if (ns <= 8) hipLaunchKernelGGL((merge_kernel<2, 4>), grid, dim3(256), 0, s, a);
+    else if (ns <= 36) hipLaunchKernelGGL((merge_kernel<9, 4>), grid, dim3(256), 0, s, a);
+    else if (ns <= 72) hipLaunchKernelGGL((merge_kernel<9, 8>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((merge_kernel<8, 16>), grid, dim3(1024), 0, s, a);
     return note_launch(hipGetLastError());
 }
 

@@ -247,6 +247,7 @@ void plan_uneven(const kv_config &c, DecodeArgs *a, int slots, int chunk, bool t
         // (and one more for the raw tokens where that fits, see plan_resid)
         const bool own = !tails && a->r > 0 && total + some <= room && most < kMaxSplits;
         a->uneven_total = (int)count(rounds, own ? 1 : 0, &most, &some);
+        a->uneven_most = most;
         return;
     }
     a->uneven = a->resid_splits = 0;
@@ -830,13 +831,7 @@ kv_status kv_decode_splits(const kv_cache *cache, int32_t layer, int32_t *n_spli
     st = fill_decode(cache, layer, &a);
     if (st != KV_OK) return st;
     *n_splits = a.n_splits;
-    if (a.uneven) {
-        *n_splits = 0; // the most of any sequence
-        for (int b = 0; b < cache->cfg.batch; b++) {
-            const int n = uneven_count(a, a.nb_seq[b], a.r_seq[b]);
-            if (n > *n_splits) *n_splits = n;
-        }
-    }
+    if (a.uneven) *n_splits = a.uneven_most;
     return KV_OK;
 }
 

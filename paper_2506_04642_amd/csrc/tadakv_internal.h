@@ -126,7 +126,7 @@ struct DecodeArgs {
     // (uneven_count); grid (uneven_total, n_kv_heads), a sequence's splits behind those of the one before
     int uneven;
     int uneven_chunk;  // tokens of such a chunk (32, 64 or 128), uneven_tails: the raw tokens are chunks, too
-    int uneven_tails, uneven_total;
+    int uneven_tails, uneven_total, uneven_most; // (most: of any sequence)
     // of a unit's splits the last resid_splits take its raw tokens (tiles of 32 in turn) and no chunks; 0: the raw
     // tokens are dealt to all splits behind their chunks (matrix-core kernel without a mean over the heads)
     int resid_splits;

@@ -129,3 +129,28 @@ def test_splits_for_the_raw_tokens(kv, oracle, bits, G, R, raw, g):
     assert torch.equal(got, again)
     img = orc.layer_image(0)
     assert np.array_equal(gpu.layers[0].cpu().numpy()[img["valid"]], img["bytes"][img["valid"]])
+
+
+@pytest.mark.parametrize("mode,Hkv", [(CHAN, 1), (1, 2)])  # (1: the mean over the heads, in kernels of its own)
+def test_merge_at_the_edges_of_its_forms(kv, oracle, mode, Hkv):
+    """Split counts on either side of what each form of the merge kernel requests at once."""
+    import torch
+
+    print("case merge_edges mode=%d" % mode, flush=True)
+    B, g, T = 1, 2, 32 * 257 + 9
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=32 * 260, dtype=BF16, mode=mode, k_bits=(4,))
+    k, v = synth.make_kv(2300, B, T, Hkv, 128, BF16)
+    gpu.append(0, to_dev(k, BF16), to_dev(v, BF16))
+    orc.append(0, k, v)
+    q = synth.make_q(2300, B, Hkv * g, 128, BF16)
+    want = orc.attend(0, q)
+    for ns in (1, 3, 4, 5, 8, 9, 35, 36, 37, 71, 72, 73, 127, 128, 129, 256):
+        kv.kv_set_decode_splits(gpu.handle, ns)
+        size = kv.kv_decode_workspace_need(gpu.handle, 0)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+        out = torch.empty((B, Hkv * g, 128), dtype=torch.float32, device="cuda:0")
+        qd = to_dev(q, BF16)
+        kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), out.data_ptr(), ws.data_ptr(), size, gpu._stream())
+        torch.cuda.synchronize()
+        err = float(np.max(np.abs(out.cpu().numpy().astype(np.float64) - want)))
+        assert err <= TOL, (ns, err)
