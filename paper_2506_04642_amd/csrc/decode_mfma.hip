@@ -1315,6 +1315,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 #pragma unroll
                 for (int ct = 0; ct < MCT; ct++) o[ct] += all[w * WAVE_DW + (hg * 10 + 2 + ct0 + ct) * 64 + lane] * wt;
             }
+            if (XH != 1 && __builtin_expect(a.direct, 0)) {
+#pragma unroll
+                for (int ct = 0; ct < MCT; ct++) put_output(a, u, head, 16 * (ct0 + ct) + n, o[ct], lsum, M);
+                continue;
+            }
             const long long at = XH == 0 ? (long long)row0 + head * ns_ + sp : ((long long)u * g + head) * ns_ + sp;
             float *dst = a.ws + at * kPartialStride;
 #pragma unroll
@@ -1351,6 +1356,7 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hip
     if (!RecLayout<B, G, GC, MEAN>::matches(a.geom)) return hipErrorInvalidValue;
     if (XH == 2 && (a.n_kv_heads < NW || a.n_kv_heads % NW != 0)) return hipErrorInvalidValue;
     if (a.uneven && XH != 0) return hipErrorInvalidValue;
+    if (a.direct && (XH == 1 || a.uneven || a.n_splits != 1 || a.len_dev)) return hipErrorInvalidValue;
     static_assert(XH != 0 || NW == kSplitWaves, "the planner of uneven splits counts on it");
     dim3 grid(XH == 2 ? a.n_splits * (a.n_kv_heads / NW) : a.n_splits, XH == 2 ? a.batch : a.batch * a.n_kv_heads);
     if (a.uneven) grid = dim3(a.uneven_total, a.n_kv_heads);

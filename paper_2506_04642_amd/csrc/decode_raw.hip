@@ -233,6 +233,10 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
             num += state[w][at] * wt;
             den += state[w][33 * ST + head] * wt;
         }
+        if (a.direct) {
+            put_output(a, u, head, c, num, den, Mx);
+            continue;
+        }
         float *dst = a.ws + ((long long)row0 + head * ns + sp) * kPartialStride;
         dst[c] = num;
         if (c == 0) {
@@ -287,7 +291,7 @@ int decode_raw_splits(const DecodeArgs &a, int cap)
 
 hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s)
 {
-    if (!decode_raw_supported(a)) return hipErrorInvalidValue;
+    if (!decode_raw_supported(a) || (a.direct && (a.uneven || a.n_splits != 1))) return hipErrorInvalidValue;
     const dim3 grid = a.uneven ? dim3(a.uneven_total, a.n_kv_heads) : dim3(a.n_splits, a.batch * a.n_kv_heads), block(64 * kRawWaves);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
     const bool pg = a.geom.table != nullptr;

@@ -25,16 +25,6 @@ __device__ __forceinline__ float widen16(uint16_t v, int dtype)
     return __half2float(__ushort_as_half(v));
 }
 __device__ __forceinline__ float f16_val(uint16_t h) { return __half2float(__ushort_as_half(h)); }
-// binary32 -> the 16-bit type, round to nearest even (finite inputs)
-__device__ __forceinline__ uint16_t narrow16_rne(float f, int dtype)
-{
-    if (dtype == 1) {
-        const uint32_t u = __float_as_uint(f);
-        return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-    }
-    return __half_as_ushort(__float2half_rn(f));
-}
-
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll

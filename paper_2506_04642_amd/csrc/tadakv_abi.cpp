@@ -277,6 +277,19 @@ void plan_resid(const kv_config &c, DecodeArgs *a, int slots, int chunk)
     a->resid_splits = nr;
 }
 
+// A launch so short that one workgroup's waves take a unit's chunks in one round (of raw rows: two): one split then,
+// whose kernel writes the output (write_direct), instead of a merge launch behind more of them.
+// Measured (attend, 8 kv heads, us): 64 tokens at 4 bits 7.8 -> 5.0 (the merge alone); 130 and 269 tokens 7.4 -> 7.6 and
+// 7.7 -> 7.8 on the GPU, but one enqueue (3 us of host time) less; a second round is too much, 525 tokens 7.9 -> 9.7.
+// 16-bit layer, 130 tokens: 9.4 -> 6.8.  Mean over the heads (a wave has its head's chunks to itself), 130 tokens:
+// 15.6 -> 17.6, so there only what is one split anyway.
+bool one_split_is_enough(const kv_cache *k, const DecodeArgs &a)
+{
+    const long long tokens = (long long)a.n_blocks * k->cfg.group_tokens;
+    if (k->decode_path != 1 && decode_mfma_supported(a)) return k->cfg.mean_mode != KV_MEAN_CROSS_HEAD && tokens <= 64 * kSplitWaves;
+    return use_raw(k, a) && tokens + a.r <= 2 * 32 * kSplitWaves;
+}
+
 // even: one split count for all sequences whatever their lengths (a launch whose lengths are on the device)
 kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = false)
 {
@@ -328,7 +341,9 @@ kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = f
         a->n_splits = decode_raw_splits(*a, a->n_splits);
     }
     a->uneven = a->resid_splits = 0;
-    if (k->forced_splits == 0) {
+    if (!even && k->forced_splits == 0 && a->n_splits > 1 && one_split_is_enough(k, *a)) {
+        a->n_splits = 1;
+    } else if (k->forced_splits == 0) {
         if (k->decode_path != 1 && c.mean_mode != KV_MEAN_CROSS_HEAD && decode_mfma_supported(*a)) {
             const int slots = decode_mfma_slots(*a), chunk = c.group_tokens == 128 ? 128 : 64;
             if (a->ragged && !even) plan_uneven(c, a, slots, chunk, false);
@@ -894,8 +909,16 @@ kv_status kv_set_decode_splits(kv_cache *cache, int32_t n_splits)
     return KV_OK;
 }
 
+// One split per unit, and the caller wants the output: the split kernel writes it.
+static void write_direct(const kv_cache *cache, DecodeArgs *a, bool mfma)
+{
+    a->direct = a->out && a->n_splits == 1 && !a->uneven && !a->xs && (mfma || use_raw(cache, *a));
+}
+
 // The split launch; *a keeps the plan, for the merge of the same call.
-static kv_status split_impl(const kv_cache *cache, int32_t layer, const void *q, void *workspace, size_t workspace_bytes,
+// out: where the output goes if the split kernel can write it (merge_planned then has nothing to do); null: partial
+// results in any case.
+static kv_status split_impl(const kv_cache *cache, int32_t layer, const void *q, float *out, void *workspace, size_t workspace_bytes,
                             void *stream, DecodeArgs *a)
 {
     kv_status st = layer_ok(cache, layer);
@@ -907,9 +930,10 @@ static kv_status split_impl(const kv_cache *cache, int32_t layer, const void *q,
     st = bind_workspace(cache, a, workspace, workspace_bytes);
     if (st != KV_OK) return st;
     a->q = (const uint16_t *)q;
-    a->out = nullptr;
+    a->out = out;
     hipStream_t s = (hipStream_t)stream;
     const bool mfma = use_mfma(cache, *a);
+    write_direct(cache, a, mfma);
     if (cache->decode_path == 2 && !mfma) return KV_E_UNSUPPORTED;
     hipError_t e = mfma ? launch_decode_split_mfma(*a, s) : use_raw(cache, *a) ? launch_decode_split_raw(*a, s) : launch_decode_split_valu(*a, s);
     return e == hipSuccess ? KV_OK : KV_E_HIP;
@@ -919,12 +943,13 @@ kv_status kv_decode_attn_split(const kv_cache *cache, int32_t layer, const void 
                                void *workspace, size_t workspace_bytes, void *stream)
 {
     DecodeArgs a{};
-    return split_impl(cache, layer, q, workspace, workspace_bytes, stream, &a);
+    return split_impl(cache, layer, q, nullptr, workspace, workspace_bytes, stream, &a);
 }
 
 // The merge of a planned launch (the plan is a function of the cache's state and the workspace).
 static kv_status merge_planned(DecodeArgs *a, float *out, uint16_t *out16, void *stream)
 {
+    if (a->direct) return KV_OK;
     a->q = nullptr;
     a->k_fresh = a->v_fresh = nullptr;
     a->out = out;
@@ -993,7 +1018,7 @@ kv_status kv_dequant_padded(const kv_cache *cache, int32_t layer, float *k_out, 
 }
 
 static kv_status append_split_impl(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
-                                   int64_t stride_b, int64_t stride_h, const void *q,
+                                   int64_t stride_b, int64_t stride_h, const void *q, float *out,
                                    void *workspace, size_t workspace_bytes, void *stream, DecodeArgs *plan)
 {
     kv_status st = layer_ok(cache, layer);
@@ -1042,10 +1067,11 @@ static kv_status append_split_impl(kv_cache *cache, int32_t layer, const void *k
         st = kv_quant_append(cache, layer, k_new, v_new, 1, stride_b, 0, stride_h, stream);
         if (st != KV_OK) return st;
         a = DecodeArgs{};
-        return split_impl(cache, layer, q, workspace, workspace_bytes, stream, &a);
+        return split_impl(cache, layer, q, out, workspace, workspace_bytes, stream, &a);
     }
     a.q = (const uint16_t *)q;
-    a.out = nullptr;
+    a.out = out;
+    write_direct(cache, &a, true);
     a.k_fresh = (const uint16_t *)k_new;
     a.v_fresh = (const uint16_t *)v_new;
     a.fresh_stride_b = stride_b;
@@ -1062,7 +1088,7 @@ kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void
                                       void *workspace, size_t workspace_bytes, void *stream)
 {
     DecodeArgs a{};
-    return append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, workspace, workspace_bytes, stream, &a);
+    return append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, nullptr, workspace, workspace_bytes, stream, &a);
 }
 
 kv_status kv_append_decode_attn(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
@@ -1072,7 +1098,7 @@ kv_status kv_append_decode_attn(kv_cache *cache, int32_t layer, const void *k_ne
     if (!out) return KV_E_NULL;
     if ((uintptr_t)out % 16) return KV_E_ALIGN;
     DecodeArgs a{};
-    kv_status st = append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, workspace, workspace_bytes, stream, &a);
+    kv_status st = append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, out, workspace, workspace_bytes, stream, &a);
     if (st != KV_OK) return st;
     return merge_planned(&a, out, nullptr, stream);
 }
@@ -1083,7 +1109,7 @@ kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, fl
     if (!out) return KV_E_NULL;
     if ((uintptr_t)out % 16) return KV_E_ALIGN;
     DecodeArgs a{};
-    kv_status st = split_impl(cache, layer, q, workspace, workspace_bytes, stream, &a);
+    kv_status st = split_impl(cache, layer, q, out, workspace, workspace_bytes, stream, &a);
     if (st != KV_OK) return st;
     return merge_planned(&a, out, nullptr, stream);
 }

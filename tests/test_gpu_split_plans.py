@@ -154,3 +154,34 @@ def test_merge_at_the_edges_of_its_forms(kv, oracle, mode, Hkv):
         torch.cuda.synchronize()
         err = float(np.max(np.abs(out.cpu().numpy().astype(np.float64) - want)))
         assert err <= TOL, (ns, err)
+
+
+@pytest.mark.parametrize("bits,G,Hkv,g,mode", [(4, 32, 2, 4, CHAN), (2, 64, 3, 8, NONE), (8, 128, 1, 1, CHAN), (16, 32, 2, 3, CHAN),
+                                               (4, 32, 4, 4, 1), (2, 64, 2, 4, 1)])
+def test_short_launches_write_the_output_themselves(kv, oracle, bits, G, Hkv, g, mode):
+    """Around the lengths up to which a call is one launch: attend (which then writes the output in the split kernel)
+    against the oracle and, bit for bit, against the split and the merge as calls of their own; a sequence
+    that is switched off gets zeros."""
+    import torch
+
+    print("case direct bits=%d G=%d heads=%d x %d mode=%d" % (bits, G, Hkv, g, mode), flush=True)
+    B, Hq = 3, Hkv * g
+    for T in (1, 31, 64, 65, 129, 255, 256, 257, 300, 513):
+        gpu, orc = make_pair(kv, oracle, B=B, Hq=Hq, Hkv=Hkv, T_max=640, G=G, Gc=G, R=G, dtype=BF16, mode=mode, k_bits=(bits,))
+        k, v = synth.make_kv(2400 + T, B, T, Hkv, 128, BF16)
+        gpu.append(0, to_dev(k, BF16), to_dev(v, BF16))
+        orc.append(0, k, v)
+        q = synth.make_q(2400, B, Hq, 128, BF16)
+        qd = to_dev(q, BF16)
+        got = gpu.attend(0, qd)
+        two = torch.empty_like(got)
+        kv.kv_decode_attn_split(gpu.handle, 0, qd.data_ptr(), gpu.workspace.data_ptr(), gpu.ws_bytes, gpu._stream())
+        kv.kv_decode_attn_merge(gpu.handle, 0, two.data_ptr(), gpu.workspace.data_ptr(), gpu.ws_bytes, gpu._stream())
+        torch.cuda.synchronize()
+        assert torch.equal(got, two), T
+        assert float(np.max(np.abs(got.cpu().numpy().astype(np.float64) - orc.attend(0, q)))) <= TOL, T
+        kv.kv_cache_set_active(gpu.handle, [1, 0, 1])
+        part = gpu.attend(0, qd)
+        torch.cuda.synchronize()
+        assert not part[1].any()
+        assert float((part[::2] - got[::2]).abs().max()) <= TOL
