@@ -11,12 +11,14 @@
 // channels, codes, packed words: quant_wave.h) on the accumulator tile, or, for tokens that stay
 // in the raw residual buffer (Sec. 3.3), by a store of the rounded rows into that buffer.
 //
-// compressv_gemm_kernel: a workgroup owns 256 tokens (eight groups of 32) x NH kv heads (128
+// compressv_gemm_kernel: in bulk a workgroup owns 256 tokens (eight groups of 32) x NH kv heads (128
 // channels each); wave (wm, wn) owns tokens 64 wm .. + 63 of head wn: 4 x 8 tiles of
 // v_mfma_f32_16x16x32 accumulators, i.e. two quantiser items, two waves per SIMD.  X and W_V tiles
 // of 64 k-values (rows of 128 bytes, whole cache lines) are fetched straight into LDS
 // (global_load_lds_dwordx4) a stage ahead, 16-byte pieces of a row XOR-swizzled by the row so that
 // the operand reads (16 rows x one piece) hit distinct banks.
+// A call of up to 1024 (group, kv head) items would leave most of the device idle that way: there a workgroup owns 64
+// tokens x one head, two waves of 32 tokens, with four stages in LDS instead of two.
 // Every output element is one chain of model_dim / 32 matrix instructions in ascending k, the same
 // chain in project_rows_kernel below, so a token's projected value does not depend on which of
 // the two kernels, or which tile, produced it.
@@ -35,9 +37,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4))); // one matrix op
 typedef const __attribute__((address_space(1))) void *gptr_t;
 typedef __attribute__((address_space(3))) void *lptr_t;
 
-constexpr int kTileTokens = 256; // tokens per workgroup
 constexpr int kStepK = 64;       // k-values per stage: rows of 128 bytes, whole cache lines
 constexpr int kEpiBytes = 16384; // per wave after the main loop: transposed 16-bit tile + record image
+constexpr int kSmallTileItems = 1024; // (32 tokens x one head) items up to which the small tile is the faster
 constexpr int kTTStride = 80;    // bytes per channel column of the transposed tile (32 tokens + pad)
 
 template <int DT> __device__ __forceinline__ v4f mfma16(const u32x4 &a, const u32x4 &b, v4f c)
@@ -57,6 +59,11 @@ template <int DT> __device__ __forceinline__ v4f mfma16(const uint4 &a, const ui
 template <int OFF> __device__ __forceinline__ void lds_read16(u32x4 &dst, uint32_t addr)
 {
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+}
+__device__ __forceinline__ void lds_reads_done(u32x4 (&a)[2], u32x4 (&b)[8])
+{
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]), "+v"(b[4]), "+v"(b[5]), "+v"(b[6]), "+v"(b[7]));
 }
 __device__ __forceinline__ void lds_reads_done(u32x4 (&a)[4], u32x4 (&b)[8])
 {
@@ -157,21 +164,24 @@ template <int N> __device__ __forceinline__ void wait_vm()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int DT, int NH, int GC, int BITS>
-__global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
+// WT: tokens of a wave's tile (64 or 32); MW: such tiles per workgroup; S: stages in LDS (a power of two).
+template <int DT, int NH, int GC, int BITS, int WT, int MW, int S>
+__global__ __launch_bounds__(64 * MW * NH) void compressv_gemm_kernel(ProjectArgs p)
 {
-    constexpr int NW = 4 * NH;                      // waves: 4 token quarters x NH heads
-    constexpr int A_BYTES = kTileTokens * 128;      // X tile of a stage: 64 k-values, rows of 128 bytes
+    constexpr int TT = WT * MW, NF = TT / 32;       // tokens per workgroup, groups of 32 of them
+    constexpr int MT = WT / 16, NI = WT / 32;       // a wave's row tiles, its items
+    constexpr int NW = MW * NH;                     // waves: MW token parts x NH heads
+    constexpr int A_BYTES = TT * 128;               // X tile of a stage: 64 k-values, rows of 128 bytes
     constexpr int B_BYTES = NH * kHeadDim * 128;    // W_V tile of a stage
     constexpr int STAGE = A_BYTES + B_BYTES;
     constexpr int PER = STAGE / 1024 / NW;          // fetch instructions (1 KiB each) per wave and stage
     static_assert(STAGE / 1024 % NW == 0, "the stage divides among the waves");
-    static_assert(NW * kEpiBytes <= 2 * STAGE, "the epilogue fits the staging buffers");
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[]; // two stages
+    static_assert((S & (S - 1)) == 0 && NW * kEpiBytes <= S * STAGE, "the epilogue fits the staging buffers");
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[]; // S stages
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wm = wave & 3, wn = wave >> 2;
+    const int wm = wave % MW, wn = wave / MW;
     // Workgroups are dealt to the eight dies in turn: the ones that share a token tile (the head
     // groups of that tile) get ids a multiple of eight apart, so they run on one die and find the
     // tile's rows of X in its cache.
@@ -179,7 +189,7 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int tile = (slot / HG) * 8 + xcd, hg = slot % HG;
     const int n_f = p.batch * p.n_groups;
-    if (tile * 8 >= n_f) return; // (the grid is padded to whole rounds of eight tiles)
+    if (tile * NF >= n_f) return; // (the grid is padded to whole rounds of eight tiles)
 
     // ---- where this lane's pieces of a stage come from: instruction q of the stage fills rows
     // 8 q .. 8 q + 7 (128 bytes each: whole cache lines), lane l the piece (l & 7) ^ (row & 7) of row 8 q + (l >> 3)
@@ -191,7 +201,7 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
             const int q = wave * PER + i;
             if (q < A_BYTES / 1024) {
                 const int row = 8 * q + r8;
-                int f = tile * 8 + (row >> 5);
+                int f = tile * NF + (row >> 5);
                 f = f < n_f ? f : n_f - 1; // past the end: any valid row, the result is not stored
                 const GroupId g = group_of(p, f);
                 int t = row & 31;
@@ -204,18 +214,18 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
         }
     }
     const int stages = p.model_dim / kStepK;
-    auto issue = [&](int sg) { // stage sg (k-values 64 sg .. + 63; the last stage again beyond it) into buffer sg % 2
+    auto issue = [&](int sg) { // stage sg (k-values 64 sg .. + 63; the last stage again beyond it) into buffer sg % S
         const int sk = sg < stages ? sg : stages - 1;
 #pragma unroll
         for (int i = 0; i < PER; i++) {
             const int q = wave * PER + i;
-            __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + (long long)sk * kStepK), (lptr_t)(lds + (sg & 1) * STAGE + q * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + (long long)sk * kStepK), (lptr_t)(lds + (sg & (S - 1)) * STAGE + q * 1024), 16, 0, 0);
         }
     };
 
-    v4f acc[4][8];
+    v4f acc[MT][8];
 #pragma unroll
-    for (int mt = 0; mt < 4; mt++)
+    for (int mt = 0; mt < MT; mt++)
 #pragma unroll
         for (int nt = 0; nt < 8; nt++) acc[mt][nt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
@@ -223,15 +233,17 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
     // this lane's operand piece inside a 16-row tile (2 KiB) for the low and the high 32 k-values of
     // a stage: row n, piece 4 half + kg, swizzled by the row
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
-    const uint32_t a_base = lds0 + wm * (64 * 128) + n * 128, b_base = lds0 + A_BYTES + wn * (kHeadDim * 128) + n * 128;
+    const uint32_t a_base = lds0 + wm * (WT * 128) + n * 128, b_base = lds0 + A_BYTES + wn * (kHeadDim * 128) + n * 128;
     const uint32_t sw_lo = (uint32_t)((kg ^ (n & 7)) << 4), sw_hi = (uint32_t)(((4 + kg) ^ (n & 7)) << 4);
-    u32x4 fa[2][4], fb[2][8]; // operands of the current half step and of the next one
-    auto read_frags = [&](int sg, uint32_t sw, u32x4(&a)[4], u32x4(&b)[8]) {
-        const uint32_t so = (uint32_t)((sg & 1) * STAGE) + sw;
+    u32x4 fa[2][MT], fb[2][8]; // operands of the current half step and of the next one
+    auto read_frags = [&](int sg, uint32_t sw, u32x4(&a)[MT], u32x4(&b)[8]) {
+        const uint32_t so = (uint32_t)((sg & (S - 1)) * STAGE) + sw;
         lds_read16<0>(a[0], a_base + so);
         lds_read16<2048>(a[1], a_base + so);
-        lds_read16<4096>(a[2], a_base + so);
-        lds_read16<6144>(a[3], a_base + so);
+        if constexpr (MT == 4) {
+            lds_read16<4096>(a[2], a_base + so);
+            lds_read16<6144>(a[3], a_base + so);
+        }
         lds_read16<0>(b[0], b_base + so);
         lds_read16<2048>(b[1], b_base + so);
         lds_read16<4096>(b[2], b_base + so);
@@ -241,10 +253,10 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
         lds_read16<12288>(b[6], b_base + so);
         lds_read16<14336>(b[7], b_base + so);
     };
-    auto mfmas = [&](u32x4(&a)[4], u32x4(&b)[8]) {
+    auto mfmas = [&](u32x4(&a)[MT], u32x4(&b)[8]) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int mt = 0; mt < 4; mt++)
+        for (int mt = 0; mt < MT; mt++)
 #pragma unroll
             for (int nt = 0; nt < 8; nt++) acc[mt][nt] = mfma16<DT>(a[mt], b[nt], acc[mt][nt]);
         __builtin_amdgcn_sched_barrier(0);
@@ -258,9 +270,9 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
     // the next stage's low operands are read.  Past the last stage the fetch repeats the last one into
     // a buffer nobody reads any more and the operand read returns unused data, so that every stage is
     // the same straight line of code.
-    issue(0);
-    issue(1);
-    wait_vm<PER>(); // stage 0 has landed
+#pragma unroll
+    for (int sg = 0; sg < S; sg++) issue(sg);
+    wait_vm<PER *(S - 1)>(); // stage 0 has landed
     __builtin_amdgcn_s_barrier();
     read_frags(0, sw_lo, fa[0], fb[0]);
     for (int sg = 0; sg < stages; sg++) {
@@ -268,9 +280,9 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
         read_frags(sg, sw_hi, fa[1], fb[1]);
         mfmas(fa[0], fb[0]);
         lds_reads_done(fa[1], fb[1]);
-        wait_vm<0>();
+        wait_vm<PER *(S - 2)>();
         __builtin_amdgcn_s_barrier();
-        issue(sg + 2);
+        issue(sg + S);
         read_frags(sg + 1, sw_lo, fa[0], fb[0]);
         mfmas(fa[1], fb[1]);
     }
@@ -281,8 +293,8 @@ __global__ __launch_bounds__(256 * NH) void compressv_gemm_kernel(ProjectArgs p)
     const int tg = lane & 3, c8 = lane >> 2;
     const int h = hg * NH + wn;
 #pragma unroll
-    for (int blk = 0; blk < 2; blk++) {
-        const int f = tile * 8 + 2 * wm + blk;
+    for (int blk = 0; blk < NI; blk++) {
+        const int f = tile * NF + NI * wm + blk;
         if (f >= n_f) break;
         const GroupId g = group_of(p, f);
         // accumulators (lane: tokens 16 mt + 4 kg .. + 3 of channel 16 nt + n), rounded, into the
@@ -386,23 +398,36 @@ __global__ __launch_bounds__(64) void project_rows_kernel(ProjectArgs p)
     }
 }
 
-template <int DT, int NH, int GC, int BITS> hipError_t launch_gemm(const ProjectArgs &p, hipStream_t s)
+template <int DT, int NH, int GC, int BITS, int WT, int MW, int S> hipError_t launch_gemm(const ProjectArgs &p, hipStream_t s)
 {
-    constexpr size_t lds = 2 * (size_t)(kTileTokens * 128 + NH * kHeadDim * 128);
-    static const bool ready = hipFuncSetAttribute((const void *)compressv_gemm_kernel<DT, NH, GC, BITS>,
+    constexpr int NF = WT * MW / 32;
+    constexpr size_t lds = S * (size_t)(WT * MW * 128 + NH * kHeadDim * 128);
+    static const bool ready = hipFuncSetAttribute((const void *)compressv_gemm_kernel<DT, NH, GC, BITS, WT, MW, S>,
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
     if (!ready) return note_launch(hipErrorInvalidValue);
     const long long n_f = (long long)p.batch * p.n_groups;
-    const long long tiles = (n_f + 7) / 8, rounds = (tiles + 7) / 8;
+    const long long tiles = (n_f + NF - 1) / NF, rounds = (tiles + 7) / 8;
     const long long grid = rounds * 8 * (p.n_kv_heads / NH);
     if (grid > 0x7FFFFFFF) return note_launch(hipErrorInvalidValue);
-    hipLaunchKernelGGL((compressv_gemm_kernel<DT, NH, GC, BITS>), dim3((unsigned)grid), dim3(256 * NH), lds, s, p);
+    hipLaunchKernelGGL((compressv_gemm_kernel<DT, NH, GC, BITS, WT, MW, S>), dim3((unsigned)grid), dim3(64 * MW * NH), lds, s, p);
     return note_launch(hipGetLastError());
 }
-template <int DT, int NH> hipError_t launch_gemm_fmt(const ProjectArgs &p, hipStream_t s)
+// The tile by the number of tokens: 256 x NH heads where that fills the device, else 64 x one head with four stages
+// on their way (a small workgroup's stage is through in a fifth of the time that its fetch takes).  Same chain per
+// element, same bytes.
+// Measured (us a call with the keys' side, large tile -> small, 8 kv heads, 4 bits, model_dim 4096): 128 tokens 97 -> 50,
+// 2048 tokens 98 -> 52, 4096 tokens (the limit: two rounds of workgroups) 99 -> 95; model_dim 1024, 1024 tokens: 38 -> 22.
+template <int DT, int GC, int BITS> hipError_t launch_gemm_tile(const ProjectArgs &p, hipStream_t s)
+{
+    const long long groups = (long long)p.batch * p.n_groups;
+    if (groups * p.n_kv_heads <= kSmallTileItems) return launch_gemm<DT, 1, GC, BITS, 32, 2, 4>(p, s);
+    if (p.n_kv_heads % 2 == 0) return launch_gemm<DT, 2, GC, BITS, 64, 4, 2>(p, s);
+    return launch_gemm<DT, 1, GC, BITS, 64, 4, 2>(p, s);
+}
+template <int DT> hipError_t launch_gemm_fmt(const ProjectArgs &p, hipStream_t s)
 {
     const int gc = p.geom.Gc, b = p.geom.v_bits;
-#define TADAKV_CV(GCV) (b == 2 ? launch_gemm<DT, NH, GCV, 2>(p, s) : b == 4 ? launch_gemm<DT, NH, GCV, 4>(p, s) : launch_gemm<DT, NH, GCV, 8>(p, s))
+#define TADAKV_CV(GCV) (b == 2 ? launch_gemm_tile<DT, GCV, 2>(p, s) : b == 4 ? launch_gemm_tile<DT, GCV, 4>(p, s) : launch_gemm_tile<DT, GCV, 8>(p, s))
     return gc == 32 ? TADAKV_CV(32) : gc == 64 ? TADAKV_CV(64) : TADAKV_CV(128);
 #undef TADAKV_CV
 }
@@ -430,8 +455,7 @@ hipError_t launch_compressv(const ProjectArgs &p, hipStream_t s)
     // raw rows of a decode step: the streaming kernel
     if (p.mode == 1 && (long long)p.batch * p.n_tok <= 256)
         return p.geom.dtype == 1 ? launch_rows<1>(p, s) : launch_rows<0>(p, s);
-    if (p.n_kv_heads % 2 == 0) return p.geom.dtype == 1 ? launch_gemm_fmt<1, 2>(p, s) : launch_gemm_fmt<0, 2>(p, s);
-    return p.geom.dtype == 1 ? launch_gemm_fmt<1, 1>(p, s) : launch_gemm_fmt<0, 1>(p, s);
+    return p.geom.dtype == 1 ? launch_gemm_fmt<1>(p, s) : launch_gemm_fmt<0>(p, s);
 }
 
 } // namespace tadakv

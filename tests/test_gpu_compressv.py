@@ -262,3 +262,36 @@ def test_llama_shape_sampled(kv, oracle):
         m = img["valid"][:n_rec]
         assert m.sum() == H * (T // 32) * (2 * 32 * 128 * bits // 8 + 512 + 256 + 32 * 4 * 4 + 256)
         assert np.array_equal(mine[m], img["bytes"][:n_rec][m])
+
+
+@pytest.mark.parametrize("H,groups", [(8, 128), (8, 129), (3, 341), (3, 342), (2, 513)])
+@pytest.mark.parametrize("dtype,kdim", [(BF16, 64), (F16, 192), (BF16, 320)])
+def test_tiles_on_either_side_of_their_limit(kv, oracle, H, groups, dtype, kdim):
+    """Calls with as many (group, head) items as the small tile takes, and with more: the bytes of the one call equal
+    those of the same tokens in two calls of half the size (whichever tile those take), down to one and five
+    stages of k-values, fewer and more than are kept in flight; a raw tail behind the last block."""
+    import torch
+
+    print("case compressv tiles H=%d groups=%d dtype=%d k=%d" % (H, groups, dtype, kdim), flush=True)
+    T = 32 * groups + 5
+    cut = 32 * (groups // 2)
+    k, _ = synth.make_kv(900 + H, 1, T, H, 128, dtype)
+    x, w = synth.make_xw(900 + kdim, 1, T, kdim, H * 128, dtype)
+    kd, xd, wd = to_dev(k, dtype), to_dev(x, dtype), to_dev(w, dtype)
+    images = []
+    for chunks in ([(0, T)], [(0, cut), (cut, T)]):
+        gpu, orc = make_pair(kv, oracle, B=1, Hq=H, Hkv=H, T_max=32 * (groups + 1), dtype=dtype, k_bits=(4,))
+        vp = torch.zeros((1, T, H, 128), dtype=kd.dtype, device="cuda:0")
+        for a, b in chunks:
+            part = torch.zeros((1, b - a, H, 128), dtype=kd.dtype, device="cuda:0")
+            gpu.append_compressv(0, kd[:, a:b], xd[:, a:b], wd, v_proj=part)
+            vp[:, a:b] = part
+        torch.cuda.synchronize()
+        images.append((gpu.layers[0].clone(), vp))
+    assert torch.equal(images[0][1].view(torch.int16), images[1][1].view(torch.int16))
+    assert torch.equal(images[0][0], images[1][0])
+    got = _from_dev16(images[0][1])
+    _check_projection(oracle, got.reshape(1, T, H * 128), x, w, dtype)
+    orc.append(0, k, got)
+    img = orc.layer_image(0)
+    assert np.array_equal(images[0][0].cpu().numpy()[img["valid"]], img["bytes"][img["valid"]])
