@@ -105,7 +105,8 @@ template <int THREADS, bool ROPE> __device__ __forceinline__ void tail_rows(cons
     constexpr int per = THREADS / 32;
     const int rows = a.copy_n * a.batch * a.n_kv_heads;
 #pragma unroll 1
-    for (int i = (int)blockIdx.x * per + ((int)threadIdx.x >> 5); i < rows; i += (int)gridDim.x * per) tail_row<ROPE>(a, i / a.copy_n, i % a.copy_n);
+    // (from the last workgroup down: the launch has some beyond those that take items, see tail_grid)
+    for (int i = (int)(gridDim.x - 1 - blockIdx.x) * per + ((int)threadIdx.x >> 5); i < rows; i += (int)gridDim.x * per) tail_row<ROPE>(a, i / a.copy_n, i % a.copy_n);
 }
 // (token, channel) of the first code of packed word w and whether the word runs along
 // channels (keys) or tokens (values); a word holds 32/bits codes.
@@ -1156,6 +1157,16 @@ __global__ __launch_bounds__(kThreads) void resid_copy_kernel(AppendArgs a)
 
 } // namespace
 
+// Workgroups of a quantiser's launch that stores the raw tail, too: those for the items and, as far as the device
+// holds them, one for every `per` rows.  (Eight items are two workgroups; with their tail, 184 rotated rows, left to
+// those two, a call took 3 us longer than with a launch of its own for the tail.)
+static int tail_grid(const AppendArgs &a, int grid, int per, int slots)
+{
+    if (!a.tail_too) return grid;
+    const long long want = grid + ((long long)a.copy_n * a.batch * a.n_kv_heads + per - 1) / per;
+    return want < slots ? (int)want : (slots > grid ? slots : grid);
+}
+
 template <int G, int GC, bool ROPE> hipError_t launch_flush_g(const AppendArgs &a, hipStream_t s)
 {
     const int U = a.batch * a.n_kv_heads;
@@ -1178,7 +1189,7 @@ template <int G, int GC, bool ROPE> hipError_t launch_flush_g(const AppendArgs &
         return per_cu * cus;
     }();
     if (slots < 1) return hipErrorInvalidValue;
-    const int grid = items < slots ? (int)items : slots;
+    const int grid = tail_grid(a, items < slots ? (int)items : slots, kThreads / 32, slots);
     hipLaunchKernelGGL((flush_block_kernel<G, GC, ROPE>), dim3(grid), dim3(kThreads), lds, s, a, (int)items);
     return note_launch(hipGetLastError());
 }
@@ -1209,7 +1220,7 @@ template <int GC, int BITS, bool ROPE> hipError_t launch_flush_wave(const Append
     }();
     if (slots < 1) return hipErrorInvalidValue;
     const long long want = (items + kThreads / 64 - 1) / (kThreads / 64);
-    const int grid = want < slots ? (int)want : slots;
+    const int grid = tail_grid(a, want < slots ? (int)want : slots, kThreads / 32, slots);
     hipLaunchKernelGGL((flush_wave_kernel<GC, BITS, ROPE>), dim3(grid), dim3(kThreads), 0, s, a, (int)items);
     return note_launch(hipGetLastError());
 }
@@ -1254,7 +1265,8 @@ template <int G, int GC, int BITS, bool ROPE> hipError_t launch_flush_coop(const
         return (per_cu * cus) & ~1; // even: see the kernel's item order
     }();
     if (slots < 2) return hipErrorInvalidValue;
-    const int grid = items < slots ? (int)items : slots; // (items is even)
+    int grid = items < slots ? (int)items : slots; // (items is even)
+    grid = (tail_grid(a, grid, threads / 32, slots) + 1) & ~1; // (slots is even)
     hipLaunchKernelGGL((flush_coop_kernel<G, GC, BITS, ROPE>), dim3(grid), dim3(threads), 0, s, a, (int)items);
     return note_launch(hipGetLastError());
 }

@@ -281,12 +281,13 @@ void plan_resid(const kv_config &c, DecodeArgs *a, int slots, int chunk)
 // whose kernel writes the output (write_direct), instead of a merge launch behind more of them.
 // Measured (attend, 8 kv heads, us): 64 tokens at 4 bits 7.8 -> 5.0 (the merge alone); 130 and 269 tokens 7.4 -> 7.6 and
 // 7.7 -> 7.8 on the GPU, but one enqueue (3 us of host time) less; a second round is too much, 525 tokens 7.9 -> 9.7.
+// More than one tile of raw tokens behind the chunk, too: 28 sequences up to 192 + 35 tokens 10.5 -> 11.0.
 // 16-bit layer, 130 tokens: 9.4 -> 6.8.  Mean over the heads (a wave has its head's chunks to itself), 130 tokens:
 // 15.6 -> 17.6, so there only what is one split anyway.
 bool one_split_is_enough(const kv_cache *k, const DecodeArgs &a)
 {
     const long long tokens = (long long)a.n_blocks * k->cfg.group_tokens;
-    if (k->decode_path != 1 && decode_mfma_supported(a)) return k->cfg.mean_mode != KV_MEAN_CROSS_HEAD && tokens <= 64 * kSplitWaves;
+    if (k->decode_path != 1 && decode_mfma_supported(a)) return k->cfg.mean_mode != KV_MEAN_CROSS_HEAD && tokens <= 64 * kSplitWaves && a.r <= 32;
     return use_raw(k, a) && tokens + a.r <= 2 * 32 * kSplitWaves;
 }
 
