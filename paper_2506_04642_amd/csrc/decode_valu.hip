@@ -366,16 +366,17 @@ template <int NB, int NW> __global__ __launch_bounds__(64 * NW) void merge_kerne
         float2 ml[NB], o[NB];
 #pragma unroll
         for (int k = 0; k < NB; k++) {
-            const float *pj = base + (j0 + NW * k < ns ? j0 + NW * k : j0) * kPartialStride;
-            ml[k] = *(const float2 *)(pj + kHeadDim);
-            o[k] = *(const float2 *)(pj + 2 * lane);
+            ml[k] = float2{-INFINITY, 0.0f};
+            o[k] = float2{0.0f, 0.0f};
+            if (j0 + NW * k < ns) { // (nothing is read in the place of a split that does not exist: 0 x inf is NaN)
+                const float *pj = base + (j0 + NW * k) * kPartialStride;
+                ml[k] = *(const float2 *)(pj + kHeadDim);
+                o[k] = *(const float2 *)(pj + 2 * lane);
+            }
         }
         float m_new = M;
 #pragma unroll
-        for (int k = 0; k < NB; k++) {
-            ml[k].x = j0 + NW * k < ns ? ml[k].x : -INFINITY;
-            m_new = fmaxf(m_new, ml[k].x);
-        }
+        for (int k = 0; k < NB; k++) m_new = fmaxf(m_new, ml[k].x);
         const float alpha = M == -INFINITY ? 0.0f : exp2f(M - m_new);
         n0 *= alpha;
         n1 *= alpha;

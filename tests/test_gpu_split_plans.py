@@ -156,6 +156,38 @@ def test_merge_at_the_edges_of_its_forms(kv, oracle, mode, Hkv):
         assert err <= TOL, (ns, err)
 
 
+@pytest.mark.parametrize("bits,mode,Hkv", [(4, CHAN, 2), (2, NONE, 2), (8, CHAN, 1), (4, 1, 4), (4, 1, 2), (16, CHAN, 2)])
+@pytest.mark.parametrize("path", [0, 1])
+def test_infinite_raw_value_through_the_merge(kv, oracle, bits, mode, Hkv, path):
+    """An infinity of either sign among the raw values: the channel is infinite whatever the split count, also where
+    a form of the merge requests more partial results than there are splits."""
+    import torch
+
+    print("case merge_infinity bits=%d mode=%d heads=%d path=%d" % (bits, mode, Hkv, path), flush=True)
+    B, g, T = 2, 4, 32 * 48 + 11
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=32 * 50, dtype=BF16, mode=mode, k_bits=(bits,))
+    kv.kv_set_decode_path(gpu.handle, path)
+    k, v = synth.make_kv(2350 + bits, B, T, Hkv, 128, BF16)
+    k[:, 1536:] = 0  # score 0: the rows' weights are far from binary32's smallest numbers
+    v[1, 1536, 0, 5], v[1, 1536, 0, 70] = 0x7F80, 0xFF80  # the first raw row: the last one has another test of its own
+    gpu.append(0, to_dev(k, BF16), to_dev(v, BF16))
+    orc.append(0, k, v)
+    q = synth.make_q(2350, B, Hkv * g, 128, BF16)
+    want = orc.attend(0, q)
+    finite = np.isfinite(want)
+    assert np.count_nonzero(~finite) == 2 * g
+    for ns in (0, 1, 2, 3, 4, 5, 8, 9, 13, 37, 40):
+        kv.kv_set_decode_splits(gpu.handle, ns)
+        ws = torch.empty(kv.kv_decode_workspace_need(gpu.handle, 0), dtype=torch.uint8, device="cuda:0")
+        out = torch.empty((B, Hkv * g, 128), dtype=torch.float32, device="cuda:0")
+        qd = to_dev(q, BF16)
+        kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel(), gpu._stream())
+        torch.cuda.synchronize()
+        got = out.cpu().numpy().astype(np.float64)
+        assert np.all(got[1, :g, 5] == np.inf) and np.all(got[1, :g, 70] == -np.inf), ns
+        assert np.max(np.abs(got[finite] - want[finite])) <= TOL, ns
+
+
 @pytest.mark.parametrize("bits,G,Hkv,g,mode", [(4, 32, 2, 4, CHAN), (2, 64, 3, 8, NONE), (8, 128, 1, 1, CHAN), (16, 32, 2, 3, CHAN),
                                                (4, 32, 4, 4, 1), (2, 64, 2, 4, 1)])
 def test_short_launches_write_the_output_themselves(kv, oracle, bits, G, Hkv, g, mode):
