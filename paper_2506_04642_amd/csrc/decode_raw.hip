@@ -92,7 +92,7 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
     };
     // Rows of this wave's chunk number it: the first key row and the first value row, and the chunk's
     // last token (a short last chunk of the raw buffer reads its last row in the place of the missing
-    // ones, whose weights are zero: finite numbers, nothing out of range).  Past the last chunk: the
+    // ones, whose scores and values are masked: nothing out of range).  Past the last chunk: the
     // first row of the one before, so that every pass of the loop issues the same loads and the
     // waits count them.
     struct Rows {
@@ -193,6 +193,12 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
 #pragma unroll
         for (int j = 0; j < 8; j++) p[j] = __builtin_amdgcn_exp2f(s[j] - M);
         l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        // (a short chunk's missing rows hold its last row, which may not be finite: 0 x inf)
+        if (left < kChunk) {
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                if (16 * (j >> 2) + 4 * row + (j & 3) >= left) v[j] = uint4{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};

@@ -81,3 +81,37 @@ def test_raw_layer_ragged_batch(kv, oracle, G, paged):
         assert (got[0] == 0).all()
         for b in range(1, B):
             assert np.max(np.abs(got[b] - want[b])) <= TOL, (splits, b)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("T", [1, 17, 161, 300, 5003])
+def test_raw_layer_infinite_value_in_the_last_row(kv, oracle, T, dtype, paged):
+    """The raw buffer's last chunk is short and its last value row holds an infinity of either sign in two
+    channels: these are infinite in the output, as any weighted sum of the rows that exist is, and the others
+    are those of finite rows."""
+    import torch
+
+    print("case raw layer infinity T=%d dtype=%d paged=%s" % (T, dtype, paged), flush=True)
+    B, g, R = 2, 4, 32
+    cap = (T // R + 2) * R
+    assert T % R != 0
+    cfg = kv.make_config(1, B, 2 * g, 2, 128, cap, R, R, R, dtype, 0, [16], [16], pool_blocks=B * cap // R if paged else 0)
+    gpu = kv.KVCache(cfg)
+    if paged:
+        gpu.set_block_table(torch.arange(B * cap // R, dtype=torch.int32).view(B, -1).flip(1).contiguous().to("cuda:0"))
+    orc = oracle.OracleCache(oracle.OracleConfig(1, B, 2 * g, 2, 128, cap, R, R, R, dtype, 0, [16], [16]))
+    k, v = synth.make_kv(41 * T + dtype, B, T, 2, 128, dtype)
+    k[:, T - 1] = 0  # score 0: the row's weight is far from binary32's smallest numbers
+    inf = 0x7F80 if dtype == BF16 else 0x7C00
+    v[1, T - 1, 0, 5], v[1, T - 1, 0, 70] = inf, inf | 0x8000
+    append_both(gpu, orc, 0, k, v, dtype)
+    q = synth.make_q(T, B, 2 * g, 128, dtype)
+    want = orc.attend(0, q)
+    for splits in (0, 1, 3):
+        kv.kv_set_decode_splits(gpu.handle, splits)
+        got = gpu.attend(0, to_dev(q, dtype)).cpu().numpy().astype(np.float64)
+        assert np.all(got[1, :g, 5] == np.inf) and np.all(got[1, :g, 70] == -np.inf), splits
+        finite = np.isfinite(want)
+        assert np.count_nonzero(~finite) == 2 * g
+        assert np.max(np.abs(got[finite] - want[finite])) <= TOL, splits
