@@ -115,3 +115,30 @@ def test_raw_layer_infinite_value_in_the_last_row(kv, oracle, T, dtype, paged):
         finite = np.isfinite(want)
         assert np.count_nonzero(~finite) == 2 * g
         assert np.max(np.abs(got[finite] - want[finite])) <= TOL, splits
+
+
+@pytest.mark.parametrize("T,splits", [(1040, 0), (8213, 0), (8213, 1), (8213, 4), (20011, 1)])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+def test_raw_layer_error_no_larger_than_the_vector_alu_kernels(kv, T, splits, dtype):
+    """Against 64 bits (2-norm over all heads) the matrix-core kernel of the 16-bit layers is no further off than
+    the vector-ALU kernel with as many splits.  Both errors are means over 2 x 32 x 128 outputs of rounding errors of
+    random sign: a tenth covers their spread from seed to seed."""
+    import torch
+
+    print("case raw layer error T=%d splits=%d dtype=%d" % (T, splits, dtype), flush=True)
+    B, Hkv, g, R = 2, 8, 4, 32
+    cfg = kv.make_config(1, B, Hkv * g, Hkv, 128, (T // R + 2) * R, R, R, R, dtype, 0, [16], [16])
+    gpu = kv.KVCache(cfg)
+    k, v = synth.make_kv_torch(51 + T, B, T, Hkv, 128, dtype, "cuda:0")
+    gpu.append(0, k, v)
+    q = synth.make_q_torch(52, B, Hkv * g, 128, dtype, "cuda:0")
+    kd, vd = (x.double().permute(0, 2, 1, 3).contiguous() for x in (k, v))  # [B, Hkv, T, 128]
+    s = torch.matmul(q.double().view(B, Hkv, g, 128), kd.transpose(2, 3).contiguous()) / 128 ** 0.5
+    want = torch.matmul(torch.softmax(s, 3), vd).view(B, Hkv * g, 128)
+    err = []
+    for path in (0, 1):
+        kv.kv_set_decode_path(gpu.handle, path)
+        kv.kv_set_decode_splits(gpu.handle, splits)
+        err.append(float((gpu.attend(0, q).double() - want).norm() / want.norm()))
+    print("  matrix cores %.3e vector ALU %.3e" % tuple(err), flush=True)
+    assert err[0] <= 1.1 * err[1]
