@@ -291,7 +291,9 @@ kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, fl
 
 /* The two halves of kv_decode_attn, exposed so that a profiler can bracket them separately:
  * _split writes per-split partial (max, sum, output) into the workspace, _merge combines them
- * into `out`.  Calling _split then _merge with the same arguments equals kv_decode_attn. */
+ * into `out`.  Calling _split then _merge with the same arguments equals kv_decode_attn.  workspace_bytes is one
+ * of them: a workspace below kv_decode_workspace_need changes how the launch is split, and with it where
+ * the partial results lie, so the two calls have to be given the same size. */
 kv_status kv_decode_attn_split(const kv_cache *cache, int32_t layer, const void *q,
                                void *workspace, size_t workspace_bytes, void *stream);
 kv_status kv_decode_attn_merge(const kv_cache *cache, int32_t layer, float *out,
@@ -371,8 +373,11 @@ kv_status kv_decode_path_used(const kv_cache *cache, int32_t layer, int32_t *pat
  * KV_E_BAD_CONFIG if n_splits < 0 or > 256. */
 kv_status kv_set_decode_splits(kv_cache *cache, int32_t n_splits);
 
-/* Workspace bytes a decode call of `layer` needs in the cache's present state (lengths, kernel
- * family, forced split count); never more than kv_workspace_bytes unless a split count is forced. */
+/* Workspace bytes for a decode call of `layer` in the cache's present state (lengths, kernel
+ * family, forced split count), enough until the number of blocks of the longest sequence changes; never
+ * more than kv_workspace_bytes unless a split count is forced.  A smaller workspace is accepted as long as
+ * it holds one split count for all sequences without splits for the raw tokens; the launch is then planned
+ * that way. */
 kv_status kv_decode_workspace_need(const kv_cache *cache, int32_t layer, size_t *bytes);
 
 /* kv_decode_attn for callers that cannot allocate or carry a workspace (code under HIP graph

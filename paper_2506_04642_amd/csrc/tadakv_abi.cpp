@@ -258,23 +258,24 @@ void plan_uneven(const kv_config &c, DecodeArgs *a, int slots, int chunk, bool t
 // behind the last of them.  That is a matter of the small launches, whose time is one chunk's latency: a tile
 // of 32 raw tokens adds 2 to 3 us to the 6 to 7 us of a launch with one
 // chunk per wavefront (4 sequences x 1500 tokens, 8 kv heads: split kernel 9.3 -> 7.1 us; one sequence of 8205: 8.9 -> 8.1).
-void plan_resid(const kv_config &c, DecodeArgs *a, int slots, int chunk)
+// Returns their number for r raw tokens (0: dealt to the chunks' splits), *nc: splits for the chunks beside them.
+// a: planned without (plan_even).
+int raw_token_splits(const kv_config &c, const DecodeArgs &a, int slots, int chunk, int r, int *nc)
 {
-    a->resid_splits = 0;
-    if (a->r == 0 || a->n_blocks == 0) return;
+    if (r == 0 || a.n_blocks == 0) return 0;
     const int U = c.batch * c.n_kv_heads;
-    const int items = (int)(((long long)a->n_blocks * c.group_tokens + chunk - 1) / chunk);
-    const int rounds = (items + a->n_splits * kSplitWaves - 1) / (a->n_splits * kSplitWaves);
+    const int items = (int)(((long long)a.n_blocks * c.group_tokens + chunk - 1) / chunk);
+    const int rounds = (items + a.n_splits * kSplitWaves - 1) / (a.n_splits * kSplitWaves);
     // (with more rounds than two, fewer splits for the chunks would cost more than the raw tokens do)
-    const int nc = rounds <= 2 ? (items + rounds * kSplitWaves - 1) / (rounds * kSplitWaves) : a->n_splits;
+    *nc = rounds <= 2 ? (items + rounds * kSplitWaves - 1) / (rounds * kSplitWaves) : a.n_splits;
     int cap = slots / U;
     if (cap > mfma_split_bound(c)) cap = mfma_split_bound(c);
-    int nr = (a->r + 31) / 32;
+    const int fit = (int)(KV_STATIC_WORKSPACE_BYTES / workspace_need(c, 1));
+    if (a.n_splits <= fit && cap > fit) cap = fit; // (what fits the static workspace goes on fitting it)
+    int nr = (r + 31) / 32;
     if (nr > 4) nr = 4;
-    if (nr > cap - nc) nr = cap - nc;
-    if (nr < 1) return;
-    a->n_splits = nc + nr;
-    a->resid_splits = nr;
+    if (nr > cap - *nc) nr = cap - *nc;
+    return nr < 1 ? 0 : nr;
 }
 
 // A launch so short that one workgroup's waves take a unit's chunks in one round (of raw rows: two): one split then,
@@ -290,6 +291,46 @@ bool one_split_is_enough(const kv_cache *k, const DecodeArgs &a)
     if (k->decode_path != 1 && decode_mfma_supported(a)) return k->cfg.mean_mode != KV_MEAN_CROSS_HEAD && tokens <= 64 * kSplitWaves && a.r <= 32;
     return use_raw(k, a) && tokens + a.r <= 2 * 32 * kSplitWaves;
 }
+
+bool use_mfma(const kv_cache *k, const DecodeArgs &a)
+{
+    if (k->decode_path == 1) return false;
+    return decode_mfma_supported(a);
+}
+
+// One split count for all sequences, the raw tokens dealt to the same splits: what every launch can be, and what a
+// launch is whose split count the caller forces.  Does not depend on the number of raw tokens (16-bit
+// layers and the vector-ALU kernels: only on whether there are any).
+void plan_even(const kv_cache *k, DecodeArgs *a)
+{
+    const kv_config &c = k->cfg;
+    a->uneven = a->resid_splits = 0;
+    choose_splits(c, a->n_blocks, a->r, &a->n_splits, &a->blocks_per_split);
+    if (use_mfma(k, *a)) {
+        // the matrix-core kernel interleaves its splits chunk by chunk and sizes the launch to
+        // the device; blocks_per_split is not used by it
+        a->n_splits = decode_mfma_splits(*a);
+        const int cap = mfma_split_bound(c);
+        if (a->n_splits > cap) a->n_splits = cap;
+    } else if (use_raw(k, *a)) {
+        // (never more splits than the vector-ALU kernel would use: the workspace a call needs, and what
+        // fits the static one, stay what they are)
+        a->n_splits = decode_raw_splits(*a, a->n_splits);
+    }
+    if (k->forced_splits > 0) {
+        const int work = a->n_blocks + (a->r > 0 ? 1 : 0);
+        int ns = k->forced_splits < work ? k->forced_splits : work;
+        a->blocks_per_split = (work + ns - 1) / ns;
+        a->n_splits = (work + a->blocks_per_split - 1) / a->blocks_per_split;
+    }
+}
+
+// Do the raw tokens of such a launch get splits of their own?
+bool own_raw_splits(const kv_cache *k, const DecodeArgs &a)
+{
+    return k->forced_splits == 0 && k->cfg.mean_mode != KV_MEAN_CROSS_HEAD && use_mfma(k, a);
+}
+int mfma_chunk(const kv_config &c) { return c.group_tokens == 128 ? 128 : 64; } // tokens a wavefront takes at a time
 
 // even: one split count for all sequences whatever their lengths (a launch whose lengths are on the device)
 kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = false)
@@ -329,43 +370,22 @@ kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = f
         }
     }
     if (a->n_blocks == 0 && a->r == 0) return KV_E_EMPTY;
-    choose_splits(c, a->n_blocks, a->r, &a->n_splits, &a->blocks_per_split);
-    if (k->decode_path != 1 && decode_mfma_supported(*a)) {
-        // the matrix-core kernel interleaves its splits chunk by chunk and sizes the launch to
-        // the device; blocks_per_split is not used by it
-        a->n_splits = decode_mfma_splits(*a);
-        const int cap = mfma_split_bound(c);
-        if (a->n_splits > cap) a->n_splits = cap;
-    } else if (use_raw(k, *a)) {
-        // (never more splits than the vector-ALU kernel would use: the workspace a call needs, and what
-        // fits the static one, stay what they are)
-        a->n_splits = decode_raw_splits(*a, a->n_splits);
-    }
-    a->uneven = a->resid_splits = 0;
-    if (!even && k->forced_splits == 0 && a->n_splits > 1 && one_split_is_enough(k, *a)) {
+    plan_even(k, a);
+    if (k->forced_splits > 0) return KV_OK;
+    if (!even && a->n_splits > 1 && one_split_is_enough(k, *a)) {
         a->n_splits = 1;
-    } else if (k->forced_splits == 0) {
-        if (k->decode_path != 1 && c.mean_mode != KV_MEAN_CROSS_HEAD && decode_mfma_supported(*a)) {
-            const int slots = decode_mfma_slots(*a), chunk = c.group_tokens == 128 ? 128 : 64;
-            if (a->ragged && !even) plan_uneven(c, a, slots, chunk, false);
-            if (!a->uneven) plan_resid(c, a, slots, chunk);
-        } else if (a->ragged && !even && use_raw(k, *a)) {
-            plan_uneven(c, a, decode_raw_slots(*a), 32, true);
+    } else if (own_raw_splits(k, *a)) {
+        const int slots = decode_mfma_slots(*a), chunk = mfma_chunk(c);
+        if (a->ragged && !even) plan_uneven(c, a, slots, chunk, false);
+        if (!a->uneven) {
+            int nc;
+            a->resid_splits = raw_token_splits(c, *a, slots, chunk, a->r, &nc);
+            if (a->resid_splits > 0) a->n_splits = nc + a->resid_splits;
         }
-    }
-    if (k->forced_splits > 0) {
-        const int work = a->n_blocks + (a->r > 0 ? 1 : 0);
-        int ns = k->forced_splits < work ? k->forced_splits : work;
-        a->blocks_per_split = (work + ns - 1) / ns;
-        a->n_splits = (work + a->blocks_per_split - 1) / a->blocks_per_split;
+    } else if (a->ragged && !even && use_raw(k, *a)) {
+        plan_uneven(c, a, decode_raw_slots(*a), 32, true);
     }
     return KV_OK;
-}
-
-bool use_mfma(const kv_cache *k, const DecodeArgs &a)
-{
-    if (k->decode_path == 1) return false;
-    return decode_mfma_supported(a);
 }
 
 // Start of the cross-head arrays in the workspace: behind the partials of the largest automatic
@@ -392,7 +412,8 @@ kv_status bind_workspace(const kv_cache *k, DecodeArgs *a, void *workspace, size
     // cross-head mean on the matrix-core path: the dense mean terms go through the workspace unless the
     // layer's format has the form of the split kernel that takes them in
     const bool xhead = c.mean_mode == KV_MEAN_CROSS_HEAD && a->geom.k_bits != 16 && use_mfma(k, *a) && !xhead_fused(*a);
-    if (a->uneven && workspace_bytes < launch_workspace_need(k, *a)) a->uneven = a->resid_splits = 0; // one split count for all may fit
+    // (a workspace that holds the plain plan only is enough: splits by length or for the raw tokens are then left out)
+    if ((a->uneven || a->resid_splits) && workspace_bytes < launch_workspace_need(k, *a)) plan_even(k, a);
     if (!workspace || workspace_bytes < launch_workspace_need(k, *a)) return KV_E_WORKSPACE;
     if ((uintptr_t)workspace % 256) return KV_E_ALIGN;
     a->ws = (float *)workspace;
@@ -1252,6 +1273,27 @@ kv_status kv_decode_workspace_need(const kv_cache *cache, int32_t layer, size_t 
     st = fill_decode(cache, layer, &a);
     if (st != KV_OK) return st;
     *bytes = launch_workspace_need(cache, a);
+    // good until the next block, whatever the raw tokens do meanwhile (with splits by length, which may ask for more as
+    // other sequences grow, for the plan with one count for all)
+    if (own_raw_splits(cache, a)) {
+        plan_even(cache, &a);
+        const int slots = decode_mfma_slots(a), chunk = mfma_chunk(cache->cfg);
+        int most = a.n_splits;
+        for (int r = 1; r < cache->cfg.resid_cap; r += 32) {
+            int nc = 0;
+            const int nr = raw_token_splits(cache->cfg, a, slots, chunk, r, &nc);
+            if (nr > 0 && nc + nr > most) most = nc + nr;
+        }
+        const size_t even = workspace_need(cache->cfg, most);
+        if (even > *bytes) *bytes = even;
+    } else if (cache->forced_splits == 0 && use_raw(cache, a)) {
+        // (the raw tokens are chunks like the others there: the bound that plan_even puts on their splits)
+        for (int r = 0; r < 2; r++) {
+            choose_splits(cache->cfg, a.n_blocks, r, &a.n_splits, &a.blocks_per_split);
+            const size_t even = workspace_need(cache->cfg, a.n_splits);
+            if (even > *bytes) *bytes = even;
+        }
+    }
     return KV_OK;
 }
 
@@ -1285,10 +1327,12 @@ void *static_scratch()
 
 extern "C" kv_status kv_decode_attn_static(const kv_cache *cache, int32_t layer, const void *q, float *out, void *stream)
 {
-    size_t need = 0;
-    kv_status st = kv_decode_workspace_need(cache, layer, &need);
+    kv_status st = layer_ok(cache, layer);
     if (st != KV_OK) return st;
-    if (need > (size_t)KV_STATIC_WORKSPACE_BYTES) return KV_E_WORKSPACE;
+    DecodeArgs a{};
+    st = fill_decode(cache, layer, &a);
+    if (st != KV_OK) return st;
+    if (launch_workspace_need(cache, a) > (size_t)KV_STATIC_WORKSPACE_BYTES) return KV_E_WORKSPACE;
     void *ws = static_scratch();
     if (!ws) return KV_E_HIP;
     return kv_decode_attn(cache, layer, q, out, ws, (size_t)KV_STATIC_WORKSPACE_BYTES, stream);

@@ -217,3 +217,50 @@ def test_short_launches_write_the_output_themselves(kv, oracle, bits, G, Hkv, g,
         torch.cuda.synchronize()
         assert not part[1].any()
         assert float((part[::2] - got[::2]).abs().max()) <= TOL
+
+
+@pytest.mark.parametrize("bits,G,R", [(4, 32, 32), (2, 64, 128), (8, 128, 128), (16, 32, 64)])
+def test_need_read_on_an_empty_raw_buffer_serves_the_tokens_that_follow(kv, oracle, bits, G, R):
+    """kv_decode_workspace_need, read when the raw buffer is empty, holds for every call until the next block: the raw
+    tokens' own splits do not make a call ask for more."""
+    import torch
+
+    print("case need_until_next_block bits=%d G=%d R=%d" % (bits, G, R), flush=True)
+    B, Hkv, g = 2, 2, 4
+    T = 1024 // R * R
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=T + 2 * R, G=G, Gc=G, R=R, dtype=BF16, k_bits=(bits,))
+    k, v = synth.make_kv(2600 + bits, B, T + R, Hkv, 128, BF16)
+    kd, vd = to_dev(k, BF16), to_dev(v, BF16)
+    gpu.append(0, kd[:, :T], vd[:, :T])
+    orc.append(0, k[:, :T], v[:, :T])
+    need = kv.kv_decode_workspace_need(gpu.handle, 0)
+    plain = B * Hkv * g * kv.kv_decode_splits(gpu.handle, 0) * 132 * 4  # the chunks' splits alone
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    out = torch.empty((B, Hkv * g, 128), dtype=torch.float32, device="cuda:0")
+    st = gpu._stream()
+    for s in range(R - 1):
+        q = synth.make_q(2600 + s, B, Hkv * g, 128, BF16)
+        qd = to_dev(q, BF16)
+        kn, vn = kd[:, T + s], vd[:, T + s]
+        kv.kv_append_decode_attn(gpu.handle, 0, kn.data_ptr(), vn.data_ptr(), kn.stride(0), kn.stride(1), qd.data_ptr(), out.data_ptr(), ws.data_ptr(), need, st)
+        orc.append(0, k[:, T + s:T + s + 1], v[:, T + s:T + s + 1])
+        again = torch.empty_like(out)
+        kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), again.data_ptr(), ws.data_ptr(), need, st)
+        torch.cuda.synchronize()
+        assert torch.equal(out, again), s
+        assert torch.equal(out, gpu.attend(0, qd)), s
+        if s % 8 == 0 or s == R - 2:
+            assert float(np.max(np.abs(out.cpu().numpy().astype(np.float64) - orc.attend(0, q)))) <= TOL, s
+        assert kv.kv_decode_workspace_need(gpu.handle, 0) <= need
+        if s % 8 == 1 and bits != 16:
+            # a workspace for the chunks' splits alone is accepted, the raw tokens go to the same splits then
+            kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), out.data_ptr(), ws.data_ptr(), plain, st)
+            kv.kv_decode_attn_split(gpu.handle, 0, qd.data_ptr(), ws.data_ptr(), plain, st)
+            kv.kv_decode_attn_merge(gpu.handle, 0, again.data_ptr(), ws.data_ptr(), plain, st)
+            torch.cuda.synchronize()
+            assert torch.equal(out, again), s
+            assert float(np.max(np.abs(out.cpu().numpy().astype(np.float64) - orc.attend(0, q)))) <= TOL, s
+            row = B * Hkv * g * 132 * 4  # (a launch with splits for the raw tokens may be the smaller of the two)
+            with pytest.raises(kv.KVError) as e:
+                kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), out.data_ptr(), ws.data_ptr(), min(plain, row * kv.kv_decode_splits(gpu.handle, 0)) - 1, st)
+            assert e.value.status == kv.KV_E_WORKSPACE
