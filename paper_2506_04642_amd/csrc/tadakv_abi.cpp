@@ -258,6 +258,11 @@ void plan_uneven(const kv_config &c, DecodeArgs *a, int slots, int chunk, bool t
 // behind the last of them.  That is a matter of the small launches, whose time is one chunk's latency: a tile
 // of 32 raw tokens adds 2 to 3 us to the 6 to 7 us of a launch with one
 // chunk per wavefront (4 sequences x 1500 tokens, 8 kv heads: split kernel 9.3 -> 7.1 us; one sequence of 8205: 8.9 -> 8.1).
+// A split takes tiles one after the other, about 2.3 us each, so there are as many as tiles where the device holds them (up
+// to 16); where a split would take more of them than when all splits share them, by more than the chunks' rounds
+// hide, the tiles are dealt to all.  Attention in us, dealt to all -> own splits, 4 bits, 8 kv heads x 4, groups of 32:
+// one sequence of 8192 + 31, 255, 511 tokens 10.9 -> 9.4, 11.1 -> 10.0, 11.2 -> 10.0, + 1023 (two tiles a split) 11.3 -> 12.4: dealt;
+// 4 x 1536 + 255 12.7 -> 9.7, + 511 15.2 -> 11.4; groups of 128, 32768 + 511 16.9 -> 15.2.
 // Returns their number for r raw tokens (0: dealt to the chunks' splits), *nc: splits for the chunks beside them.
 // a: planned without (plan_even).
 int raw_token_splits(const kv_config &c, const DecodeArgs &a, int slots, int chunk, int r, int *nc)
@@ -272,10 +277,12 @@ int raw_token_splits(const kv_config &c, const DecodeArgs &a, int slots, int chu
     if (cap > mfma_split_bound(c)) cap = mfma_split_bound(c);
     const int fit = (int)(KV_STATIC_WORKSPACE_BYTES / workspace_need(c, 1));
     if (a.n_splits <= fit && cap > fit) cap = fit; // (what fits the static workspace goes on fitting it)
-    int nr = (r + 31) / 32;
-    if (nr > 4) nr = 4;
+    const int tiles = (r + 31) / 32;
+    int nr = tiles < 16 ? tiles : 16;
     if (nr > cap - *nc) nr = cap - *nc;
-    return nr < 1 ? 0 : nr;
+    if (nr < 1) return 0;
+    const int own = (tiles + nr - 1) / nr, dealt = (tiles + a.n_splits - 1) / a.n_splits; // tiles a split takes
+    return own > 1 && own > dealt + rounds * chunk / 64 - 1 ? 0 : nr;
 }
 
 // A launch so short that one workgroup's waves take a unit's chunks in one round (of raw rows: two): one split then,
@@ -379,7 +386,8 @@ kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = f
         if (a->ragged && !even) plan_uneven(c, a, slots, chunk, false);
         if (!a->uneven) {
             int nc;
-            a->resid_splits = raw_token_splits(c, *a, slots, chunk, a->r, &nc);
+            // (lengths on the device: a recorded step replays while the buffer fills, so it is planned for a full one)
+            a->resid_splits = raw_token_splits(c, *a, slots, chunk, even ? c.resid_cap - 1 : a->r, &nc);
             if (a->resid_splits > 0) a->n_splits = nc + a->resid_splits;
         }
     } else if (a->ragged && !even && use_raw(k, *a)) {

@@ -169,6 +169,54 @@ def test_growing_decode_loop_replayed_from_one_graph(kv, oracle, mode, Hkv, G):
         assert torch.equal(gpu.attend(l, q), twin.attend(l, q))
 
 
+@pytest.mark.parametrize("G", [32, 64])
+def test_replayed_steps_under_the_automatic_plan(kv, oracle, G):
+    """A step recorded just as the raw buffer empties, blocks present, split count chosen by the library: replayed over
+    a whole block and beyond.  While the buffer fills, the replays split the launch as the eager one-call step
+    does (raw tokens in splits of their own) and give its bits; across blocks they stay with the oracle."""
+    import torch
+
+    print("case graph_steps_auto G=%d" % G, flush=True)
+    B, Hkv, Hq, steps, T = 2, 2, 8, G + 20, 16 * G - 1
+    mk = lambda: make_pair(kv, oracle, B=B, Hq=Hq, Hkv=Hkv, T_max=20 * G, G=G, Gc=G, R=G, dtype=BF16, mode=CHAN, k_bits=(4,))  # noqa: E731
+    gpu, orc = mk()
+    twin, _ = mk()
+    k, v = synth.make_kv(2700 + G, B, T + steps, Hkv, 128, BF16)
+    kd, vd = to_dev(k, BF16), to_dev(v, BF16)
+    for c in (gpu, twin):
+        c.append(0, kd[:, :T], vd[:, :T])
+    orc.append(0, k[:, :T], v[:, :T])
+    k1, v1 = torch.zeros_like(kd[:, 0]), torch.zeros_like(vd[:, 0])
+    q1, o1 = to_dev(synth.make_q(0, B, Hq, 128, BF16), BF16), torch.zeros((B, Hq, 128), dtype=torch.float32, device="cuda:0")
+    warm, _ = mk()
+    warm.append(0, kd[:, :T], vd[:, :T])
+    warm.lengths_to_device()
+    warm.step_dev(0, k1, v1, q1, o1)  # one-time queries happen outside the capture
+    gpu.lengths_to_device()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        gpu.step_dev(0, k1, v1, q1, o1)
+    torch.cuda.synchronize()
+    for s in range(steps):
+        q = synth.make_q(2700 + s, B, Hq, 128, BF16)
+        k1.copy_(kd[:, T + s])
+        v1.copy_(vd[:, T + s])
+        q1.copy_(to_dev(q, BF16))
+        graph.replay()
+        eager = twin.append_attend(0, kd[:, T + s], vd[:, T + s], to_dev(q, BF16))  # eager work between the replays
+        torch.cuda.synchronize()
+        orc.append(0, k[:, T + s:T + s + 1], v[:, T + s:T + s + 1])
+        resid = (T + s + 1) % G
+        if 0 < resid and s < G and (resid - 1) // 32 == (G - 2) // 32:  # as many tiles of raw tokens as a full buffer has
+            assert torch.equal(o1, eager), s
+        assert float((o1 - eager).abs().max()) <= 5e-5, s
+        if s % 9 == 0 or resid in (0, 1):
+            assert float(np.max(np.abs(o1.cpu().numpy().astype(np.float64) - orc.attend(0, q)))) <= ATTN_TOL, s
+
+
 def test_device_length_steps_stop_at_capacity(kv, oracle):
     """A sequence that has no room for another token keeps its state: the step attends over what is
     cached (the eager call would refuse the whole step with KV_E_CAPACITY), and kv_cache_advance

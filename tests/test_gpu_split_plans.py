@@ -131,6 +131,35 @@ def test_splits_for_the_raw_tokens(kv, oracle, bits, G, R, raw, g):
     assert np.array_equal(gpu.layers[0].cpu().numpy()[img["valid"]], img["bytes"][img["valid"]])
 
 
+@pytest.mark.parametrize("bits,G,R,T,raw,own", [(4, 32, 512, 4096, 511, 16), (2, 64, 512, 4096, 320, 10), (8, 128, 512, 4096, 511, 16),
+                                                (4, 32, 1024, 4096, 1023, 16), (4, 32, 1024, 4096, 100, 4), (4, 32, 1024, 16384, 1023, 0),
+                                                (2, 128, 2048, 16384, 2047, 0)])
+def test_long_raw_buffers(kv, oracle, bits, G, R, T, raw, own):
+    """Raw buffers of many tiles: a split of its own for every tile, up to sixteen; beyond that, where such a split would
+    take more tiles one after the other than all splits do that share them, they go to all, as many splits as
+    without raw tokens."""
+    import torch
+
+    print("case long_raw bits=%d G=%d R=%d raw=%d" % (bits, G, R, raw), flush=True)
+    B, Hkv, g = 1, 2, 4
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=T + R, G=G, Gc=G, R=R, dtype=BF16, k_bits=(bits,))
+    k, v = synth.make_kv(2250 + raw, B, T + raw, Hkv, 128, BF16)
+    kd, vd = to_dev(k, BF16), to_dev(v, BF16)
+    gpu.append(0, kd[:, :T], vd[:, :T])
+    assert gpu.lengths(0) == (T, 0)
+    empty = kv.kv_decode_splits(gpu.handle, 0)
+    gpu.append(0, kd[:, T:], vd[:, T:])
+    orc.append(0, k, v)
+    chunks = (T + (127 if G == 128 else 63)) // (128 if G == 128 else 64)
+    assert empty == -(-T // 64 // 4), "one chunk of 64 tokens per wave"
+    assert kv.kv_decode_splits(gpu.handle, 0) == (-(-chunks // 4) + own if own else empty)
+    q = synth.make_q(2250, B, Hkv * g, 128, BF16)
+    check_q = to_dev(q, BF16)
+    got = gpu.attend(0, check_q)
+    torch.cuda.synchronize()
+    assert float(np.max(np.abs(got.cpu().numpy().astype(np.float64) - orc.attend(0, q)))) <= TOL
+
+
 @pytest.mark.parametrize("mode,Hkv", [(CHAN, 1), (1, 2)])  # (1: the mean over the heads, in kernels of its own)
 def test_merge_at_the_edges_of_its_forms(kv, oracle, mode, Hkv):
     """Split counts on either side of what each form of the merge kernel requests at once."""
