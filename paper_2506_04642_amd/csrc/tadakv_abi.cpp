@@ -206,14 +206,22 @@ kv_status layer_ok(const kv_cache *k, int layer)
 bool use_raw(const kv_cache *k, const DecodeArgs &a) { return k->decode_path == 0 && decode_raw_supported(a); }
 
 // Sequences of different lengths: with one split count for all, sized for the longest, every workgroup of a
-// shorter one ends early and the device idles until the longest is through (lengths spread evenly up to the
-// longest: nearly half of it).  So a sequence gets splits by its length: the fewest rounds of chunks per
-// wavefront with which the whole launch still fits the device at once, if that is fewer than with one count
-// for all.  Never more partial results than the workspace of the configuration holds (worst_splits).
+// shorter one ends early.  So a sequence may get splits by its length: the fewest rounds of chunks per
+// wavefront with which the whole launch still fits the device at once.
+// Whether that is faster is a matter of the longest path through a launch: a wavefront's rounds, and behind them the
+// tiles of 32 raw tokens that its split takes, 1.5 rounds' time each.  What the short sequences leave of the memory's and
+// the vector ALUs' rate goes to the long ones, and from about 3.5 wavefronts per compute unit on that rate is used up:
+// neither path is shorter than all chunks divided by that.  Splits by length make more partial results
+// and put a short sequence's tiles on few splits, so the path has to fall by a fifth and by two rounds (2 and 4 bits, whose
+// chunks are fewer bytes, four).
+// Measured over 2949 drawn launches of 2 to 64 sequences (seven distributions of lengths, all widths, group sizes and head counts
+// in use), both ways: of the 1587 that could be split by length always doing so took 0.93 of the time (geometric mean), but
+// more than 1.03 in 527 and up to 2.0; under this rule 434 are, 0.914 over all, more than 1.03 in 8, at most 1.11.
+// (24 sequences up to 8011 tokens, groups of 64, 8 bits 63 -> 55 us, 4 bits left alone: 35.6 against 37.1; one of 8011 among
+// 23 of some 200, 4 bits: 22.7 -> 17.5; 64 sequences of about 2000, 4 bits: left alone, 37.7 against 45.3.)
+// Never more partial results than the workspace of the configuration holds (worst_splits).
 // `slots`: workgroups the device holds; `chunk`: tokens a wavefront takes at a time; `tails`: the raw tokens are
 // chunks like the others.
-// Measured (24 sequences, lengths spread up to 8011 tokens, paged, 4- and 8-bit layers): 101.7 -> 95.9 us
-// for both (and 94.7 with the arguments fetched at once, decode_args_here)
 void plan_uneven(const kv_config &c, DecodeArgs *a, int slots, int chunk, bool tails)
 {
     long long room = slots / c.n_kv_heads; // splits of a kv head, all sequences together
@@ -236,17 +244,44 @@ void plan_uneven(const kv_config &c, DecodeArgs *a, int slots, int chunk, bool t
         }
         return total;
     };
+    // the longest path in half rounds: every sequence in n splits (0: as many as a->uneven has it, a->resid_splits of
+    // them for the raw tokens)
+    long long all_chunks = 0;
+    for (int b = 0; b < c.batch; b++) all_chunks += uneven_chunks(*a, a->nb_seq[b], a->r_seq[b]);
+    const int floor = (int)(all_chunks * c.n_kv_heads * 4 / (7 * 256)); // (256 compute units, 3.5 wavefronts each)
+    auto path = [&](int n_all) {
+        int longest = floor;
+        for (int b = 0; b < c.batch; b++) {
+            const int chunks = uneven_chunks(*a, a->nb_seq[b], a->r_seq[b]), tiles = tails ? 0 : (a->r_seq[b] + 31) / 32;
+            const int n = n_all ? n_all : uneven_count(*a, a->nb_seq[b], a->r_seq[b]) - a->resid_splits;
+            if (n < 1) continue;
+            const int of_chunks = 2 * ((chunks + n * kSplitWaves - 1) / (n * kSplitWaves));
+            const bool own = n_all == 0 && a->resid_splits > 0;
+            const int p = own ? (of_chunks > 3 * tiles ? of_chunks : 3 * tiles) : of_chunks + 3 * ((tiles + n - 1) / n);
+            longest = p > longest ? p : longest;
+        }
+        return longest;
+    };
     int most, some;
     const long long one_round = count(1, 0, &most, &some);
     const int even_rounds = (most + a->n_splits - 1) / a->n_splits; // (most: of the longest, with one round)
+    const int even_path = path(a->n_splits);
     int rounds = room > 0 ? (int)(one_round / room) : even_rounds;  // (close below what fits)
     if (rounds < 1) rounds = 1;
     for (; rounds < even_rounds; rounds++) {
-        const long long total = count(rounds, 0, &most, &some);
+        long long total = count(rounds, 0, &most, &some);
         if (total > room || most > kMaxSplits) continue;
-        // (and one more for the raw tokens where that fits, see plan_resid)
-        const bool own = !tails && a->r > 0 && total + some <= room && most < kMaxSplits;
-        a->uneven_total = (int)count(rounds, own ? 1 : 0, &most, &some);
+        int longest = path(0);
+        // (and one more for the raw tokens where that fits and is shorter, see raw_token_splits)
+        if (!tails && a->r > 0 && total + some <= room && most < kMaxSplits) {
+            a->resid_splits = 1;
+            const int with = path(0);
+            if (with < longest) longest = with;
+            else a->resid_splits = 0;
+        }
+        const int less = a->geom.k_bits < 8 && a->geom.v_bits < 8 ? 8 : 4;
+        if (even_path - longest < less || 5 * longest > 4 * even_path) break;
+        a->uneven_total = (int)count(rounds, a->resid_splits, &most, &some);
         a->uneven_most = most;
         return;
     }
@@ -258,10 +293,12 @@ void plan_uneven(const kv_config &c, DecodeArgs *a, int slots, int chunk, bool t
 // behind the last of them.  That is a matter of the small launches, whose time is one chunk's latency: a tile
 // of 32 raw tokens adds 2 to 3 us to the 6 to 7 us of a launch with one
 // chunk per wavefront (4 sequences x 1500 tokens, 8 kv heads: split kernel 9.3 -> 7.1 us; one sequence of 8205: 8.9 -> 8.1).
-// A split takes tiles one after the other, about 2.3 us each, so there are as many as tiles where the device holds them (up
+// A split takes tiles one after the other, 2.3 us each, so there are as many as tiles where the device holds them (up
 // to 16); where a split would take more of them than when all splits share them, by more than the chunks' rounds
-// hide, the tiles are dealt to all.  Attention in us, dealt to all -> own splits, 4 bits, 8 kv heads x 4, groups of 32:
-// one sequence of 8192 + 31, 255, 511 tokens 10.9 -> 9.4, 11.1 -> 10.0, 11.2 -> 10.0, + 1023 (two tiles a split) 11.3 -> 12.4: dealt;
+// hide, the tiles are dealt to all.  Over 2644 drawn launches (2, 4 and 8 bits, raw buffers of up to 16 blocks) this takes 0.811
+// of the time of dealing them always, more than 1.03 in 11, at most 1.12; own splits always, at most four: 0.883, more than 1.03 in
+// 365, up to 3.4.  Attention in us, dealt -> own splits, 4 bits, 8 kv heads x 4, groups of 32: one sequence of
+// 8192 + 31, 255, 511 tokens 10.9 -> 9.4, 11.1 -> 10.0, 11.2 -> 10.0, + 1023 (two tiles a split) 11.3 -> 12.4: dealt;
 // 4 x 1536 + 255 12.7 -> 9.7, + 511 15.2 -> 11.4; groups of 128, 32768 + 511 16.9 -> 15.2.
 // Returns their number for r raw tokens (0: dealt to the chunks' splits), *nc: splits for the chunks beside them.
 // a: planned without (plan_even).
@@ -282,7 +319,11 @@ int raw_token_splits(const kv_config &c, const DecodeArgs &a, int slots, int chu
     if (nr > cap - *nc) nr = cap - *nc;
     if (nr < 1) return 0;
     const int own = (tiles + nr - 1) / nr, dealt = (tiles + a.n_splits - 1) / a.n_splits; // tiles a split takes
-    return own > 1 && own > dealt + rounds * chunk / 64 - 1 ? 0 : nr;
+    // tiles that the chunks' rounds hide (a round of 8 bits, one more than one of 2 or 4)
+    int hidden = rounds * chunk / 64 - 1;
+    if (hidden < 1 && (a.geom.k_bits == 8 || a.geom.v_bits == 8)) hidden = 1;
+    if (hidden > 2) hidden = 2;
+    return own > 1 && own > dealt + hidden ? 0 : nr;
 }
 
 // A launch so short that one workgroup's waves take a unit's chunks in one round (of raw rows: two): one split then,

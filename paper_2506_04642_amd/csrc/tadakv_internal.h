@@ -181,10 +181,14 @@ __host__ __device__ inline int seq_resid(const DecodeArgs &a, int b)
 }
 
 constexpr int kSplitWaves = 4; // wavefronts of a workgroup that share a unit's chunks (kernels that take uneven splits)
-// splits of a sequence that holds nb packed blocks and r raw tokens
+// chunks and splits of a sequence that holds nb packed blocks and r raw tokens
+__host__ __device__ inline int uneven_chunks(const DecodeArgs &a, int nb, int r)
+{
+    return (nb * a.geom.G + a.uneven_chunk - 1) / a.uneven_chunk + (a.uneven_tails ? (r + a.uneven_chunk - 1) / a.uneven_chunk : 0);
+}
 __host__ __device__ inline int uneven_count(const DecodeArgs &a, int nb, int r)
 {
-    const int chunks = (nb * a.geom.G + a.uneven_chunk - 1) / a.uneven_chunk + (a.uneven_tails ? (r + a.uneven_chunk - 1) / a.uneven_chunk : 0);
+    const int chunks = uneven_chunks(a, nb, r);
     const int per = kSplitWaves * a.uneven, n = (chunks + per - 1) / per;
     return n > 0 ? n + a.resid_splits : (r > 0 ? 1 + a.resid_splits : 0);
 }

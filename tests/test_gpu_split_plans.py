@@ -60,21 +60,53 @@ def test_splits_by_length(kv, oracle, bits, G, Gc, R, Hkv, g, mode, lengths):
     assert kv.kv_decode_workspace_need(gpu.handle, 0) <= gpu.ws_bytes
 
 
+def even_splits(kv, B, T, Hkv, g, G, Gc, R, dtype, mode, bits):
+    """Split count of sequences that all have T tokens (whole raw buffers): the plan with one count for all."""
+    import torch
+
+    assert T % R == 0
+    cache = kv.KVCache(kv.make_config(1, B, Hkv * g, Hkv, 128, T, G, Gc, R, dtype, mode, [bits], [bits]), zero=False)
+    row = torch.zeros((1, T, Hkv, 128), dtype=torch.bfloat16 if dtype else torch.float16, device="cuda:0").expand(B, T, Hkv, 128)
+    cache.append(0, row, row)
+    return kv.kv_decode_splits(cache.handle, 0)
+
+
 @pytest.mark.parametrize("B", [63, 64, 65, 131])
 def test_splits_by_length_over_many_sequences(kv, oracle, B):
     """More sequences than a wavefront has lanes: the launch finds a split's sequence in several steps.  One long
     sequence at either end and in the middle, empty ones between."""
     print("case uneven batch=%d" % B, flush=True)
-    gpu, orc = make_pair(kv, oracle, B=B, Hq=2, Hkv=1, T_max=4096, G=32, R=32, dtype=F16, k_bits=(4,))
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=2, Hkv=1, T_max=32768, G=32, R=32, dtype=F16, k_bits=(4,))
     lengths = [(5 * b + 1) % 47 if b % 7 else 0 for b in range(B)]
-    lengths[0], lengths[B // 2], lengths[B - 1] = 3000, 2500, 3500
+    lengths[0], lengths[B // 2], lengths[B - 1] = 23000, 12500, 29001
     fill(gpu, orc, lengths, 1, F16, 2000)
     check(kv, gpu, orc, B, 2, F16, 2000)
     # the launch is uneven: the longest sequence has more splits than one count for all would give it
-    plain, _ = make_pair(kv, oracle, B=B, Hq=2, Hkv=1, T_max=4096, G=32, R=32, dtype=F16, k_bits=(4,))
-    k, v = synth.make_kv(1, B, 3500, 1, 128, F16)
-    plain.append(0, to_dev(k, F16), to_dev(v, F16))
-    assert kv.kv_decode_splits(gpu.handle, 0) > kv.kv_decode_splits(plain.handle, 0)
+    assert kv.kv_decode_splits(gpu.handle, 0) > even_splits(kv, B, 28992, 1, 2, 32, 32, 32, F16, CHAN, 4) + 1
+
+
+def spread(B, T):
+    return [T * (1 + (5 * b + B - 1) % B) // B for b in range(B)]
+
+
+@pytest.mark.parametrize("bits,G,R,lengths,uneven", [
+    (8, 64, 64, spread(24, 8011), True), (4, 64, 64, spread(24, 8011), False), (4, 64, 128, spread(24, 8011), False),
+    (4, 64, 64, [8011] + [150 + 7 * b for b in range(23)], True), (4, 32, 64, [2000 - 13 * b for b in range(64)], False),
+    (2, 64, 128, [3990 - 13 * b for b in range(24)], False), (16, 32, 32, [4000] + [150 + 7 * b for b in range(23)], True)])
+def test_splits_by_length_only_where_they_shorten_the_launch(kv, bits, G, R, lengths, uneven):
+    """The plan of launches that were measured both ways: one long sequence among short ones and wide spreads at 8 bits get
+    splits by length, launches that the device's rate bounds and those whose raw tokens would pile up do not."""
+    import torch
+
+    print("case uneven_or_not bits=%d G=%d R=%d B=%d" % (bits, G, R, len(lengths)), flush=True)
+    B, Hkv, g, T = len(lengths), 8, 4, (max(lengths) // R + 1) * R
+    gpu = kv.KVCache(kv.make_config(1, B, Hkv * g, Hkv, 128, T, G, G, R, BF16, CHAN, [bits], [bits]))
+    row = torch.zeros((T, Hkv, 128), dtype=torch.bfloat16, device="cuda:0")
+    for b, n in enumerate(lengths):
+        gpu.append_seq(0, b, row[:n], row[:n])
+    even = even_splits(kv, B, max(lengths) // R * R, Hkv, g, G, G, R, BF16, CHAN, bits)
+    got = kv.kv_decode_splits(gpu.handle, 0)
+    assert (got > even) if uneven else (got == even), (got, even)
 
 
 def test_workspace_that_fits_one_count_only(kv, oracle):
