@@ -25,7 +25,7 @@ def kv():
     return binding
 
 
-@pytest.mark.parametrize("mode,bits", [(CHAN, 4), (CHAN, 2), (CROSS, 8)])
+@pytest.mark.parametrize("mode,bits", [(CHAN, 4), (CHAN, 2), (CROSS, 8), (CHAN, 16)])
 def test_decode_call_replayed_from_a_graph(kv, oracle, mode, bits):
     import torch
 

@@ -45,21 +45,6 @@ def check(kv, gpu, orc, B, Hq, dtype, seed):
     return q, got
 
 
-@pytest.mark.parametrize("bits,G,Gc,R,Hkv,g,mode", [(4, 32, 32, 32, 2, 4, CHAN), (2, 64, 64, 64, 1, 8, CHAN), (8, 128, 128, 128, 2, 1, NONE),
-                                                    (4, 64, 32, 128, 3, 3, CHAN), (16, 32, 32, 64, 2, 5, CHAN)])
-@pytest.mark.parametrize("lengths", [[2900, 1, 0, 130, 64, 33], [7, 0, 0, 0, 1500, 640, 31, 3], [900] * 5 + [2000]])
-def test_splits_by_length(kv, oracle, bits, G, Gc, R, Hkv, g, mode, lengths):
-    print("case uneven bits=%d G=%d Gc=%d R=%d heads=%d x %d %s" % (bits, G, Gc, R, Hkv, g, lengths), flush=True)
-    B = len(lengths)
-    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=3072, G=G, Gc=Gc, R=R, dtype=BF16, mode=mode, k_bits=(bits,))
-    fill(gpu, orc, lengths, Hkv, BF16, 1900 + bits)
-    q, got = check(kv, gpu, orc, B, Hkv * g, BF16, 1900)
-    for b, n in enumerate(lengths):
-        if n == 0:
-            assert not got[b].any()
-    assert kv.kv_decode_workspace_need(gpu.handle, 0) <= gpu.ws_bytes
-
-
 def even_splits(kv, B, T, Hkv, g, G, Gc, R, dtype, mode, bits):
     """Split count of sequences that all have T tokens (whole raw buffers): the plan with one count for all."""
     import torch
@@ -69,6 +54,36 @@ def even_splits(kv, B, T, Hkv, g, G, Gc, R, dtype, mode, bits):
     row = torch.zeros((1, T, Hkv, 128), dtype=torch.bfloat16 if dtype else torch.float16, device="cuda:0").expand(B, T, Hkv, 128)
     cache.append(0, row, row)
     return kv.kv_decode_splits(cache.handle, 0)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("bits,G,Gc,R,Hkv,g,mode", [(4, 32, 32, 32, 2, 4, CHAN), (2, 64, 64, 64, 3, 8, CHAN), (8, 128, 128, 128, 2, 1, NONE),
+                                                    (4, 64, 32, 128, 3, 3, CHAN), (16, 32, 32, 64, 2, 5, CHAN)])
+@pytest.mark.parametrize("lengths", [[24000, 9000] + [37 * b % 200 for b in range(46)],
+                                     [5 * b % 130 for b in range(30)] + [20011, 0, 17000, 0] + [64] * 14], ids=["first", "middle"])
+def test_splits_by_length(kv, oracle, bits, G, Gc, R, Hkv, g, mode, lengths, paged):
+    import torch
+
+    print("case uneven bits=%d G=%d Gc=%d R=%d heads=%d x %d paged=%s" % (bits, G, Gc, R, Hkv, g, paged), flush=True)
+    B, cap = len(lengths), (max(lengths) // R + 1) * R
+    blocks = sum(n // R * R // G for n in lengths)
+    gpu = kv.KVCache(kv.make_config(1, B, Hkv * g, Hkv, 128, cap, G, Gc, R, BF16, mode, [bits], [bits], pool_blocks=blocks + 3 if paged else 0))
+    orc = oracle.OracleCache(oracle.OracleConfig(1, B, Hkv * g, Hkv, 128, cap, G, Gc, R, BF16, mode, [bits], [bits]))
+    if paged:
+        slots = list(np.random.default_rng(G).permutation(blocks + 3))
+        table = np.full((B, cap // G), 10 ** 6, dtype=np.int32)
+        for b, n in enumerate(lengths):
+            for x in range(n // R * R // G):
+                table[b, x] = slots.pop()
+        gpu.set_block_table(torch.from_numpy(table).to("cuda:0"))
+    fill(gpu, orc, lengths, Hkv, BF16, 1900 + bits)
+    q, got = check(kv, gpu, orc, B, Hkv * g, BF16, 1900)
+    for b, n in enumerate(lengths):
+        if n == 0:
+            assert not got[b].any()
+    assert kv.kv_decode_workspace_need(gpu.handle, 0) <= gpu.ws_bytes
+    # the launch is uneven: the longest sequence has more splits than one count for all would give it
+    assert kv.kv_decode_splits(gpu.handle, 0) > even_splits(kv, B, max(lengths) // R * R, Hkv, g, G, Gc, R, BF16, mode, bits) + 1
 
 
 @pytest.mark.parametrize("B", [63, 64, 65, 131])
@@ -110,31 +125,34 @@ def test_splits_by_length_only_where_they_shorten_the_launch(kv, bits, G, R, len
 
 
 def test_workspace_that_fits_one_count_only(kv, oracle):
-    """A workspace too small for splits by length, but large enough for one count for all, is still accepted."""
+    """A workspace too small for splits by length, but large enough for one count for all, is accepted: the launch has one
+    count then, in kv_decode_attn and in the split and the merge call alike."""
     import torch
 
     print("case uneven_workspace", flush=True)
-    lengths = [6000, 40, 40, 40]
-    gpu, orc = make_pair(kv, oracle, B=4, Hq=8, Hkv=2, T_max=6144, dtype=BF16, k_bits=(2,))
-    fill(gpu, orc, lengths, 2, BF16, 2100)
-    q, got = check(kv, gpu, orc, 4, 8, BF16, 2100)
-    need = kv.kv_decode_workspace_need(gpu.handle, 0)
-    kv.kv_set_decode_splits(gpu.handle, 1)
-    one = kv.kv_decode_workspace_need(gpu.handle, 0)
-    kv.kv_set_decode_splits(gpu.handle, 0)
-    out = torch.empty((4, 8, 128), dtype=torch.float32, device="cuda:0")
+    B, Hkv, g, R = 96, 2, 4, 32
+    lengths = spread(B, 2000)
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=2048, dtype=BF16, k_bits=(8,))
+    fill(gpu, orc, lengths, Hkv, BF16, 2100)
+    q, got = check(kv, gpu, orc, B, Hkv * g, BF16, 2100)
+    even = even_splits(kv, B, 1984, Hkv, g, 32, 32, R, BF16, CHAN, 8)
+    size = B * Hkv * g * even * 132 * 4
+    assert kv.kv_decode_splits(gpu.handle, 0) > even and kv.kv_decode_workspace_need(gpu.handle, 0) > size, "the launch is uneven and takes more"
+    want = orc.attend(0, q)
     qd = to_dev(q, BF16)
-    accepted = 0
-    for size in (need, need - 1, need // 2, one, one - 1):
-        try:
-            kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), out.data_ptr(), gpu.workspace.data_ptr(), size)
-        except kv.KVError as e:
-            assert e.status == kv.KV_E_WORKSPACE and size < need
-            continue
-        torch.cuda.synchronize()
-        accepted += 1
-        assert float(np.max(np.abs(out.cpu().numpy() - got))) <= TOL
-    assert accepted >= 1
+    outs = [torch.empty((B, Hkv * g, 128), dtype=torch.float32, device="cuda:0") for _ in range(2)]
+    ws, st = gpu.workspace.data_ptr(), gpu._stream()
+    gpu.workspace.fill_(255)  # (NaN in every partial result that this launch does not write)
+    kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), outs[0].data_ptr(), ws, size, st)
+    gpu.workspace.fill_(255)
+    kv.kv_decode_attn_split(gpu.handle, 0, qd.data_ptr(), ws, size, st)
+    kv.kv_decode_attn_merge(gpu.handle, 0, outs[1].data_ptr(), ws, size, st)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    assert float(np.max(np.abs(outs[0].cpu().numpy().astype(np.float64) - want))) <= TOL
+    with pytest.raises(kv.KVError) as e:
+        kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), outs[0].data_ptr(), ws, size - 1, st)
+    assert e.value.status == kv.KV_E_WORKSPACE
 
 
 @pytest.mark.parametrize("bits,G,R,raw", [(4, 32, 32, 31), (2, 32, 128, 127), (8, 64, 256, 255), (4, 128, 128, 1), (2, 64, 128, 97)])
