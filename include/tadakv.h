@@ -336,8 +336,8 @@ kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void
                                       int64_t stride_b, int64_t stride_h, const void *q,
                                       void *workspace, size_t workspace_bytes, void *stream);
 
-/* Number of sequence splits kv_decode_attn uses for `layer` at its current length (where the sequences
- * differ in length, of the sequence with the most). */
+/* Number of sequence splits kv_decode_attn uses for `layer` at its current length, given a workspace of
+ * kv_decode_workspace_need (where the sequences differ in length, of the sequence with the most). */
 kv_status kv_decode_splits(const kv_cache *cache, int32_t layer, int32_t *n_splits);
 
 /* Bytes kv_decode_attn must read and write for `layer` at its current length: packed codes,
@@ -405,7 +405,10 @@ kv_status kv_decode_attn_static(const kv_cache *cache, int32_t layer, const void
  *       outside graph capture, after the prompts have been appended, and again after any other call
  *       that changes lengths (appends, resets).
  *   kv_decode_step_dev : as kv_append_decode_attn -- one token per sequence appended, then attention
- *       over everything cached -- with the same results, bit for bit at the same split count; enqueues three kernels (store the
+ *       over everything cached -- with the same results: bit for bit where both launches are split the same way, that is under
+ *       a forced split count (kv_set_decode_splits); under the automatic choice the recorded launch stays as it was
+ *       planned (one split count for all sequences, splits for a full raw buffer) while kv_append_decode_attn plans
+ *       every step anew, and sums may be formed in another order; enqueues three kernels (store the
  *       token, write the lengths after the step and compress the raw buffers that the token filled,
  *       none on most steps; attention; merge, which also makes the new lengths current) and does NOT change
  *       the descriptor's lengths.  A sequence that has no room for the token keeps its state and

@@ -1149,7 +1149,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     }
 
     // ---- raw residual tokens (Sec. 3.3) in tiles of 32, dealt to the splits in turn after the
-    // unit's last chunk (or to the splits that take nothing else: see plan_resid in tadakv_abi.cpp); wave w of
+    // unit's last chunk (or to the splits that take nothing else: see raw_token_splits in tadakv_abi.cpp); wave w of
     // the split takes tokens 8 w .. 8 w + 7 of a tile into its own online-softmax state, with its own LDS
     // region as scratch (no workgroup barrier).  In the fused cross-head form a wave has its unit to itself
     // and would take the four groups of eight of a tile one after the other, 1.2 us each behind its last chunk:

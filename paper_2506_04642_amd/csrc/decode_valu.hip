@@ -25,6 +25,16 @@ __device__ __forceinline__ float widen16(uint16_t v, int dtype)
     return __half2float(__ushort_as_half(v));
 }
 __device__ __forceinline__ float f16_val(uint16_t h) { return __half2float(__ushort_as_half(h)); }
+// binary32 -> the 16-bit type, round to nearest even (finite inputs)
+__device__ __forceinline__ uint16_t narrow16_rne(float f, int dtype)
+{
+    if (dtype == 1) {
+        const uint32_t u = __float_as_uint(f);
+        return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+    }
+    return __half_as_ushort(__float2half_rn(f));
+}
+
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll
@@ -616,7 +626,7 @@ hipError_t launch_decode_merge(const DecodeArgs &a, hipStream_t s)
     dim3 grid(a.batch * a.n_q_heads);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
     // everything requested at once: 2, 8 or 9 splits a wave, 4 to 16 waves (up to 8, 36, 72, 128 splits: 32 or 64 for
-    // the chunks and up to four for the raw tokens)
+    // the chunks and a few for the raw tokens)
     const int ns = a.uneven ? a.uneven_most : a.n_splits;
     if (ns <= 8) hipLaunchKernelGGL((merge_kernel<2, 4>), grid, dim3(256), 0, s, a);
     else if (ns <= 36) hipLaunchKernelGGL((merge_kernel<9, 4>), grid, dim3(256), 0, s, a);

@@ -130,7 +130,7 @@ struct DecodeArgs {
     // of a unit's splits the last resid_splits take its raw tokens (tiles of 32 in turn) and no chunks; 0: the raw
     // tokens are dealt to all splits behind their chunks (matrix-core kernel without a mean over the heads)
     int resid_splits;
-    int direct; // not 0: one split per unit, and the split kernel writes the output itself (out or out16; no merge)
+    int direct; // not 0: one split per unit, and the split kernel writes the output itself (binary32, to out; no merge)
     int blocks_per_split;
     // matrix-core kernel only: the newest residual token (index r - 1) is not in the cache yet;
     // the kernel takes it from these rows and stores it (null: every token is in the cache)
@@ -192,23 +192,11 @@ __host__ __device__ inline int uneven_count(const DecodeArgs &a, int nb, int r)
     const int per = kSplitWaves * a.uneven, n = (chunks + per - 1) / per;
     return n > 0 ? n + a.resid_splits : (r > 0 ? 1 + a.resid_splits : 0);
 }
-// binary32 -> the cache's 16-bit type, round to nearest even (finite inputs)
-__device__ __forceinline__ uint16_t narrow16_rne(float f, int dtype)
-{
-    if (dtype == 1) {
-        const uint32_t u = __float_as_uint(f);
-        return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-    }
-    return __builtin_bit_cast(uint16_t, (_Float16)f);
-}
 // channel c of query head `head` (of unit u's group) of a launch with one split per unit: the sums num and den
 // relative to the maximum M, divided as the merge does (a sequence without tokens, M == -inf, gives zero)
 __device__ __forceinline__ void put_output(const DecodeArgs &a, int u, int head, int c, float num, float den, float M)
 {
-    const float r = M == -INFINITY ? 0.0f : num / den;
-    const long long o = ((long long)u * a.g + head) * kHeadDim + c; // (n_q_heads = n_kv_heads g)
-    if (a.out16) a.out16[o] = narrow16_rne(r, a.geom.dtype);
-    else a.out[o] = r;
+    a.out[((long long)u * a.g + head) * kHeadDim + c] = M == -INFINITY ? 0.0f : num / den; // (n_q_heads = n_kv_heads g)
 }
 // Where sequence b's splits begin, and how many there are: every lane counts those of up to four sequences and
 // the lanes add up (a table of the offsets in the arguments is one more dependent load from
