@@ -289,6 +289,17 @@ kv_status kv_compressv_append(kv_cache *cache, int32_t layer, const void *k_new,
 kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, float *out,
                          void *workspace, size_t workspace_bytes, void *stream);
 
+/* The same in one launch: with a few splits per (sequence, kv head) the workgroup that is the last of them to
+ * finish joins their partial results, where kv_decode_attn launches a second kernel for that.  Same results bit for
+ * bit; with more splits, and on the vector-ALU kernels, these calls enqueue what the plain ones do.
+ *   counts : device, kv_join_counts_bytes, 64-byte aligned, zeroed by the caller once before its first use (in stream
+ *            order); every call leaves it zero again.  Like the workspace it belongs to one call at a time:
+ *            calls that may overlap need counts of their own.  NULL: as the plain call.
+ * kv_append_decode_attn_joined and kv_decode_step_dev_joined: kv_append_decode_attn and kv_decode_step_dev likewise. */
+kv_status kv_join_counts_bytes(const kv_config *cfg, size_t *bytes);
+kv_status kv_decode_attn_joined(const kv_cache *cache, int32_t layer, const void *q, float *out,
+                                void *workspace, size_t workspace_bytes, void *counts, void *stream);
+
 /* The two halves of kv_decode_attn, exposed so that a profiler can bracket them separately:
  * _split writes per-split partial (max, sum, output) into the workspace, _merge combines them
  * into `out`.  Calling _split then _merge with the same arguments equals kv_decode_attn.  workspace_bytes is one
@@ -332,6 +343,9 @@ kv_status kv_dequant_padded(const kv_cache *cache, int32_t layer, float *k_out, 
 kv_status kv_append_decode_attn(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
                                 int64_t stride_b, int64_t stride_h, const void *q, float *out,
                                 void *workspace, size_t workspace_bytes, void *stream);
+kv_status kv_append_decode_attn_joined(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
+                                       int64_t stride_b, int64_t stride_h, const void *q, float *out,
+                                       void *workspace, size_t workspace_bytes, void *counts, void *stream);
 kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
                                       int64_t stride_b, int64_t stride_h, const void *q,
                                       void *workspace, size_t workspace_bytes, void *stream);
@@ -428,6 +442,9 @@ kv_status kv_cache_lengths_to_device(kv_cache *cache, void *dev_lengths, void *s
 kv_status kv_decode_step_dev(const kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
                              int64_t stride_b, int64_t stride_h, const void *q, float *out,
                              void *workspace, size_t workspace_bytes, void *stream);
+kv_status kv_decode_step_dev_joined(const kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
+                                    int64_t stride_b, int64_t stride_h, const void *q, float *out,
+                                    void *workspace, size_t workspace_bytes, void *counts, void *stream);
 kv_status kv_cache_advance(kv_cache *cache, int32_t layer, int32_t n_steps);
 
 /* Measurement aid, not part of the method: one read-only pass over `bytes` bytes at `buf` (device,

@@ -29,7 +29,7 @@ KV_MEAN_CHANNEL_BLOCK, KV_MEAN_CROSS_HEAD, KV_MEAN_NONE = 0, 1, 2
 
 EXPORTS = [
     "kv_cache_bytes", "kv_workspace_bytes", "kv_cache_create", "kv_cache_destroy", "kv_cache_set_block_table", "kv_cache_set_active", "kv_cache_reset",
-    "kv_cache_len", "kv_cache_len_seq", "kv_cache_reset_seq", "kv_cache_describe", "kv_quant_append", "kv_quant_append_seq", "kv_rope_quant_append", "kv_compressv_append", "kv_append_decode_attn", "kv_append_decode_attn_split", "kv_decode_attn", "kv_decode_attn_split",
+    "kv_cache_len", "kv_cache_len_seq", "kv_cache_reset_seq", "kv_cache_describe", "kv_quant_append", "kv_quant_append_seq", "kv_rope_quant_append", "kv_compressv_append", "kv_append_decode_attn", "kv_append_decode_attn_joined", "kv_decode_attn_joined", "kv_decode_step_dev_joined", "kv_join_counts_bytes", "kv_append_decode_attn_split", "kv_decode_attn", "kv_decode_attn_split",
     "kv_decode_attn_merge", "kv_decode_attn_merge16", "kv_dequant", "kv_dequant_padded", "kv_decode_splits", "kv_decode_bytes", "kv_set_decode_path", "kv_decode_path_used", "kv_set_decode_splits", "kv_decode_workspace_need", "kv_decode_attn_static", "kv_dev_lengths_bytes", "kv_cache_lengths_to_device", "kv_decode_step_dev", "kv_cache_advance", "kv_stream_read_probe", "kv_time_next_split", "kv_strerror", "kv_last_hip_error",
 ]
 
@@ -74,6 +74,10 @@ _lib.kv_quant_append.argtypes = [_vp, _i32, _vp, _vp, _i32, _i64, _i64, _i64, _v
 _lib.kv_rope_quant_append.argtypes = [_vp, _i32, _vp, _vp, _i32, _i64, _i64, _i64, _vp, _vp, _i32, _vp]
 _lib.kv_compressv_append.argtypes = [_vp, _i32, _vp, _i64, _i64, _i64, _vp, _i64, _i64, _vp, _i32, _i32, _vp, _vp, _i32, _vp, _vp]
 _lib.kv_decode_attn.argtypes = [_vp, _i32, _vp, _vp, _vp, ctypes.c_size_t, _vp]
+_lib.kv_join_counts_bytes.argtypes = [_cfgp, _szp]
+_lib.kv_decode_attn_joined.argtypes = [_vp, _i32, _vp, _vp, _vp, ctypes.c_size_t, _vp, _vp]
+_lib.kv_append_decode_attn_joined.argtypes = [_vp, _i32, _vp, _vp, _i64, _i64, _vp, _vp, _vp, ctypes.c_size_t, _vp, _vp]
+_lib.kv_decode_step_dev_joined.argtypes = [_vp, _i32, _vp, _vp, _i64, _i64, _vp, _vp, _vp, ctypes.c_size_t, _vp, _vp]
 _lib.kv_append_decode_attn.argtypes = [_vp, _i32, _vp, _vp, _i64, _i64, _vp, _vp, _vp, ctypes.c_size_t, _vp]
 _lib.kv_append_decode_attn_split.argtypes = [_vp, _i32, _vp, _vp, _i64, _i64, _vp, _vp, ctypes.c_size_t, _vp]
 _lib.kv_decode_attn_split.argtypes = [_vp, _i32, _vp, _vp, ctypes.c_size_t, _vp]
@@ -244,6 +248,23 @@ def kv_append_decode_attn(cache: int, layer: int, k_ptr: int, v_ptr: int, stride
                                       ws_bytes, stream), "kv_append_decode_attn")
 
 
+def kv_join_counts_bytes(cfg: kv_config) -> int:
+    n = ctypes.c_size_t()
+    _check(_lib.kv_join_counts_bytes(ctypes.byref(cfg), ctypes.byref(n)), "kv_join_counts_bytes")
+    return n.value
+
+
+def kv_decode_attn_joined(cache: int, layer: int, q_ptr: int, out_ptr: int, ws_ptr: int, ws_bytes: int, counts_ptr: int,
+                          stream: int = 0) -> None:
+    _check(_lib.kv_decode_attn_joined(cache, layer, q_ptr, out_ptr, ws_ptr, ws_bytes, counts_ptr, stream), "kv_decode_attn_joined")
+
+
+def kv_append_decode_attn_joined(cache: int, layer: int, k_ptr: int, v_ptr: int, stride_b: int, stride_h: int, q_ptr: int,
+                                 out_ptr: int, ws_ptr: int, ws_bytes: int, counts_ptr: int, stream: int = 0) -> None:
+    _check(_lib.kv_append_decode_attn_joined(cache, layer, k_ptr, v_ptr, stride_b, stride_h, q_ptr, out_ptr, ws_ptr, ws_bytes,
+                                             counts_ptr, stream), "kv_append_decode_attn_joined")
+
+
 def kv_append_decode_attn_split(cache: int, layer: int, k_ptr: int, v_ptr: int, stride_b: int, stride_h: int,
                                 q_ptr: int, ws_ptr: int, ws_bytes: int, stream: int = 0) -> None:
     _check(_lib.kv_append_decode_attn_split(cache, layer, k_ptr, v_ptr, stride_b, stride_h, q_ptr, ws_ptr,
@@ -325,6 +346,12 @@ def kv_decode_step_dev(cache: int, layer: int, k_ptr: int, v_ptr: int, stride_b:
                                    stream), "kv_decode_step_dev")
 
 
+def kv_decode_step_dev_joined(cache: int, layer: int, k_ptr: int, v_ptr: int, stride_b: int, stride_h: int, q_ptr: int,
+                              out_ptr: int, ws_ptr: int, ws_bytes: int, counts_ptr: int, stream: int = 0) -> None:
+    _check(_lib.kv_decode_step_dev_joined(cache, layer, k_ptr, v_ptr, stride_b, stride_h, q_ptr, out_ptr, ws_ptr, ws_bytes,
+                                          counts_ptr, stream), "kv_decode_step_dev_joined")
+
+
 def kv_cache_advance(cache: int, layer: int, n_steps: int) -> None:
     _check(_lib.kv_cache_advance(cache, layer, n_steps), "kv_cache_advance")
 
@@ -358,6 +385,8 @@ class KVCache:
                        for l in range(cfg.n_layers)]
         self.ws_bytes = kv_workspace_bytes(cfg)
         self.workspace = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
+        # counts of finished workgroups, zero between calls; used by one call at a time, as the workspace is
+        self._counts = torch.zeros(kv_join_counts_bytes(cfg), dtype=torch.uint8, device=self.device)
         self.handle: Optional[int] = kv_cache_create(cfg, [t.data_ptr() for t in self.layers])
 
     def set_block_table(self, table) -> None:
@@ -427,8 +456,8 @@ class KVCache:
         assert q.is_contiguous()
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=self.device)
-        kv_decode_attn(self.handle, layer, q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(),
-                       self.ws_bytes, self._stream())
+        kv_decode_attn_joined(self.handle, layer, q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes,
+                              self._counts.data_ptr(), self._stream())
         return out
 
     def dequant(self, layer: int, t_cap: int):
@@ -460,9 +489,9 @@ class KVCache:
         assert k_new.stride(2) == 1 and k_new.element_size() == 2 and q.is_contiguous()
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=self.device)
-        kv_append_decode_attn(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), k_new.stride(0),
-                              k_new.stride(1), q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(),
-                              self.ws_bytes, self._stream())
+        kv_append_decode_attn_joined(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), k_new.stride(0), k_new.stride(1),
+                                     q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes,
+                                     self._counts.data_ptr(), self._stream())
         return out
 
     def lengths_to_device(self):
@@ -478,8 +507,9 @@ class KVCache:
         out [B, Hq, d] float32.  The cache's own lengths stay as they are (advance())."""
         assert k_new.shape == v_new.shape and k_new.stride() == v_new.stride()
         assert k_new.stride(2) == 1 and k_new.element_size() == 2 and q.is_contiguous() and out.is_contiguous()
-        kv_decode_step_dev(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), k_new.stride(0), k_new.stride(1),
-                           q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes, self._stream())
+        kv_decode_step_dev_joined(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), k_new.stride(0), k_new.stride(1),
+                                  q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes,
+                                  self._counts.data_ptr(), self._stream())
 
     def advance(self, n_steps: int, layer: int = -1) -> None:
         kv_cache_advance(self.handle, layer, n_steps)

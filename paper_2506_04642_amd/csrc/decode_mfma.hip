@@ -32,7 +32,7 @@
 //                      16-channel tile (values).
 //   key-side producer  lane (row, vq, qa): head 4*hg + row, channels 32*vq + 16*ph + 4*qa + {0..3}.
 //   matrix operands    lane (row, n): operand row / column n, 16 consecutive k-slots of group `row`.
-#include "tadakv_internal.h"
+#include "join.h"
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
 
@@ -48,32 +48,6 @@ constexpr int kWavesPerBlock = 4;
 constexpr float kScoreScale = 0.08838834764831845f * 1.4426950408889634f; // log2(e) / sqrt(128)
 constexpr uint32_t kM4 = 0x0F0F0F0Fu, kM2 = 0x03030303u;
 
-template <int CTRL> __device__ __forceinline__ uint32_t dpp_u(uint32_t x)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
-}
-template <int CTRL> __device__ __forceinline__ float dpp_f(float x)
-{
-    return __uint_as_float(dpp_u<CTRL>(__float_as_uint(x)));
-}
-// quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E, row_half_mirror = 0x141, row_mirror = 0x140:
-// after the four steps every lane of a row of 16 holds the row's total
-__device__ __forceinline__ float row_sum(float x)
-{
-    x += dpp_f<0xB1>(x);
-    x += dpp_f<0x4E>(x);
-    x += dpp_f<0x141>(x);
-    x += dpp_f<0x140>(x);
-    return x;
-}
-__device__ __forceinline__ float row_max(float x)
-{
-    x = fmaxf(x, dpp_f<0xB1>(x));
-    x = fmaxf(x, dpp_f<0x4E>(x));
-    x = fmaxf(x, dpp_f<0x141>(x));
-    x = fmaxf(x, dpp_f<0x140>(x));
-    return x;
-}
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b)
 {
     typedef unsigned short us2 __attribute__((ext_vector_type(2)));
@@ -361,7 +335,7 @@ template <> struct CodeOps<8> { // four words = one tile line; split into nibble
 // PG: paged placement (block slots through a table); the dense instances carry none of its state.
 // GS: tokens per block of the cache (32, 64, or 128 read as two halves of 64).
 template <int B, int GS, int GC, bool MEAN, int NW, int NHG, int XH, bool PG>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2 && NHG == 1 && !XH) ? (PG ? 3 : 4) : 1, 8))) void decode_split_mfma_kernel(DecodeArgs a)
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2 && NHG == 1 && !XH) ? (PG ? 3 : 4) : (B == 2 && NHG == 2 && GS == 128 && GC == 128 && !MEAN && !XH) ? 4 : 1, 8))) void decode_split_mfma_kernel(DecodeArgs a)
 {
     static_assert(!(XH && MEAN), "cross-head layers store no per-record mean");
     constexpr bool XF = XH == 2; // both mean terms in this kernel, a wave per kv head
@@ -1295,6 +1269,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
         constexpr int MCT = XF ? 8 : 8 / NW;
         const int ct0 = XF ? 0 : wave * MCT;
         const float *all = (const float *)lds_all + (XF ? wave * WAVE_DW : 0);
+        const bool joined = XH == 0 && a.direct == 2;
 #pragma unroll
         for (int hg = 0; hg < NHG; hg++) {
             const int head = 4 * hg + row;
@@ -1315,7 +1290,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 #pragma unroll
                 for (int ct = 0; ct < MCT; ct++) o[ct] += all[w * WAVE_DW + (hg * 10 + 2 + ct0 + ct) * 64 + lane] * wt;
             }
-            if (XH != 1 && __builtin_expect(a.direct, 0)) {
+            if (XH != 1 && __builtin_expect(a.direct == 1, 0)) {
 #pragma unroll
                 for (int ct = 0; ct < MCT; ct++) put_output(a, u, head, 16 * (ct0 + ct) + n, o[ct], lsum, M);
                 continue;
@@ -1323,11 +1298,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
             const long long at = XH == 0 ? (long long)row0 + head * ns_ + sp : ((long long)u * g + head) * ns_ + sp;
             float *dst = a.ws + at * kPartialStride;
 #pragma unroll
-            for (int ct = 0; ct < MCT; ct++) dst[16 * (ct0 + ct) + n] = o[ct];
+            for (int ct = 0; ct < MCT; ct++) put_partial(dst + 16 * (ct0 + ct) + n, o[ct], joined);
             if (ct0 == 0 && n == 0) {
-                dst[kHeadDim] = M;
-                dst[kHeadDim + 1] = lsum;
+                put_partial(dst + kHeadDim, M, joined);
+                put_partial(dst + kHeadDim + 1, lsum, joined);
             }
+        }
+        if constexpr (XH == 0) {
+            if (!joined || !last_of_unit<NW>(a, u, ns_, lds_all)) return;
+            join_heads<NHG, NHG == 1>(a, u, wave * NHG, row0, ns_);
+            step_is_done(a);
         }
     }
 }
@@ -1356,7 +1336,8 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hip
     if (!RecLayout<B, G, GC, MEAN>::matches(a.geom)) return hipErrorInvalidValue;
     if (XH == 2 && (a.n_kv_heads < NW || a.n_kv_heads % NW != 0)) return hipErrorInvalidValue;
     if (a.uneven && XH != 0) return hipErrorInvalidValue;
-    if (a.direct && (XH == 1 || a.uneven || a.n_splits != 1 || a.len_dev)) return hipErrorInvalidValue;
+    if (a.direct == 1 && (XH == 1 || a.uneven || a.n_splits != 1 || a.len_dev)) return hipErrorInvalidValue;
+    if (a.direct == 2 && (XH != 0 || !a.sync || (a.uneven ? a.uneven_most : a.n_splits) > (NHG == 1 ? kJoinSplits : kJoinFew))) return hipErrorInvalidValue;
     static_assert(XH != 0 || NW == kSplitWaves, "the planner of uneven splits counts on it");
     dim3 grid(XH == 2 ? a.n_splits * (a.n_kv_heads / NW) : a.n_splits, XH == 2 ? a.batch : a.batch * a.n_kv_heads);
     if (a.uneven) grid = dim3(a.uneven_total, a.n_kv_heads);

@@ -29,7 +29,7 @@
 // Measured (4 sequences of 8213 tokens, 8 kv heads x 4 query heads, 134 MB, the whole attention call with
 // the merge launch): 36.5 us, 3.7 TB/s; the vector-ALU kernel, which such layers ran on before and still do
 // where path 1 is asked for: 221 us.
-#include "tadakv_internal.h"
+#include "join.h"
 #include <hip/hip_fp16.h>
 
 namespace tadakv {
@@ -66,6 +66,7 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
     constexpr int NW = kRawWaves;
     constexpr int ST = 33; // floats per row of the state exchange (32 lanes of live columns, padded)
     __shared__ float state[NW][34 * ST];
+    __shared__ uint32_t done;
     decode_args_here(a);
     const LayerGeom &gm = a.geom;
     const int lane = threadIdx.x & 63, row = lane >> 4, n = lane & 15;
@@ -246,6 +247,7 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
         mine[33 * ST] = l;
     }
     __syncthreads();
+    const bool joined = a.direct == 2;
     for (int o = threadIdx.x; o < g * kHeadDim; o += 64 * NW) {
         const int head = o >> 7, c = o & 127;
         const int at = (4 * (c & 7) + ((c >> 3) & 3)) * ST + (c >> 5) * 8 + head;
@@ -260,17 +262,20 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
             num += state[w][at] * wt;
             den += state[w][33 * ST + head] * wt;
         }
-        if (a.direct) {
+        if (a.direct == 1) {
             put_output(a, u, head, c, num, den, Mx);
             continue;
         }
         float *dst = a.ws + ((long long)row0 + head * ns + sp) * kPartialStride;
-        dst[c] = num;
+        put_partial(dst + c, num, joined);
         if (c == 0) {
-            dst[kHeadDim] = Mx;
-            dst[kHeadDim + 1] = den;
+            put_partial(dst + kHeadDim, Mx, joined);
+            put_partial(dst + kHeadDim + 1, den, joined);
         }
     }
+    if (!joined || !last_of_unit<NW>(a, u, ns, &done)) return;
+    if (g <= NW) join_heads<1, false>(a, u, wave, row0, ns);
+    else join_heads<2, false>(a, u, 2 * wave, row0, ns);
 }
 
 template <int DT, bool PG> int resident_blocks()
@@ -318,7 +323,8 @@ int decode_raw_splits(const DecodeArgs &a, int cap)
 
 hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s)
 {
-    if (!decode_raw_supported(a) || (a.direct && (a.uneven || a.n_splits != 1))) return hipErrorInvalidValue;
+    if (!decode_raw_supported(a) || (a.direct == 1 && (a.uneven || a.n_splits != 1))) return hipErrorInvalidValue;
+    if (a.direct == 2 && (!a.sync || (a.uneven ? a.uneven_most : a.n_splits) > kJoinFew)) return hipErrorInvalidValue;
     const dim3 grid = a.uneven ? dim3(a.uneven_total, a.n_kv_heads) : dim3(a.n_splits, a.batch * a.n_kv_heads), block(64 * kRawWaves);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
     const bool pg = a.geom.table != nullptr;

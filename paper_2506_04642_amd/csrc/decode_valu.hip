@@ -10,7 +10,7 @@
 // Eq. 9-10) and 16-bit layers go through the same code with scale 1, zero 0.
 // The split's running (max, sum, output) goes to the workspace; merge_kernel combines the splits
 // with the log-sum-exp identity, in a fixed order (no atomics), so results are reproducible.
-#include "tadakv_internal.h"
+#include "join.h"
 #include <hip/hip_fp16.h>
 
 namespace tadakv {
@@ -356,9 +356,8 @@ template <int KB, int VB> __global__ __launch_bounds__(kThreads) void decode_spl
 // rising order, NB at a time, with a running maximum of its own, and the waves' states are joined in wave order,
 // so the result does not depend on timing.  Bound by latency: what the split kernel has just written comes from
 // memory, and with NW x NB at least the number of splits all of it is requested at once (launch_decode_merge).
-// Against two passes over the splits, the maxima first, with four waves (us a call): 16-bit layer of 4 x 8213
-// tokens, 24 splits, 37.4 -> 36.1; one sequence of 8205, 33 splits, 10.34 -> 10.10; 4 x 16461 with the mean over the
-// heads, 64 splits, two layers, 65.2 -> 64.4; the kernel itself with 7 splits 3.6 -> 2.9.  More splits a wave (16) or
+// Against two passes over the splits, the maxima first, with four waves (us a call): 4 x 16461 with the mean over the
+// heads, 64 splits, two layers, 65.2 -> 64.4.  More splits a wave (16) or
 // one count for all were slower: a wave's loads are then issued in two groups, or the unused ones cost.
 template <int NB, int NW> __global__ __launch_bounds__(64 * NW) void merge_kernel(DecodeArgs a)
 {
@@ -449,6 +448,29 @@ template <int NB, int NW> __global__ __launch_bounds__(64 * NW) void merge_kerne
     // a decode step on device-resident lengths ends here: the state after the step becomes the current
     // one (no workgroup of this kernel reads the lengths)
     if (a.len_dev && blockIdx.x == 0 && lane == 0) a.len_dev[4 * a.batch] = (a.len_dev[4 * a.batch] & 1) ^ 1;
+}
+
+// The same for up to kJoinSplits splits, by a wave per query head (join.h): no LDS and no barrier.  The kernel alone (us, a
+// workgroup of four waves per head -> this): 4 splits 3.0 -> 2.9, 7 2.7 -> 2.4, 33 3.7 -> 3.3, 128 units x 4 heads of 2 to 8 splits 2.6 -> 2.2.
+__global__ __launch_bounds__(64) void join_kernel(DecodeArgs a)
+{
+    // (see decode_args_here)
+    asm volatile("" : : "s"(a.g), "s"(a.n_kv_heads), "s"(a.n_splits), "s"(a.uneven), "s"(a.ws), "s"(a.out), "s"(a.out16), "s"(a.len_dev));
+    const int uq = blockIdx.x, lane = threadIdx.x;
+    int ns;
+    const float *base = a.ws + partial_row(a, uq / a.g, uq % a.g, ns) * kPartialStride;
+    join_f32x4 joined[1];
+    if (ns <= kJoinFew) join_rows<kJoinFew / 2, 1, 0>(base, ns, 1, joined);
+    else join_rows<kJoinSplits / 2, 1, 0>(base, ns, 1, joined);
+    const join_f32x4 &r = joined[0];
+    if (lane < 32) {
+        const long long o = (long long)uq * kHeadDim + 4 * lane; // (n_q_heads = n_kv_heads g)
+        if (a.out16)
+            *(uint2 *)(a.out16 + o) = uint2{(uint32_t)narrow16_rne(r.x, a.geom.dtype) | ((uint32_t)narrow16_rne(r.y, a.geom.dtype) << 16),
+                                            (uint32_t)narrow16_rne(r.z, a.geom.dtype) | ((uint32_t)narrow16_rne(r.w, a.geom.dtype) << 16)};
+        else *(join_f32x4 *)(a.out + o) = r;
+    }
+    if (a.len_dev && uq == 0 && lane == 0) a.len_dev[4 * a.batch] = (a.len_dev[4 * a.batch] & 1) ^ 1; // (see merge_kernel)
 }
 
 // Four codes of a word's field f (consecutive channels of a key word, consecutive tokens of a value
@@ -625,10 +647,10 @@ hipError_t launch_decode_merge(const DecodeArgs &a, hipStream_t s)
 {
     dim3 grid(a.batch * a.n_q_heads);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
-    // everything requested at once: 2, 8 or 9 splits a wave, 4 to 16 waves (up to 8, 36, 72, 128 splits: 32 or 64 for
-    // the chunks and a few for the raw tokens)
+    // everything requested at once: up to 34 splits by one wave per query head, else 8 or 9 splits a wave, 4 to 16 waves (up to
+    // 36, 72, 128 splits: 32 or 64 for the chunks and a few for the raw tokens)
     const int ns = a.uneven ? a.uneven_most : a.n_splits;
-    if (ns <= 8) hipLaunchKernelGGL((merge_kernel<2, 4>), grid, dim3(256), 0, s, a);
+    if (ns <= kJoinSplits && !a.xo) hipLaunchKernelGGL(join_kernel, grid, dim3(64), 0, s, a);
     else if (ns <= 36) hipLaunchKernelGGL((merge_kernel<9, 4>), grid, dim3(256), 0, s, a);
     else if (ns <= 72) hipLaunchKernelGGL((merge_kernel<9, 8>), grid, dim3(512), 0, s, a);
     else hipLaunchKernelGGL((merge_kernel<8, 16>), grid, dim3(1024), 0, s, a);

@@ -980,22 +980,44 @@ kv_status kv_set_decode_splits(kv_cache *cache, int32_t n_splits)
     return KV_OK;
 }
 
-// One split per unit, and the caller wants the output: the split kernel writes it.
-static void write_direct(const kv_cache *cache, DecodeArgs *a, bool mfma)
+// Does the split kernel join the splits itself, if it is given counts for its workgroups (join.h)?  With one query head a
+// wave up to kJoinSplits of them, whose rows the wave requests at once.  With two heads up to kJoinFew: one
+// sequence of 1100 tokens, 8 query heads per kv head, 6 splits 9.9 -> 9.4 us, of 2100, 10 splits 10.5 -> 10.8.  So, too, for 16-bit
+// layers: 2000 tokens, 8 splits 10.1 -> 9.2, but 4 x 8213, 24 splits 37.1 -> 37.6.  Not in the kernels
+// with the mean over the heads, where a wave has four heads to join: 4 x 450 tokens, 7 splits 15.8 -> 17.7.
+static bool join_in_kernel(const DecodeArgs &a)
 {
-    a->direct = a->out && a->n_splits == 1 && !a->uneven && !a->xs && (mfma || use_raw(cache, *a));
+    if (a.geom.mean_mode == KV_MEAN_CROSS_HEAD && a.geom.k_bits != 16) return false;
+    if ((a.uneven ? a.uneven_most : a.n_splits) > (a.g <= kSplitWaves && a.geom.k_bits != 16 ? kJoinSplits : kJoinFew)) return false;
+    // (nobody writes the zeros of a sequence that has no workgroup)
+    if (a.uneven)
+        for (int b = 0; b < a.batch; b++)
+            if (uneven_count(a, a.nb_seq[b], a.r_seq[b]) == 0) return false;
+    return true;
+}
+
+// One split per unit, and the caller wants the output: the split kernel writes it.
+// A few splits, and the caller has counts for the workgroups: the split kernel joins them.
+static void write_direct(const kv_cache *cache, DecodeArgs *a, bool mfma, void *sync)
+{
+    if (!a->out || a->xs || !(mfma || use_raw(cache, *a))) return;
+    a->direct = a->n_splits == 1 && !a->uneven;
+    if (!a->direct && sync && join_in_kernel(*a)) {
+        a->direct = 2;
+        a->sync = (uint32_t *)sync;
+    }
 }
 
 // The split launch; *a keeps the plan, for the merge of the same call.
 // out: where the output goes if the split kernel can write it (merge_planned then has nothing to do); null: partial
 // results in any case.
 static kv_status split_impl(const kv_cache *cache, int32_t layer, const void *q, float *out, void *workspace, size_t workspace_bytes,
-                            void *stream, DecodeArgs *a)
+                            void *sync, void *stream, DecodeArgs *a)
 {
     kv_status st = layer_ok(cache, layer);
     if (st != KV_OK) return st;
     if (!q) return KV_E_NULL;
-    if ((uintptr_t)q % 16) return KV_E_ALIGN;
+    if (((uintptr_t)q % 16) || ((uintptr_t)sync % 64)) return KV_E_ALIGN;
     st = fill_decode(cache, layer, a);
     if (st != KV_OK) return st;
     st = bind_workspace(cache, a, workspace, workspace_bytes);
@@ -1004,7 +1026,7 @@ static kv_status split_impl(const kv_cache *cache, int32_t layer, const void *q,
     a->out = out;
     hipStream_t s = (hipStream_t)stream;
     const bool mfma = use_mfma(cache, *a);
-    write_direct(cache, a, mfma);
+    write_direct(cache, a, mfma, sync);
     if (cache->decode_path == 2 && !mfma) return KV_E_UNSUPPORTED;
     hipError_t e = mfma ? launch_decode_split_mfma(*a, s) : use_raw(cache, *a) ? launch_decode_split_raw(*a, s) : launch_decode_split_valu(*a, s);
     return e == hipSuccess ? KV_OK : KV_E_HIP;
@@ -1014,7 +1036,7 @@ kv_status kv_decode_attn_split(const kv_cache *cache, int32_t layer, const void 
                                void *workspace, size_t workspace_bytes, void *stream)
 {
     DecodeArgs a{};
-    return split_impl(cache, layer, q, nullptr, workspace, workspace_bytes, stream, &a);
+    return split_impl(cache, layer, q, nullptr, workspace, workspace_bytes, nullptr, stream, &a);
 }
 
 // The merge of a planned launch (the plan is a function of the cache's state and the workspace).
@@ -1090,13 +1112,13 @@ kv_status kv_dequant_padded(const kv_cache *cache, int32_t layer, float *k_out, 
 
 static kv_status append_split_impl(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
                                    int64_t stride_b, int64_t stride_h, const void *q, float *out,
-                                   void *workspace, size_t workspace_bytes, void *stream, DecodeArgs *plan)
+                                   void *workspace, size_t workspace_bytes, void *sync, void *stream, DecodeArgs *plan)
 {
     kv_status st = layer_ok(cache, layer);
     if (st != KV_OK) return st;
     if (!k_new || !v_new || !q) return KV_E_NULL;
     const kv_config &c = cache->cfg;
-    if (((uintptr_t)k_new % 16) || ((uintptr_t)v_new % 16) || ((uintptr_t)q % 16)) return KV_E_ALIGN;
+    if (((uintptr_t)k_new % 16) || ((uintptr_t)v_new % 16) || ((uintptr_t)q % 16) || ((uintptr_t)sync % 64)) return KV_E_ALIGN;
     if (stride_b % 8 || stride_h % 8) return KV_E_ALIGN;
     if (stride_h < c.head_dim || stride_b < 0) return KV_E_BAD_CONFIG;
     bool flush = false; // does the token complete a block of some sequence
@@ -1138,11 +1160,11 @@ static kv_status append_split_impl(kv_cache *cache, int32_t layer, const void *k
         st = kv_quant_append(cache, layer, k_new, v_new, 1, stride_b, 0, stride_h, stream);
         if (st != KV_OK) return st;
         a = DecodeArgs{};
-        return split_impl(cache, layer, q, out, workspace, workspace_bytes, stream, &a);
+        return split_impl(cache, layer, q, out, workspace, workspace_bytes, sync, stream, &a);
     }
     a.q = (const uint16_t *)q;
     a.out = out;
-    write_direct(cache, &a, true);
+    write_direct(cache, &a, true, sync);
     a.k_fresh = (const uint16_t *)k_new;
     a.v_fresh = (const uint16_t *)v_new;
     a.fresh_stride_b = stride_b;
@@ -1159,17 +1181,35 @@ kv_status kv_append_decode_attn_split(kv_cache *cache, int32_t layer, const void
                                       void *workspace, size_t workspace_bytes, void *stream)
 {
     DecodeArgs a{};
-    return append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, nullptr, workspace, workspace_bytes, stream, &a);
+    return append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, nullptr, workspace, workspace_bytes, nullptr, stream, &a);
+}
+
+kv_status kv_append_decode_attn_joined(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
+                                       int64_t stride_b, int64_t stride_h, const void *q, float *out,
+                                       void *workspace, size_t workspace_bytes, void *counts, void *stream)
+{
+    if (!out) return KV_E_NULL;
+    if ((uintptr_t)out % 16) return KV_E_ALIGN;
+    DecodeArgs a{};
+    kv_status st = append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, out, workspace, workspace_bytes, counts, stream, &a);
+    if (st != KV_OK) return st;
+    return merge_planned(&a, out, nullptr, stream);
 }
 
 kv_status kv_append_decode_attn(kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
                                 int64_t stride_b, int64_t stride_h, const void *q, float *out,
                                 void *workspace, size_t workspace_bytes, void *stream)
 {
+    return kv_append_decode_attn_joined(cache, layer, k_new, v_new, stride_b, stride_h, q, out, workspace, workspace_bytes, nullptr, stream);
+}
+
+kv_status kv_decode_attn_joined(const kv_cache *cache, int32_t layer, const void *q, float *out,
+                                void *workspace, size_t workspace_bytes, void *counts, void *stream)
+{
     if (!out) return KV_E_NULL;
     if ((uintptr_t)out % 16) return KV_E_ALIGN;
     DecodeArgs a{};
-    kv_status st = append_split_impl(cache, layer, k_new, v_new, stride_b, stride_h, q, out, workspace, workspace_bytes, stream, &a);
+    kv_status st = split_impl(cache, layer, q, out, workspace, workspace_bytes, counts, stream, &a);
     if (st != KV_OK) return st;
     return merge_planned(&a, out, nullptr, stream);
 }
@@ -1177,12 +1217,16 @@ kv_status kv_append_decode_attn(kv_cache *cache, int32_t layer, const void *k_ne
 kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, float *out,
                          void *workspace, size_t workspace_bytes, void *stream)
 {
-    if (!out) return KV_E_NULL;
-    if ((uintptr_t)out % 16) return KV_E_ALIGN;
-    DecodeArgs a{};
-    kv_status st = split_impl(cache, layer, q, out, workspace, workspace_bytes, stream, &a);
+    return kv_decode_attn_joined(cache, layer, q, out, workspace, workspace_bytes, nullptr, stream);
+}
+
+kv_status kv_join_counts_bytes(const kv_config *cfg, size_t *bytes)
+{
+    if (!bytes) return KV_E_NULL;
+    kv_status st = check_config(cfg);
     if (st != KV_OK) return st;
-    return merge_planned(&a, out, nullptr, stream);
+    *bytes = ((size_t)cfg->batch * cfg->n_kv_heads + 1) * kSyncStride * sizeof(uint32_t);
+    return KV_OK;
 }
 
 kv_status kv_dev_lengths_bytes(const kv_config *cfg, size_t *bytes)
@@ -1243,12 +1287,19 @@ kv_status kv_decode_step_dev(const kv_cache *cache, int32_t layer, const void *k
                              int64_t stride_b, int64_t stride_h, const void *q, float *out,
                              void *workspace, size_t workspace_bytes, void *stream)
 {
+    return kv_decode_step_dev_joined(cache, layer, k_new, v_new, stride_b, stride_h, q, out, workspace, workspace_bytes, nullptr, stream);
+}
+
+kv_status kv_decode_step_dev_joined(const kv_cache *cache, int32_t layer, const void *k_new, const void *v_new,
+                                    int64_t stride_b, int64_t stride_h, const void *q, float *out,
+                                    void *workspace, size_t workspace_bytes, void *counts, void *stream)
+{
     kv_status st = layer_ok(cache, layer);
     if (st != KV_OK) return st;
     if (!k_new || !v_new || !q || !out) return KV_E_NULL;
     if (!cache->len_dev) return KV_E_BAD_CONFIG; // kv_cache_lengths_to_device has not been called
     const kv_config &c = cache->cfg;
-    if (((uintptr_t)k_new % 16) || ((uintptr_t)v_new % 16) || ((uintptr_t)q % 16) || ((uintptr_t)out % 16)) return KV_E_ALIGN;
+    if (((uintptr_t)k_new % 16) || ((uintptr_t)v_new % 16) || ((uintptr_t)q % 16) || ((uintptr_t)out % 16) || ((uintptr_t)counts % 64)) return KV_E_ALIGN;
     if (stride_b % 8 || stride_h % 8) return KV_E_ALIGN;
     if (stride_h < c.head_dim || stride_b < 0) return KV_E_BAD_CONFIG;
     if (!cache->active.empty()) return KV_E_UNSUPPORTED;
@@ -1274,6 +1325,10 @@ kv_status kv_decode_step_dev(const kv_cache *cache, int32_t layer, const void *k
     a.len_dev = cache->len_dev + (size_t)layer * dev_len_ints(c.batch);
     a.q = (const uint16_t *)q;
     a.out = out;
+    if (counts && join_in_kernel(a)) {
+        a.direct = 2;
+        a.sync = (uint32_t *)counts;
+    }
 
     AppendArgs ap{};
     ap.geom = cache->geom[layer];
@@ -1295,6 +1350,7 @@ kv_status kv_decode_step_dev(const kv_cache *cache, int32_t layer, const void *k
     hipStream_t s = (hipStream_t)stream;
     if (launch_flush(ap, s) != hipSuccess) return KV_E_HIP; // (stores the token, too)
     if (launch_decode_split_mfma(a, s) != hipSuccess) return KV_E_HIP;
+    if (a.direct) return KV_OK;
     return launch_decode_merge(a, s) == hipSuccess ? KV_OK : KV_E_HIP;
 }
 

@@ -9,6 +9,9 @@ constexpr int kHeadDim = 128;
 constexpr int kMaxGroupQ = 8;       // query heads per kv head the kernels are sized for
 constexpr int kPartialStride = 132; // floats per (unit, q head, split): O[128], max, sum, pad
 constexpr int kMaxSplits = 256;
+constexpr int kJoinSplits = 34;     // splits that one wavefront joins at once (join.h)
+constexpr int kJoinFew = 8;         // splits of which it joins several query heads at once
+constexpr int kSyncStride = 16;     // 32-bit words from one count of finished workgroups to the next
 constexpr int kMaxRaggedBatch = 256; // sequences whose lengths may differ from one another
 
 // Geometry of one layer's buffer; byte offsets, -1 where a field is absent.
@@ -130,7 +133,9 @@ struct DecodeArgs {
     // of a unit's splits the last resid_splits take its raw tokens (tiles of 32 in turn) and no chunks; 0: the raw
     // tokens are dealt to all splits behind their chunks (matrix-core kernel without a mean over the heads)
     int resid_splits;
-    int direct; // not 0: one split per unit, and the split kernel writes the output itself (binary32, to out; no merge)
+    // 1: one split per unit, and the split kernel writes the output itself (binary32, to out; no merge).  2: the split
+    // kernel joins the splits itself (join.h) and counts the finished workgroups of each unit at `sync`
+    int direct;
     int blocks_per_split;
     // matrix-core kernel only: the newest residual token (index r - 1) is not in the cache yet;
     // the kernel takes it from these rows and stores it (null: every token is in the cache)
@@ -153,6 +158,7 @@ struct DecodeArgs {
     // after the step's append, dev_len) instead; n_blocks and r only size the launch.  The merge makes
     // that state the current one.
     int *len_dev;
+    uint32_t *sync; // zero before the launch and after it
     uint16_t nb_seq[kMaxRaggedBatch], r_seq[kMaxRaggedBatch]; // 1 KiB of the kernel arguments
 };
 
