@@ -389,20 +389,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 
     // fused cross-head form: a workgroup takes NW kv heads of a sequence; with more heads several
     // workgroups (parts) share a (sequence, split) and read the same mean rows -- they sit 8 apart in
-    // the launch order when the split count allows (same XCD and so the same L2, resident together)
+    // the launch order (same XCD and so the same L2, resident together), whatever the split count: only the last
+    // workgroups of a launch, less than 8 to a part, sit closer.  (With
+    // neighbours as partners: 2 bits, 9 of 9000 tokens, 28 splits, 38.6 us instead of 34.1.)
     const int parts = XF ? a.n_kv_heads / NW : 1;
     int sp = blockIdx.x, half = 0, u_ = blockIdx.y, ns_ = a.n_splits, row0 = 0; // half: which part
     if (XH == 0) unit_and_split(a, u_, sp, ns_, row0);
+    int seq = blockIdx.y;
     if (XF && parts > 1) {
-        if (a.n_splits % 8 == 0) {
-            half = (sp >> 3) % parts;
-            sp = (sp & 7) | (((sp >> 3) / parts) << 3);
-        } else {
-            half = sp % parts;
-            sp /= parts;
-        }
+        const uint32_t id = blockIdx.x + gridDim.x * blockIdx.y, whole = 8 * parts, first = id / whole * whole;
+        const uint32_t left = gridDim.x * gridDim.y - first, apart = left >= whole ? 8 : left / parts;
+        half = (id - first) / apart;
+        const uint32_t pair = first / parts + (id - first) - half * apart; // sequence * splits + split
+        seq = pair / a.n_splits;
+        sp = pair - seq * a.n_splits;
     }
-    const int u = XF ? (int)blockIdx.y * a.n_kv_heads + half * NW + wave : u_;
+    const int u = XF ? seq * a.n_kv_heads + half * NW + wave : u_;
     const int b = u / a.n_kv_heads, h = u % a.n_kv_heads;
     const int g = a.g;
     const int cw0 = XF ? 0 : wave; // this wave's first local chunk
@@ -483,6 +485,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
         const uint16_t *qp = a.q + ((long long)b * a.n_q_heads + h * g + (head < g ? head : 0)) * kHeadDim;
 #pragma unroll
         for (int ph = 0; ph < 2; ph++) qraw[hg][ph] = *(const uint2 *)(qp + 32 * vq + 16 * ph + 4 * qa);
+    }
+    // (fused cross-head form: the workgroup's queries as the A operand of the score products, see below)
+    uint4 qAraw[XF ? NHG : 1][4];
+    if (XF) {
+#pragma unroll
+        for (int e = 0; e < NHG; e++) {
+            const int hp = 16 * ((wave * NHG + e) >> 2) + n, local = hp % (4 * NHG); // A row n: head of its group
+            const uint16_t *qp = a.q + ((long long)b * a.n_q_heads + (half * NW + hp / (4 * NHG)) * g + (local < g ? local : 0)) * kHeadDim + 8 * row;
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++) qAraw[e][ks] = *(const uint4 *)(qp + 32 * ks);
+        }
     }
     if (cw0 < n_chunks) issue(cw0);
     // rows 4i+3 of the operands (the unused fourth limb) must read as zero
@@ -581,7 +594,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     };
     if (XF) {
         // the key-mean rows of the first two chunks (of the first one again if there is no second) are on their
-        // way while the queries are fetched and narrowed; their scores follow below
+        // way while the queries are narrowed; their scores follow below
         u32x4 kb[2][NHG][4];
 #pragma unroll
         for (int e = 0; e < NHG; e++) km_row[e] = 16 * ((wave * NHG + e) & 3) + n;
@@ -592,11 +605,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 #pragma unroll
         for (int e = 0; e < NHG; e++) {
             const int pj = wave * NHG + e, rb = pj >> 2, tt = pj & 3; // head block, token tile
-            const int hp = 16 * rb + n, hk = half * NW + hp / HP, local = hp % HP; // A row n: kv head, head of its group
-            const uint16_t *qp = a.q + ((long long)b * a.n_q_heads + hk * g + (local < g ? local : 0)) * kHeadDim + 8 * row;
+            const int local = (16 * rb + n) % HP;
 #pragma unroll
             for (int ks = 0; ks < 4; ks++) {
-                const uint4 w = *(const uint4 *)(qp + 32 * ks);
+                const uint4 w = qAraw[e][ks];
                 const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
                 uint32_t o[4];
 #pragma unroll
@@ -1415,16 +1427,19 @@ template <int B, int G, int GC, bool PG, class F> void pick_mean_heads_pg(const 
         else f.template run<B, G, GC, false, NW, 2, 0, PG>(a);
     }
 }
-// the fused cross-head instances: a wave per kv head.  Eight kv heads go to two workgroups of four waves
-// that share a sequence's split, except at 4 bits with up to four query heads per kv head, where one
-// workgroup of eight is faster (177 against 193 us per layer on 16 sequences of 32768 tokens: every
-// mean row is fetched once per workgroup instead of once per pair that may have drifted apart in the
-// L2; at 2 bits the four-wave instance fits a compute unit twice and wins, 158 against 163 us; eight
-// 8-bit chunk buffers do not fit the LDS).
+// the fused cross-head instances: a wave per kv head.  Eight kv heads go to two workgroups of four waves that share a
+// sequence's split, except in long launches at 4 bits with up to four query heads per kv head, where one workgroup of
+// eight is faster: every mean row is fetched once per workgroup instead of once per pair that may have drifted
+// apart in the L2.  (At 2 bits the four-wave instance fits a compute unit twice and wins, 158 against 163 us per layer on 16
+// sequences of 32768 tokens; eight 8-bit chunk buffers do not fit the LDS.)  Eight waves wait for one another longer,
+// at the start and the end above all, so the line is drawn at the chunks a wave takes, 12: eight waves against
+// four, us per layer of 8 kv heads x 4: 16 x 32781 tokens (32 chunks) 182 / 193, 12 x 40000 (30) 165 / 175, 24 x 12000 (18) 106 / 112, 3 x 100000, groups
+// of 128 (18) 100 / 103; 5 x 30000 (9) 55.9 / 55.3, 16 x 8192 (8) 52.4 / 49.3, 4 x 16461, groups of 128 (4) 33.3 / 31.7, 2 x 1500 (1) 17.6 / 14.3.
 template <int B, int G, int GC, bool PG, class F> void pick_fused_pg(const DecodeArgs &a, F &f)
 {
     if constexpr (B == 4) {
-        if (a.n_kv_heads % 8 == 0 && a.g <= 4) {
+        const long long chunks = ((long long)a.n_blocks * G + 63) / 64 * a.batch * a.n_kv_heads;
+        if (a.n_kv_heads % 8 == 0 && a.g <= 4 && chunks > 12 * 256 * 8) { // (256 compute units, 8 waves each)
             f.template run<B, G, GC, false, 8, 1, 2, PG>(a);
             return;
         }
