@@ -414,10 +414,11 @@ class KVCache:
 
     def append(self, layer: int, k_new, v_new) -> None:
         """k_new, v_new: device tensors [B, n_new, Hkv, d], 16-bit, last dim contiguous."""
-        assert k_new.shape == v_new.shape and k_new.stride() == v_new.stride()
-        assert k_new.stride(3) == 1 and k_new.element_size() == 2
-        kv_quant_append(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), k_new.shape[1],
-                        k_new.stride(0), k_new.stride(1), k_new.stride(2), self._stream())
+        shape, (sb, st, sh, sc) = k_new.shape, k_new.stride()
+        assert shape == v_new.shape and (sb, st, sh, sc) == v_new.stride()
+        assert sc == 1 and k_new.element_size() == 2
+        _check(_lib.kv_quant_append(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), shape[1], sb, st, sh, self._stream()),
+               "kv_quant_append")
 
     def append_seq(self, layer: int, seq: int, k_new, v_new) -> None:
         """k_new, v_new: device tensors [n_new, Hkv, d] of one sequence of the batch."""
@@ -485,13 +486,14 @@ class KVCache:
         if k_new.dim() == 4:
             assert k_new.shape[1] == 1
             k_new, v_new = k_new[:, 0], v_new[:, 0]
-        assert k_new.shape == v_new.shape and k_new.stride() == v_new.stride()
-        assert k_new.stride(2) == 1 and k_new.element_size() == 2 and q.is_contiguous()
+        sb, sh, sc = k_new.stride()
+        assert k_new.shape == v_new.shape and (sb, sh, sc) == v_new.stride()
+        assert sc == 1 and k_new.element_size() == 2 and q.is_contiguous()
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=self.device)
-        kv_append_decode_attn_joined(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), k_new.stride(0), k_new.stride(1),
-                                     q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes,
-                                     self._counts.data_ptr(), self._stream())
+        _check(_lib.kv_append_decode_attn_joined(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), sb, sh, q.data_ptr(),
+                                                 out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes, self._counts.data_ptr(),
+                                                 self._stream()), "kv_append_decode_attn_joined")
         return out
 
     def lengths_to_device(self):
