@@ -17,8 +17,8 @@
 // of 64 k-values (rows of 128 bytes, whole cache lines) are fetched straight into LDS
 // (global_load_lds_dwordx4) a stage ahead, 16-byte pieces of a row XOR-swizzled by the row so that
 // the operand reads (16 rows x one piece) hit distinct banks.
-// A call of up to 1024 (group, kv head) items would leave most of the device idle that way: there a workgroup owns 64
-// tokens x one head, two waves of 32 tokens, with four stages in LDS instead of two.
+// A call of up to 2048 (group, kv head) items would leave half of the device idle that way: there a workgroup owns 128 tokens x one
+// head, two waves of 64 tokens; up to 512 items 64 tokens x one head, two waves of 32, with four stages in LDS instead of two.
 // Every output element is one chain of model_dim / 32 matrix instructions in ascending k, the same
 // chain in project_rows_kernel below, so a token's projected value does not depend on which of
 // the two kernels, or which tile, produced it.
@@ -39,7 +39,9 @@ typedef __attribute__((address_space(3))) void *lptr_t;
 
 constexpr int kStepK = 64;       // k-values per stage: rows of 128 bytes, whole cache lines
 constexpr int kEpiBytes = 16384; // per wave after the main loop: transposed 16-bit tile + record image
-constexpr int kSmallTileItems = 1024; // (32 tokens x one head) items up to which the small tile is the faster
+// (32 tokens x one head) items up to which the small and the middle tile are the faster: one round of them on 256 compute
+// units, one or two workgroups each
+constexpr int kSmallTileItems = 512, kMiddleTileItems = 2048;
 constexpr int kTTStride = 80;    // bytes per channel column of the transposed tile (32 tokens + pad)
 
 template <int DT> __device__ __forceinline__ v4f mfma16(const u32x4 &a, const u32x4 &b, v4f c)
@@ -412,15 +414,18 @@ template <int DT, int NH, int GC, int BITS, int WT, int MW, int S> hipError_t la
     hipLaunchKernelGGL((compressv_gemm_kernel<DT, NH, GC, BITS, WT, MW, S>), dim3((unsigned)grid), dim3(64 * MW * NH), lds, s, p);
     return note_launch(hipGetLastError());
 }
-// The tile by the number of tokens: 256 x NH heads where that fills the device, else 64 x one head with four stages
-// on their way (a small workgroup's stage is through in a fifth of the time that its fetch takes).  Same chain per
-// element, same bytes.
-// Measured (us a call with the keys' side, large tile -> small, 8 kv heads, 4 bits, model_dim 4096): 128 tokens 97 -> 50,
-// 2048 tokens 98 -> 52, 4096 tokens (the limit: two rounds of workgroups) 99 -> 95; model_dim 1024, 1024 tokens: 38 -> 22.
+// The tile by the number of tokens: 256 x NH heads where that fills the device; up to 2048 items 128 tokens x one head (two
+// waves of the same 64 x 128 tile, two such workgroups per compute unit); up to 512 items 64 tokens x one head with
+// four stages on their way (a small workgroup's stage is through in a fifth of the time that its fetch takes).  Same chain per
+// element, same bytes.  Beyond its one round a tile that is smaller than another only reads the operands more often.
+// Measured (us a call with the keys' side, bf16, 4 bits; small / middle / large): 8 kv heads, model_dim 4096: 1024 tokens 53 / 61 / 100,
+// 2048 (512 items) 55 / 63 / 100, 3072 98 / 64 / 102, 4096 99 / 66 / 103, 8192 (2048 items) 184 / 78 / 109, 12288 272 / 134 / 117,
+// 24576 539 / 250 / 245; 2 heads, model_dim 2048: 8192 tokens (512 items) 32 / 42 / 59, 16384 57 / 42 / 64, 32768 (2048) 107 / 49 / 68.
 template <int DT, int GC, int BITS> hipError_t launch_gemm_tile(const ProjectArgs &p, hipStream_t s)
 {
-    const long long groups = (long long)p.batch * p.n_groups;
-    if (groups * p.n_kv_heads <= kSmallTileItems) return launch_gemm<DT, 1, GC, BITS, 32, 2, 4>(p, s);
+    const long long items = (long long)p.batch * p.n_groups * p.n_kv_heads;
+    if (items <= kSmallTileItems) return launch_gemm<DT, 1, GC, BITS, 32, 2, 4>(p, s);
+    if (items <= kMiddleTileItems) return launch_gemm<DT, 1, GC, BITS, 64, 2, 2>(p, s);
     if (p.n_kv_heads % 2 == 0) return launch_gemm<DT, 2, GC, BITS, 64, 4, 2>(p, s);
     return launch_gemm<DT, 1, GC, BITS, 64, 4, 2>(p, s);
 }
