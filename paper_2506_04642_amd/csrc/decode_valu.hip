@@ -8,7 +8,7 @@
 //   o_c     = sum_t (p_t s_tg) code_tc + sum_t p_t z_tg + m_c sum_t p_t             values, Eq. 6, 8
 // with an online softmax across blocks (flash decoding, App. A).  Raw residual tokens (Sec. 3.3,
 // Eq. 9-10) and 16-bit layers go through the same code with scale 1, zero 0.
-// The split's running (max, sum, output) goes to the workspace; merge_kernel combines the splits
+// The split's running (max, sum, output) goes to the workspace; join_kernel or merge_kernel combines the splits
 // with the log-sum-exp identity, in a fixed order (no atomics), so results are reproducible.
 #include "join.h"
 #include <hip/hip_fp16.h>

@@ -102,7 +102,7 @@ template <int NB, int NH, int POLICY> __device__ __forceinline__ void join_rows(
 // What it costs, of a launch with one chunk a wave (one head of 1024 tokens, 4 splits; the device's clock): 0.7 us from the
 // stores to the count, 0.9 us for the join, against a second launch's 2.0 us on the device and 3.5 us of the host's time:
 // attention in us, two launches -> one: that one 8.2 -> 7.1, 8205 tokens, 8 kv heads x 4 (33 splits) 9.4 -> 8.6,
-// 4 x 1523 (7) 7.9 -> 7.2, 24 sequences up to 8011 paged (4) 45 -> 43. 
+// 4 x 1523 (7) 7.9 -> 7.2, 24 sequences up to 8011 paged (4) 45 -> 43.
 template <int NW> __device__ __forceinline__ bool last_of_unit(const DecodeArgs &a, int u, int ns, uint32_t *flag)
 {
     uint32_t *c = a.sync + u * kSyncStride;

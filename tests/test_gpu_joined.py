@@ -127,6 +127,18 @@ def test_recorded_step_makes_its_lengths_current(kv, oracle):
     assert not bool(caches[0]._counts.any())
 
 
+@pytest.mark.gpu
+def test_counts_are_zero_for_every_stream(kv):
+    """A new cache's counts are zeroed on the stream that makes it; the first call may be on another one that does not wait."""
+    cfg = kv.make_config(1, 2, 4, 1, 128, 256, 32, 32, 32, BF16, CHAN, [4], [4])
+    x = torch.ones((4096, 4096), device="cuda:0")
+    for _ in range(20):
+        x = torch.mm(x, x)
+    gpu = kv.KVCache(cfg, zero=False)
+    assert torch.cuda.current_stream().query()
+    assert not bool(gpu._counts.any())
+
+
 def test_arguments(kv):
     cfg = kv.make_config(1, 3, 8, 2, 128, 256, 32, 32, 32, BF16, CHAN, [4], [4])
     assert kv.kv_join_counts_bytes(cfg) == (3 * 2 + 1) * 64
