@@ -387,8 +387,9 @@ class KVCache:
         self.workspace = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
         # counts of finished workgroups, zero between calls; used by one call at a time, as the workspace is
         self._counts = torch.zeros(kv_join_counts_bytes(cfg), dtype=torch.uint8, device=self.device)
-        if not torch.cuda.is_current_stream_capturing():
-            torch.cuda.current_stream(self.device).synchronize()  # (the first call may be on another stream than these zeros)
+        if not zero and not torch.cuda.is_current_stream_capturing():
+            # the first call may be on another stream than these zeros (with zero=True the layers have to be waited for as well)
+            torch.cuda.current_stream(self.device).synchronize()
         self.handle: Optional[int] = kv_cache_create(cfg, [t.data_ptr() for t in self.layers])
 
     def set_block_table(self, table) -> None:
