@@ -32,6 +32,7 @@ def sources():
     return [os.path.join(CSRC, s) for s, _ in UNITS] + [
         os.path.join(CSRC, "tadakv_internal.h"),
         os.path.join(CSRC, "quant_wave.h"),
+        os.path.join(CSRC, "join.h"),
         os.path.join(os.path.dirname(HERE), "include", "tadakv.h"),
     ]
 
