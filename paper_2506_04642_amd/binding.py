@@ -385,11 +385,16 @@ class KVCache:
                        for l in range(cfg.n_layers)]
         self.ws_bytes = kv_workspace_bytes(cfg)
         self.workspace = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
-        # counts of finished workgroups, zero between calls; used by one call at a time, as the workspace is
-        self._counts = torch.zeros(kv_join_counts_bytes(cfg), dtype=torch.uint8, device=self.device)
-        if not zero and not torch.cuda.is_current_stream_capturing():
-            # the first call may be on another stream than these zeros (with zero=True the layers have to be waited for as well)
-            torch.cuda.current_stream(self.device).synchronize()
+        # counts of finished workgroups, zero between calls; used by one call at a time, as the workspace is.  A cache
+        # made while a stream is capturing has none, and its calls are the plain ones: the zeros would be
+        # recorded, and a call before the first replay would find what the memory held before.
+        self._counts, self._counts_ptr = None, 0
+        if not torch.cuda.is_current_stream_capturing():
+            self._counts = torch.zeros(kv_join_counts_bytes(cfg), dtype=torch.uint8, device=self.device)
+            self._counts_ptr = self._counts.data_ptr()
+            if not zero:
+                # the first call may be on another stream than these zeros (with zero=True the layers have to be waited for as well)
+                torch.cuda.current_stream(self.device).synchronize()
         self.handle: Optional[int] = kv_cache_create(cfg, [t.data_ptr() for t in self.layers])
 
     def set_block_table(self, table) -> None:
@@ -461,7 +466,7 @@ class KVCache:
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=self.device)
         kv_decode_attn_joined(self.handle, layer, q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes,
-                              self._counts.data_ptr(), self._stream())
+                              self._counts_ptr, self._stream())
         return out
 
     def dequant(self, layer: int, t_cap: int):
@@ -495,7 +500,7 @@ class KVCache:
         if out is None:
             out = torch.empty(q.shape, dtype=torch.float32, device=self.device)
         _check(_lib.kv_append_decode_attn_joined(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), sb, sh, q.data_ptr(),
-                                                 out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes, self._counts.data_ptr(),
+                                                 out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes, self._counts_ptr,
                                                  self._stream()), "kv_append_decode_attn_joined")
         return out
 
@@ -514,7 +519,7 @@ class KVCache:
         assert k_new.stride(2) == 1 and k_new.element_size() == 2 and q.is_contiguous() and out.is_contiguous()
         kv_decode_step_dev_joined(self.handle, layer, k_new.data_ptr(), v_new.data_ptr(), k_new.stride(0), k_new.stride(1),
                                   q.data_ptr(), out.data_ptr(), self.workspace.data_ptr(), self.ws_bytes,
-                                  self._counts.data_ptr(), self._stream())
+                                  self._counts_ptr, self._stream())
 
     def advance(self, n_steps: int, layer: int = -1) -> None:
         kv_cache_advance(self.handle, layer, n_steps)
