@@ -294,7 +294,10 @@ kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, fl
  * bit; with more splits, and on the vector-ALU kernels, these calls enqueue what the plain ones do.
  *   counts : device, kv_join_counts_bytes, 64-byte aligned, zeroed by the caller once before its first use (in stream
  *            order); every call leaves it zero again.  Like the workspace it belongs to one call at a time:
- *            calls that may overlap need counts of their own.  NULL: as the plain call.
+ *            calls that may overlap need counts of their own.  Calls of a cache that overlap all the same spoil each
+ *            other's results, and may leave counts that are not zero; a later call of the cache starts over from those.
+ *            Not so a call that was recorded into a graph, whose replays count from the number that it was recorded
+ *            with: zero the counts before the next replay then (in stream order).  NULL: as the plain call.
  * kv_append_decode_attn_joined and kv_decode_step_dev_joined: kv_append_decode_attn and kv_decode_step_dev likewise. */
 kv_status kv_join_counts_bytes(const kv_config *cfg, size_t *bytes);
 kv_status kv_decode_attn_joined(const kv_cache *cache, int32_t layer, const void *q, float *out,

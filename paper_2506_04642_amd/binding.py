@@ -469,6 +469,11 @@ class KVCache:
                               self._counts_ptr, self._stream())
         return out
 
+    def zero_counts(self) -> None:
+        """For recorded calls, after calls that overlapped (by mistake): the counts of finished workgroups are zero again."""
+        if self._counts is not None:
+            self._counts.zero_()
+
     def dequant(self, layer: int, t_cap: int):
         """The layer's reconstructed keys and values, float32 [B, t_cap, Hkv, d] each (zeros past a
         sequence's length)."""

@@ -94,6 +94,18 @@ template <int NB, int NH, int POLICY> __device__ __forceinline__ void join_rows(
         }
     }
 }
+// Counts a workgroup in at *c: true for the last of n, which leaves the count zero.  From zero a call counts down from
+// base + n - 1 to its base, and every call of a cache has a base of its own, kSyncCalls below that of the call before.  So whatever
+// calls that overlapped have left there is above what a later call counts, and starts over like zero (the
+// instruction's own rule: a value that is zero or larger than its operand is replaced by it).
+__device__ __forceinline__ bool count_in(unsigned long long *c, unsigned long long base, uint32_t n)
+{
+    const unsigned long long first = base + (n - 1);
+    const unsigned long long was = __builtin_amdgcn_atomic_dec64((unsigned long *)c, first, __ATOMIC_RELAXED, "agent");
+    if ((was - 1 < first ? was - 1 : first) != base) return false;
+    __hip_atomic_store(c, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
 // The end of a split kernel that joins the splits itself: called by every wave of a workgroup once it has stored its part
 // of the partial results (put_partial).  The workgroups of a unit count themselves in; the last of the ns finds
 // everybody's results in memory and joins them (true), the others are through.  Nobody waits for another workgroup.
@@ -105,14 +117,10 @@ template <int NB, int NH, int POLICY> __device__ __forceinline__ void join_rows(
 // 4 x 1523 (7) 7.9 -> 7.2, 24 sequences up to 8011 paged (4) 45 -> 43.
 template <int NW> __device__ __forceinline__ bool last_of_unit(const DecodeArgs &a, int u, int ns, uint32_t *flag)
 {
-    uint32_t *c = a.sync + u * kSyncStride;
-    asm volatile("s_waitcnt vmcnt(0)" : : "s"(c) : "memory"); // this wave's partial results are in memory (c: requested before)
+    unsigned long long *c = a.sync + u * kSyncStride;
+    asm volatile("s_waitcnt vmcnt(0)" : : "s"(c), "s"(a.sync_base) : "memory"); // this wave's partial results are in memory (the arguments: requested before)
     __syncthreads();                                          // everybody's are
-    if (threadIdx.x == 0) {
-        const bool last = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)ns - 1u;
-        if (last) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = last;
-    }
+    if (threadIdx.x == 0) *flag = count_in(c, a.sync_base, ns);
     __syncthreads();
     return __builtin_amdgcn_readfirstlane((int)*flag) != 0;
 }
@@ -137,9 +145,7 @@ __device__ __forceinline__ void step_is_done(const DecodeArgs &a)
 {
     if (threadIdx.x != 0 || !a.len_dev) return;
     const int units = a.batch * a.n_kv_heads;
-    uint32_t *c = a.sync + units * kSyncStride; // (behind the units' counts)
-    if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)units - 1u) return;
-    __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!count_in(a.sync + units * kSyncStride, a.sync_base, units)) return; // (behind the units' counts)
     a.len_dev[4 * a.batch] = (a.len_dev[4 * a.batch] & 1) ^ 1;
 }
 

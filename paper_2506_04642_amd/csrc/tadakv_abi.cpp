@@ -36,6 +36,7 @@ struct kv_cache {
     size_t xhead_xo_rel = 0;               // start of the value-mean output slots relative to xhead_off
     int *len_dev = nullptr;                // device-resident lengths (kv_cache_lengths_to_device), [layer][dev_len_ints]
     std::vector<int> len_image;            // what was last sent there (the copy's source stays alive)
+    mutable uint64_t joined = 0;           // calls that joined their splits in the split kernel (counted atomically)
 };
 
 namespace {
@@ -996,16 +997,20 @@ static bool join_in_kernel(const DecodeArgs &a)
     return true;
 }
 
+static void join_there(const kv_cache *cache, DecodeArgs *a, void *counts)
+{
+    a->direct = 2;
+    a->sync = (unsigned long long *)counts;
+    a->sync_base = 0 - kSyncCalls * (__atomic_fetch_add(&cache->joined, 1, __ATOMIC_RELAXED) + 1);
+}
+
 // One split per unit, and the caller wants the output: the split kernel writes it.
 // A few splits, and the caller has counts for the workgroups: the split kernel joins them.
 static void write_direct(const kv_cache *cache, DecodeArgs *a, bool mfma, void *sync)
 {
     if (!a->out || a->xs || !(mfma || use_raw(cache, *a))) return;
     a->direct = a->n_splits == 1 && !a->uneven;
-    if (!a->direct && sync && join_in_kernel(*a)) {
-        a->direct = 2;
-        a->sync = (uint32_t *)sync;
-    }
+    if (!a->direct && sync && join_in_kernel(*a)) join_there(cache, a, sync);
 }
 
 // The split launch; *a keeps the plan, for the merge of the same call.
@@ -1225,7 +1230,7 @@ kv_status kv_join_counts_bytes(const kv_config *cfg, size_t *bytes)
     if (!bytes) return KV_E_NULL;
     kv_status st = check_config(cfg);
     if (st != KV_OK) return st;
-    *bytes = ((size_t)cfg->batch * cfg->n_kv_heads + 1) * kSyncStride * sizeof(uint32_t);
+    *bytes = ((size_t)cfg->batch * cfg->n_kv_heads + 1) * kSyncStride * sizeof(uint64_t);
     return KV_OK;
 }
 
@@ -1325,10 +1330,7 @@ kv_status kv_decode_step_dev_joined(const kv_cache *cache, int32_t layer, const 
     a.len_dev = cache->len_dev + (size_t)layer * dev_len_ints(c.batch);
     a.q = (const uint16_t *)q;
     a.out = out;
-    if (counts && join_in_kernel(a)) {
-        a.direct = 2;
-        a.sync = (uint32_t *)counts;
-    }
+    if (counts && join_in_kernel(a)) join_there(cache, &a, counts);
 
     AppendArgs ap{};
     ap.geom = cache->geom[layer];

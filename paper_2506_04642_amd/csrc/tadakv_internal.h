@@ -11,7 +11,8 @@ constexpr int kPartialStride = 132; // floats per (unit, q head, split): O[128],
 constexpr int kMaxSplits = 256;
 constexpr int kJoinSplits = 34;     // splits that one wavefront joins at once (join.h)
 constexpr int kJoinFew = 8;         // splits of which it joins several query heads at once
-constexpr int kSyncStride = 16;     // 32-bit words from one count of finished workgroups to the next
+constexpr int kSyncStride = 8;      // 64-bit words from one count of finished workgroups to the next
+constexpr uint64_t kSyncCalls = 1 << 20; // what a call may count (units, workgroups of a unit), with room to spare (count_in)
 constexpr int kMaxRaggedBatch = 256; // sequences whose lengths may differ from one another
 
 // Geometry of one layer's buffer; byte offsets, -1 where a field is absent.
@@ -158,7 +159,7 @@ struct DecodeArgs {
     // after the step's append, dev_len) instead; n_blocks and r only size the launch.  The merge makes
     // that state the current one.
     int *len_dev;
-    uint32_t *sync; // zero before the launch and after it
+    unsigned long long *sync, sync_base; // counts, zero after the launch; what this call counts down to (count_in)
     uint16_t nb_seq[kMaxRaggedBatch], r_seq[kMaxRaggedBatch]; // 1 KiB of the kernel arguments
 };
 
