@@ -11,25 +11,29 @@ LIB = os.path.join(HERE, "libtadakv.so")
 # packed-fp32 instruction forms are switched off for every device translation unit
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# (source, extra flags): the quantiser is compiled without fused multiply-add contraction so
-# that every binary32 operation rounds once, in the order written
+# matrix-instruction results go straight to ordinary vector registers; the direct-to-LDS fetches
+# are issued by hand and name M0 as clobbered, which the compiler remarks on at every use
+# (the assembly text is kept next to the object and read by verify_hand_loads after the compile)
+MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm", "-save-temps=obj"]
+# (source, extra flags, object folder below _build): the quantiser is compiled without fused multiply-add contraction so
+# that every binary32 operation rounds once, in the order written; the split kernel's widths compile side by side
 UNITS = [
-    ("tadakv_abi.cpp", ["-x", "hip"]),
-    ("quant_append.hip", ["-ffp-contract=off"]),
-    ("compressv.hip", ["-ffp-contract=off", "-save-temps=obj"]),
-    ("decode_valu.hip", []),
-    # matrix-instruction results go straight to ordinary vector registers; the direct-to-LDS fetches
-    # are issued by hand and name M0 as clobbered, which the compiler remarks on at every use
-    # (the assembly text is kept next to the object and read by verify_hand_loads after the compile)
-    ("decode_mfma.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm", "-save-temps=obj"]),
-    ("decode_raw.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
-    ("xhead_dense.hip", []),
-    ("stream_probe.hip", []),
+    ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=8"], "k8"),
+    ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=4"], "k4"),
+    ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=2"], "k2"),
+    ("tadakv_abi.cpp", ["-x", "hip"], ""),
+    ("quant_append.hip", ["-ffp-contract=off"], ""),
+    ("compressv.hip", ["-ffp-contract=off", "-save-temps=obj"], ""),
+    ("decode_valu.hip", [], ""),
+    ("decode_mfma_host.cpp", ["-x", "hip"], ""),
+    ("decode_raw.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"], ""),
+    ("xhead_dense.hip", [], ""),
+    ("stream_probe.hip", [], ""),
 ]
 
 
 def sources():
-    return [os.path.join(CSRC, s) for s, _ in UNITS] + [
+    return [os.path.join(CSRC, s) for s in dict.fromkeys(u[0] for u in UNITS)] + [
         os.path.join(CSRC, "tadakv_internal.h"),
         os.path.join(CSRC, "quant_wave.h"),
         os.path.join(CSRC, "join.h"),
@@ -44,11 +48,11 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
         if all(os.path.getmtime(LIB) >= os.path.getmtime(s) for s in sources()):
             return LIB
     objdir = os.path.join(HERE, "_build")
-    os.makedirs(objdir, exist_ok=True)
     objs = []
     procs = []
-    for src, extra in UNITS:
-        obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
+    for src, extra, sub in UNITS:
+        os.makedirs(os.path.join(objdir, sub), exist_ok=True)
+        obj = os.path.join(objdir, sub, os.path.splitext(src)[0] + ".o")
         cmd = ["hipcc"] + COMMON + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd))
@@ -67,13 +71,15 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
     _v = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(_v)  # (by path: this file also runs as a script)
 
-    for unit, kernel, glob in (("decode_mfma", "decode_split_mfma_kernel", True), ("compressv", "compressv_gemm_kernel", False)):
-        checked = _v.verify(os.path.join(objdir, unit + "-hip-amdgcn-amd-amdhsa-gfx950.s"), kernel, glob)
+    hand = [("decode_mfma", k, "decode_split_mfma_kernel", True) for k in ("k2", "k4", "k8")] + [("compressv", "", "compressv_gemm_kernel", False)]
+    for unit, sub, kernel, glob in hand:
+        here = os.path.join(objdir, sub)
+        checked = _v.verify(os.path.join(here, unit + "-hip-amdgcn-amd-amdhsa-gfx950.s"), kernel, glob)
         if verbose:
-            print("verify_hand_loads: %s: %d kernels, %d global requests, %d LDS reads" % ((unit,) + checked))
-        for f in os.listdir(objdir):
+            print("verify_hand_loads: %s: %d kernels, %d global requests, %d LDS reads" % ((os.path.join(sub, unit),) + checked))
+        for f in os.listdir(here):
             if f.startswith(unit + "-") or f.startswith(unit + ".hip-"):
-                os.remove(os.path.join(objdir, f))
+                os.remove(os.path.join(here, f))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
     return LIB

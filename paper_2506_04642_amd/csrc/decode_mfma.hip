@@ -32,9 +32,14 @@
 //                      16-channel tile (values).
 //   key-side producer  lane (row, vq, qa): head 4*hg + row, channels 32*vq + 16*ph + 4*qa + {0..3}.
 //   matrix operands    lane (row, n): operand row / column n, 16 consecutive k-slots of group `row`.
+// This file is compiled once per width of the keys (TADA_KEY_BITS: 2, 4, 8), side by side; decode_mfma_host.cpp picks among the three.
 #include "join.h"
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
+
+#define TADA_NAMED_2(name, w) name##w
+#define TADA_NAMED_1(name, w) TADA_NAMED_2(name, w)
+#define TADA_NAMED(name) TADA_NAMED_1(name, TADA_KEY_BITS)
 
 namespace tadakv {
 namespace {
@@ -285,7 +290,7 @@ template <> struct CodeOps<4> { // two words = one tile line of 16 codes
     }
 };
 // Phase clocks (a build with -DTADA_PHASE_CLOCK only; the library proper carries none of it): every
-// wave sums the cycles between the marks of the main loop; kv_debug_phase_clocks hands the sums out.
+// wave sums the cycles between the marks of the main loop; kv_debug_phase_clocks_2, _4 and _8 hand the sums out.
 #ifdef TADA_PHASE_CLOCK
 __device__ unsigned long long tada_phase_clk[16];
 #define PHASE_INIT unsigned long long pclk_[14] = {}; unsigned long long plast_ = __builtin_readcyclecounter(); int piter_ = 0;
@@ -1339,11 +1344,8 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> int
     return n;
 }
 
-// Events that the calling thread's next split launch records its own begin and end into (set_split_timing_events)
-thread_local hipEvent_t t_ev_begin = nullptr, t_ev_end = nullptr;
-
 // XH == 2 (both cross-head mean terms inside the kernel): a workgroup per (sequence, split) and NW kv heads.
-template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hipError_t launch_inst(const DecodeArgs &a, hipStream_t s)
+template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hipError_t launch_inst(const DecodeArgs &a, hipStream_t s, SplitTiming &ev)
 {
     if (!RecLayout<B, G, GC, MEAN>::matches(a.geom)) return hipErrorInvalidValue;
     if (XH == 2 && (a.n_kv_heads < NW || a.n_kv_heads % NW != 0)) return hipErrorInvalidValue;
@@ -1354,11 +1356,10 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hip
     dim3 grid(XH == 2 ? a.n_splits * (a.n_kv_heads / NW) : a.n_splits, XH == 2 ? a.batch : a.batch * a.n_kv_heads);
     if (a.uneven) grid = dim3(a.uneven_total, a.n_kv_heads);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
-    if (t_ev_begin && t_ev_end) {
+    if (ev.begin && ev.end) {
         // the dispatch itself stamps the events: the kernel's execution, without the gaps before and after it
-        hipExtLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG>), grid, dim3(64 * NW), 0, s, t_ev_begin,
-                              t_ev_end, 0, a);
-        t_ev_begin = t_ev_end = nullptr;
+        hipExtLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG>), grid, dim3(64 * NW), 0, s, ev.begin, ev.end, 0, a);
+        ev = SplitTiming{};
     } else {
         hipLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG>), grid, dim3(64 * NW), 0, s, a);
     }
@@ -1388,8 +1389,9 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> int
 // what to do with the instance selected by the layer's format
 struct DoLaunch {
     hipStream_t s;
+    SplitTiming *ev;
     hipError_t result = hipErrorInvalidValue;
-    template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &a) { result = launch_inst<B, G, GC, MEAN, NW, NHG, XH, PG>(a, s); }
+    template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &a) { result = launch_inst<B, G, GC, MEAN, NW, NHG, XH, PG>(a, s, *ev); }
 };
 struct DoPlan {
     int result = 1;
@@ -1403,14 +1405,6 @@ struct DoMatch {
     bool result = false;
     template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &a) { result = RecLayout<B, G, GC, MEAN>::matches(a.geom); }
 };
-
-// Does the layer get the fused cross-head form (both mean terms inside the split kernel)?  It takes a
-// wave per kv head, a multiple of 4 kv heads.
-bool xhead_fused_fmt(const DecodeArgs &a)
-{
-    const LayerGeom &g = a.geom;
-    return g.mean_mode == 1 && a.n_kv_heads % 4 == 0;
-}
 
 template <int B, int G, int GC, bool PG, class F> void pick_mean_heads_pg(const DecodeArgs &a, F &f)
 {
@@ -1458,44 +1452,30 @@ template <int B, int G, int GC, class F> void pick_mean_heads(const DecodeArgs &
     else pick_mean_heads_pg<B, G, GC, false>(a, f);
 }
 
+// The instance for the layer's format, among those of this unit's key width.
 template <class F> void pick(const DecodeArgs &a, F &f)
 {
-    const int bits = a.geom.k_bits;
+    constexpr int W = TADA_KEY_BITS;
+    if (a.geom.k_bits != W) return;
     if (xhead_fused_fmt(a)) {
-        if (a.geom.G == 32) {
-            if (bits == 2) pick_fused<2, 32, 32>(a, f);
-            else if (bits == 4) pick_fused<4, 32, 32>(a, f);
-            else pick_fused<8, 32, 32>(a, f);
-        } else if (a.geom.G == 64) {
-            if (bits == 2) pick_fused<2, 64, 64>(a, f);
-            else if (bits == 4) pick_fused<4, 64, 64>(a, f);
-            else pick_fused<8, 64, 64>(a, f);
-        } else {
-            if (bits == 2) pick_fused<2, 128, 128>(a, f);
-            else if (bits == 4) pick_fused<4, 128, 128>(a, f);
-            else pick_fused<8, 128, 128>(a, f);
-        }
+        if (a.geom.G == 32) pick_fused<W, 32, 32>(a, f);
+        else if (a.geom.G == 64) pick_fused<W, 64, 64>(a, f);
+        else pick_fused<W, 128, 128>(a, f);
         return;
     }
-    if (a.geom.k_bits != a.geom.v_bits) {
+    if (a.geom.v_bits != W) {
         // keys and values of different widths: groups of 32 tokens / 32 channels
-        const int kb = a.geom.k_bits, vb = a.geom.v_bits;
         // (dense placement only: the paged instances of six more width pairs are not worth their compile time)
-        if (kb == 2 && vb == 4) pick_mean_heads_pg<2 | 4 << 4, 32, 32, false>(a, f);
-        else if (kb == 2 && vb == 8) pick_mean_heads_pg<2 | 8 << 4, 32, 32, false>(a, f);
-        else if (kb == 4 && vb == 2) pick_mean_heads_pg<4 | 2 << 4, 32, 32, false>(a, f);
-        else if (kb == 4 && vb == 8) pick_mean_heads_pg<4 | 8 << 4, 32, 32, false>(a, f);
-        else if (kb == 8 && vb == 2) pick_mean_heads_pg<8 | 2 << 4, 32, 32, false>(a, f);
-        else pick_mean_heads_pg<8 | 4 << 4, 32, 32, false>(a, f);
+        constexpr int V0 = W == 2 ? 4 : 2, V1 = W == 8 ? 4 : 8;
+        if (a.geom.v_bits == V0) pick_mean_heads_pg<W | V0 << 4, 32, 32, false>(a, f);
+        else pick_mean_heads_pg<W | V1 << 4, 32, 32, false>(a, f);
         return;
     }
     // every pair (tokens per key group, channels per value group) of 32, 64, 128
-#define TADAKV_PICK(GV, GCV)                                      \
-    if (a.geom.G == GV && a.geom.Gc == GCV) {                     \
-        if (bits == 2) pick_mean_heads<2, GV, GCV>(a, f);         \
-        else if (bits == 4) pick_mean_heads<4, GV, GCV>(a, f);    \
-        else pick_mean_heads<8, GV, GCV>(a, f);                   \
-        return;                                                   \
+#define TADAKV_PICK(GV, GCV)                              \
+    if (a.geom.G == GV && a.geom.Gc == GCV) {             \
+        pick_mean_heads<W, GV, GCV>(a, f);                \
+        return;                                           \
     }
     TADAKV_PICK(32, 32)
     TADAKV_PICK(64, 64)
@@ -1509,69 +1489,43 @@ template <class F> void pick(const DecodeArgs &a, F &f)
 #undef TADAKV_PICK
 }
 
-} // namespace
-
-bool xhead_fused(const DecodeArgs &a) { return decode_mfma_supported(a) && xhead_fused_fmt(a); }
-
-bool decode_mfma_supported(const DecodeArgs &a)
+bool matches(const DecodeArgs &a)
 {
-    const LayerGeom &g = a.geom;
-    if (!(g.k_bits == 2 || g.k_bits == 4 || g.k_bits == 8) || !(g.v_bits == 2 || g.v_bits == 4 || g.v_bits == 8)) return false;
-    if (g.k_bits != g.v_bits && !(g.G == 32 && g.Gc == 32 && g.mean_mode != 1 && g.table == nullptr)) return false; // different widths: one format, dense
-    const bool sizes = (g.G == 32 || g.G == 64 || g.G == 128) && (g.Gc == 32 || g.Gc == 64 || g.Gc == 128);
-    if (!sizes) return false;
-    if (g.G != g.Gc && g.mean_mode == 1) return false; // the cross-head forms take equal sizes only
-    if (a.g > 8) return false;
-    if (g.mean_mode == 1 && a.n_q_heads > 64) return false; // the dense mean terms keep all query heads of a sequence in LDS
-    if (a.batch * a.n_kv_heads > 65535) return false;
-    // the kernels address record fields with compile-time offsets
     DoMatch m;
     pick(a, m);
     return m.result;
 }
-
-int decode_mfma_splits(const DecodeArgs &a)
+int splits(const DecodeArgs &a)
 {
-    if (!decode_mfma_supported(a)) return 1;
     DoPlan p;
     pick(a, p);
     return p.result;
 }
-
-int decode_mfma_slots(const DecodeArgs &a)
+int slots(const DecodeArgs &a)
 {
-    if (!decode_mfma_supported(a)) return 0;
     DoSlots p;
     pick(a, p);
     return p.result;
 }
-
-void set_split_timing_events(hipEvent_t begin, hipEvent_t end)
+hipError_t launch(const DecodeArgs &a, hipStream_t s, SplitTiming &ev)
 {
-    t_ev_begin = begin;
-    t_ev_end = end;
-}
-
-hipError_t launch_decode_split_mfma(const DecodeArgs &a, hipStream_t s)
-{
-    if (!decode_mfma_supported(a)) return hipErrorInvalidValue;
-    if (a.geom.mean_mode == 1 && !xhead_fused_fmt(a)) {
-        if (!a.xs || !a.xp || !a.xmc) return hipErrorInvalidValue;
-        const hipError_t e = launch_xhead_scores(a, s);
-        if (e != hipSuccess) return e;
-    }
     DoLaunch l;
     l.s = s;
+    l.ev = &ev;
     pick(a, l);
     return l.result;
 }
+
+} // namespace
+
+MfmaWidth TADA_NAMED(mfma_width_)() { return MfmaWidth{matches, splits, slots, launch}; }
 
 } // namespace tadakv
 
 #ifdef TADA_PHASE_CLOCK
 // out[0..13]: cycles summed over all waves per phase; out[14]: loop iterations; out[15]: waves.
 // reset != 0 clears the sums afterwards.
-extern "C" int kv_debug_phase_clocks(unsigned long long *out, int reset)
+extern "C" int TADA_NAMED(kv_debug_phase_clocks_)(unsigned long long *out, int reset)
 {
     if (hipDeviceSynchronize() != hipSuccess) return -1;
     if (hipMemcpyFromSymbol(out, HIP_SYMBOL(tadakv::tada_phase_clk), 16 * sizeof(unsigned long long)) != hipSuccess) return -1;

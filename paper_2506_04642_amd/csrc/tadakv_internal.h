@@ -304,6 +304,18 @@ hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s);
 // the calling thread's next matrix-core split launch records its begin and end into these (one-shot; null cancels)
 void set_split_timing_events(hipEvent_t begin, hipEvent_t end);
 bool decode_mfma_supported(const DecodeArgs &a);
+// the matrix-core split kernel for keys of one width (decode_mfma.hip)
+struct SplitTiming { hipEvent_t begin, end; };
+struct MfmaWidth {
+    bool (*matches)(const DecodeArgs &a); // is the layer's record laid out as its instance takes it to be
+    int (*splits)(const DecodeArgs &a);
+    int (*slots)(const DecodeArgs &a);
+    hipError_t (*launch)(const DecodeArgs &a, hipStream_t s, SplitTiming &ev); // ev: recorded into, then cleared
+};
+MfmaWidth mfma_width_2(), mfma_width_4(), mfma_width_8();
+// Does the layer get the fused cross-head form (both mean terms inside the split kernel)?  It takes a
+// wave per kv head, a multiple of 4 kv heads.
+inline bool xhead_fused_fmt(const DecodeArgs &a) { return a.geom.mean_mode == 1 && a.n_kv_heads % 4 == 0; }
 bool xhead_fused(const DecodeArgs &a); // cross-head mean: both mean terms inside the matrix-core split kernel
 int decode_mfma_splits(const DecodeArgs &a); // preferred split count of the matrix-core kernel
 int decode_mfma_slots(const DecodeArgs &a);  // workgroups of it the device holds at once
