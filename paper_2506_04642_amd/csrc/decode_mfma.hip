@@ -339,10 +339,17 @@ template <> struct CodeOps<8> { // four words = one tile line; split into nibble
 //            progress counters instead of barriers.
 // PG: paged placement (block slots through a table); the dense instances carry none of its state.
 // GS: tokens per block of the cache (32, 64, or 128 read as two halves of 64).
-template <int B, int GS, int GC, bool MEAN, int NW, int NHG, int XH, bool PG>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2 && NHG == 1 && !XH) ? (PG ? 3 : 4) : (B == 2 && NHG == 2 && GS == 128 && GC == 128 && !MEAN && !XH) ? 4 : 1, 8))) void decode_split_mfma_kernel(DecodeArgs a)
+// JOIN: the kernel joins the splits itself (join.h).  Other launches do not carry the join, which cost the two-head instances two
+// registers and every longer launch up to 1.3 %, with the same instance for both -> now (us a call): one sequence of
+// 65543 tokens 25.96 -> 25.72, of 131079 with 64 query heads at 2 bits 34.73 -> 34.36, 2 x 75149 ragged, one head, 14.66 -> 14.58.
+// (Two of the joining instances, at 2 bits with two head groups, take 142 to 146 registers if they are left to, and a compute unit
+// holds three of their workgroups then; bound to four, 122 to 125 and no spills: 64 sequences of 1000 tokens, 4 kv heads, blocks of
+// 64 24.40 -> 20.87 us, of 128 26.08 -> 25.77.)
+template <int B, int GS, int GC, bool MEAN, int NW, int NHG, int XH, bool PG, bool JOIN>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2 && NHG == 1 && !XH) ? (PG ? 3 : 4) : (JOIN && B == 2 && NHG == 2 && GS >= 64 && GC == 128 && !MEAN) ? 4 : 1, 8))) void decode_split_mfma_kernel(DecodeArgs a)
 {
     static_assert(!(XH && MEAN), "cross-head layers store no per-record mean");
+    static_assert(!(XH && JOIN), "a wave of the cross-head forms would have four heads to join");
     constexpr bool XF = XH == 2; // both mean terms in this kernel, a wave per kv head
     constexpr int CW = XF ? 1 : NW;          // waves that share a unit's chunks
     constexpr int XSL = 3;                   // copies of every exchange buffer of the fused cross-head form
@@ -1286,7 +1293,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
         constexpr int MCT = XF ? 8 : 8 / NW;
         const int ct0 = XF ? 0 : wave * MCT;
         const float *all = (const float *)lds_all + (XF ? wave * WAVE_DW : 0);
-        const bool joined = XH == 0 && a.direct == 2;
 #pragma unroll
         for (int hg = 0; hg < NHG; hg++) {
             const int head = 4 * hg + row;
@@ -1307,7 +1313,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 #pragma unroll
                 for (int ct = 0; ct < MCT; ct++) o[ct] += all[w * WAVE_DW + (hg * 10 + 2 + ct0 + ct) * 64 + lane] * wt;
             }
-            if (XH != 1 && __builtin_expect(a.direct == 1, 0)) {
+            if (XH != 1 && !JOIN && __builtin_expect(a.direct, 0)) {
 #pragma unroll
                 for (int ct = 0; ct < MCT; ct++) put_output(a, u, head, 16 * (ct0 + ct) + n, o[ct], lsum, M);
                 continue;
@@ -1315,14 +1321,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
             const long long at = XH == 0 ? (long long)row0 + head * ns_ + sp : ((long long)u * g + head) * ns_ + sp;
             float *dst = a.ws + at * kPartialStride;
 #pragma unroll
-            for (int ct = 0; ct < MCT; ct++) put_partial(dst + 16 * (ct0 + ct) + n, o[ct], joined);
+            for (int ct = 0; ct < MCT; ct++) put_partial(dst + 16 * (ct0 + ct) + n, o[ct], JOIN);
             if (ct0 == 0 && n == 0) {
-                put_partial(dst + kHeadDim, M, joined);
-                put_partial(dst + kHeadDim + 1, lsum, joined);
+                put_partial(dst + kHeadDim, M, JOIN);
+                put_partial(dst + kHeadDim + 1, lsum, JOIN);
             }
         }
-        if constexpr (XH == 0) {
-            if (!joined || !last_of_unit<NW>(a, u, ns_, lds_all)) return;
+        if constexpr (JOIN) {
+            if (!last_of_unit<NW>(a, u, ns_, lds_all)) return;
             join_heads<NHG, NHG == 1>(a, u, wave * NHG, row0, ns_);
             step_is_done(a);
         }
@@ -1334,7 +1340,7 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> int
 {
     static const int n = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG>,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, false>,
                                                          64 * NW, 0) != hipSuccess)
             return 0;
         if (hipGetDevice(&dev) != hipSuccess) return 0;
@@ -1345,25 +1351,33 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> int
 }
 
 // XH == 2 (both cross-head mean terms inside the kernel): a workgroup per (sequence, split) and NW kv heads.
+template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG, bool JOIN> hipError_t enqueue(const DecodeArgs &a, hipStream_t s, SplitTiming &ev)
+{
+    dim3 grid(XH == 2 ? a.n_splits * (a.n_kv_heads / NW) : a.n_splits, XH == 2 ? a.batch : a.batch * a.n_kv_heads);
+    if (a.uneven) grid = dim3(a.uneven_total, a.n_kv_heads);
+    (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
+    if (ev.begin && ev.end) {
+        // the dispatch itself stamps the events: the kernel's execution, without the gaps before and after it
+        hipExtLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, JOIN>), grid, dim3(64 * NW), 0, s, ev.begin, ev.end, 0, a);
+        ev = SplitTiming{};
+    } else {
+        hipLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, JOIN>), grid, dim3(64 * NW), 0, s, a);
+    }
+    return note_launch(hipGetLastError());
+}
 template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hipError_t launch_inst(const DecodeArgs &a, hipStream_t s, SplitTiming &ev)
 {
     if (!RecLayout<B, G, GC, MEAN>::matches(a.geom)) return hipErrorInvalidValue;
     if (XH == 2 && (a.n_kv_heads < NW || a.n_kv_heads % NW != 0)) return hipErrorInvalidValue;
     if (a.uneven && XH != 0) return hipErrorInvalidValue;
     if (a.direct == 1 && (XH == 1 || a.uneven || a.n_splits != 1 || a.len_dev)) return hipErrorInvalidValue;
-    if (a.direct == 2 && (XH != 0 || !a.sync || (a.uneven ? a.uneven_most : a.n_splits) > (NHG == 1 ? kJoinSplits : kJoinFew))) return hipErrorInvalidValue;
     static_assert(XH != 0 || NW == kSplitWaves, "the planner of uneven splits counts on it");
-    dim3 grid(XH == 2 ? a.n_splits * (a.n_kv_heads / NW) : a.n_splits, XH == 2 ? a.batch : a.batch * a.n_kv_heads);
-    if (a.uneven) grid = dim3(a.uneven_total, a.n_kv_heads);
-    (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
-    if (ev.begin && ev.end) {
-        // the dispatch itself stamps the events: the kernel's execution, without the gaps before and after it
-        hipExtLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG>), grid, dim3(64 * NW), 0, s, ev.begin, ev.end, 0, a);
-        ev = SplitTiming{};
-    } else {
-        hipLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG>), grid, dim3(64 * NW), 0, s, a);
+    if (a.direct != 2) return enqueue<B, G, GC, MEAN, NW, NHG, XH, PG, false>(a, s, ev);
+    if constexpr (XH == 0) {
+        if (a.sync && (a.uneven ? a.uneven_most : a.n_splits) <= (NHG == 1 ? kJoinSplits : kJoinFew))
+            return enqueue<B, G, GC, MEAN, NW, NHG, XH, PG, true>(a, s, ev);
     }
-    return note_launch(hipGetLastError());
+    return hipErrorInvalidValue;
 }
 
 // Split count that puts every workgroup of the launch on the device at once (one "round"):

@@ -61,12 +61,12 @@ template <int DT> __device__ __forceinline__ float widen_hi(uint32_t w)
     return __half2float(__ushort_as_half((uint16_t)(w >> 16)));
 }
 
-template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attribute__((amdgpu_waves_per_eu(3, 8))) void decode_split_raw_kernel(DecodeArgs a)
+// JOIN: as in the kernel of the packed layers (decode_mfma.hip).  One sequence of 12016 tokens, whose splits are too many for it: 16.85 -> 16.73 us.
+template <int DT, bool PG, bool JOIN> __global__ __launch_bounds__(64 * kRawWaves) __attribute__((amdgpu_waves_per_eu(3, 8))) void decode_split_raw_kernel(DecodeArgs a)
 {
     constexpr int NW = kRawWaves;
     constexpr int ST = 33; // floats per row of the state exchange (32 lanes of live columns, padded)
     __shared__ float state[NW][34 * ST];
-    __shared__ uint32_t done;
     decode_args_here(a);
     const LayerGeom &gm = a.geom;
     const int lane = threadIdx.x & 63, row = lane >> 4, n = lane & 15;
@@ -247,7 +247,6 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
         mine[33 * ST] = l;
     }
     __syncthreads();
-    const bool joined = a.direct == 2;
     for (int o = threadIdx.x; o < g * kHeadDim; o += 64 * NW) {
         const int head = o >> 7, c = o & 127;
         const int at = (4 * (c & 7) + ((c >> 3) & 3)) * ST + (c >> 5) * 8 + head;
@@ -262,27 +261,30 @@ template <int DT, bool PG> __global__ __launch_bounds__(64 * kRawWaves) __attrib
             num += state[w][at] * wt;
             den += state[w][33 * ST + head] * wt;
         }
-        if (a.direct == 1) {
+        if (!JOIN && a.direct) {
             put_output(a, u, head, c, num, den, Mx);
             continue;
         }
         float *dst = a.ws + ((long long)row0 + head * ns + sp) * kPartialStride;
-        put_partial(dst + c, num, joined);
+        put_partial(dst + c, num, JOIN);
         if (c == 0) {
-            put_partial(dst + kHeadDim, Mx, joined);
-            put_partial(dst + kHeadDim + 1, den, joined);
+            put_partial(dst + kHeadDim, Mx, JOIN);
+            put_partial(dst + kHeadDim + 1, den, JOIN);
         }
     }
-    if (!joined || !last_of_unit<NW>(a, u, ns, &done)) return;
-    if (g <= NW) join_heads<1, false>(a, u, wave, row0, ns);
-    else join_heads<2, false>(a, u, 2 * wave, row0, ns);
+    if constexpr (JOIN) {
+        __shared__ uint32_t done;
+        if (!last_of_unit<NW>(a, u, ns, &done)) return;
+        if (g <= NW) join_heads<1, false>(a, u, wave, row0, ns);
+        else join_heads<2, false>(a, u, 2 * wave, row0, ns);
+    }
 }
 
 template <int DT, bool PG> int resident_blocks()
 {
     static const int n = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_raw_kernel<DT, PG>, 64 * kRawWaves, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_raw_kernel<DT, PG, false>, 64 * kRawWaves, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -327,14 +329,12 @@ hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s)
     if (a.direct == 2 && (!a.sync || (a.uneven ? a.uneven_most : a.n_splits) > kJoinFew)) return hipErrorInvalidValue;
     const dim3 grid = a.uneven ? dim3(a.uneven_total, a.n_kv_heads) : dim3(a.n_splits, a.batch * a.n_kv_heads), block(64 * kRawWaves);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
-    const bool pg = a.geom.table != nullptr;
-    if (a.geom.dtype == 1) {
-        if (pg) hipLaunchKernelGGL((decode_split_raw_kernel<1, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((decode_split_raw_kernel<1, false>), grid, block, 0, s, a);
-    } else {
-        if (pg) hipLaunchKernelGGL((decode_split_raw_kernel<0, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((decode_split_raw_kernel<0, false>), grid, block, 0, s, a);
-    }
+    const bool pg = a.geom.table != nullptr, bf16 = a.geom.dtype == 1;
+    auto go = [&](auto plain, auto joined) { hipLaunchKernelGGL(a.direct == 2 ? joined : plain, grid, block, 0, s, a); };
+    if (bf16 && pg) go(decode_split_raw_kernel<1, true, false>, decode_split_raw_kernel<1, true, true>);
+    else if (bf16) go(decode_split_raw_kernel<1, false, false>, decode_split_raw_kernel<1, false, true>);
+    else if (pg) go(decode_split_raw_kernel<0, true, false>, decode_split_raw_kernel<0, true, true>);
+    else go(decode_split_raw_kernel<0, false, false>, decode_split_raw_kernel<0, false, true>);
     return note_launch(hipGetLastError());
 }
 
