@@ -39,6 +39,26 @@ def test_split_counts(kv, oracle, bits, G, Hkv, g, B):
         assert float(np.max(np.abs(got - want))) <= TOL, ns
 
 
+@pytest.mark.parametrize("bits,Hkv,g", [(4, 1, 4), (2, 2, 8), (8, 3, 2)])
+def test_split_counts_with_the_means_apart(kv, oracle, bits, Hkv, g):
+    """Head counts that are no multiple of four: the merge adds the value mean plane's share, by forms that change at 8 and 36 splits."""
+    B, G, T = 2, 32, 40 * 64 + 7
+    gpu, orc = make_pair(kv, oracle, B=B, Hq=Hkv * g, Hkv=Hkv, T_max=41 * 64, G=G, Gc=G, dtype=BF16, mode=CROSS, k_bits=(bits,))
+    k, v = synth.make_kv(4, B, T, Hkv, 128, BF16)
+    gpu.append(0, to_dev(k, BF16), to_dev(v, BF16))
+    orc.append(0, k, v)
+    q = synth.make_q(5, B, Hkv * g, 128, BF16)
+    want = orc.attend(0, q)
+    out = torch.empty((B, Hkv * g, 128), dtype=torch.float32, device="cuda:0")
+    qd = to_dev(q, BF16)
+    for ns in (1, 2, 7, 8, 9, 27, 41):
+        kv.kv_set_decode_splits(gpu.handle, ns)
+        # (a forced count may want more than the automatic ones)
+        ws = torch.full((kv.kv_decode_workspace_need(gpu.handle, 0),), 0xFF, dtype=torch.uint8, device="cuda:0")
+        kv.kv_decode_attn(gpu.handle, 0, qd.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel(), gpu._stream())
+        assert float(np.max(np.abs(out.cpu().numpy().astype(np.float64) - want))) <= TOL, ns
+
+
 @pytest.mark.parametrize("G,T", [(32, 12224), (32, 12352), (128, 12416)])
 def test_either_side_of_the_long_launches(kv, G, T):
     """16 sequences, 8 kv heads, 4 bits: up to 24576 chunks of 64 tokens pairs of four waves, beyond that eight."""
