@@ -1443,6 +1443,9 @@ template <int B, int G, int GC, bool PG, class F> void pick_mean_heads_pg(const 
 // at the start and the end above all, so the line is drawn at the chunks a wave takes, 12: eight waves against
 // four, us per layer of 8 kv heads x 4: 16 x 32781 tokens (32 chunks) 182 / 193, 12 x 40000 (30) 165 / 175, 24 x 12000 (18) 106 / 112, 3 x 100000, groups
 // of 128 (18) 100 / 103; 5 x 30000 (9) 55.9 / 55.3, 16 x 8192 (8) 52.4 / 49.3, 4 x 16461, groups of 128 (4) 33.3 / 31.7, 2 x 1500 (1) 17.6 / 14.3.
+// Sequences of different lengths count as the longest, as ever.  By their own chunks those between the two counts would have four waves,
+// which is not the faster form for all of them: up to 16000, 16 sequences 81.8 / 73.5, up to 36000, 8, groups of 128 80.6 / 73.5, but up
+// to 30000, 12, groups of 64 96.3 / 102.6, up to 20000, 12 71.1 / 73.4.
 template <int B, int G, int GC, bool PG, class F> void pick_fused_pg(const DecodeArgs &a, F &f)
 {
     if constexpr (B == 4) {
