@@ -384,13 +384,17 @@ class KVCache:
         self.layers = [alloc(kv_cache_bytes(cfg, l), dtype=torch.uint8, device=self.device)
                        for l in range(cfg.n_layers)]
         self.ws_bytes = kv_workspace_bytes(cfg)
-        self.workspace = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
         # counts of finished workgroups, zero between calls; used by one call at a time, as the workspace is.  A cache
         # made while a stream is capturing has none, and its calls are the plain ones: the zeros would be
         # recorded, and a call before the first replay would find what the memory held before.
+        # (Behind the workspace, in one allocation with it: a small one of their own is a segment more to ask the device for.)
         self._counts, self._counts_ptr = None, 0
-        if not torch.cuda.is_current_stream_capturing():
-            self._counts = torch.zeros(kv_join_counts_bytes(cfg), dtype=torch.uint8, device=self.device)
+        if torch.cuda.is_current_stream_capturing():
+            self.workspace = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
+        else:
+            at = (self.ws_bytes + 255) // 256 * 256
+            both = torch.empty(at + kv_join_counts_bytes(cfg), dtype=torch.uint8, device=self.device)
+            self.workspace, self._counts = both[:self.ws_bytes], both[at:].zero_()
             self._counts_ptr = self._counts.data_ptr()
             if not zero:
                 # the first call may be on another stream than these zeros (with zero=True the layers have to be waited for as well)
