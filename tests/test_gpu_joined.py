@@ -129,13 +129,27 @@ def test_recorded_step_makes_its_lengths_current(kv, oracle):
 
 @pytest.mark.gpu
 def test_counts_are_zero_for_every_stream(kv):
-    """A new cache's counts are zeroed on the stream that makes it; the first call may be on another one that does not wait."""
-    cfg = kv.make_config(1, 2, 4, 1, 128, 256, 32, 32, 32, BF16, CHAN, [4], [4])
+    """A new cache's counts are zeroed on the stream that makes it; the first call may be on another one that does not wait.
+    (With zero=True the layers' own zeros have to be waited for in any case.)"""
+    cfg = kv.make_config(1, 2, 4, 1, 128, 1024, 32, 32, 32, BF16, CHAN, [4], [4])
+    k, v = synth.make_kv_torch(1, 2, 900, 1, 128, BF16, "cuda:0")
+    q = synth.make_q_torch(2, 2, 4, 128, BF16, "cuda:0")
+    got, want = (torch.full((2, 4, 128), float("nan"), dtype=torch.float32, device="cuda:0") for _ in range(2))
+    side = torch.cuda.Stream()
     x = torch.ones((4096, 4096), device="cuda:0")
+    torch.cuda.synchronize()
     for _ in range(20):
         x = torch.mm(x, x)
     gpu = kv.KVCache(cfg, zero=False)
     assert torch.cuda.current_stream().query()
+    for _ in range(20):
+        x = torch.mm(x, x)
+    with torch.cuda.stream(side):  # (does not wait for the products)
+        gpu.append(0, k, v)
+        gpu.attend(0, q, got)
+        kv.kv_decode_attn(gpu.handle, 0, q.data_ptr(), want.data_ptr(), gpu.workspace.data_ptr(), gpu.ws_bytes, gpu._stream())
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
     assert not bool(gpu._counts.any())
 
 
