@@ -291,7 +291,9 @@ kv_status kv_decode_attn(const kv_cache *cache, int32_t layer, const void *q, fl
 
 /* The same in one launch: with a few splits per (sequence, kv head) the workgroup that is the last of them to
  * finish joins their partial results, where kv_decode_attn launches a second kernel for that.  Same results bit for
- * bit; with more splits, and on the vector-ALU kernels, these calls enqueue what the plain ones do.
+ * bit.  These calls enqueue what the plain ones do with more splits than 34 (16-bit layers, and more than four query heads per
+ * kv head: 8), under the mean over the heads, on the vector-ALU kernels, and where splits by length leave a sequence
+ * without tokens no workgroup that would write its zeros.
  *   counts : device, kv_join_counts_bytes, 64-byte aligned, zeroed by the caller once before its first use (in stream
  *            order); every call leaves it zero again.  Like the workspace it belongs to one call at a time:
  *            calls that may overlap need counts of their own.  Calls of a cache that overlap all the same spoil each

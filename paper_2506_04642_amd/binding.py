@@ -370,7 +370,11 @@ def kv_stream_read_probe(buf_ptr: int, nbytes: int, sink_ptr: int = 0, stream: i
 
 class KVCache:
     """Owns the device buffers (torch uint8 tensors) of a cache and forwards calls to the C ABI
-    on torch's current HIP stream.  No arithmetic happens here."""
+    on torch's current HIP stream.  No arithmetic happens here.
+
+    With zero=True the buffers are zeroed on the stream that is current when the cache is made, and another stream has to wait
+    for that one before it uses the cache; with zero=False (contents undefined) it need not.  Calls that may overlap want
+    caches, or workspaces and counts, of their own."""
 
     def __init__(self, cfg: kv_config, device="cuda:0", zero: bool = True):
         import torch

@@ -220,6 +220,8 @@ bool use_raw(const kv_cache *k, const DecodeArgs &a) { return k->decode_path == 
 // more than 1.03 in 527 and up to 2.0; under this rule 434 are, 0.914 over all, more than 1.03 in 8, at most 1.11.
 // (24 sequences up to 8011 tokens, groups of 64, 8 bits 63 -> 55 us, 4 bits left alone: 35.6 against 37.1; one of 8011 among
 // 23 of some 200, 4 bits: 22.7 -> 17.5; 64 sequences of about 2000, 4 bits: left alone, 37.7 against 45.3.)
+// (These, and raw_token_splits', are with the splits merged by a second launch, as many of the launches still are; the lines have
+// not been drawn again for those that join them inside.)
 // Never more partial results than the workspace of the configuration holds (worst_splits).
 // `slots`: workgroups the device holds; `chunk`: tokens a wavefront takes at a time; `tails`: the raw tokens are
 // chunks like the others.
@@ -327,18 +329,15 @@ int raw_token_splits(const kv_config &c, const DecodeArgs &a, int slots, int chu
     return own > 1 && own > dealt + hidden ? 0 : nr;
 }
 
-// A launch so short that one workgroup's waves take a unit's chunks in one round (of raw rows: two): one split then,
-// whose kernel writes the output (write_direct), instead of a merge launch behind more of them.
-// Measured (attend, 8 kv heads, us): 64 tokens at 4 bits 7.8 -> 5.0 (the merge alone); 130 and 269 tokens 7.4 -> 7.6 and
-// 7.7 -> 7.8 on the GPU, but one enqueue (3 us of host time) less; a second round is too much, 525 tokens 7.9 -> 9.7.
-// More than one tile of raw tokens behind the chunk, too: 28 sequences up to 192 + 35 tokens 10.5 -> 11.0.
-// 16-bit layer, 130 tokens: 9.4 -> 6.8.  Mean over the heads (a wave has its head's chunks to itself), 130 tokens:
-// 15.6 -> 17.6, so there only what is one split anyway.
+// A 16-bit layer so short that one workgroup's waves take a unit's rows in two rounds: one split then, whose kernel writes the
+// output (write_direct).  Of 130 tokens, us a call: two splits and a merge launch 9.4, one 6.8.  (The line was drawn
+// against that second launch, and calls without counts still make it; joined inside the launch, two splits are the shorter: 130 tokens
+// 6.3 against 7.1 on the GPU, 4 x 250 6.8 against 7.3.)  Packed layers need no such rule: what one workgroup's waves take in one
+// round is one split by decode_mfma_splits, with one more for the raw tokens (8 kv heads, 130 and 269 tokens, joined, 6.0 and 6.3 us
+// against 6.3 and 7.3 in one split; but 28 sequences of 227, 7.8 against 6.9).
 bool one_split_is_enough(const kv_cache *k, const DecodeArgs &a)
 {
-    const long long tokens = (long long)a.n_blocks * k->cfg.group_tokens;
-    if (k->decode_path != 1 && decode_mfma_supported(a)) return k->cfg.mean_mode != KV_MEAN_CROSS_HEAD && tokens <= 64 * kSplitWaves && a.r <= 32;
-    return use_raw(k, a) && tokens + a.r <= 2 * 32 * kSplitWaves;
+    return use_raw(k, a) && (long long)a.n_blocks * k->cfg.group_tokens + a.r <= 2 * 32 * kSplitWaves;
 }
 
 bool use_mfma(const kv_cache *k, const DecodeArgs &a)
@@ -986,6 +985,9 @@ kv_status kv_set_decode_splits(kv_cache *cache, int32_t n_splits)
 // sequence of 1100 tokens, 8 query heads per kv head, 6 splits 9.9 -> 9.4 us, of 2100, 10 splits 10.5 -> 10.8.  So, too, for 16-bit
 // layers: 2000 tokens, 8 splits 10.1 -> 9.2, but 4 x 8213, 24 splits 37.1 -> 37.6.  Not in the kernels
 // with the mean over the heads, where a wave has four heads to join: 4 x 450 tokens, 7 splits 15.8 -> 17.7.
+// kJoinSplits: 32 for the chunks and two.  A form for 48 in its place costs those below (8205 tokens, 33 splits, 9.45 -> 9.68: the
+// loads of rows that are not there) and wins most of those between (8700 tokens, 35 splits, 10.4 -> 9.9; one head of 12000 10.1 -> 8.0,
+// but 8 bits, 11000 12.5 -> 12.8), so it would have to be a third form.
 static bool join_in_kernel(const DecodeArgs &a)
 {
     if (a.geom.mean_mode == KV_MEAN_CROSS_HEAD && a.geom.k_bits != 16) return false;

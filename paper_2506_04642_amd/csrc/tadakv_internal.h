@@ -9,7 +9,7 @@ constexpr int kHeadDim = 128;
 constexpr int kMaxGroupQ = 8;       // query heads per kv head the kernels are sized for
 constexpr int kPartialStride = 132; // floats per (unit, q head, split): O[128], max, sum, pad
 constexpr int kMaxSplits = 256;
-constexpr int kJoinSplits = 34;     // splits that one wavefront joins at once (join.h)
+constexpr int kJoinSplits = 34;     // splits that one wavefront joins at once (join.h; the line: join_in_kernel)
 constexpr int kJoinFew = 8;         // splits of which it joins several query heads at once
 constexpr int kSyncStride = 8;      // 64-bit words from one count of finished workgroups to the next
 constexpr uint64_t kSyncCalls = 1 << 20; // what a call may count (units, workgroups of a unit), with room to spare (count_in)
@@ -156,8 +156,8 @@ struct DecodeArgs {
     // sequence's own counts from these (ragged == 0: every sequence has n_blocks and r)
     int ragged;
     // not null: the kernels take every sequence's counts from these device-resident lengths (the state
-    // after the step's append, dev_len) instead; n_blocks and r only size the launch.  The merge makes
-    // that state the current one.
+    // after the step's append, dev_len) instead; n_blocks and r only size the launch.  The call's last kernel
+    // makes that state the current one: the merge, or the split kernel where it joins the splits (step_is_done).
     int *len_dev;
     unsigned long long *sync, sync_base; // counts, zero after the launch; what this call counts down to (count_in)
     uint16_t nb_seq[kMaxRaggedBatch], r_seq[kMaxRaggedBatch]; // 1 KiB of the kernel arguments
