@@ -385,23 +385,32 @@ class KVCache:
         # torch's current stream of a device as an integer handle
         self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda i: torch.cuda.current_stream(i).cuda_stream)
         alloc = torch.zeros if zero else torch.empty
-        self.layers = [alloc(kv_cache_bytes(cfg, l), dtype=torch.uint8, device=self.device)
-                       for l in range(cfg.n_layers)]
-        self.ws_bytes = kv_workspace_bytes(cfg)
         # counts of finished workgroups, zero between calls; used by one call at a time, as the workspace is.  A cache
         # made while a stream is capturing has none, and its calls are the plain ones: the zeros would be
         # recorded, and a call before the first replay would find what the memory held before.
-        # (Behind the workspace, in one allocation with it: a small one of their own is a segment more to ask the device for.)
-        self._counts, self._counts_ptr = None, 0
-        if torch.cuda.is_current_stream_capturing():
+        # They lie behind the last layer if the layers are zeroed, else behind the workspace: an allocation and a fill of their own,
+        # small as they are, made every new cache 5 to 50 us later.
+        n_counts = 0 if torch.cuda.is_current_stream_capturing() else kv_join_counts_bytes(cfg)
+        sizes = [kv_cache_bytes(cfg, l) for l in range(cfg.n_layers)]
+        self.layers = [alloc(n, dtype=torch.uint8, device=self.device) for n in sizes[:-1]]
+        self.ws_bytes = kv_workspace_bytes(cfg)
+
+        def with_counts(make, n):
+            at = (n + 255) // 256 * 256
+            both = make(at + n_counts, dtype=torch.uint8, device=self.device)
+            self._counts_in, self._counts_at, self._counts_ptr = both, at, both.data_ptr() + at
+            return both[:n]
+
+        self._counts_in, self._counts_at, self._counts_ptr = None, 0, 0
+        if zero and n_counts:
+            self.layers.append(with_counts(alloc, sizes[-1]))
             self.workspace = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
         else:
-            at = (self.ws_bytes + 255) // 256 * 256
-            both = torch.empty(at + kv_join_counts_bytes(cfg), dtype=torch.uint8, device=self.device)
-            self.workspace, self._counts = both[:self.ws_bytes], both[at:].zero_()
-            self._counts_ptr = self._counts.data_ptr()
-            if not zero:
+            self.layers.append(alloc(sizes[-1], dtype=torch.uint8, device=self.device))
+            self.workspace = with_counts(torch.empty, self.ws_bytes) if n_counts else torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
+            if n_counts:
                 # the first call may be on another stream than these zeros (with zero=True the layers have to be waited for as well)
+                self.zero_counts()
                 torch.cuda.current_stream(self.device).synchronize()
         self.handle: Optional[int] = kv_cache_create(cfg, [t.data_ptr() for t in self.layers])
 
@@ -477,9 +486,13 @@ class KVCache:
                               self._counts_ptr, self._stream())
         return out
 
+    @property
+    def _counts(self):
+        return None if self._counts_in is None else self._counts_in[self._counts_at:]
+
     def zero_counts(self) -> None:
         """For recorded calls, after calls that overlapped (by mistake): the counts of finished workgroups are zero again."""
-        if self._counts is not None:
+        if self._counts_in is not None:
             self._counts.zero_()
 
     def dequant(self, layer: int, t_cap: int):
