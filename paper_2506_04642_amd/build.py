@@ -23,7 +23,7 @@ UNITS = [
     ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=2"], "k2"),
     ("tadakv_abi.cpp", ["-x", "hip"], ""),
     ("quant_append.hip", ["-ffp-contract=off"], ""),
-    ("compressv.hip", ["-ffp-contract=off", "-save-temps=obj"], ""),
+    ("compressv.hip", ["-ffp-contract=off", "-mllvm", "-amdgpu-mfma-vgpr-form", "-save-temps=obj"], ""),
     ("decode_valu.hip", [], ""),
     ("decode_mfma_host.cpp", ["-x", "hip"], ""),
     ("decode_raw.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"], ""),

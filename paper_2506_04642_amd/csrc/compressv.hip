@@ -15,8 +15,11 @@
 // channels each); wave (wm, wn) owns tokens 64 wm .. + 63 of head wn: 4 x 8 tiles of
 // v_mfma_f32_16x16x32 accumulators, i.e. two quantiser items, two waves per SIMD.  X and W_V tiles
 // of 64 k-values (rows of 128 bytes, whole cache lines) are fetched straight into LDS
-// (global_load_lds_dwordx4) a stage ahead, 16-byte pieces of a row XOR-swizzled by the row so that
-// the operand reads (16 rows x one piece) hit distinct banks.
+// (global_load_lds_dwordx4), 16-byte pieces of a row XOR-swizzled by the row so that
+// the operand reads (16 rows x one piece) hit distinct banks (4.1 cycles a read instruction; rows of 64 bytes: 8).
+// LDS holds three stages of X, which comes from HBM, and two of W_V, which the L2 and the cache behind it serve: all of the
+// 160 KiB.  With two of each (a stage's 64 KiB requested one stage ahead) the fetches alone, without a matrix
+// instruction, took 1.27 us a stage: 0.55 of transfer and the latency; the matrix instructions alone take 0.85.
 // A call of up to 2048 (group, kv head) items would leave half of the device idle that way: there a workgroup owns 128 tokens x one
 // head, two waves of 64 tokens; up to 512 items 64 tokens x one head, two waves of 32, with four stages in LDS instead of two.
 // Every output element is one chain of model_dim / 32 matrix instructions in ascending k, the same
@@ -26,6 +29,7 @@
 // project_rows_kernel: the decode step's shape (a handful of rows against the whole of W_V): one
 // wave per 16 output channels and 16 rows, its operands streamed with sixteen steps in flight.
 #include "quant_wave.h"
+#include <type_traits>
 
 namespace tadakv {
 namespace {
@@ -161,13 +165,22 @@ __device__ __forceinline__ void tile_out(const ProjectArgs &p, float (&x)[8][8],
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the image is in registers before the next group overwrites it
 }
 
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <int N, int I = 0, class F> __device__ __forceinline__ void static_for(const F &f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<N, I + 1>(f);
+    }
+}
+
 template <int N> __device__ __forceinline__ void wait_vm()
 {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// WT: tokens of a wave's tile (64 or 32); MW: such tiles per workgroup; S: stages in LDS (a power of two).
-template <int DT, int NH, int GC, int BITS, int WT, int MW, int S>
+// WT: tokens of a wave's tile (64 or 32); MW: such tiles per workgroup; SA, SB: stages of X and of W_V in LDS (SA >= SB >= 2).
+template <int DT, int NH, int GC, int BITS, int WT, int MW, int SA, int SB>
 __global__ __launch_bounds__(64 * MW * NH) void compressv_gemm_kernel(ProjectArgs p)
 {
     constexpr int TT = WT * MW, NF = TT / 32;       // tokens per workgroup, groups of 32 of them
@@ -175,10 +188,9 @@ __global__ __launch_bounds__(64 * MW * NH) void compressv_gemm_kernel(ProjectArg
     constexpr int NW = MW * NH;                     // waves: MW token parts x NH heads
     constexpr int A_BYTES = TT * 128;               // X tile of a stage: 64 k-values, rows of 128 bytes
     constexpr int B_BYTES = NH * kHeadDim * 128;    // W_V tile of a stage
-    constexpr int STAGE = A_BYTES + B_BYTES;
-    constexpr int PER = STAGE / 1024 / NW;          // fetch instructions (1 KiB each) per wave and stage
-    static_assert(STAGE / 1024 % NW == 0, "the stage divides among the waves");
-    static_assert((S & (S - 1)) == 0 && NW * kEpiBytes <= S * STAGE, "the epilogue fits the staging buffers");
+    constexpr int PA = A_BYTES / 1024 / NW, PB = B_BYTES / 1024 / NW; // fetch instructions (1 KiB each) per wave and stage
+    static_assert(A_BYTES / 1024 % NW == 0 && B_BYTES / 1024 % NW == 0, "a stage divides among the waves");
+    static_assert(SA >= SB && SB >= 2 && NW * kEpiBytes <= SA * A_BYTES + SB * B_BYTES, "the epilogue fits the staging buffers");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[]; // S stages
 
     const int lane = threadIdx.x & 63;
@@ -193,36 +205,34 @@ __global__ __launch_bounds__(64 * MW * NH) void compressv_gemm_kernel(ProjectArg
     const int n_f = p.batch * p.n_groups;
     if (tile * NF >= n_f) return; // (the grid is padded to whole rounds of eight tiles)
 
-    // ---- where this lane's pieces of a stage come from: instruction q of the stage fills rows
+    // ---- where this lane's pieces of a stage come from: instruction q of a tile fills rows
     // 8 q .. 8 q + 7 (128 bytes each: whole cache lines), lane l the piece (l & 7) ^ (row & 7) of row 8 q + (l >> 3)
-    const uint16_t *src[PER];
+    const uint16_t *src_a[PA], *src_b[PB];
     {
         const int r8 = lane >> 3, pc = (lane & 7) ^ r8;
 #pragma unroll
-        for (int i = 0; i < PER; i++) {
-            const int q = wave * PER + i;
-            if (q < A_BYTES / 1024) {
-                const int row = 8 * q + r8;
-                int f = tile * NF + (row >> 5);
-                f = f < n_f ? f : n_f - 1; // past the end: any valid row, the result is not stored
-                const GroupId g = group_of(p, f);
-                int t = row & 31;
-                t = t < g.nv ? t : g.nv - 1;
-                src[i] = p.x + (long long)g.b * p.x_stride_b + (long long)(p.t0 + 32 * g.gi + t) * p.x_stride_t + pc * 8;
-            } else {
-                const int row = 8 * (q - A_BYTES / 1024) + r8; // output channel within the workgroup's heads
-                src[i] = p.w + ((long long)hg * NH * kHeadDim + row) * p.model_dim + pc * 8;
-            }
+        for (int i = 0; i < PA; i++) {
+            const int row = 8 * (wave * PA + i) + r8;
+            int f = tile * NF + (row >> 5);
+            f = f < n_f ? f : n_f - 1; // past the end: any valid row, the result is not stored
+            const GroupId g = group_of(p, f);
+            int t = row & 31;
+            t = t < g.nv ? t : g.nv - 1;
+            src_a[i] = p.x + (long long)g.b * p.x_stride_b + (long long)(p.t0 + 32 * g.gi + t) * p.x_stride_t + pc * 8;
         }
+#pragma unroll
+        for (int i = 0; i < PB; i++) // (output channel within the workgroup's heads)
+            src_b[i] = p.w + ((long long)hg * NH * kHeadDim + 8 * (wave * PB + i) + r8) * p.model_dim + pc * 8;
     }
     const int stages = p.model_dim / kStepK;
-    auto issue = [&](int sg) { // stage sg (k-values 64 sg .. + 63; the last stage again beyond it) into buffer sg % S
+    // this wave's piece i of a tile of stage sg (k-values 64 sg .. + 63; the last stage again beyond it) into the buffer at byte `at`
+    auto issue_a = [&](int sg, uint32_t at, int i) {
         const int sk = sg < stages ? sg : stages - 1;
-#pragma unroll
-        for (int i = 0; i < PER; i++) {
-            const int q = wave * PER + i;
-            __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + (long long)sk * kStepK), (lptr_t)(lds + (sg & (S - 1)) * STAGE + q * 1024), 16, 0, 0);
-        }
+        __builtin_amdgcn_global_load_lds((gptr_t)(src_a[i] + (long long)sk * kStepK), (lptr_t)(lds + at + (wave * PA + i) * 1024), 16, 0, 0);
+    };
+    auto issue_b = [&](int sg, uint32_t at, int i) {
+        const int sk = sg < stages ? sg : stages - 1;
+        __builtin_amdgcn_global_load_lds((gptr_t)(src_b[i] + (long long)sk * kStepK), (lptr_t)(lds + at + (wave * PB + i) * 1024), 16, 0, 0);
     };
 
     v4f acc[MT][8];
@@ -235,59 +245,85 @@ __global__ __launch_bounds__(64 * MW * NH) void compressv_gemm_kernel(ProjectArg
     // this lane's operand piece inside a 16-row tile (2 KiB) for the low and the high 32 k-values of
     // a stage: row n, piece 4 half + kg, swizzled by the row
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
-    const uint32_t a_base = lds0 + wm * (WT * 128) + n * 128, b_base = lds0 + A_BYTES + wn * (kHeadDim * 128) + n * 128;
+    const uint32_t a_base = lds0 + wm * (WT * 128) + n * 128, b_base = lds0 + wn * (kHeadDim * 128) + n * 128;
     const uint32_t sw_lo = (uint32_t)((kg ^ (n & 7)) << 4), sw_hi = (uint32_t)(((4 + kg) ^ (n & 7)) << 4);
     u32x4 fa[2][MT], fb[2][8]; // operands of the current half step and of the next one
-    auto read_frags = [&](int sg, uint32_t sw, u32x4(&a)[MT], u32x4(&b)[8]) {
-        const uint32_t so = (uint32_t)((sg & (S - 1)) * STAGE) + sw;
-        lds_read16<0>(a[0], a_base + so);
-        lds_read16<2048>(a[1], a_base + so);
-        if constexpr (MT == 4) {
-            lds_read16<4096>(a[2], a_base + so);
-            lds_read16<6144>(a[3], a_base + so);
-        }
-        lds_read16<0>(b[0], b_base + so);
-        lds_read16<2048>(b[1], b_base + so);
-        lds_read16<4096>(b[2], b_base + so);
-        lds_read16<6144>(b[3], b_base + so);
-        lds_read16<8192>(b[4], b_base + so);
-        lds_read16<10240>(b[5], b_base + so);
-        lds_read16<12288>(b[6], b_base + so);
-        lds_read16<14336>(b[7], b_base + so);
+    // operand r of a half step: a wave's row tile r, or its column tile r - MT
+    auto read_frag = [&](auto rc, uint32_t ra, uint32_t rb, u32x4(&a)[MT], u32x4(&b)[8]) {
+        constexpr int r = decltype(rc)::value;
+        if constexpr (r < MT) lds_read16<r * 2048>(a[r], ra);
+        else lds_read16<(r - MT) * 2048>(b[r - MT], rb);
     };
-    auto mfmas = [&](u32x4(&a)[MT], u32x4(&b)[8]) {
-        __builtin_amdgcn_sched_barrier(0);
+    // 8 MT matrix instructions on one half step's operands, four at a time, and between the fours the reads of the half
+    // step after it (from ra and rb) and, with FETCH, this wave's fetches of W_V stage sg + SB and X stage sg + SA (to
+    // the buffers of stage sg at wa and wb).
+    constexpr int NG = 2 * MT, NR = MT + 8;
+    auto half_step = [&](auto fetch, int sg, uint32_t wa, uint32_t wb, uint32_t ra, uint32_t rb, u32x4(&a)[MT], u32x4(&b)[8], u32x4(&na)[MT], u32x4(&nb)[8]) {
+        static_for<NG>([&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            static_for<NR>([&](auto rc) {
+                if constexpr (decltype(rc)::value * (3 * NG / 4) / NR == g) read_frag(rc, ra, rb, na, nb);
+            });
+            if constexpr (decltype(fetch)::value) {
 #pragma unroll
-        for (int mt = 0; mt < MT; mt++)
+                for (int i = 0; i < PA + PB; i++)
+                    if (i * NG / (PA + PB) == g) {
+                        if (i < PB) issue_b(sg + SB, wb, i);
+                        else issue_a(sg + SA, wa, i - PB);
+                    }
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int nt = 0; nt < 8; nt++) acc[mt][nt] = mfma16<DT>(a[mt], b[nt], acc[mt][nt]);
-        __builtin_amdgcn_sched_barrier(0);
+            for (int nt = 0; nt < 4; nt++) {
+                constexpr int mt = g / 2, n0 = 4 * (g & 1);
+                acc[mt][n0 + nt] = mfma16<DT>(a[mt], b[n0 + nt], acc[mt][n0 + nt]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
+    constexpr uint32_t B0 = SA * A_BYTES; // the W_V buffers lie behind the X buffers
+    auto after_a = [](uint32_t at) { return at + A_BYTES == B0 ? 0u : at + A_BYTES; };
+    auto after_b = [](uint32_t at) { return at + B_BYTES == B0 + SB * B_BYTES ? B0 : at + B_BYTES; };
 
+    // (Requested in one burst behind the barrier, a stage's 64 fetches and 96 reads keep every wave from its matrix instructions
+    // until the memory pipe has taken them, up to a thousand cycles: 65536 tokens, 8 heads, model_dim 4096: 503 us a call; spread
+    // out 471, with the third stage of X 445.  What is left above the matrix instructions is mostly the clock: the same call on
+    // zeros, which cost the matrix cores less power, takes 378; the epilogue 28, the keys' side 38.)
     // A stage is consumed in two half steps of 32 k-values (32 matrix instructions per wave each);
     // the operands of a half step are read from LDS while the matrix instructions of the half step
     // before it run.  Once a wave holds the high half's operands it is done with the stage's buffer;
     // at the one barrier of a stage everybody is, and everybody's part of the next stage (fetched one
-    // stage earlier) has landed; then the stage after the next is fetched into the freed buffer and
+    // stage earlier, or two) has landed; then later stages are fetched into the freed buffers and
     // the next stage's low operands are read.  Past the last stage the fetch repeats the last one into
     // a buffer nobody reads any more and the operand read returns unused data, so that every stage is
     // the same straight line of code.
+    // (in the order of the loop: W_V of stage sg + SB, then X of stage sg + SA)
 #pragma unroll
-    for (int sg = 0; sg < S; sg++) issue(sg);
-    wait_vm<PER *(S - 1)>(); // stage 0 has landed
-    __builtin_amdgcn_s_barrier();
-    read_frags(0, sw_lo, fa[0], fb[0]);
-    for (int sg = 0; sg < stages; sg++) {
-        lds_reads_done(fa[0], fb[0]);
-        read_frags(sg, sw_hi, fa[1], fb[1]);
-        mfmas(fa[0], fb[0]);
-        lds_reads_done(fa[1], fb[1]);
-        wait_vm<PER *(S - 2)>();
-        __builtin_amdgcn_s_barrier();
-        issue(sg + S);
-        read_frags(sg + 1, sw_lo, fa[0], fb[0]);
-        mfmas(fa[1], fb[1]);
+    for (int sg = -SA; sg < 0; sg++) {
+        if (sg + SB >= 0)
+#pragma unroll
+            for (int i = 0; i < PB; i++) issue_b(sg + SB, B0 + (sg + SB) * B_BYTES, i);
+#pragma unroll
+        for (int i = 0; i < PA; i++) issue_a(sg + SA, (sg + SA) * A_BYTES, i);
     }
+    // fetches that may be on their way when the next stage's two tiles have to be there
+    constexpr int LATER = (SB - 2) * (PA + PB) + (SA > SB ? PA : 0);
+    wait_vm<LATER + PA + PB>(); // stage 0 has landed
+    __builtin_amdgcn_s_barrier();
+    uint32_t at_a = 0, at_b = B0;
+    static_for<NR>([&](auto rc) { read_frag(rc, a_base + sw_lo, b_base + B0 + sw_lo, fa[0], fb[0]); });
+    for (int sg = 0; sg < stages; sg++) {
+        const uint32_t na = after_a(at_a), nb = after_b(at_b);
+        lds_reads_done(fa[0], fb[0]);
+        half_step(std::false_type(), 0, 0u, 0u, a_base + at_a + sw_hi, b_base + at_b + sw_hi, fa[0], fb[0], fa[1], fb[1]);
+        lds_reads_done(fa[1], fb[1]);
+        wait_vm<LATER>();
+        __builtin_amdgcn_s_barrier();
+        half_step(std::true_type(), sg, at_a, at_b, a_base + na + sw_lo, b_base + nb + sw_lo, fa[1], fb[1], fa[0], fb[0]);
+        at_a = na;
+        at_b = nb;
+    }
+    lds_reads_done(fa[0], fb[0]); // (of the stage past the last)
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads(); // the staging buffers are free: each wave takes 16 KiB of them for its epilogue
     unsigned char *tt = lds + wave * kEpiBytes;  // [128 channels][32 tokens] 16-bit, kTTStride bytes per channel
@@ -400,34 +436,34 @@ __global__ __launch_bounds__(64) void project_rows_kernel(ProjectArgs p)
     }
 }
 
-template <int DT, int NH, int GC, int BITS, int WT, int MW, int S> hipError_t launch_gemm(const ProjectArgs &p, hipStream_t s)
+template <int DT, int NH, int GC, int BITS, int WT, int MW, int SA, int SB> hipError_t launch_gemm(const ProjectArgs &p, hipStream_t s)
 {
     constexpr int NF = WT * MW / 32;
-    constexpr size_t lds = S * (size_t)(WT * MW * 128 + NH * kHeadDim * 128);
-    static const bool ready = hipFuncSetAttribute((const void *)compressv_gemm_kernel<DT, NH, GC, BITS, WT, MW, S>,
+    constexpr size_t lds = SA * (size_t)(WT * MW * 128) + SB * (size_t)(NH * kHeadDim * 128);
+    static const bool ready = hipFuncSetAttribute((const void *)compressv_gemm_kernel<DT, NH, GC, BITS, WT, MW, SA, SB>,
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
     if (!ready) return note_launch(hipErrorInvalidValue);
     const long long n_f = (long long)p.batch * p.n_groups;
     const long long tiles = (n_f + NF - 1) / NF, rounds = (tiles + 7) / 8;
     const long long grid = rounds * 8 * (p.n_kv_heads / NH);
     if (grid > 0x7FFFFFFF) return note_launch(hipErrorInvalidValue);
-    hipLaunchKernelGGL((compressv_gemm_kernel<DT, NH, GC, BITS, WT, MW, S>), dim3((unsigned)grid), dim3(64 * MW * NH), lds, s, p);
+    hipLaunchKernelGGL((compressv_gemm_kernel<DT, NH, GC, BITS, WT, MW, SA, SB>), dim3((unsigned)grid), dim3(64 * MW * NH), lds, s, p);
     return note_launch(hipGetLastError());
 }
 // The tile by the number of tokens: 256 x NH heads where that fills the device; up to 2048 items 128 tokens x one head (two
 // waves of the same 64 x 128 tile, two such workgroups per compute unit); up to 512 items 64 tokens x one head with
-// four stages on their way (a small workgroup's stage is through in a fifth of the time that its fetch takes).  Same chain per
-// element, same bytes.  Beyond its one round a tile that is smaller than another only reads the operands more often.
-// Measured (us a call with the keys' side, bf16, 4 bits; small / middle / large): 8 kv heads, model_dim 4096: 1024 tokens 53 / 61 / 100,
-// 2048 (512 items) 55 / 63 / 100, 3072 98 / 64 / 102, 4096 99 / 66 / 103, 8192 (2048 items) 184 / 78 / 109, 12288 272 / 134 / 117,
-// 24576 539 / 250 / 245; 2 heads, model_dim 2048: 8192 tokens (512 items) 32 / 42 / 59, 16384 57 / 42 / 64, 32768 (2048) 107 / 49 / 68.
+// four stages on their way (a small workgroup's stage is through in a fifth of the time that its fetch takes; six are 2 % slower).  Same
+// chain per element, same bytes.  Beyond its one round a tile that is smaller than another only reads the operands more often.
+// Measured (us a call with the keys' side, bf16, 4 bits; small / middle / large): 8 kv heads, model_dim 4096: 1024 tokens 35 / 55 / 81,
+// 2048 (512 items) 36 / 55 / 82, 3072 64 / 55 / 82, 4096 64 / 56 / 82, 8192 (2048 items) 123 / 71 / 85, 12288 186 / 132 / 99,
+// 24576 369 / 230 / 206; 2 heads, model_dim 2048: 8192 tokens (512 items) 24 / 35 / 50, 16384 41 / 36 / 50, 32768 (2048) 80 / 60 / 66.
 template <int DT, int GC, int BITS> hipError_t launch_gemm_tile(const ProjectArgs &p, hipStream_t s)
 {
     const long long items = (long long)p.batch * p.n_groups * p.n_kv_heads;
-    if (items <= kSmallTileItems) return launch_gemm<DT, 1, GC, BITS, 32, 2, 4>(p, s);
-    if (items <= kMiddleTileItems) return launch_gemm<DT, 1, GC, BITS, 64, 2, 2>(p, s);
-    if (p.n_kv_heads % 2 == 0) return launch_gemm<DT, 2, GC, BITS, 64, 4, 2>(p, s);
-    return launch_gemm<DT, 1, GC, BITS, 64, 4, 2>(p, s);
+    if (items <= kSmallTileItems) return launch_gemm<DT, 1, GC, BITS, 32, 2, 4, 4>(p, s);
+    if (items <= kMiddleTileItems) return launch_gemm<DT, 1, GC, BITS, 64, 2, 3, 2>(p, s);
+    if (p.n_kv_heads % 2 == 0) return launch_gemm<DT, 2, GC, BITS, 64, 4, 3, 2>(p, s);
+    return launch_gemm<DT, 1, GC, BITS, 64, 4, 3, 3>(p, s);
 }
 template <int DT> hipError_t launch_gemm_fmt(const ProjectArgs &p, hipStream_t s)
 {
