@@ -161,7 +161,7 @@ __device__ __forceinline__ void tile_out(const ProjectArgs &p, float (&x)[8][8],
     const int part_bytes = (gm.mean_mode == 0 ? gm.v_mean + 256 : gm.v_meta + G * NGV * 4) - base_off;
     unsigned char *rec = p.layer + record_offset(gm, p.n_kv_heads, p.b0 + g.b, h, p.first_block + g.gi);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // this wave's LDS writes have landed
-    for (int off = lane * 16; off < part_bytes; off += 64 * 16) *(uint4 *)(rec + base_off + off) = *(const uint4 *)(img + off);
+    for (int off = lane * 16; off < part_bytes; off += 64 * 16) put_record((uint4 *)(rec + base_off + off), *(const uint4 *)(img + off));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the image is in registers before the next group overwrites it
 }
 

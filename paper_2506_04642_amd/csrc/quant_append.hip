@@ -712,7 +712,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
         if (which == 0) part_bytes = (gm.mean_mode == 0 ? gm.k_mean : gm.k_zero) + 256 - base_off;
         else part_bytes = (gm.mean_mode == 0 ? gm.v_mean + 256 : gm.v_meta + G * NGV * 4) - base_off;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // this wave's LDS writes have landed
-        for (int off = lane * 16; off < part_bytes; off += 64 * 16) *(uint4 *)(rec + base_off + off) = *(const uint4 *)(img + off);
+        for (int off = lane * 16; off < part_bytes; off += 64 * 16) put_record((uint4 *)(rec + base_off + off), *(const uint4 *)(img + off));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the image is in registers before the next item overwrites it
     }
     tail_rows<kThreads, ROPE>(a);
@@ -1075,7 +1075,7 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
         if (which == 0) part_bytes = (mode == 0 ? gm.k_mean : gm.k_zero) + 256 - base_off;
         else part_bytes = (mode == 0 ? gm.v_mean + 256 : gm.v_meta + G * NGV * 4) - base_off;
         for (int off = (int)threadIdx.x * 16; off < part_bytes; off += NP * 64 * 16)
-            *(uint4 *)(rec + base_off + off) = *(const uint4 *)(img + off);
+            put_record((uint4 *)(rec + base_off + off), *(const uint4 *)(img + off));
         __syncthreads(); // the image is in registers before the next item's rows overwrite it
     }
 }

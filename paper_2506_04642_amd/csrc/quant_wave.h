@@ -296,6 +296,16 @@ __device__ __forceinline__ void rope_rows(uint4 (&pre)[8], unsigned char *rows, 
 #undef TADAKV_ROPE
 }
 
+// A piece of a record on its way out of a bulk append: nobody reads it before the call has ended, and the prompt's rows, which other
+// kernels (the next layer's append here, the caller's own attention) read again or have just written, stay in the caches in
+// its place: plain -> streaming stores, 3 x 65536 tokens of the same input at 2, 4 and 8 bits 234 -> 202 us; one
+// layer at 4 bits of 32000 tokens 41.6 -> 34.0, 48000 60.3 -> 58.1, 65536 78.3 -> 79.9 (an input as large as the last cache).
+__device__ __forceinline__ void put_record(uint4 *p, const uint4 &v)
+{
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4 *)p);
+}
+
 // Minimum / maximum as the bare instructions.  fminf / fmaxf make the compiler put a quieting
 // instruction in front of every operand it cannot prove to be free of signalling NaNs (every value
 // that came through a lane exchange, for one), which doubled the cost of the extrema below; the
