@@ -424,7 +424,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((G == 
 // groups' extrema move by quad DPP; a value group (one token, Gc channels) is lanes 4 apart in a
 // row of 16; an 8-token run of one channel (a value word at 4 bits) and 8 channels of one token
 // (a key word at 4 bits) are both in one lane.
-template <int GC, int BITS, bool ROPE>
+// DT: the input's type (0 binary16, 1 bfloat16).  With the type and the mean's mode as branches around the 64 values of a lane, the
+// compiler moved every value to a common register behind each (64 of a value item's 1130 vector instructions), and the extrema's lane exchanges
+// were moves of their own (32 more).  Without: 2 x 15003 tokens of 8 heads at 4 and 2 bits, rotated, 90.8 -> 83.5 us;
+// plain, 16 x 4096 at 2, 4 and 8 bits 207.5 -> 200, 16 x 2000 at 4 bits 36.5 -> 34.1.
+template <int GC, int BITS, bool ROPE, int DT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))) void flush_wave_kernel(AppendArgs a, int n_items)
 {
     constexpr int G = 32;
@@ -494,7 +498,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
             // complete in the order issued.
             float s0 = 0.0f, s1 = 0.0f;
             if (turn) {
-                rope_rows(pre, img, a, fb * G - a.r_old, lane, s0, s1);
+                rope_rows<DT>(pre, img, a, fb * G - a.r_old, lane, s0, s1);
             } else {
                 const int piece_w = (c8 + 4 * tg) & 15;
 #pragma unroll
@@ -508,46 +512,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
                 uint32_t w[8];
 #pragma unroll
                 for (int k = 0; k < 8; k++) w[k] = *(const uint32_t *)(rq + k * 256);
-                if (gm.dtype == 1) {
 #pragma unroll
-                    for (int k = 0; k < 8; k++) {
-                        s0 = s0 + __uint_as_float(w[k] << 16);
-                        s1 = s1 + __uint_as_float(w[k] & 0xFFFF0000u);
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 8; k++) {
-                        s0 = s0 + f16_val((uint16_t)(w[k] & 0xFFFFu));
-                        s1 = s1 + f16_val((uint16_t)(w[k] >> 16));
-                    }
+                for (int k = 0; k < 8; k++) {
+                    s0 = s0 + low16<DT>(w[k]);
+                    s1 = s1 + high16<DT>(w[k]);
                 }
             }
             mean_pair = (uint32_t)f16_rne(s0 / (float)G) | ((uint32_t)f16_rne(s1 / (float)G) << 16);
         }
 
         float x[8][8]; // [token j][channel e]
-        widen_pieces(pre, gm.dtype, x);
+        widen_pieces<DT>(pre, x);
 
         // ---- mean-centring
-        if (gm.mean_mode == 0) {
-            // per channel over the block: the sum runs over the tokens in order
-            float m[8];
-            const int mean_off = (which == 0 ? gm.k_mean : gm.v_mean) - base_off;
-            // (summed above, while only the raw rows were held) the record's mean row is the lanes'
-            // words in order
-            const uint32_t mp = mean_pair;
-            *(uint32_t *)(img + mean_off + lane * 4) = mp;
-            // channels 8 c8 + 2 k and + 2 k + 1 are quad lane k's
-            const uint32_t q0 = quad_bcast_u<0>(mp), q1 = quad_bcast_u<1>(mp), q2 = quad_bcast_u<2>(mp), q3 = quad_bcast_u<3>(mp);
-            m[0] = f16_val((uint16_t)(q0 & 0xFFFFu)); m[1] = f16_val((uint16_t)(q0 >> 16));
-            m[2] = f16_val((uint16_t)(q1 & 0xFFFFu)); m[3] = f16_val((uint16_t)(q1 >> 16));
-            m[4] = f16_val((uint16_t)(q2 & 0xFFFFu)); m[5] = f16_val((uint16_t)(q2 >> 16));
-            m[6] = f16_val((uint16_t)(q3 & 0xFFFFu)); m[7] = f16_val((uint16_t)(q3 >> 16));
-#pragma unroll
-            for (int j = 0; j < 8; j++)
-#pragma unroll
-                for (int e = 0; e < 8; e++) x[j][e] = x[j][e] - m[e];
-        } else if (gm.mean_mode == 1) {
+        if (gm.mean_mode == 1) {
             // mean over the kv heads per (token, channel), written by xhead_mean_kernel before this launch
             const uint16_t *xm = (const uint16_t *)(a.layer + xmean_offset(gm, a.b0 + b, first_block + fb, which));
 #pragma unroll
@@ -558,13 +536,30 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
                 for (int k = 0; k < 4; k++) {
                     x[j][2 * k] = x[j][2 * k] - f16_val((uint16_t)(wv[k] & 0xFFFFu));
                     x[j][2 * k + 1] = x[j][2 * k + 1] - f16_val((uint16_t)(wv[k] >> 16));
+                    // (or the compiler makes one subtraction of this and the other branch's, behind a move per value of what is subtracted)
+                    asm("" : "+v"(x[j][2 * k]), "+v"(x[j][2 * k + 1]));
                 }
             }
         } else {
+            // per channel over the block, the sum over the tokens in order (formed above, while only the raw rows were
+            // held); no mean is a mean of zero: one subtraction for both, where a branch of its own for either moved every value
+            uint32_t mp = 0u;
+            if (gm.mean_mode == 0) {
+                mp = mean_pair;
+                // the record's mean row is the lanes' words in order
+                *(uint32_t *)(img + ((which == 0 ? gm.k_mean : gm.v_mean) - base_off) + lane * 4) = mp;
+            }
+            // channels 8 c8 + 2 k and + 2 k + 1 are quad lane k's
+            const uint32_t q[4] = {quad_bcast_u<0>(mp), quad_bcast_u<1>(mp), quad_bcast_u<2>(mp), quad_bcast_u<3>(mp)};
 #pragma unroll
-            for (int j = 0; j < 8; j++)
+            for (int k = 0; k < 4; k++) {
+                const float m0 = f16_val((uint16_t)(q[k] & 0xFFFFu)), m1 = f16_val((uint16_t)(q[k] >> 16));
 #pragma unroll
-                for (int e = 0; e < 8; e++) x[j][e] = x[j][e] - 0.0f;
+                for (int j = 0; j < 8; j++) {
+                    x[j][2 * k] = x[j][2 * k] - m0;
+                    x[j][2 * k + 1] = x[j][2 * k + 1] - m1;
+                }
+            }
         }
 
         constexpr int qmax = (1 << bits) - 1;
@@ -576,11 +571,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
             for (int e = 0; e < 8; e++) {
                 float lo = vmin(vmin3(x[0][e], x[1][e], x[2][e]), vmin3(x[3][e], x[4][e], vmin3(x[5][e], x[6][e], x[7][e])));
                 float hi = vmax(vmax3(x[0][e], x[1][e], x[2][e]), vmax3(x[3][e], x[4][e], vmax3(x[5][e], x[6][e], x[7][e])));
-                lo = vmin(lo, dpp_f<0xB1>(lo));
-                hi = vmax(hi, dpp_f<0xB1>(hi));
-                mn[e] = vmin(lo, dpp_f<0x4E>(lo));
-                mx[e] = vmax(hi, dpp_f<0x4E>(hi));
+                mn[e] = lo;
+                mx[e] = hi;
             }
+            quad_extrema(mn, mx);
             // quad lane tg works out the metadata of channels 2 tg and 2 tg + 1, then all share
             const MetaOut ma = meta_of(pick4(tg, mn[0], mn[2], mn[4], mn[6]), pick4(tg, mx[0], mx[2], mx[4], mx[6]), qmax);
             const MetaOut mb = meta_of(pick4(tg, mn[1], mn[3], mn[5], mn[7]), pick4(tg, mx[1], mx[3], mx[5], mx[7]), qmax);
@@ -642,21 +636,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
             for (int j = 0; j < 8; j++) {
                 float lo = vmin(vmin3(x[j][0], x[j][1], x[j][2]), vmin3(x[j][3], x[j][4], vmin3(x[j][5], x[j][6], x[j][7])));
                 float hi = vmax(vmax3(x[j][0], x[j][1], x[j][2]), vmax3(x[j][3], x[j][4], vmax3(x[j][5], x[j][6], x[j][7])));
-                // lanes 4 and 8 apart in the row of 16 (rotations: the coset is covered either way)
-                lo = vmin(lo, dpp_f<0x124>(lo));
-                hi = vmax(hi, dpp_f<0x124>(hi));
-                lo = vmin(lo, dpp_f<0x128>(lo));
-                hi = vmax(hi, dpp_f<0x128>(hi));
-                if (GC >= 64) {
-                    lo = vmin(lo, from_lane_f(lo, lane ^ 16));
-                    hi = vmax(hi, from_lane_f(hi, lane ^ 16));
-                }
-                if (GC >= 128) {
-                    lo = vmin(lo, from_lane_f(lo, lane ^ 32));
-                    hi = vmax(hi, from_lane_f(hi, lane ^ 32));
-                }
                 mn[j] = lo;
                 mx[j] = hi;
+            }
+            row_extrema(mn, mx); // lanes 4 and 8 apart in the row of 16 (rotations: the coset is covered either way)
+            if (GC >= 64) {
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+                    mn[j] = vmin(mn[j], from_lane_f(mn[j], lane ^ 16));
+                    mx[j] = vmax(mx[j], from_lane_f(mx[j], lane ^ 16));
+                    if (GC >= 128) {
+                        mn[j] = vmin(mn[j], from_lane_f(mn[j], lane ^ 32));
+                        mx[j] = vmax(mx[j], from_lane_f(mx[j], lane ^ 32));
+                    }
+                }
             }
             // lane with q4 = c8 & 3 works out tokens 2 q4 and 2 q4 + 1 of its group, then the four share
             const int q4 = c8 & 3;
@@ -901,11 +894,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
 // Codes, metadata and mean go into one image of the record's key or value part in LDS (it takes the
 // place of the raw rows, which nobody needs once the sums are formed), which the waves then write out
 // together as one linear run.  For the bulk append; a step on
-// device-resident lengths uses flush_wave_parts_kernel, which reads the block twice.  With the rotation three
-// waves per SIMD and 8 to 14 spilled registers beat two without spills at G = 64 and 4 or 8 bits (137 -> 129,
-// 147 -> 138 us per 65536 tokens of 8 kv heads) and lose or draw elsewhere.
-template <int G, int GC, int BITS, bool ROPE>
-__global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(ROPE && !(G == 64 && BITS > 2) ? 2 : 3, 8))) void flush_coop_kernel(AppendArgs a, int n_items)
+// device-resident lengths uses flush_wave_parts_kernel, which reads the block twice.  Three waves per SIMD: with the rotation two,
+// without spills, are slower (65536 tokens of 8 kv heads, us a call, two -> three: G = 64 at 2 bits 109 -> 92, G = 128 at 2, 4 and 8 bits
+// 117 -> 99, 119 -> 102, 128 -> 108).
+// DT: the input's type, as in flush_wave_kernel (65536 tokens, us a call: rotated, G = 64 at 4 bits 117 -> 93, plain, G = 64 at 4 bits
+// 81.3 -> 76.5, G = 128 at 2 bits 87.8 -> 79.7; 33536 tokens, G = 64, 8 bits 46.0 -> 43.0).
+template <int G, int GC, int BITS, bool ROPE, int DT>
+__global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(3, 8))) void flush_coop_kernel(AppendArgs a, int n_items)
 {
     constexpr int NP = G / 32; // parts of 32 tokens = waves of the workgroup
     constexpr int NGV = kHeadDim / GC;
@@ -944,7 +939,7 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
         // rotated by four per eight tokens: see flush_wave_kernel); new key rows are turned there
         if (ROPE && which == 0) {
             float s0 = 0.0f, s1 = 0.0f; // (the part's own sums: not those the mean is formed from)
-            rope_rows(pre, raw, a, fb * G + 32 * part - a.r_old, lane, s0, s1);
+            rope_rows<DT>(pre, raw, a, fb * G + 32 * part - a.r_old, lane, s0, s1);
         } else if (mode == 0) {
             const int piece_w = (c8 + 4 * tg) & 15;
 #pragma unroll
@@ -964,13 +959,8 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
 #pragma unroll
                 for (int k = 0; k < 8; k++) {
                     const uint32_t w = *(const uint32_t *)(rq + k * 256);
-                    if (gm.dtype == 1) {
-                        xs0[8 * tq + k] = __uint_as_float(w << 16);
-                        xs1[8 * tq + k] = __uint_as_float(w & 0xFFFF0000u);
-                    } else {
-                        xs0[8 * tq + k] = f16_val((uint16_t)(w & 0xFFFFu));
-                        xs1[8 * tq + k] = f16_val((uint16_t)(w >> 16));
-                    }
+                    xs0[8 * tq + k] = low16<DT>(w);
+                    xs1[8 * tq + k] = high16<DT>(w);
                 }
             }
             // the waves add in turn
@@ -1010,7 +1000,7 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
 
         // ---- deviations
         float x[8][8]; // [token j][channel e]
-        widen_pieces(pre, gm.dtype, x);
+        widen_pieces<DT>(pre, x);
         if (mode == 1) {
             // mean over the kv heads per (token, channel), written by xhead_mean_kernel before this launch
             const uint16_t *xm = (const uint16_t *)(a.layer + xmean_offset(gm, a.b0 + b, a.first_block + fb, which));
@@ -1038,11 +1028,10 @@ __global__ __launch_bounds__(64 * (G / 32)) __attribute__((amdgpu_waves_per_eu(R
             for (int e = 0; e < 8; e++) {
                 float lo = vmin(vmin3(x[0][e], x[1][e], x[2][e]), vmin3(x[3][e], x[4][e], vmin3(x[5][e], x[6][e], x[7][e])));
                 float hi = vmax(vmax3(x[0][e], x[1][e], x[2][e]), vmax3(x[3][e], x[4][e], vmax3(x[5][e], x[6][e], x[7][e])));
-                lo = vmin(lo, dpp_f<0xB1>(lo));
-                hi = vmax(hi, dpp_f<0xB1>(hi));
-                mn[e] = vmin(lo, dpp_f<0x4E>(lo));
-                mx[e] = vmax(hi, dpp_f<0x4E>(hi));
+                mn[e] = lo;
+                mx[e] = hi;
             }
+            quad_extrema(mn, mx);
             if (tg == 0) {
                 *(float4 *)&lds_ext[part][0][8 * c8] = float4{mn[0], mn[1], mn[2], mn[3]};
                 *(float4 *)&lds_ext[part][0][8 * c8 + 4] = float4{mn[4], mn[5], mn[6], mn[7]};
@@ -1243,14 +1232,14 @@ template <int G> hipError_t launch_flush_gc(const AppendArgs &a, hipStream_t s)
     return launch_flush_g<G, 128, false>(a, s);
 }
 
-template <int GC, int BITS, bool ROPE> hipError_t launch_flush_wave(const AppendArgs &a, hipStream_t s)
+template <int GC, int BITS, bool ROPE, int DT> hipError_t launch_flush_wave_t(const AppendArgs &a, hipStream_t s)
 {
     const int U = a.batch * a.n_kv_heads;
     const long long items = (long long)a.n_flush_blocks * U * (a.sides ? 1 : 2);
     if (items > 0x7FFFFFFF) return hipErrorInvalidValue;
     static const int slots = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_wave_kernel<GC, BITS, ROPE>, kThreads, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_wave_kernel<GC, BITS, ROPE, DT>, kThreads, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -1259,8 +1248,13 @@ template <int GC, int BITS, bool ROPE> hipError_t launch_flush_wave(const Append
     if (slots < 1) return hipErrorInvalidValue;
     const long long want = (items + kThreads / 64 - 1) / (kThreads / 64);
     const int grid = tail_grid(a, want < slots ? (int)want : slots, kThreads / 32, slots);
-    hipLaunchKernelGGL((flush_wave_kernel<GC, BITS, ROPE>), dim3(grid), dim3(kThreads), 0, s, a, (int)items);
+    hipLaunchKernelGGL((flush_wave_kernel<GC, BITS, ROPE, DT>), dim3(grid), dim3(kThreads), 0, s, a, (int)items);
     return note_launch(hipGetLastError());
+}
+
+template <int GC, int BITS, bool ROPE> hipError_t launch_flush_wave(const AppendArgs &a, hipStream_t s)
+{
+    return a.geom.dtype == 1 ? launch_flush_wave_t<GC, BITS, ROPE, 1>(a, s) : launch_flush_wave_t<GC, BITS, ROPE, 0>(a, s);
 }
 
 template <int G, int GC, int BITS> hipError_t launch_flush_wave_parts(const AppendArgs &a, hipStream_t s)
@@ -1288,7 +1282,7 @@ template <int G, int GC, int BITS> hipError_t launch_flush_wave_parts(const Appe
     return note_launch(hipGetLastError());
 }
 
-template <int G, int GC, int BITS, bool ROPE> hipError_t launch_flush_coop(const AppendArgs &a, hipStream_t s)
+template <int G, int GC, int BITS, bool ROPE, int DT> hipError_t launch_flush_coop_t(const AppendArgs &a, hipStream_t s)
 {
     const int U = a.batch * a.n_kv_heads;
     const long long items = (long long)a.n_flush_blocks * U * 2;
@@ -1296,7 +1290,7 @@ template <int G, int GC, int BITS, bool ROPE> hipError_t launch_flush_coop(const
     constexpr int threads = 64 * (G / 32);
     static const int slots = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_coop_kernel<G, GC, BITS, ROPE>, threads, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_coop_kernel<G, GC, BITS, ROPE, DT>, threads, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -1305,8 +1299,13 @@ template <int G, int GC, int BITS, bool ROPE> hipError_t launch_flush_coop(const
     if (slots < 2) return hipErrorInvalidValue;
     int grid = items < slots ? (int)items : slots; // (items is even)
     grid = (tail_grid(a, grid, threads / 32, slots) + 1) & ~1; // (slots is even)
-    hipLaunchKernelGGL((flush_coop_kernel<G, GC, BITS, ROPE>), dim3(grid), dim3(threads), 0, s, a, (int)items);
+    hipLaunchKernelGGL((flush_coop_kernel<G, GC, BITS, ROPE, DT>), dim3(grid), dim3(threads), 0, s, a, (int)items);
     return note_launch(hipGetLastError());
+}
+
+template <int G, int GC, int BITS, bool ROPE> hipError_t launch_flush_coop(const AppendArgs &a, hipStream_t s)
+{
+    return a.geom.dtype == 1 ? launch_flush_coop_t<G, GC, BITS, ROPE, 1>(a, s) : launch_flush_coop_t<G, GC, BITS, ROPE, 0>(a, s);
 }
 
 hipError_t launch_flush(const AppendArgs &a, hipStream_t s)

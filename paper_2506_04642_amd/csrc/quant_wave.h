@@ -173,8 +173,9 @@ __device__ __forceinline__ MetaOut meta_of(float mn, float mx, int qmax)
 template <int DT> __device__ __forceinline__ uint32_t narrow2(float lo, float hi)
 {
     if (DT == 1) {
-        const __bf16 a = (__bf16)lo, b = (__bf16)hi; // the conversion instruction of this chip
-        return (uint32_t) * (const uint16_t *)&a | ((uint32_t) * (const uint16_t *)&b << 16);
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2)); // one conversion instruction for both
     }
     return (uint32_t)f16_rne(lo) | ((uint32_t)f16_rne(hi) << 16);
 }
@@ -279,21 +280,15 @@ __device__ __forceinline__ void rope_rows_t(uint4 (&pre)[8], unsigned char *rows
 #pragma unroll
     for (int j = 0; j < 8; j++) pre[j] = *(const uint4 *)(rows + (8 * tg + j) * 256 + piece_w * 16);
 }
-__device__ __forceinline__ void rope_rows(uint4 (&pre)[8], unsigned char *rows, const AppendArgs &a, int tn0, int lane, float &s0, float &s1)
+template <int DT> __device__ __forceinline__ void rope_rows(uint4 (&pre)[8], unsigned char *rows, const AppendArgs &a, int tn0, int lane, float &s0, float &s1)
 {
-#define TADAKV_ROPE(DT, HALF)                                                      \
-    do {                                                                           \
-        if (tn0 < 0) rope_rows_t<DT, HALF, true>(pre, rows, a, tn0, lane, s0, s1); \
-        else rope_rows_t<DT, HALF, false>(pre, rows, a, tn0, lane, s0, s1);        \
-    } while (0)
-    if (a.geom.dtype == 1) {
-        if (a.rope == 1) TADAKV_ROPE(1, true);
-        else TADAKV_ROPE(1, false);
+    if (a.rope == 1) {
+        if (tn0 < 0) rope_rows_t<DT, true, true>(pre, rows, a, tn0, lane, s0, s1);
+        else rope_rows_t<DT, true, false>(pre, rows, a, tn0, lane, s0, s1);
     } else {
-        if (a.rope == 1) TADAKV_ROPE(0, true);
-        else TADAKV_ROPE(0, false);
+        if (tn0 < 0) rope_rows_t<DT, false, true>(pre, rows, a, tn0, lane, s0, s1);
+        else rope_rows_t<DT, false, false>(pre, rows, a, tn0, lane, s0, s1);
     }
-#undef TADAKV_ROPE
 }
 
 // A piece of a record on its way out of a bulk append: nobody reads it before the call has ended, and the prompt's rows, which other
@@ -315,31 +310,46 @@ __device__ __forceinline__ float vmax(float a, float b) { float r; asm("v_max_f3
 __device__ __forceinline__ float vmin3(float a, float b, float c) { float r; asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
 __device__ __forceinline__ float vmax3(float a, float b, float c) { float r; asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c)); return r; }
 
-// The eight 16-byte pieces a lane loaded (eight 16-bit values each), widened to binary32; the
-// branch on the input type is taken once for all 64 values instead of as a select per value.
-__device__ __forceinline__ void widen_pieces(const uint4 (&pre)[8], int dtype, float (&x)[8][8])
+// Minima and maxima of eight values a lane each over two lane exchanges A and B (the text of DPP controls), the exchange as an operand of the
+// instruction: a move per value and exchange less than with the exchanges as instructions of their own (32 of a
+// quantiser item's thousand).  The compiler does not look for the wait states between a write and an exchanged
+// read here: two ahead of the first, and every value is written sixteen instructions before it is read again.
+#define TADAKV_EXT1(OP, I, CTRL) "v_" OP "_f32_dpp %" I ", %" I ", %" I " " CTRL " row_mask:0xf bank_mask:0xf\n\t"
+#define TADAKV_EXT16(CTRL)                                                                                                               \
+    TADAKV_EXT1("min", "0", CTRL) TADAKV_EXT1("min", "1", CTRL) TADAKV_EXT1("min", "2", CTRL) TADAKV_EXT1("min", "3", CTRL)     \
+    TADAKV_EXT1("min", "4", CTRL) TADAKV_EXT1("min", "5", CTRL) TADAKV_EXT1("min", "6", CTRL) TADAKV_EXT1("min", "7", CTRL)     \
+    TADAKV_EXT1("max", "8", CTRL) TADAKV_EXT1("max", "9", CTRL) TADAKV_EXT1("max", "10", CTRL) TADAKV_EXT1("max", "11", CTRL)   \
+    TADAKV_EXT1("max", "12", CTRL) TADAKV_EXT1("max", "13", CTRL) TADAKV_EXT1("max", "14", CTRL) TADAKV_EXT1("max", "15", CTRL)
+#define TADAKV_EXTREMA(A, B, lo, hi)                                                                                                      \
+    asm("s_nop 1\n\t" TADAKV_EXT16(A) TADAKV_EXT16(B) "s_nop 1"                                                                       \
+        : "+v"(lo[0]), "+v"(lo[1]), "+v"(lo[2]), "+v"(lo[3]), "+v"(lo[4]), "+v"(lo[5]), "+v"(lo[6]), "+v"(lo[7]), "+v"(hi[0]),         \
+          "+v"(hi[1]), "+v"(hi[2]), "+v"(hi[3]), "+v"(hi[4]), "+v"(hi[5]), "+v"(hi[6]), "+v"(hi[7]))
+// over the four lanes of a quad
+__device__ __forceinline__ void quad_extrema(float (&lo)[8], float (&hi)[8]) { TADAKV_EXTREMA("quad_perm:[1,0,3,2]", "quad_perm:[2,3,0,1]", lo, hi); }
+// over the lanes 4, 8 and 12 further in the row of sixteen (rotations)
+__device__ __forceinline__ void row_extrema(float (&lo)[8], float (&hi)[8]) { TADAKV_EXTREMA("row_ror:4", "row_ror:8", lo, hi); }
+#undef TADAKV_EXTREMA
+#undef TADAKV_EXT16
+#undef TADAKV_EXT1
+
+// The eight 16-byte pieces a lane loaded (eight 16-bit values each), widened to binary32.
+template <int DT> __device__ __forceinline__ void widen_pieces(const uint4 (&pre)[8], float (&x)[8][8])
 {
-    if (dtype == 1) {
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const uint32_t wv[4] = {pre[j].x, pre[j].y, pre[j].z, pre[j].w};
+    for (int j = 0; j < 8; j++) {
+        const uint32_t wv[4] = {pre[j].x, pre[j].y, pre[j].z, pre[j].w};
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                x[j][2 * k] = __uint_as_float(wv[k] << 16);
-                x[j][2 * k + 1] = __uint_as_float(wv[k] & 0xFFFF0000u);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const uint32_t wv[4] = {pre[j].x, pre[j].y, pre[j].z, pre[j].w};
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                x[j][2 * k] = f16_val((uint16_t)(wv[k] & 0xFFFFu));
-                x[j][2 * k + 1] = f16_val((uint16_t)(wv[k] >> 16));
-            }
+        for (int k = 0; k < 4; k++) {
+            x[j][2 * k] = low16<DT>(wv[k]);
+            x[j][2 * k + 1] = high16<DT>(wv[k]);
         }
     }
+}
+// (with the type at run time: the branch is taken once for all 64 values instead of as a select per value)
+__device__ __forceinline__ void widen_pieces(const uint4 (&pre)[8], int dtype, float (&x)[8][8])
+{
+    if (dtype == 1) widen_pieces<1>(pre, x);
+    else widen_pieces<0>(pre, x);
 }
 
 // Codes and packed words of 32 key tokens held as deviations x[token j][channel e] (lane = (tg, c8)),
