@@ -34,6 +34,7 @@
 //   matrix operands    lane (row, n): operand row / column n, 16 consecutive k-slots of group `row`.
 // This file is compiled once per width of the keys (TADA_KEY_BITS: 2, 4, 8), side by side; decode_mfma_host.cpp picks among the three.
 #include "join.h"
+#include <type_traits>
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
 
@@ -170,26 +171,29 @@ template <int B, int G, int GC, bool MEAN> struct RecLayout {
 // wait for ALL outstanding fetches, the wave's next chunk included, which is exactly the overlap
 // this kernel lives on.  Every read of a staged buffer therefore follows a wait written here
 // (stage_wait, stage_wait_but).
-template <int OFF> __device__ __forceinline__ void stage_fetch16(const unsigned char *gp, uint32_t lds)
+// NT: past the caches (a.stream).
+template <int OFF, bool NT> __device__ __forceinline__ void stage_fetch16(const unsigned char *gp, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2"
+    if (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2 nt"
+                 : : "s"(lds), "v"(gp), "n"(OFF) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2"
                  : : "s"(lds), "v"(gp), "n"(OFF) : "memory", "m0");
 }
-template <int NBYTES>
+template <int NBYTES, bool NT>
 __device__ __forceinline__ void stage_issue(const unsigned char *src, uint32_t *dst, int lane)
 {
 #pragma unroll
     for (int base = 0; base < NBYTES; base += 4096) {
         const unsigned char *gp = src + base + lane * 16;
         const uint32_t lp = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)(dst + base / 4));
-        if (base + 0 * 1024 + 1024 <= NBYTES) stage_fetch16<0>(gp, lp);
-        else if (base + 0 * 1024 < NBYTES && base + lane * 16 < NBYTES) stage_fetch16<0>(gp, lp);
-        if (base + 1 * 1024 + 1024 <= NBYTES) stage_fetch16<1024>(gp, lp);
-        else if (base + 1 * 1024 < NBYTES && base + 1024 + lane * 16 < NBYTES) stage_fetch16<1024>(gp, lp);
-        if (base + 2 * 1024 + 1024 <= NBYTES) stage_fetch16<2048>(gp, lp);
-        else if (base + 2 * 1024 < NBYTES && base + 2048 + lane * 16 < NBYTES) stage_fetch16<2048>(gp, lp);
-        if (base + 3 * 1024 + 1024 <= NBYTES) stage_fetch16<3072>(gp, lp);
-        else if (base + 3 * 1024 < NBYTES && base + 3072 + lane * 16 < NBYTES) stage_fetch16<3072>(gp, lp);
+        if (base + 0 * 1024 + 1024 <= NBYTES) stage_fetch16<0, NT>(gp, lp);
+        else if (base + 0 * 1024 < NBYTES && base + lane * 16 < NBYTES) stage_fetch16<0, NT>(gp, lp);
+        if (base + 1 * 1024 + 1024 <= NBYTES) stage_fetch16<1024, NT>(gp, lp);
+        else if (base + 1 * 1024 < NBYTES && base + 1024 + lane * 16 < NBYTES) stage_fetch16<1024, NT>(gp, lp);
+        if (base + 2 * 1024 + 1024 <= NBYTES) stage_fetch16<2048, NT>(gp, lp);
+        else if (base + 2 * 1024 < NBYTES && base + 2048 + lane * 16 < NBYTES) stage_fetch16<2048, NT>(gp, lp);
+        if (base + 3 * 1024 + 1024 <= NBYTES) stage_fetch16<3072, NT>(gp, lp);
+        else if (base + 3 * 1024 < NBYTES && base + 3072 + lane * 16 < NBYTES) stage_fetch16<3072, NT>(gp, lp);
     }
 }
 __device__ __forceinline__ void stage_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -265,20 +269,20 @@ __device__ __forceinline__ void glb_got(u32x4 &r) { asm volatile("; by hand %0" 
 // holds the image of a 64-token record, which is what the arithmetic below works on.  A wave
 // takes the two halves of a block one after the other; the pieces they share are fetched with the
 // first (shared) and stay in the buffer for the second.
-template <int B, int GC, bool MEAN>
+template <int B, int GC, bool MEAN, bool NT>
 __device__ __forceinline__ void stage_issue_half(const unsigned char *src, int hf, bool shared, uint32_t *dst, int lane)
 {
     typedef RecLayout<B, 64, GC, MEAN> RL;   // the image
     typedef RecLayout<B, 128, GC, MEAN> RS;  // the record
     constexpr int NG = kHeadDim / GC;
     static_assert(RS::KC == 2 * RL::KC && RL::KC % 1024 == 0 && RL::KC == RL::VC, "code halves (one width for keys and values)");
-    stage_issue<RL::KC>(src + RS::K_CODES + hf * RL::KC, dst + RL::K_CODES / 4, lane);
-    if (shared) stage_issue<512 + (MEAN ? 256 : 0)>(src + RS::K_SCALE, dst + RL::K_SCALE / 4, lane);
+    stage_issue<RL::KC, NT>(src + RS::K_CODES + hf * RL::KC, dst + RL::K_CODES / 4, lane);
+    if (shared) stage_issue<512 + (MEAN ? 256 : 0), NT>(src + RS::K_SCALE, dst + RL::K_SCALE / 4, lane);
 #pragma unroll
     for (int r = 0; r < RL::KC / 1024; r++)
-        stage_issue<1024>(src + RS::V_CODES + (2 * r + hf) * 1024, dst + (RL::V_CODES + r * 1024) / 4, lane);
-    stage_issue<64 * NG * 4>(src + RS::V_META + hf * 64 * NG * 4, dst + RL::V_META / 4, lane);
-    if (MEAN && shared) stage_issue<256>(src + RS::V_MEAN, dst + RL::V_MEAN / 4, lane);
+        stage_issue<1024, NT>(src + RS::V_CODES + (2 * r + hf) * 1024, dst + (RL::V_CODES + r * 1024) / 4, lane);
+    stage_issue<64 * NG * 4, NT>(src + RS::V_META + hf * 64 * NG * 4, dst + RL::V_META / 4, lane);
+    if (MEAN && shared) stage_issue<256, NT>(src + RS::V_MEAN, dst + RL::V_MEAN / 4, lane);
 }
 
 // int8 operand of the matrix instruction for the codes held in a lane
@@ -461,7 +465,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     };
     if (PG) load_slots(0);
 
-    auto issue = [&](int ci) {
+    auto issue_as = [&](auto nt, int ci) {
+        constexpr bool NT = decltype(nt)::value;
         const int blk0 = blk_of(ci);
         if (PG) {
             // every block of the chunk has a place of its own
@@ -471,22 +476,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
             for (int bi = 0; bi < NBC; bi++) {
                 const long long slot = __builtin_amdgcn_readlane(slotv[bi], it - slot_base);
                 const unsigned char *rec = a.layer + (slot * a.n_kv_heads + h) * SREC;
-                if constexpr (H2) stage_issue_half<B, GC, MEAN>(rec, blk0 & 1, !(blk0 & 1), stage, lane);
-                else stage_issue<REC>(rec, stage + bi * (REC / 4), lane);
+                if constexpr (H2) stage_issue_half<B, GC, MEAN, NT>(rec, blk0 & 1, !(blk0 & 1), stage, lane);
+                else stage_issue<REC, NT>(rec, stage + bi * (REC / 4), lane);
             }
             return;
         }
         const unsigned char *src = unit_base + (long long)(blk0 / HB) * SREC;
         if constexpr (H2) {
-            stage_issue_half<B, GC, MEAN>(src, blk0 & 1, !(blk0 & 1), stage, lane);
+            stage_issue_half<B, GC, MEAN, NT>(src, blk0 & 1, !(blk0 & 1), stage, lane);
         } else if (NBC == 1 || blk0 + 1 < b_end) {
-            stage_issue<CB>(src, stage, lane);
+            stage_issue<CB, NT>(src, stage, lane);
         } else {
             // the chunk's second block does not exist: stage the first one twice so that the
             // (masked) arithmetic on the second half still sees finite numbers
-            stage_issue<REC>(src, stage, lane);
-            stage_issue<REC>(src, stage + (NBC - 1) * (REC / 4), lane);
+            stage_issue<REC, NT>(src, stage, lane);
+            stage_issue<REC, NT>(src, stage + (NBC - 1) * (REC / 4), lane);
         }
+    };
+    auto issue = [&](int ci) {
+        if (a.stream) issue_as(std::true_type(), ci);
+        else issue_as(std::false_type(), ci);
     };
     // the query words are requested ahead of the first chunk: loads return in order, and the
     // query is worked on while the chunk is still on its way

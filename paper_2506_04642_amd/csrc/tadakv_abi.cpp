@@ -381,6 +381,15 @@ bool own_raw_splits(const kv_cache *k, const DecodeArgs &a)
 int mfma_chunk(const kv_config &c) { return c.group_tokens == 128 ? 128 : 64; } // tokens a wavefront takes at a time
 
 // even: one split count for all sequences whatever their lengths (a launch whose lengths are on the device)
+// Bytes of packed records from which a decode launch fetches them past the caches: its next reader, the next step, comes when the
+// other layers have gone by, and as ordinary reads the records only took the place of one another in the last cache (256 MB).  Below, a
+// cache of few layers is found in the L2s (32 MB together) or, with the fewer bytes a time of 2-bit records, still pays in
+// the last cache.  us a layer, 8 kv heads x 4, blocks of 32, ordinary -> past the caches, a cache of one layer, two in turn: 4 bits, 8205 tokens (12 MB)
+// 8.9 -> 9.3, 16400 (23 MB) 13.9 -> 13.7, 65536 24.9 -> 24.1, 131072 42.6 -> 39.0, 393216 102 -> 94; 8 bits, 16 x 2000 tokens (78 MB) 21.5 -> 20.8,
+// 16 x 8000 61.5 -> 54.4, 16 x 32781 223 -> 193; 2 bits, 16 x 6000 (86 MB) 23.5 -> 23.5, 16 x 8000 (115 MB) 27.2 -> 27.5,
+// 16 x 12000 (172 MB) 39.6 -> 36.4, 16 x 32781 94 -> 91.
+constexpr long long kStreamBytes = 16ll << 20, kStreamBytes2 = 128ll << 20;
+
 kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = false)
 {
     const kv_config &c = k->cfg;
@@ -407,8 +416,10 @@ kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = f
     if (a->ragged && c.batch > kMaxRaggedBatch) return KV_E_UNSUPPORTED;
     a->n_blocks = 0;
     a->r = 0;
+    long long blocks = 0;
     for (int b = 0; b < c.batch; b++) {
         const int nb = k->on(b) ? k->P(layer, b) / c.group_tokens : 0, r = k->on(b) ? k->R(layer, b) : 0;
+        blocks += nb;
         if (nb > a->n_blocks) a->n_blocks = nb;
         if (r > a->r) a->r = r;
         if (a->ragged) {
@@ -418,6 +429,7 @@ kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = f
         }
     }
     if (a->n_blocks == 0 && a->r == 0) return KV_E_EMPTY;
+    a->stream = blocks * c.n_kv_heads * a->geom.rec_bytes >= (a->geom.k_bits == 2 ? kStreamBytes2 : kStreamBytes);
     plan_even(k, a);
     if (k->forced_splits > 0) return KV_OK;
     if (!even && a->n_splits > 1 && one_split_is_enough(k, *a)) {
