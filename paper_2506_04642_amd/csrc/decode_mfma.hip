@@ -503,7 +503,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
 #pragma unroll
     for (int hg = 0; hg < NHG; hg++) {
         const int head = 4 * hg + row;
-        const uint16_t *qp = a.q + ((long long)b * a.n_q_heads + h * g + (head < g ? head : 0)) * kHeadDim;
+        const uint16_t *qp = a.q + ((long long)u * g + (head < g ? head : 0)) * kHeadDim; // (n_q_heads = n_kv_heads g)
 #pragma unroll
         for (int ph = 0; ph < 2; ph++) qraw[hg][ph] = *(const uint2 *)(qp + 32 * vq + 16 * ph + 4 * qa);
     }
@@ -518,7 +518,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
             for (int ks = 0; ks < 4; ks++) qAraw[e][ks] = *(const uint4 *)(qp + 32 * ks);
         }
     }
-    if (cw0 < n_chunks) issue(cw0);
+    // (a first chunk, cw0 < n_chunks, without waiting for the quotients that n_chunks is made of: in a launch of one chunk a wave
+    // every division ahead of the first request adds to the whole)
+    if (H2 ? cw0 < n_chunks : sp < b_mine && sp + ns * cw0 < chunks_total) issue(cw0);
     // rows 4i+3 of the operands (the unused fourth limb) must read as zero
     for (int i = lane; i < OPER_DW; i += 64) ak[i] = 0u;
     // fused cross-head form: row r (token of the chunk that starts with block blk0) of the key (which
@@ -772,10 +774,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     for (int ci = cw0, itn = 0; ci < n_chunks; ci += CW, itn++) {
         PHASE_ITER
         if (KB != 8 || VB != 8) { // the 8-bit instance runs one wave per SIMD: nothing to arbitrate
-            const int quart = itn * 4 / my_iters;
-            if (quart == 0) __builtin_amdgcn_s_setprio(3);
-            else if (quart == 1) __builtin_amdgcn_s_setprio(2);
-            else if (quart == 2) __builtin_amdgcn_s_setprio(1);
+            if (4 * itn < my_iters) __builtin_amdgcn_s_setprio(3);
+            else if (4 * itn < 2 * my_iters) __builtin_amdgcn_s_setprio(2);
+            else if (4 * itn < 3 * my_iters) __builtin_amdgcn_s_setprio(1);
             else __builtin_amdgcn_s_setprio(0);
         }
         const int blk0 = blk_of(ci);
