@@ -61,8 +61,17 @@ template <int DT> __device__ __forceinline__ float widen_hi(uint32_t w)
     return __half2float(__ushort_as_half((uint16_t)(w >> 16)));
 }
 
+// NT: a large launch (a.stream) requests its value rows past the caches.  The key rows stay ordinary reads: a request covers half of a
+// cache line of every row, and past the caches each half is fetched by itself (16 x 3000 tokens, 8 kv heads: ordinary 41.7 us, values past the
+// caches 35.2, both 38.4; 2 x 25000 45.4 / 39.2 / 41.4).
+template <bool NT> __device__ __forceinline__ uint4 load_past(const unsigned char *p)
+{
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    if (NT) return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4 *)p));
+    return *(const uint4 *)p;
+}
 // JOIN: as in the kernel of the packed layers (decode_mfma.hip).  One sequence of 12016 tokens, whose splits are too many for it: 16.85 -> 16.73 us.
-template <int DT, bool PG, bool JOIN> __global__ __launch_bounds__(64 * kRawWaves) __attribute__((amdgpu_waves_per_eu(3, 8))) void decode_split_raw_kernel(DecodeArgs a)
+template <int DT, bool PG, bool JOIN, bool NT> __global__ __launch_bounds__(64 * kRawWaves) __attribute__((amdgpu_waves_per_eu(3, 8))) void decode_split_raw_kernel(DecodeArgs a)
 {
     constexpr int NW = kRawWaves;
     constexpr int ST = 33; // floats per row of the state exchange (32 lanes of live columns, padded)
@@ -142,7 +151,7 @@ template <int DT, bool PG, bool JOIN> __global__ __launch_bounds__(64 * kRawWave
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             const int t = min(16 * (j >> 2) + 4 * row + (j & 3), w.lim);
-            x[j] = *(const uint4 *)(w.v + (t * kRowBytes + n * 16));
+            x[j] = load_past<NT>(w.v + (t * kRowBytes + n * 16));
         }
     };
 
@@ -284,7 +293,7 @@ template <int DT, bool PG> int resident_blocks()
 {
     static const int n = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_raw_kernel<DT, PG, false>, 64 * kRawWaves, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_raw_kernel<DT, PG, false, false>, 64 * kRawWaves, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -330,11 +339,17 @@ hipError_t launch_decode_split_raw(const DecodeArgs &a, hipStream_t s)
     const dim3 grid = a.uneven ? dim3(a.uneven_total, a.n_kv_heads) : dim3(a.n_splits, a.batch * a.n_kv_heads), block(64 * kRawWaves);
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
     const bool pg = a.geom.table != nullptr, bf16 = a.geom.dtype == 1;
-    auto go = [&](auto plain, auto joined) { hipLaunchKernelGGL(a.direct == 2 ? joined : plain, grid, block, 0, s, a); };
-    if (bf16 && pg) go(decode_split_raw_kernel<1, true, false>, decode_split_raw_kernel<1, true, true>);
-    else if (bf16) go(decode_split_raw_kernel<1, false, false>, decode_split_raw_kernel<1, false, true>);
-    else if (pg) go(decode_split_raw_kernel<0, true, false>, decode_split_raw_kernel<0, true, true>);
-    else go(decode_split_raw_kernel<0, false, false>, decode_split_raw_kernel<0, false, true>);
+    auto go = [&](auto plain, auto joined, auto stream, auto stream_joined) {
+        hipLaunchKernelGGL(a.stream ? (a.direct == 2 ? stream_joined : stream) : (a.direct == 2 ? joined : plain), grid, block, 0, s, a);
+    };
+#define TADAKV_RAW(DT, PG)                                                                                                      \
+    go(decode_split_raw_kernel<DT, PG, false, false>, decode_split_raw_kernel<DT, PG, true, false>, decode_split_raw_kernel<DT, PG, false, true>, \
+       decode_split_raw_kernel<DT, PG, true, true>)
+    if (bf16 && pg) TADAKV_RAW(1, true);
+    else if (bf16) TADAKV_RAW(1, false);
+    else if (pg) TADAKV_RAW(0, true);
+    else TADAKV_RAW(0, false);
+#undef TADAKV_RAW
     return note_launch(hipGetLastError());
 }
 
