@@ -64,7 +64,7 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed: %s\n%s" % (" ".join(cmd), out))
         if verbose and out.strip():
             print(out)
-    # the kernels that issue loads by hand: the compiler must have left the destinations alone
+    # the kernels that issue loads by hand: the compiler must have left the destinations alone, and the order of counted fetches
     import importlib.util
 
     spec = importlib.util.spec_from_file_location("verify_hand_loads", os.path.join(HERE, "verify_hand_loads.py"))
@@ -77,6 +77,8 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
         checked = _v.verify(os.path.join(here, unit + "-hip-amdgcn-amd-amdhsa-gfx950.s"), kernel, glob)
         if verbose:
             print("verify_hand_loads: %s: %d kernels, %d global requests, %d LDS reads" % ((os.path.join(sub, unit),) + checked))
+        if unit == "compressv":
+            _v.verify_fetch_order(os.path.join(here, unit + "-hip-amdgcn-amd-amdhsa-gfx950.s"))
         for f in os.listdir(here):
             if f.startswith(unit + "-") or f.startswith(unit + ".hip-"):
                 os.remove(os.path.join(here, f))

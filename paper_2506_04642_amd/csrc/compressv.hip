@@ -297,14 +297,17 @@ __global__ __launch_bounds__(64 * MW * NH) void compressv_gemm_kernel(ProjectArg
     // the next stage's low operands are read.  Past the last stage the fetch repeats the last one into
     // a buffer nobody reads any more and the operand read returns unused data, so that every stage is
     // the same straight line of code.
-    // (in the order of the loop: W_V of stage sg + SB, then X of stage sg + SA)
+    // (in the order of the loop: W_V of stage sg + SB, then X of stage sg + SA.  The waits count on it, and to the compiler the
+    // buffers are unrelated: the barriers keep it from exchanging requests, and the build reads the order that came out)
 #pragma unroll
     for (int sg = -SA; sg < 0; sg++) {
         if (sg + SB >= 0)
 #pragma unroll
             for (int i = 0; i < PB; i++) issue_b(sg + SB, B0 + (sg + SB) * B_BYTES, i);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < PA; i++) issue_a(sg + SA, (sg + SA) * A_BYTES, i);
+        __builtin_amdgcn_sched_barrier(0);
     }
     // fetches that may be on their way when the next stage's two tiles have to be there
     constexpr int LATER = (SB - 2) * (PA + PB) + (SA > SB ? PA : 0);

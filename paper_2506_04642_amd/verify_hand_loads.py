@@ -16,6 +16,11 @@ build reads what the compiler produced and refuses it unless, in every kernel,
     next `s_waitcnt` with `lgkmcnt(0)` names a destination of such a read;
   * no scratch-memory instruction lies between a request and its hand-over.
 
+The projection kernel of csrc/compressv.hip also counts its fetches into LDS: a wait for all but the last
+N of them is a wait for a tile only if the requests went out in the order that the source gives, and
+to the compiler the staging buffers are unrelated memory.  verify_fetch_order reads the requests
+ahead of the kernel's first wait for them.
+
 The check follows the text in order, as the requests and hand-overs are written in straight-line code
 (a wait may sit inside a branch, never a request or a hand-over); from reads at the end of a loop body
 it follows the path that leaves the loop, not the back edge."""
@@ -119,6 +124,62 @@ def check_text(text, kernel="decode_split_mfma_kernel"):
         total += n
         total_lds += nl
     return problems, kernels, total, total_lds
+
+
+_GEMM = re.compile(r"_Z\S*compressv_gemm_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E\S*:\s*")
+
+
+def fetch_order(heads, tokens, waves, sa, sb):
+    """The first requests of a wave of the projection kernel, as (byte of the staging buffers, pieces of 1 KiB): W_V of
+    stage s + sb, then X of stage s + sa, for s = -sa .. -1."""
+    a, b = tokens * 128, heads * 128 * 128
+    out = []
+    for s in range(-sa, 0):
+        if s + sb >= 0:
+            out.append((sa * a + (s + sb) * b, b // 1024 // waves))
+        out.append(((s + sa) * a, a // 1024 // waves))
+    return out
+
+
+def check_fetch_order(text):
+    """(problems, kernels checked) of an assembly file: do the projection kernels request their first stages in
+    the order that their waits count on?"""
+    lines = text.split("\n")
+    problems, kernels = [], 0
+    for start, line in enumerate(lines):
+        m = _GEMM.match(line)
+        if not m:
+            continue
+        kernels += 1
+        _, heads, _, _, wt, mw, sa, sb = (int(x) for x in m.groups())
+        name, got, m0 = line.split(":")[0], [], None
+        for no in range(start + 1, len(lines)):
+            code = _code(lines[no])
+            if lines[no].startswith(".Lfunc_end") or code.startswith("s_barrier"):
+                break
+            if re.match(r"s_\S+\s+m0,", code):
+                # the wave's own place in a tile is in the register, the buffer's in the literal
+                at = re.match(r"s_(?:mov_b32|add_i32|add_u32)\s+m0, (s\d+)(?:, (0x[0-9a-f]+|\d+))?$", code)
+                m0 = int(at.group(2) or "0", 0) if at else None
+            elif code.startswith("global_load_lds_dwordx4"):
+                if m0 is None:
+                    problems.append("%s: line %d: where a fetch goes is not known" % (name, no + 1))
+                got.append(m0)
+        want = [at + 1024 * i for at, n in fetch_order(heads, wt * mw, mw * heads, sa, sb) for i in range(n)]
+        if got != want:
+            problems.append("%s: the first fetches go to %s, the waits count on %s" % (name, got, want))
+    return problems, kernels
+
+
+def verify_fetch_order(path):
+    """Raises RuntimeError unless every projection kernel in the assembly file at `path` keeps its order."""
+    with open(path) as f:
+        problems, kernels = check_fetch_order(f.read())
+    if kernels == 0:
+        raise RuntimeError("%s: no projection kernel found: nothing was checked" % path)
+    if problems:
+        raise RuntimeError("order of fetches: %d problem(s) in %s\n%s" % (len(problems), path, "\n".join(problems[:20])))
+    return kernels
 
 
 def verify(path, kernel="decode_split_mfma_kernel", global_loads=True):

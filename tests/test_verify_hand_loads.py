@@ -108,3 +108,32 @@ def test_a_file_without_hand_loads_is_refused(tmp_path):
     g = tmp_path / "good.s"
     g.write_text(GOOD)
     assert v.verify(str(g)) == (1, 1, 1)
+
+
+def projection(order):
+    """The start of a kernel of 256 tokens x 2 heads with three stages of X and two of W_V, its first fetches in this order of tiles."""
+    place = {"X0": 0, "X1": 0x8000, "X2": 0x10000, "W0": 0x18000, "W1": 0x20000}
+    body = ["_ZN6tadakv12_GLOBAL__N_121compressv_gemm_kernelILi1ELi2ELi32ELi4ELi64ELi4ELi3ELi2EEEvNS_11ProjectArgsE:"]
+    for tile in order.split():
+        for i in range(4):
+            at = place[tile] + 1024 * i
+            body.append("\ts_add_i32 m0, s7, %s" % hex(at) if at else "\ts_mov_b32 m0, s7")
+            body.append("\tglobal_load_lds_dwordx4 v[2:3], off")
+    return "\n".join(body + ["\ts_waitcnt vmcnt(12)", "\ts_barrier", "\ts_endpgm", ".Lfunc_end0:"])
+
+
+def test_the_projection_requests_its_stages_in_the_order_its_waits_count_on():
+    assert v.check_fetch_order(projection("X0 W0 X1 W1 X2")) == ([], 1)
+    # X of the third stage ahead of W_V of the second: the wait for all but four lets the loop read W_V too early
+    for order in ("X0 W0 X1 X2 W1", "X0 X1 W0 W1 X2", "X0 W0 X1 W1"):
+        problems, kernels = v.check_fetch_order(projection(order))
+        assert kernels == 1 and len(problems) == 1, order
+    unread = projection("X0 W0 X1 W1 X2").replace("s_mov_b32 m0, s7", "s_lshl_b32 m0, s7, 2")
+    assert any("not known" in p for p in v.check_fetch_order(unread)[0])
+
+
+def test_a_file_without_projection_kernels_is_refused(tmp_path):
+    f = tmp_path / "other.s"
+    f.write_text(GOOD)
+    with pytest.raises(RuntimeError):
+        v.verify_fetch_order(str(f))
