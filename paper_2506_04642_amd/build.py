@@ -16,11 +16,14 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # (the assembly text is kept next to the object and read by verify_hand_loads after the compile)
 MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm", "-save-temps=obj"]
 # (source, extra flags, object folder below _build): the quantiser is compiled without fused multiply-add contraction so
-# that every binary32 operation rounds once, in the order written; the split kernel's widths compile side by side
+# that every binary32 operation rounds once, in the order written; the split kernel's units compile side by side
 UNITS = [
     ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=8"], "k8"),
     ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=4"], "k4"),
     ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=2"], "k2"),
+    ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=8", "-DTADA_STREAM=1"], "k8s"),
+    ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=4", "-DTADA_STREAM=1"], "k4s"),
+    ("decode_mfma.hip", MFMA + ["-DTADA_KEY_BITS=2", "-DTADA_STREAM=1"], "k2s"),
     ("tadakv_abi.cpp", ["-x", "hip"], ""),
     ("quant_append.hip", ["-ffp-contract=off"], ""),
     ("compressv.hip", ["-ffp-contract=off", "-mllvm", "-amdgpu-mfma-vgpr-form", "-save-temps=obj"], ""),
@@ -71,7 +74,7 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
     _v = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(_v)  # (by path: this file also runs as a script)
 
-    hand = [("decode_mfma", k, "decode_split_mfma_kernel", True) for k in ("k2", "k4", "k8")] + [("compressv", "", "compressv_gemm_kernel", False)]
+    hand = [("decode_mfma", k, "decode_split_mfma_kernel", True) for k in ("k2", "k4", "k8", "k2s", "k4s", "k8s")] + [("compressv", "", "compressv_gemm_kernel", False)]
     for unit, sub, kernel, glob in hand:
         here = os.path.join(objdir, sub)
         checked = _v.verify(os.path.join(here, unit + "-hip-amdgcn-amd-amdhsa-gfx950.s"), kernel, glob)

@@ -32,15 +32,18 @@
 //                      16-channel tile (values).
 //   key-side producer  lane (row, vq, qa): head 4*hg + row, channels 32*vq + 16*ph + 4*qa + {0..3}.
 //   matrix operands    lane (row, n): operand row / column n, 16 consecutive k-slots of group `row`.
-// This file is compiled once per width of the keys (TADA_KEY_BITS: 2, 4, 8), side by side; decode_mfma_host.cpp picks among the three.
+// This file is compiled twice per width of the keys (TADA_KEY_BITS: 2, 4, 8), side by side: for launches that fetch their records past
+// the caches (TADA_STREAM 1: DecodeArgs::stream) and for the others, which so carry nothing of it.  decode_mfma_host.cpp picks.
 #include "join.h"
-#include <type_traits>
 #include <hip/hip_ext.h>
 #include <hip/hip_fp16.h>
 
 #define TADA_NAMED_2(name, w) name##w
 #define TADA_NAMED_1(name, w) TADA_NAMED_2(name, w)
 #define TADA_NAMED(name) TADA_NAMED_1(name, TADA_KEY_BITS)
+#ifndef TADA_STREAM
+#define TADA_STREAM 0
+#endif
 
 namespace tadakv {
 namespace {
@@ -171,7 +174,7 @@ template <int B, int G, int GC, bool MEAN> struct RecLayout {
 // wait for ALL outstanding fetches, the wave's next chunk included, which is exactly the overlap
 // this kernel lives on.  Every read of a staged buffer therefore follows a wait written here
 // (stage_wait, stage_wait_but).
-// NT: past the caches (a.stream).
+// NT: past the caches.
 template <int OFF, bool NT> __device__ __forceinline__ void stage_fetch16(const unsigned char *gp, uint32_t lds)
 {
     if (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2 nt"
@@ -294,7 +297,7 @@ template <> struct CodeOps<4> { // two words = one tile line of 16 codes
     }
 };
 // Phase clocks (a build with -DTADA_PHASE_CLOCK only; the library proper carries none of it): every
-// wave sums the cycles between the marks of the main loop; kv_debug_phase_clocks_2, _4 and _8 hand the sums out.
+// wave sums the cycles between the marks of the main loop; kv_debug_phase_clocks_2, _4 and _8 (kv_debug_phase_clocks_stream_2 ..) hand the sums out.
 #ifdef TADA_PHASE_CLOCK
 __device__ unsigned long long tada_phase_clk[16];
 #define PHASE_INIT unsigned long long pclk_[14] = {}; unsigned long long plast_ = __builtin_readcyclecounter(); int piter_ = 0;
@@ -349,7 +352,11 @@ template <> struct CodeOps<8> { // four words = one tile line; split into nibble
 // (Two of the joining instances, at 2 bits with two head groups, take 142 to 146 registers if they are left to, and a compute unit
 // holds three of their workgroups then; bound to four, 122 to 125 and no spills: 64 sequences of 1000 tokens, 4 kv heads, blocks of
 // 64 24.40 -> 20.87 us, of 128 26.08 -> 25.77.)
-template <int B, int GS, int GC, bool MEAN, int NW, int NHG, int XH, bool PG, bool JOIN>
+// NT: the records are fetched past the caches.  A matter of the instance, not of a branch at the two places that request a
+// chunk: with the code of both a kernel was 3 to 14 % longer and spilled up to 13 scalar registers (3 now), which short launches, that never fetch
+// past the caches, paid for: both -> one (us a call), 2 x 2000 tokens paged, blocks of 128, 8 kv heads x 4, 8 bits 9.09 -> 8.86, 2 bits
+// 7.79 -> 7.68; 4 x 1000 tokens, blocks of 64, no mean, 8 heads a kv head, 4 bits 9.76 -> 9.68.
+template <int B, int GS, int GC, bool MEAN, int NW, int NHG, int XH, bool PG, bool JOIN, bool NT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2 && NHG == 1 && !XH) ? (PG ? 3 : 4) : (JOIN && B == 2 && NHG == 2 && GS >= 64 && GC == 128 && !MEAN) ? 4 : 1, 8))) void decode_split_mfma_kernel(DecodeArgs a)
 {
     static_assert(!(XH && MEAN), "cross-head layers store no per-record mean");
@@ -465,8 +472,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     };
     if (PG) load_slots(0);
 
-    auto issue_as = [&](auto nt, int ci) {
-        constexpr bool NT = decltype(nt)::value;
+    auto issue = [&](int ci) {
         const int blk0 = blk_of(ci);
         if (PG) {
             // every block of the chunk has a place of its own
@@ -492,10 +498,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
             stage_issue<REC, NT>(src, stage, lane);
             stage_issue<REC, NT>(src, stage + (NBC - 1) * (REC / 4), lane);
         }
-    };
-    auto issue = [&](int ci) {
-        if (a.stream) issue_as(std::true_type(), ci);
-        else issue_as(std::false_type(), ci);
     };
     // the query words are requested ahead of the first chunk: loads return in order, and the
     // query is worked on while the chunk is still on its way
@@ -1345,21 +1347,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((B == 2
     }
 }
 
-// Resident workgroups of one instantiation on the whole device (0 if the query fails).
-template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> int resident_blocks()
-{
-    static const int n = [] {
-        int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, false>,
-                                                         64 * NW, 0) != hipSuccess)
-            return 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        return per_cu * cus;
-    }();
-    return n;
-}
-
 // XH == 2 (both cross-head mean terms inside the kernel): a workgroup per (sequence, split) and NW kv heads.
 template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG, bool JOIN> hipError_t enqueue(const DecodeArgs &a, hipStream_t s, SplitTiming &ev)
 {
@@ -1368,10 +1355,10 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG, boo
     (void)hipGetLastError(); // drop any stale error left by earlier runtime calls of this thread
     if (ev.begin && ev.end) {
         // the dispatch itself stamps the events: the kernel's execution, without the gaps before and after it
-        hipExtLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, JOIN>), grid, dim3(64 * NW), 0, s, ev.begin, ev.end, 0, a);
+        hipExtLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, JOIN, TADA_STREAM>), grid, dim3(64 * NW), 0, s, ev.begin, ev.end, 0, a);
         ev = SplitTiming{};
     } else {
-        hipLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, JOIN>), grid, dim3(64 * NW), 0, s, a);
+        hipLaunchKernelGGL((decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, JOIN, TADA_STREAM>), grid, dim3(64 * NW), 0, s, a);
     }
     return note_launch(hipGetLastError());
 }
@@ -1388,6 +1375,22 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> hip
             return enqueue<B, G, GC, MEAN, NW, NHG, XH, PG, true>(a, s, ev);
     }
     return hipErrorInvalidValue;
+}
+
+#if !TADA_STREAM // (a launch is planned as one without)
+// Resident workgroups of one instantiation on the whole device (0 if the query fails).
+template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> int resident_blocks()
+{
+    static const int n = [] {
+        int per_cu = 0, dev = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_split_mfma_kernel<B, G, GC, MEAN, NW, NHG, XH, PG, false, false>,
+                                                         64 * NW, 0) != hipSuccess)
+            return 0;
+        if (hipGetDevice(&dev) != hipSuccess) return 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        return per_cu * cus;
+    }();
+    return n;
 }
 
 // Split count that puts every workgroup of the launch on the device at once (one "round"):
@@ -1409,6 +1412,7 @@ template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> int
     if (ns < 1) ns = 1;
     return ns;
 }
+#endif
 
 // what to do with the instance selected by the layer's format
 struct DoLaunch {
@@ -1417,6 +1421,7 @@ struct DoLaunch {
     hipError_t result = hipErrorInvalidValue;
     template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &a) { result = launch_inst<B, G, GC, MEAN, NW, NHG, XH, PG>(a, s, *ev); }
 };
+#if !TADA_STREAM
 struct DoPlan {
     int result = 1;
     template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &a) { result = plan_inst<B, G, GC, MEAN, NW, NHG, XH, PG>(a); }
@@ -1429,6 +1434,7 @@ struct DoMatch {
     bool result = false;
     template <int B, int G, int GC, bool MEAN, int NW, int NHG, int XH, bool PG> void run(const DecodeArgs &a) { result = RecLayout<B, G, GC, MEAN>::matches(a.geom); }
 };
+#endif
 
 template <int B, int G, int GC, bool PG, class F> void pick_mean_heads_pg(const DecodeArgs &a, F &f)
 {
@@ -1516,6 +1522,7 @@ template <class F> void pick(const DecodeArgs &a, F &f)
 #undef TADAKV_PICK
 }
 
+#if !TADA_STREAM
 bool matches(const DecodeArgs &a)
 {
     DoMatch m;
@@ -1534,6 +1541,7 @@ int slots(const DecodeArgs &a)
     pick(a, p);
     return p.result;
 }
+#endif
 hipError_t launch(const DecodeArgs &a, hipStream_t s, SplitTiming &ev)
 {
     DoLaunch l;
@@ -1545,14 +1553,22 @@ hipError_t launch(const DecodeArgs &a, hipStream_t s, SplitTiming &ev)
 
 } // namespace
 
-MfmaWidth TADA_NAMED(mfma_width_)() { return MfmaWidth{matches, splits, slots, launch}; }
+#if TADA_STREAM
+hipError_t TADA_NAMED(mfma_stream_)(const DecodeArgs &a, hipStream_t s, SplitTiming &ev) { return launch(a, s, ev); }
+#else
+MfmaWidth TADA_NAMED(mfma_width_)() { return MfmaWidth{matches, splits, slots, launch, TADA_NAMED(mfma_stream_)}; }
+#endif
 
 } // namespace tadakv
 
 #ifdef TADA_PHASE_CLOCK
 // out[0..13]: cycles summed over all waves per phase; out[14]: loop iterations; out[15]: waves.
 // reset != 0 clears the sums afterwards.
+#if TADA_STREAM
+extern "C" int TADA_NAMED(kv_debug_phase_clocks_stream_)(unsigned long long *out, int reset)
+#else
 extern "C" int TADA_NAMED(kv_debug_phase_clocks_)(unsigned long long *out, int reset)
+#endif
 {
     if (hipDeviceSynchronize() != hipSuccess) return -1;
     if (hipMemcpyFromSymbol(out, HIP_SYMBOL(tadakv::tada_phase_clk), 16 * sizeof(unsigned long long)) != hipSuccess) return -1;

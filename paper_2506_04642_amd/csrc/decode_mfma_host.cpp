@@ -1,5 +1,5 @@
-// The matrix-core split kernel's host side: which layers it serves, and which of its three units, one per width of the
-// keys, a layer's instance is in (decode_mfma.hip).
+// The matrix-core split kernel's host side: which layers it serves, and which of its six units, two per width of the
+// keys, a launch's instance is in (decode_mfma.hip).
 #include "tadakv_internal.h"
 
 namespace tadakv {
@@ -43,7 +43,8 @@ hipError_t launch_decode_split_mfma(const DecodeArgs &a, hipStream_t s)
         const hipError_t e = launch_xhead_scores(a, s);
         if (e != hipSuccess) return e;
     }
-    return width(a).launch(a, s, t_ev);
+    const MfmaWidth w = width(a);
+    return a.stream ? w.launch_stream(a, s, t_ev) : w.launch(a, s, t_ev);
 }
 
 } // namespace tadakv

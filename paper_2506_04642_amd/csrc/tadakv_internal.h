@@ -138,7 +138,8 @@ struct DecodeArgs {
     // kernel joins the splits itself (join.h) and counts the finished workgroups of each unit at `sync`
     int direct;
     int blocks_per_split;
-    // the launch's records are fetched past the caches (matrix-core kernel and the kernel of the 16-bit layers)
+    // the launch's records are fetched past the caches (matrix-core kernel and the kernel of the 16-bit layers; read by the host, which
+    // launches another instance)
     int stream;
     // matrix-core kernel only: the newest residual token (index r - 1) is not in the cache yet;
     // the kernel takes it from these rows and stores it (null: every token is in the cache)
@@ -246,7 +247,7 @@ __device__ __forceinline__ void decode_args_here(const DecodeArgs &a)
 {
     const LayerGeom &g = a.geom;
     asm volatile("" : : "s"(a.n_kv_heads), "s"(a.n_q_heads), "s"(a.batch), "s"(a.g), "s"(a.n_blocks), "s"(a.r), "s"(a.n_splits),
-                 "s"(a.uneven), "s"(a.resid_splits), "s"(a.direct), "s"(a.stream), "s"(a.out), "s"(a.ragged), "s"(a.len_dev), "s"(a.layer), "s"(a.q), "s"(a.ws),
+                 "s"(a.uneven), "s"(a.resid_splits), "s"(a.direct), "s"(a.out), "s"(a.ragged), "s"(a.len_dev), "s"(a.layer), "s"(a.q), "s"(a.ws),
                  "s"(g.NB), "s"(g.R), "s"(g.dtype), "s"(g.k_resid_off), "s"(g.v_resid_off), "s"(a.k_fresh), "s"(g.table),
                  "s"(g.table_stride), "s"(g.pool));
 }
@@ -313,8 +314,11 @@ struct MfmaWidth {
     int (*splits)(const DecodeArgs &a);
     int (*slots)(const DecodeArgs &a);
     hipError_t (*launch)(const DecodeArgs &a, hipStream_t s, SplitTiming &ev); // ev: recorded into, then cleared
+    hipError_t (*launch_stream)(const DecodeArgs &a, hipStream_t s, SplitTiming &ev); // with DecodeArgs::stream
 };
 MfmaWidth mfma_width_2(), mfma_width_4(), mfma_width_8();
+hipError_t mfma_stream_2(const DecodeArgs &a, hipStream_t s, SplitTiming &ev), mfma_stream_4(const DecodeArgs &a, hipStream_t s, SplitTiming &ev),
+    mfma_stream_8(const DecodeArgs &a, hipStream_t s, SplitTiming &ev);
 // Does the layer get the fused cross-head form (both mean terms inside the split kernel)?  It takes a
 // wave per kv head, a multiple of 4 kv heads.
 inline bool xhead_fused_fmt(const DecodeArgs &a) { return a.geom.mean_mode == 1 && a.n_kv_heads % 4 == 0; }

@@ -14,7 +14,9 @@ build reads what the compiler produced and refuses it unless, in every kernel,
     hand-over names any of its registers;
   * no instruction between a hand-issued `ds_read_b128` (inside an inline-assembly block) and the
     next `s_waitcnt` with `lgkmcnt(0)` names a destination of such a read;
-  * no scratch-memory instruction lies between a request and its hand-over.
+  * no scratch-memory instruction lies between a request and its hand-over;
+  * the fetches from global memory into LDS are all past the caches (`nt`) or none is: which of the two a launch
+    wants is a matter of the instance it calls, so that no kernel carries the code of both.
 
 The projection kernel of csrc/compressv.hip also counts its fetches into LDS: a wait for all but the last
 N of them is a wait for a tile only if the requests went out in the order that the source gives, and
@@ -54,6 +56,7 @@ def check_kernel(name, lines):
     lds_pending = {}
     in_asm = False
     n_requests = n_lds = 0
+    forms = set()  # of the fetches into LDS
     for no, line in lines:
         if "#ASMSTART" in line:
             in_asm = True
@@ -90,6 +93,8 @@ def check_kernel(name, lines):
         if code.startswith("s_waitcnt") and "lgkmcnt(0)" in code:
             lds_pending.clear()  # (whoever issued it: nothing read from LDS is still on its way)
             continue
+        if code.startswith("global_load_lds"):
+            forms.add("nt" in code.split())
         named = _regs(code)
         if pending:
             if code.startswith("scratch_"):
@@ -102,6 +107,8 @@ def check_kernel(name, lines):
                 problems.append("%s: line %d `%s` names a register of the LDS read at line %d" % (name, no, code, at))
         if code.startswith("s_endpgm") and (pending or lds_pending):
             problems.append("%s: requests never handed over: lines %s" % (name, sorted(pending) + sorted(lds_pending)))
+    if len(forms) > 1:
+        problems.append("%s: fetches into LDS both past the caches and not" % name)
     return problems, n_requests, n_lds
 
 

@@ -100,6 +100,14 @@ def test_scratch_traffic_and_early_use_of_an_lds_read_are_found():
     assert any("LDS read" in p for p in problems)
 
 
+def test_fetches_of_both_forms_in_one_kernel_are_found():
+    plain, past = "\tglobal_load_lds_dwordx4 v[2:3], off offset:1024\n", "\tglobal_load_lds_dwordx4 v[2:3], off offset:1024 nt\n"
+    for body in (plain * 2, past * 2):
+        assert v.check_text(kernel(body))[0] == []
+    problems, _, _, _ = v.check_text(kernel(plain + past))
+    assert len(problems) == 1 and "both past the caches and not" in problems[0]
+
+
 def test_a_file_without_hand_loads_is_refused(tmp_path):
     f = tmp_path / "empty.s"
     f.write_text(kernel("\tv_mov_b32_e32 v0, v1\n"))
