@@ -384,6 +384,10 @@ kv_status kv_set_decode_path(kv_cache *cache, int32_t path);
  * of the rate: this call makes that visible.  (A 16-bit layer reports 1 as well, see kv_set_decode_path.)  Errors as kv_decode_splits. */
 kv_status kv_decode_path_used(const kv_cache *cache, int32_t layer, int32_t *path);
 
+/* Would a decode call of `layer` on the matrix-core kernels or the kernel of the 16-bit layers fetch the layer's records past
+ * the caches, in the cache's present state (*past = 1), or through them (0)?  A matter of the records' bytes; the output is the same. */
+kv_status kv_decode_past_caches(const kv_cache *cache, int32_t layer, int32_t *past);
+
 /* Force the number of sequence splits of later decode calls on this cache (clamped to the number
  * of blocks); 0 restores the automatic choice.  The workspace must then hold
  * batch * n_q_heads * n_splits * 132 floats (with KV_MEAN_CROSS_HEAD on the matrix-core kernels: the

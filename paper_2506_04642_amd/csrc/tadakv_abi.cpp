@@ -380,16 +380,30 @@ bool own_raw_splits(const kv_cache *k, const DecodeArgs &a)
 }
 int mfma_chunk(const kv_config &c) { return c.group_tokens == 128 ? 128 : 64; } // tokens a wavefront takes at a time
 
-// even: one split count for all sequences whatever their lengths (a launch whose lengths are on the device)
-// Bytes of packed records from which a decode launch fetches them past the caches: its next reader, the next step, comes when the
-// other layers have gone by, and as ordinary reads the records only took the place of one another in the last cache (256 MB).  Below, a
-// cache of few layers is found in the L2s (32 MB together) or, with the fewer bytes a time of 2-bit records, still pays in
-// the last cache.  us a layer, 8 kv heads x 4, blocks of 32, ordinary -> past the caches, a cache of one layer, two in turn: 4 bits, 8205 tokens (12 MB)
-// 8.9 -> 9.3, 16400 (23 MB) 13.9 -> 13.7, 65536 24.9 -> 24.1, 131072 42.6 -> 39.0, 393216 102 -> 94; 8 bits, 16 x 2000 tokens (78 MB) 21.5 -> 20.8,
-// 16 x 8000 61.5 -> 54.4, 16 x 32781 223 -> 193; 2 bits, 16 x 6000 (86 MB) 23.5 -> 23.5, 16 x 8000 (115 MB) 27.2 -> 27.5,
-// 16 x 12000 (172 MB) 39.6 -> 36.4, 16 x 32781 94 -> 91.
-constexpr long long kStreamBytes = 16ll << 20, kStreamBytes2 = 128ll << 20;
+// Does a decode launch over `blocks` packed blocks of a layer fetch their records past the caches?  A record's next reader, the
+// next step, comes when the other layers have gone by, and as ordinary reads the records only take the place of one another.
+// What the L2s (32 MB together) hold is left to them; layers of 2 bits take fewer bytes a time, for which the last cache (256 MB) is fast
+// enough, and have a line of their own.  us a layer, ordinary -> past the caches, for one layer, two, four or eight (1:, 2: ..) in turn:
+//   4 bits, 24 MB  1: 12.3 -> 13.0  2: 13.6 -> 13.2  4: 13.7 -> 13.8  8: 14.0 -> 14.2   8 bits  1: 10.9 -> 11.6  2: 12.2 -> 12.0  4: 12.3 -> 12.4
+//           44 MB  1: 14.0 -> 12.8  2: 14.7 -> 14.0                                             1: 15.7 -> 14.3  2: 16.2 -> 15.3
+//          640 MB  1: 122 -> 108    2: 122 -> 110                                               1: 120 -> 105    2: 120 -> 106
+//   8 bits, blocks of 128, 48 MB  1: 14.4 -> 13.5  2: 14.4 -> 14.8   keys 2, values 8 bits, 48 MB  1: 16.8 -> 15.6  2: 17.0 -> 16.5
+//   4 bits, mean over the heads, 24 MB  1: 20.7 -> 21.4  8: 21.5 -> 21.9   48 MB  1: 26.2 -> 26.8  2: 26.1 -> 28.0  8: 28.5 -> 27.3
+//   16 bits, 24 MB  1: 11.0 -> 11.2  8: 9.9 -> 10.2   48 MB  1: 16.1 -> 15.9  2: 16.2 -> 16.9  8: 18.3 -> 17.2   256 MB  1: 46.1 -> 46.4  2: 54.8 -> 46.8
+//   2 bits, 64 MB  1: 21.0 -> 20.2  4: 20.4 -> 21.2   128 MB  1: 31.5 -> 31.3  2: 31.2 -> 32.4  4: 34.6 -> 32.7   192 MB  1: 42.6 -> 42.7  2: 46.3 -> 42.2
+// (Past the line one or two layers that the last cache holds together still lose, up to 7 % with the mean over the heads, 4 % at 16 bits and
+// 6 % at 8 bits in blocks of 128; the layers of a model do not fit it.)
+// Under paged placement sequences may name the same slots, whose records the caches then serve to all but the first: no more bytes
+// than the pool's are counted (one slot for all, 8 bits, 16 x 2000 tokens 16.3 -> 16.8; 16 x 30000, a pool of 73 MB, 172 -> 163).
+constexpr long long kStreamBytes = 40ll << 20, kStreamBytes2 = 128ll << 20;
+bool past_the_caches(const kv_cache *k, int layer, long long blocks)
+{
+    const LayerGeom &g = k->geom[layer];
+    if (k->cfg.pool_blocks > 0 && blocks > k->cfg.pool_blocks) blocks = k->cfg.pool_blocks;
+    return blocks * k->cfg.n_kv_heads * g.rec_bytes >= (g.k_bits == 2 && g.v_bits == 2 ? kStreamBytes2 : kStreamBytes);
+}
 
+// even: one split count for all sequences whatever their lengths (a launch whose lengths are on the device)
 kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = false)
 {
     const kv_config &c = k->cfg;
@@ -429,7 +443,7 @@ kv_status fill_decode(const kv_cache *k, int layer, DecodeArgs *a, bool even = f
         }
     }
     if (a->n_blocks == 0 && a->r == 0) return KV_E_EMPTY;
-    a->stream = blocks * c.n_kv_heads * a->geom.rec_bytes >= (a->geom.k_bits == 2 ? kStreamBytes2 : kStreamBytes);
+    a->stream = past_the_caches(k, layer, blocks);
     plan_even(k, a);
     if (k->forced_splits > 0) return KV_OK;
     if (!even && a->n_splits > 1 && one_split_is_enough(k, *a)) {
@@ -981,6 +995,18 @@ kv_status kv_decode_path_used(const kv_cache *cache, int32_t layer, int32_t *pat
     if (st != KV_OK) return st;
     if (cache->decode_path == 2 && !decode_mfma_supported(a)) return KV_E_UNSUPPORTED;
     *path = use_mfma(cache, a) ? 2 : 1;
+    return KV_OK;
+}
+
+kv_status kv_decode_past_caches(const kv_cache *cache, int32_t layer, int32_t *past)
+{
+    kv_status st = layer_ok(cache, layer);
+    if (st != KV_OK) return st;
+    if (!past) return KV_E_NULL;
+    long long blocks = 0;
+    for (int b = 0; b < cache->cfg.batch; b++)
+        if (cache->on(b)) blocks += cache->P(layer, b) / cache->cfg.group_tokens;
+    *past = past_the_caches(cache, layer, blocks);
     return KV_OK;
 }
 
