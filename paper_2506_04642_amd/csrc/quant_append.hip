@@ -428,7 +428,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((G == 
 // compiler moved every value to a common register behind each (64 of a value item's 1130 vector instructions), and the extrema's lane exchanges
 // were moves of their own (32 more).  Without: 2 x 15003 tokens of 8 heads at 4 and 2 bits, rotated, 90.8 -> 83.5 us;
 // plain, 16 x 4096 at 2, 4 and 8 bits 207.5 -> 200, 16 x 2000 at 4 bits 36.5 -> 34.1.
-template <int GC, int BITS, bool ROPE, int DT>
+// Items (8 KiB of rows each) from which a call's input, 320 MiB and more, comes from memory whatever was read before it.  Memory is then busy
+// with fewer waves, and more of them only get in one another's way, where an item is little work for its bytes: at 8 bits, and at 4
+// bits without a mean, two workgroups a compute unit in place of three.  At 8 bits, with half as many bytes written as read, the records of
+// eight sequences and more are stored plainly (PLAIN): as streaming stores they leave for many distant places at once.
+// us a call, 8 kv heads, three inputs in turn, before -> with this: 8 bits, 16 x 6000 tokens 133 -> 130, 16 x 8192 178 -> 172, 32 x 5000 235 -> 217,
+// 1 x 131072 168 -> 162, 1 x 262144 339 -> 322 (16 x 12288 314 -> 318), without a mean 16 x 8192 212 -> 196; 4 bits without a mean,
+// 16 x 16384 289 -> 272, 1 x 131072 137 -> 131, 12 x 9001 123 -> 123.  Elsewhere it loses: two workgroups, 8 bits, 16 x 1000 20.8 -> 23.6, 4 bits with a
+// mean 1 x 131072 146 -> 157, 2 bits without one 123 -> 128; plain stores, 4 bits 16 x 6000 108 -> 113 (16 x 16384 319 -> 309), mean over the heads
+// at 8 bits 337 -> 353.
+constexpr int kLongItems = 40960;
+template <int GC, int BITS, bool ROPE, int DT, bool PLAIN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))) void flush_wave_kernel(AppendArgs a, int n_items)
 {
     constexpr int G = 32;
@@ -705,7 +715,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
         if (which == 0) part_bytes = (gm.mean_mode == 0 ? gm.k_mean : gm.k_zero) + 256 - base_off;
         else part_bytes = (gm.mean_mode == 0 ? gm.v_mean + 256 : gm.v_meta + G * NGV * 4) - base_off;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // this wave's LDS writes have landed
-        for (int off = lane * 16; off < part_bytes; off += 64 * 16) put_record((uint4 *)(rec + base_off + off), *(const uint4 *)(img + off));
+        for (int off = lane * 16; off < part_bytes; off += 64 * 16) put_record<!PLAIN>((uint4 *)(rec + base_off + off), *(const uint4 *)(img + off));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the image is in registers before the next item overwrites it
     }
     tail_rows<kThreads, ROPE>(a);
@@ -1239,16 +1249,25 @@ template <int GC, int BITS, bool ROPE, int DT> hipError_t launch_flush_wave_t(co
     if (items > 0x7FFFFFFF) return hipErrorInvalidValue;
     static const int slots = [] {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_wave_kernel<GC, BITS, ROPE, DT>, kThreads, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, flush_wave_kernel<GC, BITS, ROPE, DT, false>, kThreads, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
         return per_cu * cus;
     }();
     if (slots < 1) return hipErrorInvalidValue;
+    const int mode = a.geom.mean_mode;
+    const bool fewer = !ROPE && items >= kLongItems && a.sides == 0 && (BITS == 8 ? mode != 1 : BITS == 4 && mode == 2) && slots >= 3;
+    const int use = fewer ? slots / 3 * 2 : slots;
     const long long want = (items + kThreads / 64 - 1) / (kThreads / 64);
-    const int grid = tail_grid(a, want < slots ? (int)want : slots, kThreads / 32, slots);
-    hipLaunchKernelGGL((flush_wave_kernel<GC, BITS, ROPE, DT>), dim3(grid), dim3(kThreads), 0, s, a, (int)items);
+    const int grid = tail_grid(a, want < use ? (int)want : use, kThreads / 32, use);
+    if constexpr (BITS == 8 && !ROPE) {
+        if (fewer && a.batch >= 8) {
+            hipLaunchKernelGGL((flush_wave_kernel<GC, BITS, ROPE, DT, true>), dim3(grid), dim3(kThreads), 0, s, a, (int)items);
+            return note_launch(hipGetLastError());
+        }
+    }
+    hipLaunchKernelGGL((flush_wave_kernel<GC, BITS, ROPE, DT, false>), dim3(grid), dim3(kThreads), 0, s, a, (int)items);
     return note_launch(hipGetLastError());
 }
 

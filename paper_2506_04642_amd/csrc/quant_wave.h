@@ -291,14 +291,18 @@ template <int DT> __device__ __forceinline__ void rope_rows(uint4 (&pre)[8], uns
     }
 }
 
-// A piece of a record on its way out of a bulk append: nobody reads it before the call has ended, and the prompt's rows, which other
-// kernels (the next layer's append here, the caller's own attention) read again or have just written, stay in the caches in
-// its place: plain -> streaming stores, 3 x 65536 tokens of the same input at 2, 4 and 8 bits 234 -> 202 us; one
-// layer at 4 bits of 32000 tokens 41.6 -> 34.0, 48000 60.3 -> 58.1, 65536 78.3 -> 79.9 (an input as large as the last cache).
-__device__ __forceinline__ void put_record(uint4 *p, const uint4 &v)
+// A piece of a record on its way out of an append: its first reader is a decode step's attention, and the rows that other kernels
+// read again (the caller's own attention, a next layer that is given the same ones) or have just written stay in the caches in its
+// place.  us a call, plain -> streaming stores, 8 kv heads: three layers with rows of their own, 4 bits, 16 x 1000 tokens 63.2 -> 56.0,
+// 16 x 2000 130 -> 126, 1 x 65536 223 -> 221; 8 bits, 16 x 1000 74 -> 62, 16 x 2000 145 -> 137, but 16 x 3000 214 -> 228; three layers at 2, 4
+// and 8 bits with the same rows, 16 x 4096, 233 -> 205; the value projection's records, 65536 tokens, model_dim 1024, 190 -> 176, 4096 471 -> 467.
+// A short call, a decode step that completes a block among them, takes the same time either way, and so does the attention behind
+// it (64 to 2048 tokens and one attention 14.8 to 15.2 both).  Long calls at 8 bits: kLongItems (quant_append.hip).
+template <bool PAST = true> __device__ __forceinline__ void put_record(uint4 *p, const uint4 &v)
 {
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4 *)p);
+    if (PAST) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4 *)p);
+    else *p = v;
 }
 
 // Minimum / maximum as the bare instructions.  fminf / fmaxf make the compiler put a quieting
