@@ -428,15 +428,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((G == 
 // compiler moved every value to a common register behind each (64 of a value item's 1130 vector instructions), and the extrema's lane exchanges
 // were moves of their own (32 more).  Without: 2 x 15003 tokens of 8 heads at 4 and 2 bits, rotated, 90.8 -> 83.5 us;
 // plain, 16 x 4096 at 2, 4 and 8 bits 207.5 -> 200, 16 x 2000 at 4 bits 36.5 -> 34.1.
-// Items (8 KiB of rows each) from which a call's input, 320 MiB and more, comes from memory whatever was read before it.  Memory is then busy
-// with fewer waves, and more of them only get in one another's way, where an item is little work for its bytes: at 8 bits, and at 4
-// bits without a mean, two workgroups a compute unit in place of three.  At 8 bits, with half as many bytes written as read, the records of
-// eight sequences and more are stored plainly (PLAIN): as streaming stores they leave for many distant places at once.
-// us a call, 8 kv heads, three inputs in turn, before -> with this: 8 bits, 16 x 6000 tokens 133 -> 130, 16 x 8192 178 -> 172, 32 x 5000 235 -> 217,
-// 1 x 131072 168 -> 162, 1 x 262144 339 -> 322 (16 x 12288 314 -> 318), without a mean 16 x 8192 212 -> 196; 4 bits without a mean,
-// 16 x 16384 289 -> 272, 1 x 131072 137 -> 131, 12 x 9001 123 -> 123.  Elsewhere it loses: two workgroups, 8 bits, 16 x 1000 20.8 -> 23.6, 4 bits with a
-// mean 1 x 131072 146 -> 157, 2 bits without one 123 -> 128; plain stores, 4 bits 16 x 6000 108 -> 113 (16 x 16384 319 -> 309), mean over the heads
-// at 8 bits 337 -> 353.
+// Items (8 KiB of rows each) from which a call has more rows than the last cache holds (320 MiB and more), and memory is what it waits for,
+// whatever was read or written before it.
+// Its records are stored plainly (PLAIN): as streaming stores they leave while memory is still busy with the rows, and with the rows' own
+// way out of the cache where a kernel has just written them.  us for a kernel that writes the rows and the append, streaming -> plain
+// stores, 8 kv heads: 4 bits, 16 x 8192 tokens 359 -> 351, 32 x 5000 452 -> 433, 1 x 131072 355 -> 347, 16 x 6000 255 -> 255; 2 bits, 16 x 8192 347 -> 345,
+// 1 x 90000 242 -> 235; 8 bits, 1 x 131072 374 -> 365 (268 MB of rows: 4 bits, 16 x 4096 172 -> 173, 1 x 65536 165 -> 172).  The append on rows
+// that no cache holds: 4 bits, 32 x 5000 205 -> 195, 16 x 16384 319 -> 309, 1 x 131072 143 -> 146, 16 x 6000 108 -> 113.  Not with the mean over the
+// heads (8 bits, 16 x 8192 337 -> 353), the rotation (373 -> 372) or in the quantiser of larger blocks, which gain nothing by it.
+// Where an item is little work for its bytes, at 8 bits and, without a mean, at 4, more waves than memory needs only get in
+// one another's way: two workgroups a compute unit in place of three, 8 bits, with the plain stores: 16 x 8192 178 -> 172, 32 x 5000 235 -> 217,
+// 1 x 262144 339 -> 322 (16 x 12288 314 -> 318), without a mean 16 x 8192 212 -> 196; 4 bits without a mean 16 x 16384 289 -> 272, 12 x 9001 123 -> 123.
+// Elsewhere it loses: 8 bits, 16 x 1000 20.8 -> 23.6, 4 bits with a mean 1 x 131072 146 -> 157, 2 bits without one 123 -> 128.
 constexpr int kLongItems = 40960;
 template <int GC, int BITS, bool ROPE, int DT, bool PLAIN>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))) void flush_wave_kernel(AppendArgs a, int n_items)
@@ -1257,12 +1260,12 @@ template <int GC, int BITS, bool ROPE, int DT> hipError_t launch_flush_wave_t(co
     }();
     if (slots < 1) return hipErrorInvalidValue;
     const int mode = a.geom.mean_mode;
-    const bool fewer = !ROPE && items >= kLongItems && a.sides == 0 && (BITS == 8 ? mode != 1 : BITS == 4 && mode == 2) && slots >= 3;
-    const int use = fewer ? slots / 3 * 2 : slots;
+    const bool plain = !ROPE && items >= kLongItems && a.sides == 0 && mode != 1;
+    const int use = plain && (BITS == 8 || (BITS == 4 && mode == 2)) && slots >= 3 ? slots / 3 * 2 : slots;
     const long long want = (items + kThreads / 64 - 1) / (kThreads / 64);
     const int grid = tail_grid(a, want < use ? (int)want : use, kThreads / 32, use);
-    if constexpr (BITS == 8 && !ROPE) {
-        if (fewer && a.batch >= 8) {
+    if constexpr (!ROPE) {
+        if (plain) {
             hipLaunchKernelGGL((flush_wave_kernel<GC, BITS, ROPE, DT, true>), dim3(grid), dim3(kThreads), 0, s, a, (int)items);
             return note_launch(hipGetLastError());
         }

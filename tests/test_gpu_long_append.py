@@ -1,6 +1,6 @@
-"""Long appends in blocks of 32 tokens: from 40960 items (blocks x units x 2) on, 8 bits and 4 bits without a mean run on fewer
-workgroups, and 8 bits of eight sequences and more store the records plainly.  A call on each side of the line against one call per
-sequence, all of which are below it: the same bytes."""
+"""Long appends in blocks of 32 tokens: from 40960 items (blocks x units x 2) on another instance stores the records plainly, at 8 bits and
+at 4 bits without a mean on fewer workgroups.  A call on each side of the line against one call per sequence, all of which
+are below it: the same bytes."""
 import pytest
 import torch
 
@@ -12,7 +12,7 @@ ITEMS, H = 40960, 8
 
 
 @pytest.mark.parametrize("bits,B,mode,dtype,Gc", [(8, 8, CHAN, BF16, 32), (8, 9, NONE, F16, 64), (8, 7, CHAN, F16, 128), (8, 8, CROSS, BF16, 32),
-                                                  (4, 8, NONE, BF16, 32), (4, 8, CHAN, BF16, 32)])
+                                                  (4, 8, NONE, BF16, 32), (4, 8, CHAN, F16, 128), (2, 9, CHAN, BF16, 64)])
 def test_same_bytes_on_both_sides(bits, B, mode, dtype, Gc):
     assert torch.cuda.is_available(), "these tests need the GPU"
     from paper_2506_04642_amd import binding as kv
