@@ -381,9 +381,11 @@ bool own_raw_splits(const kv_cache *k, const DecodeArgs &a)
 int mfma_chunk(const kv_config &c) { return c.group_tokens == 128 ? 128 : 64; } // tokens a wavefront takes at a time
 
 // Does a decode launch over `blocks` packed blocks of a layer fetch their records past the caches?  A record's next reader, the
-// next step, comes when the other layers have gone by, and as ordinary reads the records only take the place of one another.
-// What the L2s (32 MB together) hold is left to them; layers of 2 bits take fewer bytes a time, for which the last cache (256 MB) is fast
-// enough, and have a line of their own.  us a layer, ordinary -> past the caches, for one layer, two, four or eight (1:, 2: ..) in turn:
+// next step, comes when the other layers have gone by, and as ordinary reads the records only take the place of one another in the last
+// cache (256 MB; the L2s serve nothing from one call to the next in either form: FETCH_SIZE is the layer's bytes in both).
+// Short launches are no faster that way with many layers in turn and slower where the last cache holds them all; layers of
+// 2 bits take fewer bytes a time, for which it is fast enough for longer, and have a line of their own.  Where the lines lie is measured:
+// us a layer, ordinary -> past the caches, for one layer, two, four or eight (1:, 2: ..) in turn:
 //   4 bits, 24 MB  1: 12.3 -> 13.0  2: 13.6 -> 13.2  4: 13.7 -> 13.8  8: 14.0 -> 14.2   8 bits  1: 10.9 -> 11.6  2: 12.2 -> 12.0  4: 12.3 -> 12.4
 //           44 MB  1: 14.0 -> 12.8  2: 14.7 -> 14.0                                             1: 15.7 -> 14.3  2: 16.2 -> 15.3
 //          640 MB  1: 122 -> 108    2: 122 -> 110                                               1: 120 -> 105    2: 120 -> 106

@@ -192,8 +192,8 @@ def test_device_length_steps_host_side(kv):
     (4, 4, 32, "CHANNEL_BLOCK", 40), (8, 8, 32, "CHANNEL_BLOCK", 40), (8, 8, 128, "NONE", 40), (4, 4, 64, "CROSS_HEAD", 40), (16, 16, 32, "CHANNEL_BLOCK", 40),
     (2, 2, 32, "CHANNEL_BLOCK", 128), (2, 2, 128, "CROSS_HEAD", 128), (2, 8, 32, "CHANNEL_BLOCK", 40), (4, 2, 32, "NONE", 40)])
 def test_which_launches_fetch_past_the_caches(kv, k_bits, v_bits, G, mode, limit):
-    """The layer's records against 40 MiB, more than the L2s hold (128 MiB where keys and values have 2 bits): the first count of blocks
-    there and the one before it, inactive sequences and raw tokens left out, no more slots than a pool has."""
+    """The layer's records against 40 MiB (128 MiB where keys and values have 2 bits): the first count of blocks there and the one before
+    it, inactive sequences and raw tokens left out, no more slots than a pool has."""
     B, H, limit = 3, 8, limit << 20
     over = dict(n_layers=1, n_q_heads=32, n_kv_heads=H, group_tokens=G, group_channels=G, resid_cap=G, mean_mode=getattr(kv, "KV_MEAN_" + mode), k_bits=[k_bits], v_bits=[v_bits])
     h = kv.kv_cache_create(_cfg(kv, batch=1, max_tokens=128, **over), [0x100000])
@@ -218,7 +218,7 @@ def test_which_launches_fetch_past_the_caches(kv, k_bits, v_bits, G, mode, limit
             kv.kv_cache_destroy(h)
 
 
-def test_a_single_layer_that_the_l2s_hold_is_read_through_them(kv):
+def test_a_short_launch_reads_through_the_caches(kv):
     # 8205 tokens of 8 kv heads at 8 bits: 20 MB, fetched past the caches 11.4 us a call, through them 10.4
     h = kv.kv_cache_create(_cfg(kv, n_layers=1, batch=1, n_q_heads=32, n_kv_heads=8, max_tokens=8224, k_bits=[8], v_bits=[8]), [0x100000])
     kv.kv_cache_advance(h, 0, 8205)
