@@ -21,7 +21,8 @@
 // 160 KiB.  With two of each (a stage's 64 KiB requested one stage ahead) the fetches alone, without a matrix
 // instruction, took 1.27 us a stage: 0.55 of transfer and the latency; the matrix instructions alone take 0.85.
 // A call of up to 2048 (group, kv head) items would leave half of the device idle that way: there a workgroup owns 128 tokens x one
-// head, two waves of 64 tokens; up to 512 items 64 tokens x one head, two waves of 32, with four stages in LDS instead of two.
+// head, two waves of 64 tokens (three stages of X and two of W_V); up to 512 items 64 tokens x one head, two waves of 32, with four stages of
+// both.  (Large tiles of one head, where their number is odd: three of both.)
 // Every output element is one chain of model_dim / 32 matrix instructions in ascending k, the same
 // chain in project_rows_kernel below, so a token's projected value does not depend on which of
 // the two kernels, or which tile, produced it.
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(64 * MW * NH) void compressv_gemm_kernel(ProjectArg
     constexpr int PA = A_BYTES / 1024 / NW, PB = B_BYTES / 1024 / NW; // fetch instructions (1 KiB each) per wave and stage
     static_assert(A_BYTES / 1024 % NW == 0 && B_BYTES / 1024 % NW == 0, "a stage divides among the waves");
     static_assert(SA >= SB && SB >= 2 && NW * kEpiBytes <= SA * A_BYTES + SB * B_BYTES, "the epilogue fits the staging buffers");
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[]; // S stages
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[]; // SA stages of X, behind them SB of W_V
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -457,9 +458,9 @@ template <int DT, int NH, int GC, int BITS, int WT, int MW, int SA, int SB> hipE
 // waves of the same 64 x 128 tile, two such workgroups per compute unit); up to 512 items 64 tokens x one head with
 // four stages on their way (a small workgroup's stage is through in a fifth of the time that its fetch takes; six are 2 % slower).  Same
 // chain per element, same bytes.  Beyond its one round a tile that is smaller than another only reads the operands more often.
-// Measured (us a call with the keys' side, bf16, 4 bits; small / middle / large): 8 kv heads, model_dim 4096: 1024 tokens 35 / 55 / 81,
-// 2048 (512 items) 36 / 55 / 82, 3072 64 / 55 / 82, 4096 64 / 56 / 82, 8192 (2048 items) 123 / 71 / 85, 12288 186 / 132 / 99,
-// 24576 369 / 230 / 206; 2 heads, model_dim 2048: 8192 tokens (512 items) 24 / 35 / 50, 16384 41 / 36 / 50, 32768 (2048) 80 / 60 / 66.
+// Measured (us a call with the keys' side, bf16, 4 bits, calls in a row; small / middle / large): 8 kv heads, model_dim 4096: 1024 tokens
+// 35 / 55 / 81, 2048 (512 items) 37 / 55 / 81, 3072 65 / 56 / 82, 4096 65 / 56 / 81, 8192 (2048 items) 122 / 70 / 86, 12288 177 / 118 / 93,
+// 24576 365 / 202 / 194; 2 heads, model_dim 2048: 8192 tokens (512 items) 24 / 34 / 49, 16384 40 / 35 / 49, 32768 (2048) 75 / 44 / 54.
 template <int DT, int GC, int BITS> hipError_t launch_gemm_tile(const ProjectArgs &p, hipStream_t s)
 {
     const long long items = (long long)p.batch * p.n_groups * p.n_kv_heads;
