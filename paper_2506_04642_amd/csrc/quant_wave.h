@@ -298,7 +298,9 @@ template <int DT> __device__ __forceinline__ void rope_rows(uint4 (&pre)[8], uns
 // and 8 bits with the same rows, 16 x 4096, 233 -> 205; the value projection's records, 65536 tokens, model_dim 1024, 190 -> 176, 4096 471 -> 467.
 // A short call, a decode step that completes a block among them, takes the same time either way, and so does the attention behind
 // it (64 to 2048 tokens and one attention 14.8 to 15.2 both).  On rows that a kernel has just written, that kernel and the append: 4 bits, 16 x
-// 1000 40.9 -> 39.3, 16 x 4096 173 -> 172; 8 bits, 46.6 -> 41.2, 187 -> 186.  More rows than the last cache holds: kLongItems (quant_append.hip).
+// 1000 40.9 -> 39.3, 16 x 4096 173 -> 172; 8 bits, 46.6 -> 41.2, 187 -> 186.  Where that kernel had twice the bytes in 32 bits beside them,
+// 134 MB of rows still gain (4 x 8192 245 -> 243), 268 MB, as much as the last cache holds, lose: 16 x 4096 at 2, 4, 8 bits 472 -> 481, 473 -> 486, 483 -> 500.
+// More rows than it holds: kLongItems (quant_append.hip).
 template <bool PAST = true> __device__ __forceinline__ void put_record(uint4 *p, const uint4 &v)
 {
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
